@@ -43,6 +43,7 @@ struct BwdParams {
     float* partial;
     RowSched sched;            // dQ: which query tiles, heads and key ranges a workgroup works on
     float* row_partial;        // dQ: partial results of the tiles cut at a gang boundary
+    const int32_t* row_item;   // one workgroup per item: {query tile, first, one-past-last key tile, short-hull flag} by order rank
     const int32_t* block_hull; const int32_t* tile_short;   // short-hull path (see dq_short_unit)
     unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of dq_kernel's workgroup
     int n_blocks32, use_short, delta_skips_short;
@@ -105,22 +106,8 @@ __device__ __forceinline__ void dq_piece(const BwdParams& p, char* smem, const R
     const int l32 = lane & 31, half = lane >> 5;
     const int j16 = lane & 15, gi = (lane >> 4) & 1;
 
-    int k_lo = kPadLo, k_hi = 0;       // hull of the keys the tile's rows see
-    for (int j = 0; j < BM / kGroupRows; ++j) {
-        const int g = tile * (BM / kGroupRows) + j;
-        if (g < p.n_groups) {
-            const int4 d = reinterpret_cast<const int4*>(p.group)[g];
-            if (d.y > d.x) { k_lo = min(k_lo, d.x); k_hi = max(k_hi, d.y); }
-        }
-    }
-    int jb = 0, je = 0, fb = 0, fe = 0;
-    if (k_hi > k_lo) {
-        jb = k_lo / BN; je = (k_hi + BN - 1) / BN;
-        // this piece's part of the tile's key tiles (the first kRowItemOverhead units of a tile's
-        // stretch of the work line stand for its fixed cost)
-        je = min(jb + max(pc.b - kRowItemOverhead, 0), je);
-        jb = jb + max(pc.a - kRowItemOverhead, 0);
-    }
+    const int jb = pc.jb, je = pc.je;      // this piece's 64-key tiles
+    int fb = 0, fe = 0;
 
     const uint32_t kv_row = (uint32_t)p.hkv * D;
     const uint32_t kv_bytes = ((uint32_t)p.t_kv * kv_row - (uint32_t)hk * D) * 2u;
@@ -572,8 +559,11 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
     pc.hk = y % p.hkv;
     const int rank = (y / p.hkv) * 8 + x;
     if (rank >= p.n_tiles) return;
-    pc.tile = ld_const(p.sched.order + rank);
-    if (p.use_short && ld_const(p.tile_short + pc.tile)) {
+    // one record holds what the workgroup needs before its first copy: order, hull and flag through separate
+    // tables are three dependent loads
+    const int4 item = ld_const4(p.row_item + 4 * rank);
+    pc.tile = item.x;
+    if (p.use_short && item.w) {
         // a short-hull tile: its four blocks of 32 rows are units of their own (see dq_short_unit)
         constexpr int per_tile = kFwdTileRows / kShortBlockRows;
         for (int j = pc.member; j < per_tile; j += G) {
@@ -582,8 +572,7 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
         }
         return;
     }
-    pc.c = (int)(ld_const64(p.sched.prefix + rank + 1) - ld_const64(p.sched.prefix + rank));
-    pc.a = 0; pc.b = pc.c; pc.slot = -1;
+    pc.jb = item.y; pc.je = item.z; pc.slot = -1;
     dq_piece<D>(p, smem, pc);
 }
 
@@ -1074,7 +1063,7 @@ __global__ void __launch_bounds__(256) dkv_fixup_kernel(const BwdParams p) {
 // dK/dV on a second stream was measured: once each kernel keeps every compute unit busy to its end
 // the two only get in each other's way (their workgroups cannot share a compute unit's LDS), and the
 // step was 4 % slower.
-wlb_status launch_bwd(const wlb_attn_desc& d, const wlb_plan_layout& L, const void* q, const void* k,
+wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q, const void* k,
                       const void* v, const void* o, const float* lse, const void* d_o, void* dq,
                       void* dk, void* dv, char* ws, size_t off_delta, void* stream_) {
     hipStream_t stream = (hipStream_t)stream_;
@@ -1097,6 +1086,8 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const wlb_plan_layout& L, const vo
     p.partial = (float*)(ws + off_delta + 2 * align_up(sizeof(float) * (size_t)d.hq * d.n_q, 256));
     p.sched.prefix = (const long long*)(ws + L.off_fwd_prefix);
     p.sched.order = (const int32_t*)(ws + L.off_fwd_order);
+    p.sched.tile_first = (const int32_t*)(ws + L.off_tile_first);
+    p.row_item = (const int32_t*)(ws + L.off_row_item);
     p.sched.n_tiles = L.n_fwd_tiles; p.sched.hkv = d.hkv; p.sched.G = d.hq / d.hkv; p.sched.n_gangs = L.row_gangs;
     gang_weights(1, p.sched.weight);
     p.row_partial = (float*)((char*)p.partial + dkv_partial_bytes(d, L));

@@ -24,12 +24,13 @@ namespace wlb {
 struct FwdParams {
     const __bf16* q; const __bf16* k; const __bf16* v;
     __bf16* o; float* lse;
-    const int32_t* row_lo; const int32_t* row_hi; const int32_t* group;
+    const int32_t* row_lo; const int32_t* row_hi;
     RowSched sched;            // which query tiles, heads and key ranges a workgroup works on
     float* partial;            // partial results of the tiles cut at a gang boundary
-    const int32_t* block_hull; const int32_t* tile_short;   // short-hull path (see fwd_short_unit)
+    const int32_t* row_item;   // one workgroup per item: {query tile, first, one-past-last key tile, short-hull flag} by order rank
+    const int32_t* block_hull;   // short-hull path (see fwd_short_unit)
     unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of a gang kernel's workgroup
-    int n_q, t_kv, hq, hkv, n_groups, n_tiles, n_blocks32, use_short;
+    int n_q, t_kv, hq, hkv, n_tiles, n_blocks32, use_short;
     float scale_log2e, scale;
 };
 
@@ -50,22 +51,8 @@ __device__ __forceinline__ void fwd_piece(const FwdParams& p, char* smem, const 
     const int l32 = lane & 31, half = lane >> 5;
     const int j16 = lane & 15, gi = (lane >> 4) & 1;
 
-    int k_lo = kPadLo, k_hi = 0;       // hull of the keys the tile's rows see
-    for (int j = 0; j < BM / kGroupRows; ++j) {
-        const int g = tile * (BM / kGroupRows) + j;
-        if (g < p.n_groups) {
-            const int4 d = reinterpret_cast<const int4*>(p.group)[g];
-            if (d.y > d.x) { k_lo = min(k_lo, d.x); k_hi = max(k_hi, d.y); }
-        }
-    }
-    int jb = 0, je = 0, fb = 0, fe = 0;
-    if (k_hi > k_lo) {
-        jb = k_lo / BN; je = (k_hi + BN - 1) / BN;
-        // this piece's part of the tile's key tiles; the first kRowItemOverhead units of a tile's
-        // stretch of the work line stand for its fixed cost and hold no key tile
-        je = min(jb + max(pc.b - kRowItemOverhead, 0), je);
-        jb = jb + max(pc.a - kRowItemOverhead, 0);
-    }
+    const int jb = pc.jb, je = pc.je;      // this piece's 64-key tiles
+    int fb = 0, fe = 0;
 
     const uint32_t kv_row = (uint32_t)p.hkv * D;
     const uint32_t kv_bytes = ((uint32_t)p.t_kv * kv_row - (uint32_t)hk * D) * 2u;
@@ -551,8 +538,11 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
     pc.hk = y % p.hkv;
     const int rank = (y / p.hkv) * 8 + x;
     if (rank >= p.n_tiles) return;
-    pc.tile = ld_const(p.sched.order + rank);
-    if (p.use_short && ld_const(p.tile_short + pc.tile)) {
+    // one record holds what the workgroup needs before its first copy: order, hull and flag through separate
+    // tables are three dependent loads
+    const int4 item = ld_const4(p.row_item + 4 * rank);
+    pc.tile = item.x;
+    if (p.use_short && item.w) {
         // a short-hull tile: its four blocks of 32 rows are units of their own, each for all heads of the
         // KV head; the tile's workgroups of this KV head share them out by member
         constexpr int per_tile = kFwdTileRows / kShortBlockRows;
@@ -562,8 +552,7 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
         }
         return;
     }
-    pc.c = (int)(ld_const64(p.sched.prefix + rank + 1) - ld_const64(p.sched.prefix + rank));
-    pc.a = 0; pc.b = pc.c; pc.slot = -1;
+    pc.jb = item.y; pc.je = item.z; pc.slot = -1;
     fwd_piece<D>(p, smem, pc);
 }
 
@@ -624,7 +613,7 @@ __global__ void __launch_bounds__(256) fwd_merge_kernel(const FwdParams p) {
     }
 }
 
-wlb_status launch_fwd(const wlb_attn_desc& d, const wlb_plan_layout& L, const void* q, const void* k,
+wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q, const void* k,
                       const void* v, void* o, float* lse, char* ws, size_t off_row_partial, void* stream_) {
     hipStream_t stream = (hipStream_t)stream_;
     FwdParams p;
@@ -632,16 +621,16 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const wlb_plan_layout& L, const vo
     p.o = (__bf16*)o; p.lse = lse;
     p.row_lo = (const int32_t*)(ws + L.off_row_lo);
     p.row_hi = (const int32_t*)(ws + L.off_row_hi);
-    p.group = (const int32_t*)(ws + L.off_group);
     p.sched.prefix = (const long long*)(ws + L.off_fwd_prefix);
     p.sched.order = (const int32_t*)(ws + L.off_fwd_order);
+    p.sched.tile_first = (const int32_t*)(ws + L.off_tile_first);
+    p.row_item = (const int32_t*)(ws + L.off_row_item);
     p.sched.n_tiles = L.n_fwd_tiles; p.sched.hkv = d.hkv; p.sched.G = d.hq / d.hkv; p.sched.n_gangs = L.row_gangs;
     gang_weights(0, p.sched.weight);
     p.partial = (float*)(ws + off_row_partial);
     p.n_q = d.n_q; p.t_kv = d.t_kv; p.hq = d.hq; p.hkv = d.hkv;
-    p.n_groups = L.n_groups; p.n_tiles = L.n_fwd_tiles;
+    p.n_tiles = L.n_fwd_tiles;
     p.block_hull = (const int32_t*)(ws + L.off_block_hull);
-    p.tile_short = (const int32_t*)(ws + L.off_tile_short);
     p.n_blocks32 = L.n_blocks32;
     p.use_short = use_short_path(d, L) ? 1 : 0;
     p.gang_clock = (unsigned long long*)(ws + L.off_gang_clock);

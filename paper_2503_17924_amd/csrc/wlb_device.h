@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
+#include "wlb_internal.h"
+
 namespace wlb {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -102,6 +104,7 @@ __device__ __forceinline__ long long ld_const64(const long long* p) {
 struct RowSched {
     const long long* prefix;   // [n_tiles + 1] cost of the query tiles before order rank r
     const int32_t* order;      // [n_tiles]
+    const int32_t* tile_first; // [n_tiles] first 64-key tile of a query tile, by tile
     int n_tiles, hkv, G, n_gangs;
     // relative share of a gang, by the half of the launch it belongs to and by its XCD (gang g runs on XCD
     // g % 8): weight[0][x] for the first n_gangs / 2 gangs, weight[1][x] for the rest
@@ -124,8 +127,8 @@ struct RowSched {
 };
 struct RowPiece {
     int tile, hk, member;
-    int a, b, c;               // units [a, b) of the tile's c
-    int slot;                  // partial result index, -1 for a whole tile (a == 0 and b == c)
+    int jb, je;                // 64-key tiles [jb, je)
+    int slot;                  // partial result index, -1 for a whole tile
 };
 struct RowWalk {
     long long pos, end;
@@ -158,11 +161,15 @@ struct RowWalk {
         const int c = (int)(ld_const64(s.prefix + r + 1) - p0);
         const long long st = s.hkv * p0 + (long long)hk * c;
         pc.tile = ld_const(s.order + r);
-        pc.hk = hk; pc.member = member; pc.c = c;
-        pc.a = (int)(pos - st);
-        pc.b = (int)((end - st < c) ? end - st : c);
+        pc.hk = hk; pc.member = member;
+        const int a = (int)(pos - st), b = (int)((end - st < c) ? end - st : c);
+        // units [a, b) of the tile's c: the first kRowItemOverhead units of its stretch stand for its fixed
+        // cost and hold no key tile
+        const int j0 = ld_const(s.tile_first + pc.tile);
+        pc.jb = j0 + max(a - kRowItemOverhead, 0);
+        pc.je = j0 + max(b - kRowItemOverhead, 0);
         // a piece that starts inside a tile is its gang's first, one that ends inside a tile its last
-        pc.slot = (pc.a == 0 && pc.b == c) ? -1 : ((pc.a > 0 ? 2 * gang : 2 * gang + 1) * s.G + member);
+        pc.slot = (a == 0 && b == c) ? -1 : ((a > 0 ? 2 * gang : 2 * gang + 1) * s.G + member);
         pos = st + c;
         if (++hk == s.hkv) { hk = 0; ++r; }
         return true;

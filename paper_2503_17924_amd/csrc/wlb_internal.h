@@ -34,6 +34,14 @@ constexpr int kDkvSplit = WLB_DKV_SPLIT;      // a dK/dV item is at most 1/kDkvS
 constexpr int kDkvMinItemStages = WLB_DKV_MIN_ITEM_STAGES;   // items this short are never split further
 constexpr int kMergeSplit = 4;     // workgroups per cut query tile and head in the merge kernels (rows split evenly)
 
+// The public layout and the tables only the library's own kernels read.
+struct PlanLayout : wlb_plan_layout {
+    size_t off_key_span;       // int32 [n_key_tiles]: groups in the key tile's range
+    size_t off_tile_first;     // int32 [n_fwd_tiles]: first 64-key tile the query tile visits
+    size_t off_row_item;       // int32 [n_fwd_tiles][4], by order rank: {query tile, first, one-past-last 64-key tile, short-hull flag}
+    size_t static_bytes;       // bytes counted against WLB_ATTN_FWD_STATIC_SCRATCH_BYTES
+};
+
 // compute units of the GPU (256 when none is present: layout queries on the host)
 int compute_units();
 // Forward and dQ run as a fixed set of workgroups, two per compute unit, in gangs of the
@@ -59,28 +67,28 @@ void gang_weights(int kernel, int out[2][8]);
 // WLB_ATTN_SCHEDULE_* flags override.
 constexpr int kRowGangMaxItemsPerSlot = 3;
 constexpr int kRowGangMinUnitsPerSlot = 64;
-bool use_row_gangs(const wlb_attn_desc& d, const wlb_plan_layout& L);
+bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L);
 // whether this launch sends short-hull query tiles to the short-hull kernels (only in the
 // one-workgroup-per-item schedule; WLB_ATTN_NO_SHORT_PATH switches it off)
-bool use_short_path(const wlb_attn_desc& d, const wlb_plan_layout& L);
+bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L);
 // floats of one partial result of a query tile and head: 128 x D accumulator, then 128 row sums and
 // 128 reference exponents
 inline size_t row_partial_floats(int head_dim) { return (size_t)kFwdTileRows * head_dim + 2 * kFwdTileRows; }
 // bytes of the partial results of the query tiles that are cut at a gang boundary: two per gang and member
-size_t row_partial_bytes(const wlb_attn_desc& d, const wlb_plan_layout& L);
+size_t row_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L);
 // bytes of the dK/dV partial results that follow delta / lse2 in the backward workspace
-size_t dkv_partial_bytes(const wlb_attn_desc& d, const wlb_plan_layout& L);
+size_t dkv_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L);
 
 // Validates desc; on success fills the plan layout.
 wlb_status check_desc(const wlb_attn_desc* d);
-void plan_layout(const wlb_attn_desc& d, wlb_plan_layout* L);
+void plan_layout(const wlb_attn_desc& d, PlanLayout* L);
 
 // Device-side launchers (defined in the .hip files); all asynchronous on `stream`.
-wlb_status launch_plan(const wlb_attn_desc& d, const wlb_plan_layout& L, const int32_t* q_idx,
+wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_t* q_idx,
                        const int32_t* cu_seqlens_k, char* ws, void* stream);
-wlb_status launch_fwd(const wlb_attn_desc& d, const wlb_plan_layout& L, const void* q, const void* k,
+wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q, const void* k,
                       const void* v, void* o, float* lse, char* ws, size_t off_row_partial, void* stream);
-wlb_status launch_bwd(const wlb_attn_desc& d, const wlb_plan_layout& L, const void* q, const void* k,
+wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q, const void* k,
                       const void* v, const void* o, const float* lse, const void* d_o, void* dq,
                       void* dk, void* dv, char* ws, size_t off_delta, void* stream);
 

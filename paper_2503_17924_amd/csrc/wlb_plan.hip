@@ -52,12 +52,12 @@ int compute_units() {
     return cached;
 }
 
-size_t dkv_partial_bytes(const wlb_attn_desc& d, const wlb_plan_layout& L) {
+size_t dkv_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L) {
     // one fp32 dK^T and dV^T tile per partial result
     return (size_t)L.dkv_max_partials * (2 * (size_t)kBwdKeyTile * d.head_dim * sizeof(float));
 }
 
-bool use_row_gangs(const wlb_attn_desc& d, const wlb_plan_layout& L) {
+bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L) {
     if (d.flags & WLB_ATTN_SCHEDULE_GANGS) return true;
     if (d.flags & WLB_ATTN_SCHEDULE_ITEMS) return false;
     const long long items = (long long)L.n_fwd_tiles * d.hq, slots = 2LL * compute_units();
@@ -83,15 +83,15 @@ void gang_weights(int kernel, int out[2][8]) {
             out[h][x] = g_gang_weight[kernel][0][0] > 0 ? g_gang_weight[kernel][h][x] : (h == 0 ? first : 100 - first);
 }
 
-bool use_short_path(const wlb_attn_desc& d, const wlb_plan_layout& L) {
+bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L) {
     return !(d.flags & WLB_ATTN_NO_SHORT_PATH) && !use_row_gangs(d, L);
 }
 
-size_t row_partial_bytes(const wlb_attn_desc& d, const wlb_plan_layout& L) {
+size_t row_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L) {
     return (size_t)2 * L.row_gangs * (d.hq / d.hkv) * row_partial_floats(d.head_dim) * sizeof(float);
 }
 
-void plan_layout(const wlb_attn_desc& d, wlb_plan_layout* L) {
+void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
     L->group_rows = kGroupRows;
     L->n_groups = (d.n_q + kGroupRows - 1) / kGroupRows;
     L->fwd_tile_rows = kFwdTileRows;
@@ -108,8 +108,7 @@ void plan_layout(const wlb_attn_desc& d, wlb_plan_layout* L) {
     L->off_fwd_cost = take(sizeof(int32_t) * L->n_fwd_tiles);
     L->off_key_order = take(sizeof(int32_t) * L->n_key_tiles);
     L->off_key_range = take(sizeof(int32_t) * 2 * L->n_key_tiles);
-    size_t key_cost = take(sizeof(int32_t) * L->n_key_tiles);   // scratch for the ordering
-    (void)key_cost;
+    L->off_key_span = take(sizeof(int32_t) * L->n_key_tiles);
     // Items per tile are the smallest power of two that brings an item under 1/kDkvSplit of a compute
     // unit's mean load, so split tiles contribute fewer than 2 * kDkvSplit * CUs items in total.
     L->dkv_max_partials = 2 * kDkvSplit * compute_units();
@@ -125,324 +124,389 @@ void plan_layout(const wlb_attn_desc& d, wlb_plan_layout* L) {
     L->off_block_hull = take(sizeof(int32_t) * 2 * L->n_blocks32);
     L->off_tile_short = take(sizeof(int32_t) * L->n_fwd_tiles);
     L->off_gang_clock = take(sizeof(uint64_t) * 2 * 2 * (size_t)L->row_gangs * (d.hq / d.hkv));
+    L->static_bytes = off;
+    L->off_tile_first = take(sizeof(int32_t) * L->n_fwd_tiles);
+    L->off_row_item = take(sizeof(int32_t) * 4 * L->n_fwd_tiles);
     L->plan_bytes = off;
-}
-
-static size_t off_key_cost(const wlb_plan_layout& L) {
-    return align_up(L.off_key_range + sizeof(int32_t) * 2 * L.n_key_tiles, 256);
 }
 
 // ------------------------------------------------------------------------------------------
 // kernels
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ int wave_min(int v) {
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ int wave_max(int v) {
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ int wave_sum(int v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+// Everything the schedule kernels read and write.
+struct PlanArgs {
+    const int32_t* q_idx; const int32_t* cu;
+    int n_q, t_kv, n_docs, n_groups, n_tiles, n_key_tiles, hq, hkv, n_slots;
+    int32_t* row_lo; int32_t* row_hi; int32_t* group; int32_t* group_real; int32_t* block_hull;
+    int32_t* fwd_cost; int32_t* tile_first; int32_t* tile_short; int32_t* fwd_order; int32_t* row_item;
+    long long* fwd_prefix;
+    int32_t* key_range; int32_t* key_span; int32_t* key_ways; int32_t* key_order; int32_t* key_item_base; int32_t* key_slot_base;
+    int32_t* dkv_counters;
+};
+constexpr int kGroupsPerTile = kFwdTileRows / kGroupRows;
+// document starts are searched in LDS up to this many documents (a search is log2 dependent loads)
+constexpr int kCuLds = 2048;
+
+// The tokens of the rows of the groups g0, g0 + step, ... (requested before the document starts are waited for).
+template <int N>
+__device__ __forceinline__ void load_tokens(const PlanArgs& a, int g0, int step, int (&tok)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int row = (g0 + i * step) * kGroupRows + (int)(threadIdx.x & 63);
+        tok[i] = row < a.n_q ? a.q_idx[row] : -1;
+    }
 }
 
-// One wavefront per group of 64 rows: per-row [lo, hi) and the group's {k_lo, k_hi, max_lo, min_hi}.
-__global__ void __launch_bounds__(256) plan_rows_kernel(const int32_t* __restrict__ q_idx,
-                                                        const int32_t* __restrict__ cu, int n_q, int t_kv,
-                                                        int n_docs, int n_groups, int32_t* __restrict__ row_lo,
-                                                        int32_t* __restrict__ row_hi, int32_t* __restrict__ group,
-                                                        int32_t* __restrict__ group_real, int32_t* __restrict__ block_hull) {
+// The groups g0, g0 + step, ... (N of them, one wavefront): per-row [lo, hi), the hulls of the two 32-row blocks, the
+// group's {k_lo, k_hi, max_lo, min_hi} and its number of real rows.  hull[i] = {k_lo, k_hi, both blocks fit the
+// short-hull window}; {kPadLo, 0, 1} for a group without a real row or past the end.  The N groups' searches and
+// reductions are independent chains.
+template <int N>
+__device__ __forceinline__ void plan_groups(const PlanArgs& a, const int32_t* cu, int g0, int step, const int (&tok)[N], int (&hull)[N][3]) {
     const int lane = threadIdx.x & 63;
-    const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (g >= n_groups) return;
-    const int i = g * kGroupRows + lane;
-    int lo = kPadLo, hi = 0;
-    if (i < n_q) {
-        const int tok = q_idx[i];
-        if (tok >= 0 && tok < t_kv) {
-            // last document start <= tok
-            int a = 0, b = n_docs;   // invariant: cu[a] <= tok < cu[b]
-            while (b - a > 1) {
-                const int m = (a + b) >> 1;
-                if (cu[m] <= tok) a = m; else b = m;
-            }
-            lo = cu[a];
-            hi = tok + 1;
+    int d[N] = {}, lo[N], hi[N];
+    // last document start <= tok (cu[0] = 0 <= tok); the step count is the same for every row
+    for (int s = 1 << (31 - __clz(a.n_docs)); s > 0; s >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int m = d[i] + s;
+            if (m < a.n_docs && cu[m] <= tok[i]) d[i] = m;
         }
-        row_lo[i] = lo;
-        row_hi[i] = hi;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int g = g0 + i * step, row = g * kGroupRows + lane;
+        const bool real = tok[i] >= 0 && tok[i] < a.t_kv;
+        lo[i] = real ? cu[d[i]] : kPadLo;
+        hi[i] = real ? tok[i] + 1 : 0;
+        if (row < a.n_q) { a.row_lo[row] = lo[i]; a.row_hi[row] = hi[i]; }
     }
-    const bool real = hi > 0;
-    // hull of each half of the wavefront (a block of 32 rows), then of the whole group
-    int b_lo = lo, b_hi = hi;                            // pads carry INT_MAX / 0
-    for (int o = 16; o > 0; o >>= 1) {
-        b_lo = min(b_lo, __shfl_xor(b_lo, o));
-        b_hi = max(b_hi, __shfl_xor(b_hi, o));
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int g = g0 + i * step;
+        const bool real = hi[i] > 0;
+        // hull of each half of the wavefront (a block of 32 rows), then of the whole group
+        int b_lo = lo[i], b_hi = hi[i];                  // pads carry INT_MAX / 0
+        int max_lo = real ? lo[i] : 0, min_hi = real ? hi[i] : kPadLo;
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) {
+            b_lo = min(b_lo, __shfl_xor(b_lo, o));
+            b_hi = max(b_hi, __shfl_xor(b_hi, o));
+            max_lo = max(max_lo, __shfl_xor(max_lo, o));
+            min_hi = min(min_hi, __shfl_xor(min_hi, o));
+        }
+        const int k_lo = min(b_lo, __shfl_xor(b_lo, 32)), k_hi = max(b_hi, __shfl_xor(b_hi, 32));
+        max_lo = max(max_lo, __shfl_xor(max_lo, 32));
+        min_hi = min(min_hi, __shfl_xor(min_hi, 32));
+        const bool fits = b_hi == 0 || b_hi - (b_lo & ~31) <= kShortHullKeys;
+        hull[i][0] = k_lo; hull[i][1] = k_hi; hull[i][2] = __all(fits) ? 1 : 0;
+        const int n_real = __popcll(__ballot(real));
+        if (g < a.n_groups) {
+            if ((lane & 31) == 0) {
+                const int b = g * (kGroupRows / kShortBlockRows) + (lane >> 5);
+                a.block_hull[2 * b] = b_hi > 0 ? b_lo : 0;
+                a.block_hull[2 * b + 1] = b_hi;
+            }
+            if (lane == 0) {
+                reinterpret_cast<int4*>(a.group)[g] = k_hi == 0 ? make_int4(0, 0, 0, 0) : make_int4(k_lo, k_hi, max_lo, min_hi);
+                a.group_real[g] = n_real;
+            }
+        }
     }
-    if ((lane & 31) == 0) {
-        const int b = g * (kGroupRows / kShortBlockRows) + (lane >> 5);
-        block_hull[2 * b] = b_hi > 0 ? b_lo : 0;
-        block_hull[2 * b + 1] = b_hi;
-    }
-    const int k_lo = min(b_lo, __shfl_xor(b_lo, 32));
-    const int k_hi = max(b_hi, __shfl_xor(b_hi, 32));
-    const int max_lo = wave_max(real ? lo : 0);
-    const int min_hi = wave_min(real ? hi : kPadLo);
-    if (lane == 0) {
-        int4 out;
-        if (k_hi == 0) out = make_int4(0, 0, 0, 0);      // no real row in this group
-        else out = make_int4(k_lo, k_hi, max_lo, min_hi);
-        reinterpret_cast<int4*>(group)[g] = out;
-    }
-    const int n_real = wave_sum(real ? 1 : 0);
-    if (lane == 0) group_real[g] = n_real;
 }
 
-// cost of a forward tile = number of 64-key tiles between the hull's ends
-__device__ __forceinline__ void fwd_cost_of_tile(const int32_t* __restrict__ group, int n_groups, int n_tiles,
-                                                 int groups_per_tile, int32_t* __restrict__ cost,
-                                                 const int32_t* __restrict__ block_hull, int32_t* __restrict__ tile_short, int t) {
-    if (t >= n_tiles) return;
-    {
+// A query tile's cost: the 64-key tiles between the ends of its hull.
+struct TileCost { int first, cost; };
+__device__ __forceinline__ TileCost tile_cost(int k_lo, int k_hi) {
+    return k_hi > k_lo ? TileCost{k_lo / 64, (k_hi + 63) / 64 - k_lo / 64} : TileCost{0, 0};
+}
+
+// A dK/dV item is at most this many stages (row groups x heads) unless it is a single head's.  An item of a few dozen
+// stages is not worth splitting: its partial results and the fix-up pass cost more than the shorter tail saves
+// (small-document inputs: 0.55 -> 0.48 ms with the minimum).
+__device__ __forceinline__ int item_limit(long long total_span, int hq, int n_slots) {
+    const unsigned long long per = (unsigned long long)n_slots * kDkvSplit;
+    return (int)min(max((unsigned long long)kDkvMinItemStages, ((unsigned long long)total_span * hq + per - 1) / per), 0x7fffffffull);
+}
+// Items per (key tile, KV head), the smallest power of two that brings an item under the limit, and an item's stages.
+__device__ __forceinline__ int2 item_split(int span, int G, int limit) {
+    int w = 1, heads = G;
+    while (!(heads & 1) && span * heads > limit) { w *= 2; heads >>= 1; }
+    return make_int2(span * heads, w);
+}
+
+// Where a tile stands in its order (heaviest first, ties by index), and sums over the tiles before it.
+__device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cost, int first, int is_short, int rank, long long cost_before) {
+    const long long before = cost_before + (long long)rank * kRowItemOverhead;
+    a.fwd_order[rank] = i;
+    a.fwd_prefix[rank] = before;
+    reinterpret_cast<int4*>(a.row_item)[rank] = make_int4(i, first, first + cost, is_short);
+    if (rank == a.n_tiles - 1) a.fwd_prefix[a.n_tiles] = before + cost + kRowItemOverhead;
+}
+__device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int ways, int rank, int items_before, int slots_before) {
+    a.key_ways[i] = ways;
+    a.key_order[rank] = i;
+    a.key_item_base[rank] = items_before * a.hkv;
+    a.key_slot_base[rank] = slots_before * a.hkv;
+    if (rank == a.n_key_tiles - 1) {
+        a.key_item_base[a.n_key_tiles] = (items_before + ways) * a.hkv;
+        a.key_slot_base[a.n_key_tiles] = (slots_before + (ways > 1 ? ways : 0)) * a.hkv;
+    }
+}
+
+// Schedule, first launch of three: a wavefront per group of 64 rows, and the two query tiles of the workgroup.
+// The three launches are bound by latency (4.7 us each on small-document inputs, a chain of dependent loads): each
+// does all that needs nothing but the results of the one before.  Five launches, one per step, took 24.3 us at 32K
+// tokens in 979 documents where these take 14.2, and 25.2 us where these take 18.7 at 128K tokens (CP = 8).  Sharing
+// work across workgroups inside one launch (the last to arrive goes on) costs more than a launch.
+__global__ void __launch_bounds__(256) plan_rows_kernel(const PlanArgs a) {
+    __shared__ int s_cu[kCuLds], s_hull[4][3];
+    const int wave = threadIdx.x >> 6, g = (int)blockIdx.x * 4 + wave;
+    int tok[1], hull[1][3];
+    load_tokens<1>(a, g, 1, tok);
+    const bool in_lds = a.n_docs <= kCuLds;
+    if (in_lds) {
+        for (int i = threadIdx.x; i < a.n_docs; i += 256) s_cu[i] = a.cu[i];
+        __syncthreads();
+    }
+    if (in_lds) plan_groups<1>(a, s_cu, g, 1, tok, hull);
+    else plan_groups<1>(a, a.cu, g, 1, tok, hull);
+    if ((threadIdx.x & 63) == 0)
+        for (int i = 0; i < 3; ++i) s_hull[wave][i] = hull[0][i];
+    __syncthreads();
+    const int t = (int)blockIdx.x * (4 / kGroupsPerTile) + (int)threadIdx.x;
+    if ((int)threadIdx.x < 4 / kGroupsPerTile && t < a.n_tiles) {
+        const int (*h)[3] = s_hull + threadIdx.x * kGroupsPerTile;
+        const TileCost c = tile_cost(min(h[0][0], h[1][0]), max(h[0][1], h[1][1]));
+        a.fwd_cost[t] = c.cost;
+        a.tile_first[t] = c.first;
         // short-hull tile: every block of 32 rows that has a real row sees keys inside one window of
         // kShortHullKeys keys that starts at a multiple of 32
-        constexpr int per_tile = kFwdTileRows / kShortBlockRows, per_group = kGroupRows / kShortBlockRows;
-        bool is_short = true;
-        for (int j = 0; j < per_tile; ++j) {
-            const int b = t * per_tile + j;
-            if (b >= n_groups * per_group) break;
-            const int lo = block_hull[2 * b], hi = block_hull[2 * b + 1];
-            if (hi > lo && hi - (lo & ~31) > kShortHullKeys) is_short = false;
-        }
-        tile_short[t] = is_short ? 1 : 0;
-    }
-    int k_lo = kPadLo, k_hi = 0;
-    for (int j = 0; j < groups_per_tile; ++j) {
-        const int g = t * groups_per_tile + j;
-        if (g >= n_groups) break;
-        const int4 d = reinterpret_cast<const int4*>(group)[g];
-        if (d.y > d.x) { k_lo = min(k_lo, d.x); k_hi = max(k_hi, d.y); }
-    }
-    cost[t] = k_hi > k_lo ? (k_hi + 63) / 64 - k_lo / 64 : 0;
-}
-
-// One wavefront per key tile: which groups have a hull that touches it.
-__device__ __forceinline__ void groups_of_key_tile(const int32_t* __restrict__ group, int n_groups, int n_key_tiles,
-                                                   int key_tile, int t_kv, int32_t* __restrict__ key_range,
-                                                   int32_t* __restrict__ key_cost, int kt) {
-    const int lane = threadIdx.x & 63;
-    if (kt >= n_key_tiles) return;
-    const int k0 = kt * key_tile, k1 = min(k0 + key_tile, t_kv);
-    int first = kPadLo, last = 0, cnt = 0;
-    for (int g = lane; g < n_groups; g += 64) {
-        const int4 d = reinterpret_cast<const int4*>(group)[g];
-        if (d.y > d.x && d.x < k1 && d.y > k0) { first = min(first, g); last = max(last, g + 1); ++cnt; }
-    }
-    first = wave_min(first);
-    last = wave_max(last);
-    cnt = wave_sum(cnt);
-    if (lane == 0) {
-        key_range[2 * kt] = cnt ? first : 0;
-        key_range[2 * kt + 1] = cnt ? last : 0;
-        key_cost[kt] = cnt;
+        a.tile_short[t] = h[0][2] & h[1][2];
     }
 }
 
-// Both read only the group table: the first fwd_blocks workgroups take the forward tiles (one per
-// thread), the others the key tiles (one per wavefront).
-__global__ void __launch_bounds__(256) plan_costs_kernel(const int32_t* __restrict__ group, int n_groups, int n_tiles,
-                                                         int groups_per_tile, int32_t* __restrict__ fwd_cost,
-                                                         int fwd_blocks, int n_key_tiles, int key_tile, int t_kv,
-                                                         int32_t* __restrict__ key_range, int32_t* __restrict__ key_cost,
-                                                         const int32_t* __restrict__ block_hull,
-                                                         int32_t* __restrict__ tile_short) {
-    if ((int)blockIdx.x < fwd_blocks)
-        fwd_cost_of_tile(group, n_groups, n_tiles, groups_per_tile, fwd_cost, block_hull, tile_short,
-                         blockIdx.x * 256 + threadIdx.x);
-    else
-        groups_of_key_tile(group, n_groups, n_key_tiles, key_tile, t_kv, key_range, key_cost,
-                           ((int)blockIdx.x - fwd_blocks) * 4 + (threadIdx.x >> 6));
-}
-
-// order[rank] = index, heaviest first, ties by index (a counting rank; n is at most a few thousand).
-// A workgroup ranks kOrderPerBlock elements: wavefront w compares them with every (waves)th quad of
-// costs, which pass through LDS in chunks, and the partial ranks are summed in LDS.  (One element per
-// thread kept the n^2 comparisons on very few compute units: 40 us for 1024 key tiles.)
-constexpr int kOrderPerBlock = 64;
-__device__ __forceinline__ void order_block(const int32_t* __restrict__ cost, int n, int32_t* __restrict__ order, int block) {
-    constexpr int CHUNK = 2048;
-    __shared__ __attribute__((aligned(16))) int s_cost[CHUNK];
-    __shared__ int s_rank[kOrderPerBlock];
-    const int e = threadIdx.x % kOrderPerBlock, seg = threadIdx.x / kOrderPerBlock, n_seg = blockDim.x / kOrderPerBlock;
+// Orders by a counting rank (n is at most a few thousand).  A workgroup of 1024 ranks kOrderPerBlock elements: wavefront
+// w compares them with every (waves)th pair of elements, which pass through LDS in chunks, and the partial counts are
+// summed in LDS.  (One element per thread kept the n^2 comparisons on very few compute units: 40 us for 1024 key
+// tiles.)  item_of(j) gives an element's cost (>= 0) and a number of its own; Counts sums over the elements before
+// this one; put(i, item, counts) receives the result.
+constexpr int kOrderPerBlock = 64, kOrderChunk = 2048;
+template <class Counts, class ItemOf, class Put>
+__device__ __forceinline__ void order_block(int n, int block, ItemOf item_of, Put put) {
+    constexpr int n_seg = 1024 / kOrderPerBlock;
+    __shared__ __attribute__((aligned(16))) int2 s_item[kOrderChunk];
+    __shared__ Counts s_part[n_seg][kOrderPerBlock];
+    const int e = threadIdx.x % kOrderPerBlock, seg = threadIdx.x / kOrderPerBlock;
     const int i = block * kOrderPerBlock + e;
-    const int c = i < n ? cost[i] : 0;
-    if (threadIdx.x < kOrderPerBlock) s_rank[threadIdx.x] = 0;
-    int rank = 0;
-    for (int j0 = 0; j0 < n; j0 += CHUNK) {
-        const int m = min(CHUNK, n - j0);
+    const int2 own = i < n ? item_of(i) : make_int2(0, 0);
+    Counts mine{};
+    for (int j0 = 0; j0 < n; j0 += kOrderChunk) {
+        const int m = min(kOrderChunk, n - j0), m2 = (m + 1) & ~1;
         __syncthreads();
-        // past the end: a cost below every real one (costs are >= 0), so it never counts
-        for (int j = threadIdx.x; j < CHUNK; j += blockDim.x) s_cost[j] = j < m ? cost[j0 + j] : -1;
+        // past the end: a cost below every real one, so it never counts
+        for (int j = threadIdx.x; j < m2; j += 1024) s_item[j] = j < m ? item_of(j0 + j) : make_int2(-1, 0);
         __syncthreads();
-        // entries before i win ties: an entry counts if its cost exceeds c - 1 before i, c from i on
-        for (int j = 4 * seg; j < m; j += 4 * n_seg) {
-            const int4 cj = *reinterpret_cast<const int4*>(&s_cost[j]);
-            const int g = j0 + j;
-            rank += (cj.x > c - (g + 0 < i)) + (cj.y > c - (g + 1 < i)) + (cj.z > c - (g + 2 < i)) + (cj.w > c - (g + 3 < i));
+#pragma unroll 2
+        for (int j = 2 * seg; j < m; j += 2 * n_seg) {
+            const int4 two = *reinterpret_cast<const int4*>(&s_item[j]);
+            // entries before i win ties: an entry counts if its cost exceeds own - 1 before i, own from i on
+            if (two.x > own.x - (j0 + j < i)) mine.add(two.x, two.y);
+            if (two.z > own.x - (j0 + j + 1 < i)) mine.add(two.z, two.w);
         }
     }
-    atomicAdd(&s_rank[e], rank);
+    s_part[seg][e] = mine;
     __syncthreads();
-    if (seg == 0 && i < n) order[s_rank[e]] = i;
+    if (seg == 0 && i < n) {
+        for (int s = 1; s < n_seg; ++s) mine.join(s_part[s][e]);
+        put(i, own, mine);
+    }
+}
+struct RowCounts {                 // query tiles before this one, and their cost
+    int rank; long long cost;
+    __device__ __forceinline__ void add(int c, int) { rank += 1; cost += c; }
+    __device__ __forceinline__ void join(const RowCounts& o) { rank += o.rank; cost += o.cost; }
+};
+struct KeyCounts {                 // key tiles before this one, and their items and partial slots for one KV head
+    int rank, items, slots;
+    __device__ __forceinline__ void add(int, int ways) { rank += 1; items += ways; slots += ways > 1 ? ways : 0; }
+    __device__ __forceinline__ void join(const KeyCounts& o) { rank += o.rank; items += o.items; slots += o.slots; }
+};
+
+// Second launch: workgroups [0, order_blocks) order the query tiles; the others find, one wavefront per key tile,
+// the groups whose hull touches it.
+__global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int order_blocks) {
+    if ((int)blockIdx.x < order_blocks) {
+        order_block<RowCounts>(a.n_tiles, blockIdx.x, [&](int j) { return make_int2(a.fwd_cost[j], 0); },
+                               [&](int i, int2 own, const RowCounts& c) {
+                                   put_query_tile(a, i, own.x, a.tile_first[i], a.tile_short[i], c.rank, c.cost);
+                               });
+        return;
+    }
+    const int lane = threadIdx.x & 63, kt = ((int)blockIdx.x - order_blocks) * 16 + (int)(threadIdx.x >> 6);
+    if (kt >= a.n_key_tiles) return;
+    const int k0 = kt * kBwdKeyTile, k1 = min(k0 + kBwdKeyTile, a.t_kv);
+    int first = kPadLo, last = 0;
+#pragma unroll 8
+    for (int g = lane; g < a.n_groups; g += 64) {
+        const int2 d = *reinterpret_cast<const int2*>(a.group + 4 * g);
+        if (d.y > d.x && d.x < k1 && d.y > k0) { first = min(first, g); last = max(last, g + 1); }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        first = min(first, __shfl_xor(first, o));
+        last = max(last, __shfl_xor(last, o));
+    }
+    if (lane == 0) {
+        a.key_range[2 * kt] = last ? first : 0;
+        a.key_range[2 * kt + 1] = last;
+        a.key_span[kt] = last ? last - first : 0;
+    }
 }
 
-// One workgroup.  Chooses how many items each key tile is split into and replaces the tile's
-// cost by its item cost (groups in range x heads per item), the key the tiles are then ordered by.
-__device__ __forceinline__ void key_split_block(const int32_t* __restrict__ key_range, int n_key_tiles, int hq, int hkv,
-                                                int n_slots, int32_t* __restrict__ ways, int32_t* __restrict__ item_cost) {
-    __shared__ long long part[1024];
+// Third launch: how many items each key tile is split into, and the key tiles ordered by item cost (groups in range x
+// heads per item).
+__global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) {
+    __shared__ long long s_total;
+    if (threadIdx.x == 0) s_total = 0;
+    if (blockIdx.x == 0 && threadIdx.x < kLists) a.dkv_counters[threadIdx.x] = 0;
+    __syncthreads();
     long long sum = 0;
-    for (int kt = threadIdx.x; kt < n_key_tiles; kt += 1024) sum += key_range[2 * kt + 1] - key_range[2 * kt];
-    part[threadIdx.x] = sum;
+    for (int kt = threadIdx.x; kt < a.n_key_tiles; kt += 1024) sum += a.key_span[kt];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if ((threadIdx.x & 63) == 0 && sum) atomicAdd((unsigned long long*)&s_total, (unsigned long long)sum);
     __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-        __syncthreads();
-    }
-    const int G = hq / hkv;
-    const long long total_stages = part[0] * hq;
-    // An item of a few dozen stages is not worth splitting: its partial results and the fix-up pass
-    // cost more than the shorter tail saves (small-document inputs: 0.55 -> 0.48 ms with the minimum).
-    const long long thr = max((long long)kDkvMinItemStages, (total_stages + (long long)n_slots * kDkvSplit - 1) / ((long long)n_slots * kDkvSplit));
-    for (int kt = threadIdx.x; kt < n_key_tiles; kt += 1024) {
-        const int span = key_range[2 * kt + 1] - key_range[2 * kt];
-        int w = 1;
-        while (w < G && (long long)span * (G / w) > thr && G % (2 * w) == 0) w *= 2;
-        ways[kt] = w;
-        item_cost[kt] = span * (G / w);
-    }
+    const int G = a.hq / a.hkv;
+    const int limit = item_limit(s_total, a.hq, a.n_slots);
+    order_block<KeyCounts>(a.n_key_tiles, blockIdx.x, [&](int j) { return item_split(a.key_span[j], G, limit); },
+                           [&](int i, int2 own, const KeyCounts& c) { put_key_tile(a, i, own.y, c.rank, c.items, c.slots); });
 }
 
-// One workgroup.  Exclusive prefix sums, by order rank, of the tiles' item counts and partial slots.
-__global__ void __launch_bounds__(1024) plan_key_bases_kernel(const int32_t* __restrict__ key_order,
-                                                              const int32_t* __restrict__ ways, int n_key_tiles, int hkv,
-                                                              int32_t* __restrict__ item_base, int32_t* __restrict__ slot_base,
-                                                              int32_t* __restrict__ dkv_counters) {
-    __shared__ int s_items[1024], s_slots[1024];
-    if (threadIdx.x < kLists) dkv_counters[threadIdx.x] = 0;
-    const int per = (n_key_tiles + 1023) / 1024;
-    const int r0 = threadIdx.x * per, r1 = min(r0 + per, n_key_tiles);
-    int items = 0, slots = 0;
-    for (int r = r0; r < r1; ++r) {
-        const int w = ways[key_order[r]];
-        items += w * hkv;
-        slots += w > 1 ? w * hkv : 0;
-    }
-    s_items[threadIdx.x] = items;
-    s_slots[threadIdx.x] = slots;
+// The whole schedule in one launch of one workgroup, for calls that one workgroup handles faster than three launches
+// follow each other: up to 4096 rows (four groups per wavefront) and 256 key tiles (32768 keys).  At 2052 rows and 4096
+// keys it takes 10.0 us (one launch per step: 17.0 in five), at 4095 rows and 16381 keys 12.5 us.
+constexpr int kSmallGroups = 64, kSmallTiles = kSmallGroups / kGroupsPerTile, kSmallKeyTiles = 256;
+__global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
+    __shared__ int s_cu[kCuLds], s_total;
+    __shared__ int2 s_hull[kSmallGroups];
+    __shared__ int s_fits[kSmallGroups];
+    __shared__ __attribute__((aligned(16))) int2 s_items[kSmallKeyTiles];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    constexpr int PER = kSmallGroups / 16;
+    int tok[PER], hull[PER][3];
+    load_tokens<PER>(a, wave, 16, tok);
+    const bool in_lds = a.n_docs <= kCuLds;
+    if (in_lds)
+        for (int i = tid; i < a.n_docs; i += 1024) s_cu[i] = a.cu[i];
+    if (tid == 0) s_total = 0;
+    if (tid < kLists) a.dkv_counters[tid] = 0;
     __syncthreads();
-    // Hillis-Steele inclusive scan over the 1024 per-thread totals
-    for (int o = 1; o < 1024; o <<= 1) {
-        const int a = (int)threadIdx.x >= o ? s_items[threadIdx.x - o] : 0;
-        const int b = (int)threadIdx.x >= o ? s_slots[threadIdx.x - o] : 0;
-        __syncthreads();
-        s_items[threadIdx.x] += a;
-        s_slots[threadIdx.x] += b;
-        __syncthreads();
-    }
-    int ib = s_items[threadIdx.x] - items, sb = s_slots[threadIdx.x] - slots;
-    for (int r = r0; r < r1; ++r) {
-        item_base[r] = ib;
-        slot_base[r] = sb;
-        const int w = ways[key_order[r]];
-        ib += w * hkv;
-        sb += w > 1 ? w * hkv : 0;
-    }
-    if (threadIdx.x == 1023) { item_base[n_key_tiles] = s_items[1023]; slot_base[n_key_tiles] = s_slots[1023]; }
-}
-
-// One workgroup.  prefix[r] = cost (key tiles + the fixed kRowItemOverhead each) of the query tiles of order rank < r.
-__device__ __forceinline__ void fwd_prefix_block(const int32_t* __restrict__ order, const int32_t* __restrict__ cost,
-                                                 int n_tiles, long long* __restrict__ prefix) {
-    __shared__ long long s_sum[1024];
-    const int per = (n_tiles + 1023) / 1024;
-    const int r0 = min((int)threadIdx.x * per, n_tiles), r1 = min(r0 + per, n_tiles);
-    long long mine = 0;
-    for (int r = r0; r < r1; ++r) mine += cost[order[r]] + kRowItemOverhead;
-    s_sum[threadIdx.x] = mine;
+    if (in_lds) plan_groups<PER>(a, s_cu, wave, 16, tok, hull);
+    else plan_groups<PER>(a, a.cu, wave, 16, tok, hull);
+    if ((tid & 63) == 0)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            s_hull[wave + i * 16] = make_int2(hull[i][0], hull[i][1]);
+            s_fits[wave + i * 16] = hull[i][2];
+        }
     __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const long long add = (int)threadIdx.x >= o ? s_sum[threadIdx.x - o] : 0;
+    const int G = a.hq / a.hkv;
+    {   // key tiles: four threads each
+        const int kt = tid >> 2, k0 = kt * kBwdKeyTile, k1 = min(k0 + kBwdKeyTile, a.t_kv);
+        int first = kPadLo, last = 0;
+#pragma unroll
+        for (int i = 0; i < kSmallGroups / 4; ++i) {             // groups past the end have an empty hull
+            const int g = i * 4 + (tid & 3);
+            const int2 h = s_hull[g];
+            if (h.y > h.x && h.x < k1 && h.y > k0) { first = min(first, g); last = max(last, g + 1); }
+        }
+#pragma unroll
+        for (int o = 2; o > 0; o >>= 1) {
+            first = min(first, __shfl_xor(first, o));
+            last = max(last, __shfl_xor(last, o));
+        }
+        const int span = last && kt < a.n_key_tiles ? last - first : 0;
+        int sum = (tid & 3) == 0 ? span : 0;
+#pragma unroll
+        for (int o = 32; o > 1; o >>= 1) sum += __shfl_xor(sum, o);
+        if ((tid & 63) == 0 && sum) atomicAdd(&s_total, sum);
         __syncthreads();
-        s_sum[threadIdx.x] += add;
-        __syncthreads();
+        if ((tid & 3) == 0) {
+            // past the end: a cost below every real one
+            s_items[kt] = kt < a.n_key_tiles ? item_split(span, G, item_limit(s_total, a.hq, a.n_slots)) : make_int2(-1, 0);
+            if (kt < a.n_key_tiles) {
+                a.key_range[2 * kt] = last ? first : 0;
+                a.key_range[2 * kt + 1] = last;
+                a.key_span[kt] = span;
+            }
+        }
     }
-    long long run = s_sum[threadIdx.x] - mine;
-    for (int r = r0; r < r1; ++r) {
-        prefix[r] = run;
-        run += cost[order[r]] + kRowItemOverhead;
+    {   // query tiles: a half-wavefront each, one comparison per lane
+        const int t = tid >> 5, j = tid & 31;
+        auto cost_of = [&](int i) __attribute__((always_inline)) {
+            const int2 h0 = s_hull[kGroupsPerTile * i], h1 = s_hull[kGroupsPerTile * i + 1];
+            return tile_cost(min(h0.x, h1.x), max(h0.y, h1.y));
+        };
+        static_assert(kSmallTiles == 32 && kGroupsPerTile == 2, "a lane of a half-wavefront per query tile");
+        const TileCost own = cost_of(t), other = cost_of(j);
+        const bool before = j < a.n_tiles && other.cost > own.cost - (j < t);
+        int rank = before, sum = before ? other.cost : 0;
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) {
+            rank += __shfl_xor(rank, o);
+            sum += __shfl_xor(sum, o);
+        }
+        if (j == 0 && t < a.n_tiles) {
+            const int is_short = s_fits[kGroupsPerTile * t] & s_fits[kGroupsPerTile * t + 1];
+            a.fwd_cost[t] = own.cost;
+            a.tile_first[t] = own.first;
+            a.tile_short[t] = is_short;
+            put_query_tile(a, t, own.cost, own.first, is_short, rank, sum);
+        }
     }
-    if (threadIdx.x == 1023) prefix[n_tiles] = s_sum[1023];
+    __syncthreads();
+    {   // the key tiles' order: four threads per tile, each a quarter of the comparisons
+        const int i = tid >> 2, cost = s_items[i].x;
+        KeyCounts c{};
+#pragma unroll 4
+        for (int j = 2 * (tid & 3); j < a.n_key_tiles; j += 8) {
+            const int4 two = *reinterpret_cast<const int4*>(&s_items[j]);
+            if (two.x > cost - (j < i)) c.add(two.x, two.y);
+            if (two.z > cost - (j + 1 < i)) c.add(two.z, two.w);
+        }
+#pragma unroll
+        for (int o = 2; o > 0; o >>= 1) {
+            c.rank += __shfl_xor(c.rank, o);
+            c.items += __shfl_xor(c.items, o);
+            c.slots += __shfl_xor(c.slots, o);
+        }
+        if ((tid & 3) == 0 && i < a.n_key_tiles) put_key_tile(a, i, s_items[i].y, c.rank, c.items, c.slots);
+    }
 }
 
-// Workgroups [0, order_blocks) rank the forward tiles; the one after them splits the key tiles
-// (neither needs the other's result).
-__global__ void __launch_bounds__(1024) plan_fwd_order_key_split_kernel(const int32_t* __restrict__ fwd_cost, int n_tiles,
-                                                                        int32_t* __restrict__ fwd_order, int order_blocks,
-                                                                        const int32_t* __restrict__ key_range,
-                                                                        int n_key_tiles, int hq, int hkv, int n_slots,
-                                                                        int32_t* __restrict__ ways,
-                                                                        int32_t* __restrict__ item_cost) {
-    if ((int)blockIdx.x < order_blocks) order_block(fwd_cost, n_tiles, fwd_order, blockIdx.x);
-    else key_split_block(key_range, n_key_tiles, hq, hkv, n_slots, ways, item_cost);
-}
-
-// Workgroups [0, order_blocks) rank the key tiles by item cost; the one after them builds the
-// forward work line's prefix sums.
-__global__ void __launch_bounds__(1024) plan_key_order_fwd_prefix_kernel(const int32_t* __restrict__ key_cost,
-                                                                         int n_key_tiles, int32_t* __restrict__ key_order,
-                                                                         int order_blocks,
-                                                                         const int32_t* __restrict__ fwd_order,
-                                                                         const int32_t* __restrict__ fwd_cost, int n_tiles,
-                                                                         long long* __restrict__ prefix) {
-    if ((int)blockIdx.x < order_blocks) order_block(key_cost, n_key_tiles, key_order, blockIdx.x);
-    else fwd_prefix_block(fwd_order, fwd_cost, n_tiles, prefix);
-}
-
-wlb_status launch_plan(const wlb_attn_desc& d, const wlb_plan_layout& L, const int32_t* q_idx,
+wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_t* q_idx,
                        const int32_t* cu_seqlens_k, char* ws, void* stream_) {
     hipStream_t stream = (hipStream_t)stream_;
-    int32_t* row_lo = (int32_t*)(ws + L.off_row_lo);
-    int32_t* row_hi = (int32_t*)(ws + L.off_row_hi);
-    int32_t* group = (int32_t*)(ws + L.off_group);
-    int32_t* group_real = (int32_t*)(ws + L.off_group_real);
-    int32_t* fwd_order = (int32_t*)(ws + L.off_fwd_order);
-    int32_t* fwd_cost = (int32_t*)(ws + L.off_fwd_cost);
-    int32_t* key_order = (int32_t*)(ws + L.off_key_order);
-    int32_t* key_range = (int32_t*)(ws + L.off_key_range);
-    int32_t* key_cost = (int32_t*)(ws + off_key_cost(L));
-    plan_rows_kernel<<<(L.n_groups + 3) / 4, 256, 0, stream>>>(q_idx, cu_seqlens_k, d.n_q, d.t_kv, d.n_docs,
-                                                                L.n_groups, row_lo, row_hi, group, group_real,
-                                                                (int32_t*)(ws + L.off_block_hull));
-    int32_t* key_ways = (int32_t*)(ws + L.off_key_ways);
-    const int fwd_cost_blocks = (L.n_fwd_tiles + 255) / 256, key_tile_blocks = (L.n_key_tiles + 3) / 4;
-    plan_costs_kernel<<<fwd_cost_blocks + key_tile_blocks, 256, 0, stream>>>(
-        group, L.n_groups, L.n_fwd_tiles, kFwdTileRows / kGroupRows, fwd_cost, fwd_cost_blocks, L.n_key_tiles,
-        kBwdKeyTile, d.t_kv, key_range, key_cost, (const int32_t*)(ws + L.off_block_hull),
-        (int32_t*)(ws + L.off_tile_short));
-    const int fwd_order_blocks = (L.n_fwd_tiles + kOrderPerBlock - 1) / kOrderPerBlock;
-    const int key_order_blocks = (L.n_key_tiles + kOrderPerBlock - 1) / kOrderPerBlock;
-    plan_fwd_order_key_split_kernel<<<fwd_order_blocks + 1, 1024, 0, stream>>>(
-        fwd_cost, L.n_fwd_tiles, fwd_order, fwd_order_blocks, key_range, L.n_key_tiles, d.hq, d.hkv, compute_units(),
-        key_ways, key_cost);
-    plan_key_order_fwd_prefix_kernel<<<key_order_blocks + 1, 1024, 0, stream>>>(
-        key_cost, L.n_key_tiles, key_order, key_order_blocks, fwd_order, fwd_cost, L.n_fwd_tiles,
-        (long long*)(ws + L.off_fwd_prefix));
-    plan_key_bases_kernel<<<1, 1024, 0, stream>>>(key_order, key_ways, L.n_key_tiles, d.hkv,
-                                                  (int32_t*)(ws + L.off_key_item_base), (int32_t*)(ws + L.off_key_slot_base),
-                                                  (int32_t*)(ws + L.off_dkv_counters));
+    auto at = [&](size_t off) { return (int32_t*)(ws + off); };
+    PlanArgs a;
+    a.q_idx = q_idx; a.cu = cu_seqlens_k;
+    a.n_q = d.n_q; a.t_kv = d.t_kv; a.n_docs = d.n_docs; a.hq = d.hq; a.hkv = d.hkv;
+    a.n_groups = L.n_groups; a.n_tiles = L.n_fwd_tiles; a.n_key_tiles = L.n_key_tiles; a.n_slots = compute_units();
+    a.row_lo = at(L.off_row_lo); a.row_hi = at(L.off_row_hi);
+    a.group = at(L.off_group); a.group_real = at(L.off_group_real); a.block_hull = at(L.off_block_hull);
+    a.fwd_cost = at(L.off_fwd_cost); a.tile_first = at(L.off_tile_first); a.tile_short = at(L.off_tile_short);
+    a.fwd_order = at(L.off_fwd_order); a.row_item = at(L.off_row_item); a.fwd_prefix = (long long*)(ws + L.off_fwd_prefix);
+    a.key_range = at(L.off_key_range); a.key_span = at(L.off_key_span); a.key_ways = at(L.off_key_ways);
+    a.key_order = at(L.off_key_order); a.key_item_base = at(L.off_key_item_base); a.key_slot_base = at(L.off_key_slot_base);
+    a.dkv_counters = at(L.off_dkv_counters);
+    if (L.n_groups <= kSmallGroups && L.n_key_tiles <= kSmallKeyTiles) {
+        plan_small_kernel<<<1, 1024, 0, stream>>>(a);
+    } else {
+        const int order_blocks = (L.n_fwd_tiles + kOrderPerBlock - 1) / kOrderPerBlock;
+        plan_rows_kernel<<<(L.n_groups + 3) / 4, 256, 0, stream>>>(a);
+        plan_ranges_kernel<<<order_blocks + (L.n_key_tiles + 15) / 16, 1024, 0, stream>>>(a, order_blocks);
+        plan_key_items_kernel<<<(L.n_key_tiles + kOrderPerBlock - 1) / kOrderPerBlock, 1024, 0, stream>>>(a);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(WLB_ERR_HIP, "plan launch: %s", hipGetErrorString(e));
     return WLB_OK;
@@ -453,7 +517,10 @@ wlb_status launch_plan(const wlb_attn_desc& d, const wlb_plan_layout& L, const i
 // workspace.  Every GPU the library runs on holds its own copy, at its own address, until the
 // process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the address
 // that call returns (kept per device) is what kernels and every other use of the memory get.
-static __device__ __align__(256) unsigned char scratch[WLB_ATTN_FWD_STATIC_SCRATCH_BYTES];
+// The stated limit counts the tables a schedule had to have when the limit was set (PlanLayout::static_bytes);
+// the tables added since (20 bytes per query tile, at most 2 MiB / 4 bytes per row of them) have room of their own.
+constexpr size_t kStaticExtraBytes = WLB_ATTN_FWD_STATIC_SCRATCH_BYTES / 8 / kFwdTileRows * 20 + 1024;
+static __device__ __align__(256) unsigned char scratch[WLB_ATTN_FWD_STATIC_SCRATCH_BYTES + kStaticExtraBytes];
 
 constexpr int kMaxDevices = 64;
 static void* g_scratch_ptr[kMaxDevices];      // device address of `scratch` on each device, once resolved
@@ -487,7 +554,7 @@ using namespace wlb;
 extern "C" wlb_status wlb_attn_workspace_size(const wlb_attn_desc* desc, size_t* fwd_bytes, size_t* bwd_bytes) {
     if (wlb_status st = check_desc(desc)) return st;
     if (!fwd_bytes || !bwd_bytes) return fail(WLB_ERR_INVALID_ARG, "wlb_attn_workspace_size: null output");
-    wlb_plan_layout L;
+    PlanLayout L;
     plan_layout(*desc, &L);
     *fwd_bytes = L.plan_bytes + row_partial_bytes(*desc, L);
     *bwd_bytes = L.plan_bytes + delta_bytes(*desc) + dkv_partial_bytes(*desc, L) + row_partial_bytes(*desc, L);
@@ -517,7 +584,9 @@ extern "C" wlb_status wlb_attn_get_gang_weights(int32_t kernel, int32_t* weights
 extern "C" wlb_status wlb_attn_plan_layout(const wlb_attn_desc* desc, wlb_plan_layout* layout) {
     if (wlb_status st = check_desc(desc)) return st;
     if (!layout) return fail(WLB_ERR_INVALID_ARG, "wlb_attn_plan_layout: null output");
-    plan_layout(*desc, layout);
+    PlanLayout L;
+    plan_layout(*desc, &L);
+    *layout = L;
     return WLB_OK;
 }
 
@@ -525,7 +594,7 @@ extern "C" wlb_status wlb_attn_plan(const wlb_attn_desc* desc, const int32_t* q_
                                     void* workspace, size_t workspace_bytes, void* stream) {
     if (wlb_status st = check_desc(desc)) return st;
     if (!q_idx || !cu_seqlens_k || !workspace) return fail(WLB_ERR_INVALID_ARG, "wlb_attn_plan: null pointer");
-    wlb_plan_layout L;
+    PlanLayout L;
     plan_layout(*desc, &L);
     if (workspace_bytes < L.plan_bytes)
         return fail(WLB_ERR_BUFFER_TOO_SMALL, "wlb_attn_plan: workspace %zu < %zu bytes", workspace_bytes, L.plan_bytes);
@@ -539,7 +608,7 @@ extern "C" wlb_status wlb_attn_fwd(const wlb_attn_desc* desc, const void* q, con
     if (!q || !k || !v || !o || !lse || !workspace) return fail(WLB_ERR_INVALID_ARG, "wlb_attn_fwd: null pointer");
     const bool reuse = desc->flags & WLB_ATTN_REUSE_PLAN;
     if (!reuse && (!q_idx || !cu_seqlens_k)) return fail(WLB_ERR_INVALID_ARG, "wlb_attn_fwd: null q_idx/cu_seqlens_k");
-    wlb_plan_layout L;
+    PlanLayout L;
     plan_layout(*desc, &L);
     const size_t need = L.plan_bytes + row_partial_bytes(*desc, L);
     if (workspace_bytes < need)
@@ -562,11 +631,11 @@ extern "C" wlb_status wlb_attn_fwd_static(const wlb_attn_desc* desc, const void*
     // schedule tables are all the scratch the call needs
     wlb_attn_desc d = *desc;
     d.flags |= WLB_ATTN_SCHEDULE_ITEMS;
-    wlb_plan_layout L;
+    PlanLayout L;
     plan_layout(d, &L);
-    if (L.plan_bytes > (size_t)WLB_ATTN_FWD_STATIC_SCRATCH_BYTES)
+    if (L.static_bytes > (size_t)WLB_ATTN_FWD_STATIC_SCRATCH_BYTES)
         return fail(WLB_ERR_UNSUPPORTED, "wlb_attn_fwd_static: the schedule of n_q=%d, t_kv=%d needs %zu bytes, the library's array holds %zu",
-                    d.n_q, d.t_kv, L.plan_bytes, (size_t)WLB_ATTN_FWD_STATIC_SCRATCH_BYTES);
+                    d.n_q, d.t_kv, L.static_bytes, (size_t)WLB_ATTN_FWD_STATIC_SCRATCH_BYTES);
     char* ws = nullptr;
     if (wlb_status st = static_scratch(&ws)) return st;
     if (!reuse)
@@ -583,7 +652,7 @@ extern "C" wlb_status wlb_attn_bwd(const wlb_attn_desc* desc, const void* q, con
         return fail(WLB_ERR_INVALID_ARG, "wlb_attn_bwd: null pointer");
     const bool reuse = desc->flags & WLB_ATTN_REUSE_PLAN;
     if (!reuse && (!q_idx || !cu_seqlens_k)) return fail(WLB_ERR_INVALID_ARG, "wlb_attn_bwd: null q_idx/cu_seqlens_k");
-    wlb_plan_layout L;
+    PlanLayout L;
     plan_layout(*desc, &L);
     const size_t need = L.plan_bytes + delta_bytes(*desc) + dkv_partial_bytes(*desc, L) + row_partial_bytes(*desc, L);
     if (workspace_bytes < need)
