@@ -194,8 +194,10 @@ enum {
      * backward, so one schedule serves them all. */
     WLB_ATTN_REUSE_PLAN = 1,
     /* Measurement aids for wlb_attn_bwd, so that one kernel can be timed or profiled alone:
-     * reuse the delta the previous backward call left in this workspace; do not run the dQ
-     * kernel (dq is left untouched); do not run the dK/dV kernel (dk, dv left untouched). */
+     * reuse the delta the previous backward call left in this workspace (the dQ kernel forms its
+     * own in any case, so this matters only together with the next flag: without it the call then
+     * runs a delta pass); do not run the dQ kernel (dq is left untouched); do not run the dK/dV
+     * kernel (dk, dv left untouched). */
     WLB_ATTN_BWD_SKIP_DELTA = 2,
     WLB_ATTN_BWD_SKIP_DQ = 4,
     WLB_ATTN_BWD_SKIP_DKV = 8,

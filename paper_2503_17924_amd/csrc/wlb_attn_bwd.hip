@@ -6,11 +6,13 @@
 // dK/dV summed over the query heads that share a KV head.  As in all-gather context
 // parallelism (Section 2.1) dK/dV hold only the calling rank's rows' contribution.
 //
-// Five kernels, no atomics, deterministic:
-//   delta_kernel      delta[h][i] = -sum_d dO*O (stored negated: the dK/dV kernel starts its dP
-//                     accumulators from it) and the log2-scaled LSE copy (0 / +inf for padding rows)
+// No atomics, deterministic:
 //   dq_kernel         query-stationary, same tiling and work schedule as the forward: S^T and dP^T
-//                     per lane column, dQ^T += K^T dS^T with K^T read from LDS by transpose reads
+//                     per lane column, dQ^T += K^T dS^T with K^T read from LDS by transpose reads.
+//                     It also forms delta[h][i] = -sum_d dO*O of its rows (stored negated: the dK/dV
+//                     kernel starts its dP accumulators from it) and leaves it and a log2-scaled LSE
+//                     copy (0 / +inf for padding rows) for the dK/dV kernel, which runs after it
+//   delta_kernel      the same for a call that leaves dQ out (WLB_ATTN_BWD_SKIP_DQ)
 //   dq_merge_kernel   sums the fp32 partial dQ of query tiles cut at a gang boundary
 //   dkv_kernel        key-stationary: a work item owns 128 keys of one KV head and streams the row
 //                     groups that can see them through LDS for some or all query heads of the KV
@@ -44,9 +46,9 @@ struct BwdParams {
     RowSched sched;            // dQ: which query tiles, heads and key ranges a workgroup works on
     float* row_partial;        // dQ: partial results of the tiles cut at a gang boundary
     const int32_t* row_item;   // one workgroup per item: {query tile, first, one-past-last key tile, short-hull flag} by order rank
-    const int32_t* block_hull; const int32_t* tile_short;   // short-hull path (see dq_short_unit)
+    const int32_t* block_hull;   // short-hull path (see dq_short_unit)
     unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of dq_kernel's workgroup
-    int n_blocks32, use_short, delta_skips_short;
+    int n_blocks32, use_short;
     int n_q, t_kv, hq, hkv, n_groups, n_tiles, n_key_tiles;
     float scale_log2e, scale;
 };
@@ -56,11 +58,10 @@ template <int D>
 __global__ void __launch_bounds__(256) delta_kernel(const BwdParams p) {
     constexpr int LPR = D / 8;                       // lanes per (row, head)
     const size_t total = (size_t)p.n_q * p.hq;
-    // gridDim.x / n_tiles workgroups share the (row, head) pairs of a query tile.  A short-hull tile, whose delta
-    // and LSE copy come from the short-hull dQ units, costs its workgroups one table lookup.
+    // gridDim.x / n_tiles workgroups share the (row, head) pairs of a query tile
     const int split = (int)gridDim.x / p.n_tiles;
     const int tile = (int)blockIdx.x / split, part = (int)blockIdx.x % split;
-    if (tile >= p.n_tiles || (p.delta_skips_short && ld_const(p.tile_short + tile))) return;
+    if (tile >= p.n_tiles) return;
     const size_t first = (size_t)tile * kFwdTileRows * p.hq * LPR, lanes = (size_t)kFwdTileRows * p.hq * LPR;
     for (size_t off = (size_t)part * 256; off < lanes; off += (size_t)split * 256) {
         const size_t idx = first + off + threadIdx.x;
@@ -92,6 +93,10 @@ __global__ void __launch_bounds__(256) delta_kernel(const BwdParams p) {
 // keys a wavefront computes S^T = K Q^T and dP^T = V dO^T (lane = its query column), forms
 // dS^T = P^T o (dP^T - delta) in registers and accumulates dQ^T += K^T dS^T with K^T read
 // from the same swizzled K tile by transpose reads.
+// delta comes from the dO operands the wavefront holds anyway and its rows of O: a pass of its own read dO a second
+// time and cost a launch (129 of 5800 us at 32K tokens with 32 query heads, 40 of 813 us in four layers of 8191
+// tokens); here it is D / 16 loads
+// per lane beside the copies of the first tiles (5712 -> 5629 us, 807 -> 767 us with the schedule's shorter launches).
 template <int D>
 __device__ __forceinline__ void dq_piece(const BwdParams& p, char* smem, const RowPiece& pc) {
     constexpr int NW = 4, BM = 128, BN = 64;
@@ -137,20 +142,31 @@ __device__ __forceinline__ void dq_piece(const BwdParams& p, char* smem, const R
     // padding rows: zero operands and LSE = +inf make P, dS and dQ exactly 0
     const float lsec = real ? p.lse[(size_t)h * p.n_q + rc] * 1.4426950408889634f : INFINITY;
     float lsec_unmasked = other_doc ? INFINITY : lsec;           // inside [fb, fe): +inf switches the lane off
-    const float dl = real ? p.delta[(size_t)h * p.n_q + rc] : 0.f;
+    float dl = 0.f;                    // -delta
     bf16x8 qf[KS], dof[KS];
     {
         const __bf16* qp = p.q + ((size_t)rc * p.hq + h) * D + half * 8;
         const __bf16* gp = p.d_o + ((size_t)rc * p.hq + h) * D + half * 8;
+        const __bf16* op = p.o + ((size_t)rc * p.hq + h) * D + half * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             bf16x8 a = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
             bf16x8 g = *reinterpret_cast<const bf16x8*>(gp + ks * 16);
+            const bf16x8 o = *reinterpret_cast<const bf16x8*>(op + ks * 16);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) dl = fmaf(-(float)g[i], (float)o[i], dl);
             if (!real) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) { a[i] = (__bf16)0.f; g[i] = (__bf16)0.f; }
             }
             qf[ks] = a; dof[ks] = g;
+        }
+        dl += xhalf(dl);
+        if (!real) dl = 0.f;
+        // the tile's first piece leaves them for the dK/dV kernel; +inf makes every probability of a padding row 0
+        if (pc.first && in && half == 0) {
+            p.delta[(size_t)h * p.n_q + row] = dl;
+            p.lse2[(size_t)h * p.n_q + row] = lsec;
         }
     }
 
@@ -572,7 +588,7 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
         }
         return;
     }
-    pc.jb = item.y; pc.je = item.z; pc.slot = -1;
+    pc.jb = item.y; pc.je = item.z; pc.slot = -1; pc.first = true;
     dq_piece<D>(p, smem, pc);
 }
 
@@ -1059,7 +1075,7 @@ __global__ void __launch_bounds__(256) dkv_fixup_kernel(const BwdParams p) {
     }
 }
 
-// delta, then dK/dV (+ fix-up), then dQ (+ merge), all on the caller's stream.  Running dQ beside
+// dQ (+ merge), which leaves delta, then dK/dV (+ fix-up), all on the caller's stream.  Running dQ beside
 // dK/dV on a second stream was measured: once each kernel keeps every compute unit busy to its end
 // the two only get in each other's way (their workgroups cannot share a compute unit's LDS), and the
 // step was 4 % slower.
@@ -1092,7 +1108,6 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     gang_weights(1, p.sched.weight);
     p.row_partial = (float*)((char*)p.partial + dkv_partial_bytes(d, L));
     p.block_hull = (const int32_t*)(ws + L.off_block_hull);
-    p.tile_short = (const int32_t*)(ws + L.off_tile_short);
     p.n_blocks32 = L.n_blocks32;
     p.gang_clock = (unsigned long long*)(ws + L.off_gang_clock) + 2 * (size_t)L.row_gangs * (d.hq / d.hkv);
     p.n_q = d.n_q; p.t_kv = d.t_kv; p.hq = d.hq; p.hkv = d.hkv;
@@ -1114,31 +1129,19 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     const bool do_dq = !(d.flags & WLB_ATTN_BWD_SKIP_DQ);
     const bool do_dkv = !(d.flags & WLB_ATTN_BWD_SKIP_DKV);
     p.use_short = use_short_path(d, L) ? 1 : 0;
-    // the short-hull dQ kernel forms delta for its own rows (and runs before dK/dV, which reads it);
-    // when it does not run, the delta pass covers every row
-    p.delta_skips_short = (p.use_short && do_dq) ? 1 : 0;
-    // Order: delta, then dK/dV (+ fix-up), then dQ (+ merge) -- except when short-hull units run inside the
-    // dQ launch: they leave delta for their rows, which dK/dV reads, so dQ goes first.
     auto run = [&](auto dtag) {
         constexpr int D = decltype(dtag)::value;
-        if (do_delta) delta_kernel<D><<<grid_delta, 256, 0, stream>>>(p);
-        auto dkv = [&] {
-            if (!do_dkv) return;
+        if (do_dq && gangs) {
+            dq_kernel<D><<<grid_dq, 256, 0, stream>>>(p);
+            dq_merge_kernel<D><<<grid_dq * kMergeSplit, 256, 0, stream>>>(p);
+        } else if (do_dq) {
+            dq_items_kernel<D><<<grid_dq_items, 256, 0, stream>>>(p);
+        } else if (do_delta) {
+            delta_kernel<D><<<grid_delta, 256, 0, stream>>>(p);
+        }
+        if (do_dkv) {
             dkv_kernel<D><<<grid_dkv, 512, 0, stream>>>(p);
             dkv_fixup_kernel<D><<<grid_fix * kMergeSplit, 256, 0, stream>>>(p);
-        };
-        if (gangs) {
-            dkv();
-            if (do_dq) {
-                dq_kernel<D><<<grid_dq, 256, 0, stream>>>(p);
-                dq_merge_kernel<D><<<grid_dq * kMergeSplit, 256, 0, stream>>>(p);
-            }
-        } else if (p.use_short) {
-            if (do_dq) dq_items_kernel<D><<<grid_dq_items, 256, 0, stream>>>(p);
-            dkv();
-        } else {
-            dkv();
-            if (do_dq) dq_items_kernel<D><<<grid_dq_items, 256, 0, stream>>>(p);
         }
     };
     if (d.head_dim == 128) run(std::integral_constant<int, 128>{});

@@ -552,7 +552,7 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
         }
         return;
     }
-    pc.jb = item.y; pc.je = item.z; pc.slot = -1;
+    pc.jb = item.y; pc.je = item.z; pc.slot = -1; pc.first = true;
     fwd_piece<D>(p, smem, pc);
 }
 

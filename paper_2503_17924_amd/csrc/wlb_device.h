@@ -128,6 +128,7 @@ struct RowSched {
 struct RowPiece {
     int tile, hk, member;
     int jb, je;                // 64-key tiles [jb, je)
+    bool first;                // the piece its tile begins with
     int slot;                  // partial result index, -1 for a whole tile
 };
 struct RowWalk {
@@ -166,6 +167,7 @@ struct RowWalk {
         // units [a, b) of the tile's c: the first kRowItemOverhead units of its stretch stand for its fixed
         // cost and hold no key tile
         const int j0 = ld_const(s.tile_first + pc.tile);
+        pc.first = a == 0;
         pc.jb = j0 + max(a - kRowItemOverhead, 0);
         pc.je = j0 + max(b - kRowItemOverhead, 0);
         // a piece that starts inside a tile is its gang's first, one that ends inside a tile its last
