@@ -39,8 +39,8 @@ struct BwdParams {
     const float* lse; float* delta; float* lse2;
     __bf16* dq; __bf16* dk; __bf16* dv;
     const int32_t* row_lo; const int32_t* row_hi; const int32_t* group; const int32_t* group_real;
-    const int32_t* key_order; const int32_t* key_range;
-    const int32_t* key_ways; const int32_t* key_item_base; const int32_t* key_slot_base;
+    const int32_t* key_order; const int32_t* key_ways; const int32_t* key_item_base; const int32_t* key_slot_base;
+    const int32_t* dkv_item;   // two int4 per item (PlanLayout::off_dkv_item)
     int32_t* dkv_counters;     // [8]: items of each XCD's list handed out so far (zero before every dK/dV launch)
     float* partial;
     RowSched sched;            // dQ: which query tiles, heads and key ranges a workgroup works on
@@ -656,14 +656,14 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     __shared__ __attribute__((aligned(2 * PBYTES))) char pbuf[2 * PBYTES];
     __shared__ __attribute__((aligned(256))) int small_s[NBUF][4][GR];       // per stage buffer: lse2 | delta | row_lo | row_hi
 
-    const int G = p.hq / p.hkv;
     // Work items: tiles in order (heaviest item first), a tile's items consecutive: KV head major, head
     // part minor.  The launch is one workgroup per compute unit, and each takes item after item until
     // none is left.  Item i belongs to XCD i % 8 (workgroup b runs on XCD b % 8): the same head part of
     // neighbouring tiles then shares an XCD and its L2 copy of the Q / dO tiles.  A workgroup takes its own
     // XCD's items first, through one counter per XCD, and the other XCDs' once those are gone: the XCDs
     // of one GPU differ in speed by several percent (the same ones are slower in every launch), and with
-    // one workgroup per item the hardware hands every XCD the same number of them.
+    // one workgroup per item the hardware hands every XCD the same number of them.  (A first item by
+    // workgroup index and reading all counters at once near the end measured the same.)
     __shared__ int s_item;
     const int n_items = ld_const(p.key_item_base + p.n_key_tiles);
   for (;;) {
@@ -680,19 +680,12 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     __syncthreads();
     const int item = uniform(s_item);
     if (item < 0) break;
-    int r = 0;
-    for (int hi = p.n_key_tiles; hi - r > 1;) {
-        const int mid = (r + hi) >> 1;
-        if (ld_const(p.key_item_base + mid) <= item) r = mid; else hi = mid;
-    }
-    const int kt = ld_const(p.key_order + r);
-    const int ways = ld_const(p.key_ways + kt);
-    const int j = item - ld_const(p.key_item_base + r);
-    const int hk = j / ways, part = j % ways;
-    const int nh = G / ways;                 // query heads of this item: hk * G + part * nh + [0, nh)
-    const int h_first = hk * G + part * nh;
-    const bool whole = ways == 1;
-    const int slot = ld_const(p.key_slot_base + r) + j;
+    // one record per item: finding the tile by a search of the item bases and then its tables was a chain of a dozen
+    // dependent loads in front of every item
+    const int4 rec0 = ld_const4(p.dkv_item + 8 * item), rec1 = ld_const4(p.dkv_item + 8 * item + 4);
+    const int kt = rec0.x, hk = rec0.y, h_first = rec0.z, nh = rec0.w;   // query heads [h_first, h_first + nh)
+    const int slot = rec1.x;
+    const bool whole = slot < 0;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     // role and key block are left as per-lane values: as scalars they raise the register pressure
@@ -950,8 +943,7 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
 
     // stage t of the item is row group g_first + t / nh with query head h_first + t % nh; every
     // group of the tile's range is a stage (one whose hull misses the tile, rare, costs a copy and no math)
-    const int g_first = ld_const(p.key_range + 2 * kt);
-    const int t1 = (ld_const(p.key_range + 2 * kt + 1) - g_first) * nh;
+    const int g_first = rec1.y, t1 = rec1.z;
 
     // The schedule data of a stage (its group's hull, fully visible range and real-row count) comes
     // by scalar loads issued right after the barrier of the stage before and is turned into flags
@@ -1061,18 +1053,40 @@ __global__ void __launch_bounds__(256) dkv_fixup_kernel(const BwdParams p) {
     const float* src = p.partial + (size_t)(p.key_slot_base[r] + hk * ways) * (2 * BNK * D);
     constexpr int V4 = D / 4;                   // float4 per row
     constexpr int PER = 2 * BNK * V4 / kMergeSplit;
-    for (int e = quarter * PER + threadIdx.x; e < (quarter + 1) * PER; e += 256) {
-        const int which = e / (BNK * V4), rem = e % (BNK * V4);
-        const int key = rem / V4, d4 = rem % V4;
-        if (key >= nk) continue;
-        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-        for (int i = 0; i < ways; ++i)
-                sum += *reinterpret_cast<const f32x4*>(src + (size_t)i * (2 * BNK * D) + (size_t)which * BNK * D +
-                                                       (size_t)key * D + d4 * 4);
-        const float f = which == 0 ? p.scale : 1.0f;
-        __bf16* op = (which == 0 ? p.dk : p.dv) + ((size_t)(k0 + key) * p.hkv + hk) * D + d4 * 4;
-        *reinterpret_cast<bf16x4*>(op) = pack4(sum[0] * f, sum[1] * f, sum[2] * f, sum[3] * f);
-    }
+    // The pass is bound by the latency of its loads: those of U elements and W parts (W = 8: in turns) are requested
+    // together (8191 tokens, 8/2 heads: 13.8 -> 7.6 us).
+    auto sum_parts = [&](auto parts_tag) __attribute__((always_inline)) {
+        constexpr int W = decltype(parts_tag)::value, U = PER / 256 < 4 ? PER / 256 : 4;
+        static_assert(PER % (U * 256) == 0, "elements per thread");
+        for (int e0 = quarter * PER + (int)threadIdx.x; e0 < (quarter + 1) * PER; e0 += U * 256) {
+            f32x4 sum[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int i0 = 0; i0 < ways; i0 += W) {
+                f32x4 x[U][W];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int i = 0; i < W; ++i)
+                        x[u][i] = *reinterpret_cast<const f32x4*>(src + (size_t)(i0 + i) * (2 * BNK * D) + (size_t)(e0 + u * 256) * 4);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int i = 0; i < W; ++i) sum[u] += x[u][i];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int e = e0 + u * 256, which = e / (BNK * V4), rem = e % (BNK * V4);
+                const int key = rem / V4, d4 = rem % V4;
+                const float f = which == 0 ? p.scale : 1.0f;
+                __bf16* op = (which == 0 ? p.dk : p.dv) + ((size_t)(k0 + key) * p.hkv + hk) * D + d4 * 4;
+                if (key < nk) *reinterpret_cast<bf16x4*>(op) = pack4(sum[u][0] * f, sum[u][1] * f, sum[u][2] * f, sum[u][3] * f);
+            }
+        }
+    };
+    if (ways == 2) sum_parts(std::integral_constant<int, 2>{});
+    else if (ways == 4) sum_parts(std::integral_constant<int, 4>{});
+    else sum_parts(std::integral_constant<int, 8>{});        // a power of two
 }
 
 // dQ (+ merge), which leaves delta, then dK/dV (+ fix-up), all on the caller's stream.  Running dQ beside
@@ -1094,7 +1108,7 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.group = (const int32_t*)(ws + L.off_group);
     p.group_real = (const int32_t*)(ws + L.off_group_real);
     p.key_order = (const int32_t*)(ws + L.off_key_order);
-    p.key_range = (const int32_t*)(ws + L.off_key_range);
+    p.dkv_item = (const int32_t*)(ws + L.off_dkv_item);
     p.key_ways = (const int32_t*)(ws + L.off_key_ways);
     p.key_item_base = (const int32_t*)(ws + L.off_key_item_base);
     p.key_slot_base = (const int32_t*)(ws + L.off_key_slot_base);

@@ -39,6 +39,9 @@ struct PlanLayout : wlb_plan_layout {
     size_t off_key_span;       // int32 [n_key_tiles]: groups in the key tile's range
     size_t off_tile_first;     // int32 [n_fwd_tiles]: first 64-key tile the query tile visits
     size_t off_row_item;       // int32 [n_fwd_tiles][4], by order rank: {query tile, first, one-past-last 64-key tile, short-hull flag}
+    // Last, because a forward's schedule (wlb_attn_fwd_static) leaves it out.
+    size_t off_dkv_item;       // int32 [dkv_max_items][8], by item: {key tile, KV head, first query head, query heads, partial slot or -1,
+                               // first row group, stages, 0}
     size_t static_bytes;       // bytes counted against WLB_ATTN_FWD_STATIC_SCRATCH_BYTES
 };
 
@@ -85,7 +88,7 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L);
 
 // Device-side launchers (defined in the .hip files); all asynchronous on `stream`.
 wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_t* q_idx,
-                       const int32_t* cu_seqlens_k, char* ws, void* stream);
+                       const int32_t* cu_seqlens_k, char* ws, bool forward_only, void* stream);
 wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q, const void* k,
                       const void* v, void* o, float* lse, char* ws, size_t off_row_partial, void* stream);
 wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q, const void* k,

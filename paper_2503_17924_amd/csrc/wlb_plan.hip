@@ -127,6 +127,7 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
     L->static_bytes = off;
     L->off_tile_first = take(sizeof(int32_t) * L->n_fwd_tiles);
     L->off_row_item = take(sizeof(int32_t) * 4 * L->n_fwd_tiles);
+    L->off_dkv_item = take(sizeof(int32_t) * 8 * (size_t)L->dkv_max_items);
     L->plan_bytes = off;
 }
 
@@ -136,12 +137,12 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
 // Everything the schedule kernels read and write.
 struct PlanArgs {
     const int32_t* q_idx; const int32_t* cu;
-    int n_q, t_kv, n_docs, n_groups, n_tiles, n_key_tiles, hq, hkv, n_slots;
+    int n_q, t_kv, n_docs, n_groups, n_tiles, n_key_tiles, hq, hkv, n_slots, forward_only;
     int32_t* row_lo; int32_t* row_hi; int32_t* group; int32_t* group_real; int32_t* block_hull;
     int32_t* fwd_cost; int32_t* tile_first; int32_t* tile_short; int32_t* fwd_order; int32_t* row_item;
     long long* fwd_prefix;
     int32_t* key_range; int32_t* key_span; int32_t* key_ways; int32_t* key_order; int32_t* key_item_base; int32_t* key_slot_base;
-    int32_t* dkv_counters;
+    int32_t* dkv_item; int32_t* dkv_counters;
 };
 constexpr int kGroupsPerTile = kFwdTileRows / kGroupRows;
 // document starts are searched in LDS up to this many documents (a search is log2 dependent loads)
@@ -242,7 +243,7 @@ __device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cos
     reinterpret_cast<int4*>(a.row_item)[rank] = make_int4(i, first, first + cost, is_short);
     if (rank == a.n_tiles - 1) a.fwd_prefix[a.n_tiles] = before + cost + kRowItemOverhead;
 }
-__device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int ways, int rank, int items_before, int slots_before) {
+__device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 range, int ways, int rank, int items_before, int slots_before) {
     a.key_ways[i] = ways;
     a.key_order[rank] = i;
     a.key_item_base[rank] = items_before * a.hkv;
@@ -251,6 +252,14 @@ __device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int ways,
         a.key_item_base[a.n_key_tiles] = (items_before + ways) * a.hkv;
         a.key_slot_base[a.n_key_tiles] = (slots_before + (ways > 1 ? ways : 0)) * a.hkv;
     }
+    // one record per item, KV head major, head part minor: what a workgroup needs to begin
+    const int G = a.hq / a.hkv, nh = G / ways, item0 = items_before * a.hkv, slot0 = slots_before * a.hkv;
+    for (int hk = 0, j = 0; hk < a.hkv; ++hk)
+        for (int part = 0; part < ways; ++part, ++j) {
+            int4* rec = reinterpret_cast<int4*>(a.dkv_item) + 2 * (size_t)(item0 + j);
+            rec[0] = make_int4(i, hk, hk * G + part * nh, nh);
+            rec[1] = make_int4(ways > 1 ? slot0 + j : -1, range.x, (range.y - range.x) * nh, 0);
+        }
 }
 
 // Schedule, first launch of three: a wavefront per group of 64 rows, and the two query tiles of the workgroup.
@@ -379,11 +388,13 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
     const int G = a.hq / a.hkv;
     const int limit = item_limit(s_total, a.hq, a.n_slots);
     order_block<KeyCounts>(a.n_key_tiles, blockIdx.x, [&](int j) { return item_split(a.key_span[j], G, limit); },
-                           [&](int i, int2 own, const KeyCounts& c) { put_key_tile(a, i, own.y, c.rank, c.items, c.slots); });
+                           [&](int i, int2 own, const KeyCounts& c) {
+                               put_key_tile(a, i, make_int2(a.key_range[2 * i], a.key_range[2 * i + 1]), own.y, c.rank, c.items, c.slots);
+                           });
 }
 
 // The whole schedule in one launch of one workgroup, for calls that one workgroup handles faster than three launches
-// follow each other: up to 4096 rows (four groups per wavefront) and 256 key tiles (32768 keys).  At 2052 rows and 4096
+// follow each other: up to 4096 rows (four groups per wavefront), 256 key tiles (32768 keys) and the documents the LDS holds.  At 2052 rows and 4096
 // keys it takes 10.0 us (one launch per step: 17.0 in five), at 4095 rows and 16381 keys 12.5 us.
 constexpr int kSmallGroups = 64, kSmallTiles = kSmallGroups / kGroupsPerTile, kSmallKeyTiles = 256;
 __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
@@ -395,14 +406,11 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
     constexpr int PER = kSmallGroups / 16;
     int tok[PER], hull[PER][3];
     load_tokens<PER>(a, wave, 16, tok);
-    const bool in_lds = a.n_docs <= kCuLds;
-    if (in_lds)
-        for (int i = tid; i < a.n_docs; i += 1024) s_cu[i] = a.cu[i];
+    for (int i = tid; i < a.n_docs; i += 1024) s_cu[i] = a.cu[i];
     if (tid == 0) s_total = 0;
     if (tid < kLists) a.dkv_counters[tid] = 0;
     __syncthreads();
-    if (in_lds) plan_groups<PER>(a, s_cu, wave, 16, tok, hull);
-    else plan_groups<PER>(a, a.cu, wave, 16, tok, hull);
+    plan_groups<PER>(a, s_cu, wave, 16, tok, hull);
     if ((tid & 63) == 0)
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
@@ -411,6 +419,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
         }
     __syncthreads();
     const int G = a.hq / a.hkv;
+    int2 range = make_int2(0, 0);      // of key tile tid / 4
     {   // key tiles: four threads each
         const int kt = tid >> 2, k0 = kt * kBwdKeyTile, k1 = min(k0 + kBwdKeyTile, a.t_kv);
         int first = kPadLo, last = 0;
@@ -425,7 +434,8 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             first = min(first, __shfl_xor(first, o));
             last = max(last, __shfl_xor(last, o));
         }
-        const int span = last && kt < a.n_key_tiles ? last - first : 0;
+        if (last && kt < a.n_key_tiles) range = make_int2(first, last);
+        const int span = range.y - range.x;
         int sum = (tid & 3) == 0 ? span : 0;
 #pragma unroll
         for (int o = 32; o > 1; o >>= 1) sum += __shfl_xor(sum, o);
@@ -435,8 +445,8 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             // past the end: a cost below every real one
             s_items[kt] = kt < a.n_key_tiles ? item_split(span, G, item_limit(s_total, a.hq, a.n_slots)) : make_int2(-1, 0);
             if (kt < a.n_key_tiles) {
-                a.key_range[2 * kt] = last ? first : 0;
-                a.key_range[2 * kt + 1] = last;
+                a.key_range[2 * kt] = range.x;
+                a.key_range[2 * kt + 1] = range.y;
                 a.key_span[kt] = span;
             }
         }
@@ -464,6 +474,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             put_query_tile(a, t, own.cost, own.first, is_short, rank, sum);
         }
     }
+    if (a.forward_only) return;
     __syncthreads();
     {   // the key tiles' order: four threads per tile, each a quarter of the comparisons
         const int i = tid >> 2, cost = s_items[i].x;
@@ -480,12 +491,12 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             c.items += __shfl_xor(c.items, o);
             c.slots += __shfl_xor(c.slots, o);
         }
-        if ((tid & 3) == 0 && i < a.n_key_tiles) put_key_tile(a, i, s_items[i].y, c.rank, c.items, c.slots);
+        if ((tid & 3) == 0 && i < a.n_key_tiles) put_key_tile(a, i, range, s_items[i].y, c.rank, c.items, c.slots);
     }
 }
 
 wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_t* q_idx,
-                       const int32_t* cu_seqlens_k, char* ws, void* stream_) {
+                       const int32_t* cu_seqlens_k, char* ws, bool forward_only, void* stream_) {
     hipStream_t stream = (hipStream_t)stream_;
     auto at = [&](size_t off) { return (int32_t*)(ws + off); };
     PlanArgs a;
@@ -498,14 +509,15 @@ wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_
     a.fwd_order = at(L.off_fwd_order); a.row_item = at(L.off_row_item); a.fwd_prefix = (long long*)(ws + L.off_fwd_prefix);
     a.key_range = at(L.off_key_range); a.key_span = at(L.off_key_span); a.key_ways = at(L.off_key_ways);
     a.key_order = at(L.off_key_order); a.key_item_base = at(L.off_key_item_base); a.key_slot_base = at(L.off_key_slot_base);
-    a.dkv_counters = at(L.off_dkv_counters);
-    if (L.n_groups <= kSmallGroups && L.n_key_tiles <= kSmallKeyTiles) {
+    a.dkv_counters = at(L.off_dkv_counters); a.dkv_item = at(L.off_dkv_item);
+    a.forward_only = forward_only ? 1 : 0;
+    if (L.n_groups <= kSmallGroups && L.n_key_tiles <= kSmallKeyTiles && d.n_docs <= kCuLds) {
         plan_small_kernel<<<1, 1024, 0, stream>>>(a);
     } else {
         const int order_blocks = (L.n_fwd_tiles + kOrderPerBlock - 1) / kOrderPerBlock;
         plan_rows_kernel<<<(L.n_groups + 3) / 4, 256, 0, stream>>>(a);
         plan_ranges_kernel<<<order_blocks + (L.n_key_tiles + 15) / 16, 1024, 0, stream>>>(a, order_blocks);
-        plan_key_items_kernel<<<(L.n_key_tiles + kOrderPerBlock - 1) / kOrderPerBlock, 1024, 0, stream>>>(a);
+        if (!forward_only) plan_key_items_kernel<<<(L.n_key_tiles + kOrderPerBlock - 1) / kOrderPerBlock, 1024, 0, stream>>>(a);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(WLB_ERR_HIP, "plan launch: %s", hipGetErrorString(e));
@@ -598,7 +610,7 @@ extern "C" wlb_status wlb_attn_plan(const wlb_attn_desc* desc, const int32_t* q_
     plan_layout(*desc, &L);
     if (workspace_bytes < L.plan_bytes)
         return fail(WLB_ERR_BUFFER_TOO_SMALL, "wlb_attn_plan: workspace %zu < %zu bytes", workspace_bytes, L.plan_bytes);
-    return launch_plan(*desc, L, q_idx, cu_seqlens_k, (char*)workspace, stream);
+    return launch_plan(*desc, L, q_idx, cu_seqlens_k, (char*)workspace, false, stream);
 }
 
 extern "C" wlb_status wlb_attn_fwd(const wlb_attn_desc* desc, const void* q, const void* k, const void* v,
@@ -614,7 +626,7 @@ extern "C" wlb_status wlb_attn_fwd(const wlb_attn_desc* desc, const void* q, con
     if (workspace_bytes < need)
         return fail(WLB_ERR_BUFFER_TOO_SMALL, "wlb_attn_fwd: workspace %zu < %zu bytes", workspace_bytes, need);
     if (!reuse)
-        if (wlb_status st = launch_plan(*desc, L, q_idx, cu_seqlens_k, (char*)workspace, stream)) return st;
+        if (wlb_status st = launch_plan(*desc, L, q_idx, cu_seqlens_k, (char*)workspace, false, stream)) return st;
     return launch_fwd(*desc, L, q, k, v, o, lse, (char*)workspace, L.plan_bytes, stream);
 }
 
@@ -639,7 +651,7 @@ extern "C" wlb_status wlb_attn_fwd_static(const wlb_attn_desc* desc, const void*
     char* ws = nullptr;
     if (wlb_status st = static_scratch(&ws)) return st;
     if (!reuse)
-        if (wlb_status st = launch_plan(d, L, q_idx, cu_seqlens_k, ws, stream)) return st;
+        if (wlb_status st = launch_plan(d, L, q_idx, cu_seqlens_k, ws, true, stream)) return st;
     return launch_fwd(d, L, q, k, v, o, lse, ws, L.plan_bytes, stream);
 }
 
@@ -658,6 +670,6 @@ extern "C" wlb_status wlb_attn_bwd(const wlb_attn_desc* desc, const void* q, con
     if (workspace_bytes < need)
         return fail(WLB_ERR_BUFFER_TOO_SMALL, "wlb_attn_bwd: workspace %zu < %zu bytes", workspace_bytes, need);
     if (!reuse)
-        if (wlb_status st = launch_plan(*desc, L, q_idx, cu_seqlens_k, (char*)workspace, stream)) return st;
+        if (wlb_status st = launch_plan(*desc, L, q_idx, cu_seqlens_k, (char*)workspace, false, stream)) return st;
     return launch_bwd(*desc, L, q, k, v, o, lse, d_o, dq, dk, dv, (char*)workspace, L.plan_bytes, stream);
 }
