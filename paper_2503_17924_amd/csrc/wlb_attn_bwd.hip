@@ -45,7 +45,9 @@ struct BwdParams {
     float* partial;
     RowSched sched;            // dQ: which query tiles, heads and key ranges a workgroup works on
     float* row_partial;        // dQ: partial results of the tiles cut at a gang boundary
-    const int32_t* row_item;   // one workgroup per item: {query tile, first, one-past-last key tile, short-hull flag} by order rank
+    const int32_t* row_item;   // one workgroup per item: records (PlanLayout::off_row_item, or off_row_part with row_part_base)
+    const int32_t* row_part_base;     // null: whole tiles only
+    int first_half;                   // see paired_index
     const int32_t* block_hull;   // short-hull path (see dq_short_unit)
     unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of dq_kernel's workgroup
     int n_blocks32, use_short;
@@ -573,13 +575,15 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
     RowPiece pc;
     pc.member = y % G; y /= G;
     pc.hk = y % p.hkv;
-    const int rank = (y / p.hkv) * 8 + x;
-    if (rank >= p.n_tiles) return;
+    const int n_items = p.row_part_base ? ld_const(p.row_part_base + p.n_tiles) : p.n_tiles;
+    int index = (y / p.hkv) * 8 + x;
+    if (index >= n_items) return;
+    index = paired_index(index, n_items, p.first_half);
     // one record holds what the workgroup needs before its first copy: order, hull and flag through separate
     // tables are three dependent loads
-    const int4 item = ld_const4(p.row_item + 4 * rank);
+    const int4 item = ld_const4(p.row_item + 4 * index);
     pc.tile = item.x;
-    if (p.use_short && item.w) {
+    if (p.use_short && item.w == -2) {
         // a short-hull tile: its four blocks of 32 rows are units of their own (see dq_short_unit)
         constexpr int per_tile = kFwdTileRows / kShortBlockRows;
         for (int j = pc.member; j < per_tile; j += G) {
@@ -588,44 +592,74 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
         }
         return;
     }
-    pc.jb = item.y; pc.je = item.z; pc.slot = -1; pc.first = true;
+    pc.jb = item.y; pc.je = item.z;
+    pc.first = item.w < 0 || !(item.w & 1);
+    pc.slot = item.w < 0 ? -1 : (item.w >> 1) * p.hq + pc.hk * G + pc.member;
     dq_piece<D>(p, smem, pc);
 }
 
 // Sums the partial dQ of a query tile that was cut at gang boundaries.  One workgroup per
 // (gang, member): it acts if its gang's last piece is the first part of a tile, and then takes
 // that part and the first piece of every later gang whose (non-empty) share begins inside the tile.
-template <int D>
-__global__ void __launch_bounds__(256) dq_merge_kernel(const BwdParams p) {
-    constexpr int BM = kFwdTileRows, PF = BM * D + 2 * BM, V4 = D / 4;
-    const RowSched& s = p.sched;
-    const int job = (int)blockIdx.x / kMergeSplit, quarter = (int)blockIdx.x % kMergeSplit;
-    const int gang = job / s.G, member = job % s.G;
-    RowCut cut;
-    if (!cut.find(s, gang)) return;
-    const int tile = cut.tile;
-    const int h = cut.hk * s.G + member;
-    auto part = [&](int slot) { return p.row_partial + ((size_t)slot * s.G + member) * PF; };
-    const float* first = part(cut.first_slot());
-    constexpr int CAP = 32;
-    __shared__ int s_slots[CAP], s_count;
-    const int n_later = gather_later_parts<CAP>(cut, s_slots, &s_count);
-    constexpr int PER = BM * V4 / kMergeSplit;
-    for (int e = quarter * PER + threadIdx.x; e < (quarter + 1) * PER; e += 256) {
+template <int D, int SPLIT, class PartOf>
+__device__ __forceinline__ void dq_merge_rows(const BwdParams& p, int tile, int h, int which, int n, PartOf part_of) {
+    constexpr int BM = kFwdTileRows, V4 = D / 4;
+    constexpr int PER = BM * V4 / SPLIT;
+    static_assert(PER % 256 == 0, "whole passes");
+#pragma unroll
+    for (int k = 0; k < PER / 256; ++k) {
+        const int e = which * PER + k * 256 + (int)threadIdx.x;
         const int rl = e / V4, d4 = e % V4;
         const int row = tile * BM + rl;
         if (row >= p.n_q) continue;
         const size_t at = (size_t)rl * D + d4 * 4;
-        f32x4 sum = *reinterpret_cast<const f32x4*>(first + at);
-        if (n_later <= CAP) {
-            for (int i = 0; i < n_later; ++i) sum += *reinterpret_cast<const f32x4*>(part(s_slots[i]) + at);
-        } else {
-            cut.later_parts([&](int slot) { sum += *reinterpret_cast<const f32x4*>(part(slot) + at); });
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+        for (int i0 = 0; i0 < n; i0 += 4) {                      // the loads of four parts together
+            f32x4 x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(part_of(min(i0 + i, n - 1)) + at);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (i0 + i < n) sum += x[i];
         }
         const bool real = p.row_hi[row] > 0;
         *reinterpret_cast<bf16x4*>(p.dq + ((size_t)row * p.hq + h) * D + d4 * 4) =
             real ? pack4(sum[0] * p.scale, sum[1] * p.scale, sum[2] * p.scale, sum[3] * p.scale) : pack4(0.f, 0.f, 0.f, 0.f);
     }
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) dq_merge_kernel(const BwdParams p) {
+    constexpr int BM = kFwdTileRows, PF = BM * D + 2 * BM;
+    const RowSched& s = p.sched;
+    const int job = (int)blockIdx.x / kGangMergeSplit, which = (int)blockIdx.x % kGangMergeSplit;
+    const int gang = job / s.G, member = job % s.G;
+    RowCut cut;
+    if (!cut.find(s, gang)) return;
+    auto part = [&](int slot) { return p.row_partial + ((size_t)slot * s.G + member) * PF; };
+    constexpr int CAP = 32;
+    __shared__ int s_slots[CAP], s_count;
+    const int n_later = gather_later_parts<CAP>(cut, s_slots, &s_count);
+    dq_merge_rows<D, kGangMergeSplit>(p, cut.tile, cut.hk * s.G + member, which, n_later + 1, [&](int i) __attribute__((always_inline)) {
+        int slot = cut.first_slot();
+        if (i > 0 && n_later <= CAP) slot = s_slots[i - 1];
+        else if (i > 0) cut.later_parts([&](int later) { if (--i == 0) slot = later; });
+        return part(slot);
+    });
+}
+
+// The same for tiles divided into parts: the tile of order rank job / hq, if it is one of them.
+template <int D>
+__global__ void __launch_bounds__(256) dq_merge_parts_kernel(const BwdParams p) {
+    constexpr int PF = kFwdTileRows * D + 2 * kFwdTileRows;
+    const int job = (int)blockIdx.x / kMergeSplit, which = (int)blockIdx.x % kMergeSplit;
+    const int rank = job / p.hq, h = job % p.hq;
+    const int base = ld_const(p.row_part_base + rank), n = ld_const(p.row_part_base + rank + 1) - base;
+    if (n < 2) return;
+    const float* first = p.row_partial + ((size_t)base * p.hq + h) * PF;
+    dq_merge_rows<D, kMergeSplit>(p, ld_const(p.sched.order + rank), h, which, n, [&](int i) __attribute__((always_inline)) {
+        return first + (size_t)i * p.hq * PF;
+    });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1044,7 +1078,7 @@ __global__ void __launch_bounds__(256) dkv_fixup_kernel(const BwdParams p) {
     constexpr int BNK = kBwdKeyTile;
     // the item counters of the dK/dV launch that has just finished go back to zero for the next one
     if (blockIdx.x == 0 && threadIdx.x < kLists) p.dkv_counters[threadIdx.x] = 0;
-    const int job = (int)blockIdx.x / kMergeSplit, quarter = (int)blockIdx.x % kMergeSplit;
+    const int job = (int)blockIdx.x / kMergeSplit, which = (int)blockIdx.x % kMergeSplit;
     const int hk = job % p.hkv, r = job / p.hkv;
     const int kt = p.key_order[r];
     const int ways = p.key_ways[kt];
@@ -1058,7 +1092,7 @@ __global__ void __launch_bounds__(256) dkv_fixup_kernel(const BwdParams p) {
     auto sum_parts = [&](auto parts_tag) __attribute__((always_inline)) {
         constexpr int W = decltype(parts_tag)::value, U = PER / 256 < 4 ? PER / 256 : 4;
         static_assert(PER % (U * 256) == 0, "elements per thread");
-        for (int e0 = quarter * PER + (int)threadIdx.x; e0 < (quarter + 1) * PER; e0 += U * 256) {
+        for (int e0 = which * PER + (int)threadIdx.x; e0 < (which + 1) * PER; e0 += U * 256) {
             f32x4 sum[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1076,10 +1110,10 @@ __global__ void __launch_bounds__(256) dkv_fixup_kernel(const BwdParams p) {
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int e = e0 + u * 256, which = e / (BNK * V4), rem = e % (BNK * V4);
+                const int e = e0 + u * 256, grad = e / (BNK * V4), rem = e % (BNK * V4);
                 const int key = rem / V4, d4 = rem % V4;
-                const float f = which == 0 ? p.scale : 1.0f;
-                __bf16* op = (which == 0 ? p.dk : p.dv) + ((size_t)(k0 + key) * p.hkv + hk) * D + d4 * 4;
+                const float f = grad == 0 ? p.scale : 1.0f;
+                __bf16* op = (grad == 0 ? p.dk : p.dv) + ((size_t)(k0 + key) * p.hkv + hk) * D + d4 * 4;
                 if (key < nk) *reinterpret_cast<bf16x4*>(op) = pack4(sum[u][0] * f, sum[u][1] * f, sum[u][2] * f, sum[u][3] * f);
             }
         }
@@ -1117,7 +1151,10 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.sched.prefix = (const long long*)(ws + L.off_fwd_prefix);
     p.sched.order = (const int32_t*)(ws + L.off_fwd_order);
     p.sched.tile_first = (const int32_t*)(ws + L.off_tile_first);
-    p.row_item = (const int32_t*)(ws + L.off_row_item);
+    const bool parts = use_row_parts(d, L);
+    p.first_half = compute_units() / d.hq;
+    p.row_item = (const int32_t*)(ws + (parts ? L.off_row_part : L.off_row_item));
+    p.row_part_base = parts ? (const int32_t*)(ws + L.off_row_part_base) : nullptr;
     p.sched.n_tiles = L.n_fwd_tiles; p.sched.hkv = d.hkv; p.sched.G = d.hq / d.hkv; p.sched.n_gangs = L.row_gangs;
     gang_weights(1, p.sched.weight);
     p.row_partial = (float*)((char*)p.partial + dkv_partial_bytes(d, L));
@@ -1134,7 +1171,8 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     const size_t delta_split = std::max<size_t>(1, std::min(tile_iters, (8 * (size_t)compute_units() + L.n_fwd_tiles - 1) / L.n_fwd_tiles));
     const unsigned grid_delta = (unsigned)(delta_split * L.n_fwd_tiles);
     const unsigned grid_dq = (unsigned)L.row_gangs * (unsigned)(d.hq / d.hkv);
-    const unsigned grid_dq_items = (unsigned)((L.n_fwd_tiles + 7) / 8) * 8u * (unsigned)d.hq;
+    const unsigned grid_dq_items = (unsigned)((L.n_fwd_tiles + (parts ? row_parts_added(d, L) : 0) + 7) / 8) * 8u * (unsigned)d.hq;
+    const unsigned grid_dq_parts = (unsigned)std::min(L.n_fwd_tiles, row_parts_added(d, L)) * (unsigned)d.hq * kMergeSplit;
     const bool gangs = use_row_gangs(d, L);
     // one workgroup per compute unit, each taking item after item
     const unsigned grid_dkv = (unsigned)std::min(L.dkv_max_items, compute_units());   // one workgroup per compute unit, each taking item after item
@@ -1147,9 +1185,10 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
         constexpr int D = decltype(dtag)::value;
         if (do_dq && gangs) {
             dq_kernel<D><<<grid_dq, 256, 0, stream>>>(p);
-            dq_merge_kernel<D><<<grid_dq * kMergeSplit, 256, 0, stream>>>(p);
+            dq_merge_kernel<D><<<grid_dq * kGangMergeSplit, 256, 0, stream>>>(p);
         } else if (do_dq) {
             dq_items_kernel<D><<<grid_dq_items, 256, 0, stream>>>(p);
+            if (parts) dq_merge_parts_kernel<D><<<grid_dq_parts, 256, 0, stream>>>(p);
         } else if (do_delta) {
             delta_kernel<D><<<grid_delta, 256, 0, stream>>>(p);
         }

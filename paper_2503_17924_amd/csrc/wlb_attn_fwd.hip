@@ -14,6 +14,7 @@
 // reads.  K and V tiles of 64 keys are copied global->LDS asynchronously, double buffered.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "wlb_device.h"
@@ -27,7 +28,9 @@ struct FwdParams {
     const int32_t* row_lo; const int32_t* row_hi;
     RowSched sched;            // which query tiles, heads and key ranges a workgroup works on
     float* partial;            // partial results of the tiles cut at a gang boundary
-    const int32_t* row_item;   // one workgroup per item: {query tile, first, one-past-last key tile, short-hull flag} by order rank
+    const int32_t* row_item;   // one workgroup per item: records (PlanLayout::off_row_item, or off_row_part with row_part_base)
+    const int32_t* row_part_base;     // null: whole tiles only
+    int first_half;                   // see paired_index
     const int32_t* block_hull;   // short-hull path (see fwd_short_unit)
     unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of a gang kernel's workgroup
     int n_q, t_kv, hq, hkv, n_tiles, n_blocks32, use_short;
@@ -536,13 +539,15 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
     RowPiece pc;
     pc.member = y % G; y /= G;
     pc.hk = y % p.hkv;
-    const int rank = (y / p.hkv) * 8 + x;
-    if (rank >= p.n_tiles) return;
+    const int n_items = p.row_part_base ? ld_const(p.row_part_base + p.n_tiles) : p.n_tiles;
+    int index = (y / p.hkv) * 8 + x;
+    if (index >= n_items) return;
+    index = paired_index(index, n_items, p.first_half);
     // one record holds what the workgroup needs before its first copy: order, hull and flag through separate
     // tables are three dependent loads
-    const int4 item = ld_const4(p.row_item + 4 * rank);
+    const int4 item = ld_const4(p.row_item + 4 * index);
     pc.tile = item.x;
-    if (p.use_short && item.w) {
+    if (p.use_short && item.w == -2) {
         // a short-hull tile: its four blocks of 32 rows are units of their own, each for all heads of the
         // KV head; the tile's workgroups of this KV head share them out by member
         constexpr int per_tile = kFwdTileRows / kShortBlockRows;
@@ -552,7 +557,9 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
         }
         return;
     }
-    pc.jb = item.y; pc.je = item.z; pc.slot = -1; pc.first = true;
+    pc.jb = item.y; pc.je = item.z;
+    pc.first = item.w < 0 || !(item.w & 1);
+    pc.slot = item.w < 0 ? -1 : (item.w >> 1) * p.hq + pc.hk * G + pc.member;
     fwd_piece<D>(p, smem, pc);
 }
 
@@ -561,49 +568,47 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
 // that part and the following gangs' first pieces.  With reference exponents e_i (log2 units), row
 // sums l_i and accumulators A_i:  E = max e_i,  L = sum l_i 2^(e_i - E),  O = sum A_i 2^(e_i - E) / L,
 // LSE = (E + log2 L) ln 2.
-template <int D>
-__global__ void __launch_bounds__(256) fwd_merge_kernel(const FwdParams p) {
-    constexpr int BM = kFwdTileRows, PF = BM * D + 2 * BM, V4 = D / 4;
-    const RowSched& s = p.sched;
-    // kMergeSplit workgroups share a tile's rows: the work is a few dependent loads per element, so
-    // the launch needs many wavefronts in flight rather than long loops
-    const int job = (int)blockIdx.x / kMergeSplit, quarter = (int)blockIdx.x % kMergeSplit;
-    const int gang = job / s.G, member = job % s.G;
-    RowCut cut;
-    if (!cut.find(s, gang)) return;
-    const int tile = cut.tile;
-    const int h = cut.hk * s.G + member;
-    auto part = [&](int slot) { return p.partial + ((size_t)slot * s.G + member) * PF; };
-    const float* first = part(cut.first_slot());
-    constexpr int CAP = 32;
-    __shared__ int s_slots[CAP], s_count;
-    const int n_later = gather_later_parts<CAP>(cut, s_slots, &s_count);
-    auto later_parts = [&](auto f) __attribute__((always_inline)) {
-        if (n_later <= CAP) {
-            for (int i = 0; i < n_later; ++i) f(part(s_slots[i]));
-        } else {
-            cut.later_parts([&](int slot) { f(part(slot)); });
-        }
-    };
-    constexpr int PER = BM * V4 / kMergeSplit;
-    for (int e = quarter * PER + threadIdx.x; e < (quarter + 1) * PER; e += 256) {
+// 1 / SPLIT of a tile's rows; part_of(i) points to the i-th of its n parts.  A piece of work that is a few dependent
+// loads per element: the loads of four parts are requested together (a running maximum joins the fours), and the launch
+// needs many wavefronts in flight rather than long loops.
+template <int D, int SPLIT, class PartOf>
+__device__ __forceinline__ void fwd_merge_rows(const FwdParams& p, int tile, int h, int which, int n, PartOf part_of) {
+    constexpr int BM = kFwdTileRows, V4 = D / 4;
+    constexpr int PER = BM * V4 / SPLIT;
+    static_assert(PER % 256 == 0, "whole passes");
+#pragma unroll
+    for (int k = 0; k < PER / 256; ++k) {
+        const int e = which * PER + k * 256 + (int)threadIdx.x;
         const int rl = e / V4, d4 = e % V4;
         const int row = tile * BM + rl;
         if (row >= p.n_q) continue;
-        float E = first[BM * D + BM + rl];
-        later_parts([&](const float* pp) { E = fmaxf(E, pp[BM * D + BM + rl]); });
-        float L = 0.f;
+        float E = -INFINITY, L = 0.f;
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
-        auto add = [&](const float* pp) __attribute__((always_inline)) {
-            const float ei = pp[BM * D + BM + rl];
-            if (ei == -INFINITY) return;
-            const float wgt = fast_exp2(ei - E);
-            L += wgt * pp[BM * D + rl];
-            o += wgt * *reinterpret_cast<const f32x4*>(pp + (size_t)rl * D + d4 * 4);
-        };
-        if (E > -INFINITY) {
-            add(first);
-            later_parts(add);
+        for (int i0 = 0; i0 < n; i0 += 4) {
+            float ei[4], li[4];
+            f32x4 x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float* pp = part_of(min(i0 + i, n - 1));
+                ei[i] = pp[BM * D + BM + rl];
+                li[i] = pp[BM * D + rl];
+                x[i] = *reinterpret_cast<const f32x4*>(pp + (size_t)rl * D + d4 * 4);
+            }
+            float top = E;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) top = fmaxf(top, ei[i]);
+            if (top == -INFINITY) continue;                      // no key seen so far
+            const float keep = E == -INFINITY ? 0.f : fast_exp2(E - top);
+            E = top;
+            L *= keep;
+            o *= keep;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (i0 + i >= n || ei[i] == -INFINITY) continue;
+                const float wgt = fast_exp2(ei[i] - top);
+                L += wgt * li[i];
+                o += wgt * x[i];
+            }
         }
         const bool live = p.row_hi[row] > 0 && L > 0.f;
         const float inv = live ? 1.0f / L : 0.f;
@@ -611,6 +616,40 @@ __global__ void __launch_bounds__(256) fwd_merge_kernel(const FwdParams p) {
             live ? pack4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv) : pack4(0.f, 0.f, 0.f, 0.f);
         if (d4 == 0) p.lse[(size_t)h * p.n_q + row] = live ? (E + __log2f(L)) * 0.6931471805599453f : -INFINITY;
     }
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) fwd_merge_kernel(const FwdParams p) {
+    constexpr int BM = kFwdTileRows, PF = BM * D + 2 * BM;
+    const RowSched& s = p.sched;
+    const int job = (int)blockIdx.x / kGangMergeSplit, which = (int)blockIdx.x % kGangMergeSplit;
+    const int gang = job / s.G, member = job % s.G;
+    RowCut cut;
+    if (!cut.find(s, gang)) return;
+    auto part = [&](int slot) { return p.partial + ((size_t)slot * s.G + member) * PF; };
+    constexpr int CAP = 32;
+    __shared__ int s_slots[CAP], s_count;
+    const int n_later = gather_later_parts<CAP>(cut, s_slots, &s_count);
+    fwd_merge_rows<D, kGangMergeSplit>(p, cut.tile, cut.hk * s.G + member, which, n_later + 1, [&](int i) __attribute__((always_inline)) {
+        int slot = cut.first_slot();
+        if (i > 0 && n_later <= CAP) slot = s_slots[i - 1];
+        else if (i > 0) cut.later_parts([&](int later) { if (--i == 0) slot = later; });
+        return part(slot);
+    });
+}
+
+// The same for tiles divided into parts: the tile of order rank job / hq, if it is one of them.
+template <int D>
+__global__ void __launch_bounds__(256) fwd_merge_parts_kernel(const FwdParams p) {
+    constexpr int PF = kFwdTileRows * D + 2 * kFwdTileRows;
+    const int job = (int)blockIdx.x / kMergeSplit, which = (int)blockIdx.x % kMergeSplit;
+    const int rank = job / p.hq, h = job % p.hq;
+    const int base = ld_const(p.row_part_base + rank), n = ld_const(p.row_part_base + rank + 1) - base;
+    if (n < 2) return;
+    const float* first = p.partial + ((size_t)base * p.hq + h) * PF;
+    fwd_merge_rows<D, kMergeSplit>(p, ld_const(p.sched.order + rank), h, which, n, [&](int i) __attribute__((always_inline)) {
+        return first + (size_t)i * p.hq * PF;
+    });
 }
 
 wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q, const void* k,
@@ -624,7 +663,10 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.sched.prefix = (const long long*)(ws + L.off_fwd_prefix);
     p.sched.order = (const int32_t*)(ws + L.off_fwd_order);
     p.sched.tile_first = (const int32_t*)(ws + L.off_tile_first);
-    p.row_item = (const int32_t*)(ws + L.off_row_item);
+    const bool parts = use_row_parts(d, L);
+    p.first_half = compute_units() / d.hq;
+    p.row_item = (const int32_t*)(ws + (parts ? L.off_row_part : L.off_row_item));
+    p.row_part_base = parts ? (const int32_t*)(ws + L.off_row_part_base) : nullptr;
     p.sched.n_tiles = L.n_fwd_tiles; p.sched.hkv = d.hkv; p.sched.G = d.hq / d.hkv; p.sched.n_gangs = L.row_gangs;
     gang_weights(0, p.sched.weight);
     p.partial = (float*)(ws + off_row_partial);
@@ -640,15 +682,22 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
         const unsigned grid = (unsigned)L.row_gangs * (unsigned)(d.hq / d.hkv);
         if (d.head_dim == 128) {
             fwd_kernel<128><<<grid, 256, 0, stream>>>(p);
-            fwd_merge_kernel<128><<<grid * kMergeSplit, 256, 0, stream>>>(p);
+            fwd_merge_kernel<128><<<grid * kGangMergeSplit, 256, 0, stream>>>(p);
         } else {
             fwd_kernel<64><<<grid, 256, 0, stream>>>(p);
-            fwd_merge_kernel<64><<<grid * kMergeSplit, 256, 0, stream>>>(p);
+            fwd_merge_kernel<64><<<grid * kGangMergeSplit, 256, 0, stream>>>(p);
         }
     } else {
-        const unsigned grid = (unsigned)((L.n_fwd_tiles + 7) / 8) * 8u * (unsigned)d.hq;
-        if (d.head_dim == 128) fwd_items_kernel<128><<<grid, 256, 0, stream>>>(p);
-        else fwd_items_kernel<64><<<grid, 256, 0, stream>>>(p);
+        const int items = L.n_fwd_tiles + (parts ? row_parts_added(d, L) : 0);
+        const unsigned grid = (unsigned)((items + 7) / 8) * 8u * (unsigned)d.hq;
+        const unsigned grid_merge = (unsigned)std::min(L.n_fwd_tiles, row_parts_added(d, L)) * (unsigned)d.hq * kMergeSplit;
+        if (d.head_dim == 128) {
+            fwd_items_kernel<128><<<grid, 256, 0, stream>>>(p);
+            if (parts) fwd_merge_parts_kernel<128><<<grid_merge, 256, 0, stream>>>(p);
+        } else {
+            fwd_items_kernel<64><<<grid, 256, 0, stream>>>(p);
+            if (parts) fwd_merge_parts_kernel<64><<<grid_merge, 256, 0, stream>>>(p);
+        }
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(WLB_ERR_HIP, "forward launch: %s", hipGetErrorString(e));

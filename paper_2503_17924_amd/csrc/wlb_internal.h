@@ -32,13 +32,19 @@ constexpr int kDkvSplit = WLB_DKV_SPLIT;      // a dK/dV item is at most 1/kDkvS
 #define WLB_DKV_MIN_ITEM_STAGES 32
 #endif
 constexpr int kDkvMinItemStages = WLB_DKV_MIN_ITEM_STAGES;   // items this short are never split further
-constexpr int kMergeSplit = 4;     // workgroups per cut query tile and head in the merge kernels (rows split evenly)
+// workgroups per cut query tile and head in the merge kernels, and per key tile and KV head in the dK/dV fix-up (rows
+// split evenly); the gangs' merges, where finding a tile's parts costs more than summing them, take fewer
+constexpr int kMergeSplit = 8, kGangMergeSplit = 4;
 
 // The public layout and the tables only the library's own kernels read.
 struct PlanLayout : wlb_plan_layout {
     size_t off_key_span;       // int32 [n_key_tiles]: groups in the key tile's range
     size_t off_tile_first;     // int32 [n_fwd_tiles]: first 64-key tile the query tile visits
-    size_t off_row_item;       // int32 [n_fwd_tiles][4], by order rank: {query tile, first, one-past-last 64-key tile, short-hull flag}
+    // Work records of the one-workgroup-per-item launches: {query tile, first, one-past-last 64-key tile, code}, code = -1:
+    // a whole tile, -2: a whole short-hull tile, else 2 * partial slot + (1: not the tile's first part)
+    size_t off_row_item;       // int32 [n_fwd_tiles][4], by order rank: whole tiles only
+    size_t off_row_part;       // int32 [n_fwd_tiles + row_parts_added(..)][4]: heavy tiles divided into parts (row_part_limit), by rank, a tile's parts in turn
+    size_t off_row_part_base;  // int32 [n_fwd_tiles + 1]: parts before the tile of order rank r
     // Last, because a forward's schedule (wlb_attn_fwd_static) leaves it out.
     size_t off_dkv_item;       // int32 [dkv_max_items][8], by item: {key tile, KV head, first query head, query heads, partial slot or -1,
                                // first row group, stages, 0}
@@ -54,6 +60,13 @@ inline int row_gangs(int hq, int hkv, int cus) {
     const int per_xcd = (2 * cus / kLists) / (hq / hkv);
     return kLists * (per_xcd > 0 ? per_xcd : 1);
 }
+// Division of heavy query tiles along their keys, for launches with few items: a part holds at most kRowPartMean / 4
+// of the mean work of a workgroup slot (4 / 4, 6 / 4, 8 / 4 measured at 4095 rows, 16 heads: forward + dQ 218, 203 and
+// 229 us; undivided 247) and at most kRowPartMin key tiles where that is less (4 - 12: within 1 us at 2052 rows).
+constexpr int kRowPartMin = 6, kRowPartMean = 6;
+bool use_row_parts(const wlb_attn_desc& d, const PlanLayout& L);
+// upper bound of the number of divided tiles, and of the parts they add (each is at least a slot's mean work)
+inline int row_parts_added(const wlb_attn_desc& d, const PlanLayout& L) { return L.row_gangs * (d.hq / d.hkv) / d.hq; }
 // fixed cost of a query tile (loading Q, the first copies, the output) in units of one key tile's work
 constexpr int kRowItemOverhead = 6;
 // Default relative work share (percent) of a gang of the first half of a launch; a gang of the second half
@@ -70,6 +83,11 @@ void gang_weights(int kernel, int out[2][8]);
 // WLB_ATTN_SCHEDULE_* flags override.
 constexpr int kRowGangMaxItemsPerSlot = 3;
 constexpr int kRowGangMinUnitsPerSlot = 64;
+// Query tiles are divided into parts (use_row_parts) when the items fill at most a quarter of the workgroup slots, or
+// when they hold this many units on average: the launch that merges the parts takes 5 us, which at 18 units per item
+// (8191 tokens, 8 heads: forward 43 us) is more than the better balance returns (47 us), at 39 (4095 rows of a
+// 16K-token micro-batch, 16 heads) a third of it (106 -> 89 us).
+constexpr int kRowPartMeanUnits = 24;
 bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L);
 // whether this launch sends short-hull query tiles to the short-hull kernels (only in the
 // one-workgroup-per-item schedule; WLB_ATTN_NO_SHORT_PATH switches it off)

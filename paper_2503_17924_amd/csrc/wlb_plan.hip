@@ -10,6 +10,7 @@
 // wholly in other documents cost nothing (the tile-level waste described in Section 5.2).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -57,18 +58,30 @@ size_t dkv_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L) {
     return (size_t)L.dkv_max_partials * (2 * (size_t)kBwdKeyTile * d.head_dim * sizeof(float));
 }
 
+// Units (key tiles and the fixed cost) of an item, on average: from the caller's pair count when it gave one (a tile of
+// 128 rows x 64 keys holds 8192 pairs), else from the mean document length (a tile sees about half its document:
+// length / 128 key tiles), since the host does not see the mask.
+static long long mean_item_units(const wlb_attn_desc& d, const PlanLayout& L) {
+    return (d.visible_pairs > 0 ? d.visible_pairs / ((long long)L.n_fwd_tiles * kFwdTileRows * 64)
+                                : (long long)(d.t_kv / d.n_docs / (2 * 64))) + kRowItemOverhead;
+}
+
 bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L) {
     if (d.flags & WLB_ATTN_SCHEDULE_GANGS) return true;
     if (d.flags & WLB_ATTN_SCHEDULE_ITEMS) return false;
     const long long items = (long long)L.n_fwd_tiles * d.hq, slots = 2LL * compute_units();
     if (items >= (long long)kRowGangMaxItemsPerSlot * slots) return false;
-    // and only when a slot's share is worth cutting tiles for.  The work line's length in key tiles per item:
-    // from the caller's pair count when it gave one (a tile of 128 rows x 64 keys holds 8192 pairs), else
-    // estimated from the mean document length (a tile sees about half its document: length / 128 key tiles),
-    // since the host does not see the mask
-    const long long per_item = (d.visible_pairs > 0 ? d.visible_pairs / ((long long)L.n_fwd_tiles * kFwdTileRows * 64)
-                                                    : (long long)(d.t_kv / d.n_docs / (2 * 64))) + kRowItemOverhead;
-    return items * per_item >= (long long)kRowGangMinUnitsPerSlot * slots;
+    // and only when a slot's share is worth cutting tiles for
+    return items * mean_item_units(d, L) >= (long long)kRowGangMinUnitsPerSlot * slots;
+}
+
+// Parts of tiles, in launches with few items per slot whose shares are too short for the gangs: when the items fill at
+// most a quarter of the slots, or when they are long enough for the merge launch to pay off.
+bool use_row_parts(const wlb_attn_desc& d, const PlanLayout& L) {
+    if ((d.flags & WLB_ATTN_SCHEDULE_ITEMS) || use_row_gangs(d, L) || row_parts_added(d, L) < 1) return false;
+    const long long items = (long long)L.n_fwd_tiles * d.hq, slots = 2LL * compute_units();
+    if (items >= (long long)kRowGangMaxItemsPerSlot * slots) return false;
+    return items * 4 <= slots || mean_item_units(d, L) >= kRowPartMeanUnits;
 }
 
 // gang share weights: process-wide, set by wlb_attn_set_gang_weights (0 = not set: the defaults)
@@ -127,6 +140,8 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
     L->static_bytes = off;
     L->off_tile_first = take(sizeof(int32_t) * L->n_fwd_tiles);
     L->off_row_item = take(sizeof(int32_t) * 4 * L->n_fwd_tiles);
+    L->off_row_part_base = take(sizeof(int32_t) * (L->n_fwd_tiles + 1));
+    L->off_row_part = take(sizeof(int32_t) * 4 * (size_t)(L->n_fwd_tiles + row_parts_added(d, *L)));
     L->off_dkv_item = take(sizeof(int32_t) * 8 * (size_t)L->dkv_max_items);
     L->plan_bytes = off;
 }
@@ -137,9 +152,9 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
 // Everything the schedule kernels read and write.
 struct PlanArgs {
     const int32_t* q_idx; const int32_t* cu;
-    int n_q, t_kv, n_docs, n_groups, n_tiles, n_key_tiles, hq, hkv, n_slots, forward_only;
+    int n_q, t_kv, n_docs, n_groups, n_tiles, n_key_tiles, hq, hkv, n_slots, row_slots, forward_only;
     int32_t* row_lo; int32_t* row_hi; int32_t* group; int32_t* group_real; int32_t* block_hull;
-    int32_t* fwd_cost; int32_t* tile_first; int32_t* tile_short; int32_t* fwd_order; int32_t* row_item;
+    int32_t* fwd_cost; int32_t* tile_first; int32_t* tile_short; int32_t* fwd_order; int32_t* row_item; int32_t* row_part; int32_t* row_part_base;
     long long* fwd_prefix;
     int32_t* key_range; int32_t* key_span; int32_t* key_ways; int32_t* key_order; int32_t* key_item_base; int32_t* key_slot_base;
     int32_t* dkv_item; int32_t* dkv_counters;
@@ -235,13 +250,32 @@ __device__ __forceinline__ int2 item_split(int span, int G, int limit) {
     return make_int2(span * heads, w);
 }
 
+// A query tile with more key tiles than this is divided (equally) among parts that have at most as many.
+__device__ __forceinline__ int row_part_limit(long long total_cost, const PlanArgs& a) {
+    const unsigned long long units = ((unsigned long long)total_cost + (unsigned long long)a.n_tiles * kRowItemOverhead) * a.hq;
+    return (int)min(max((unsigned long long)kRowPartMin, (units * kRowPartMean / 4 + a.row_slots - 1) / a.row_slots), 0x7fffffffull);
+}
+__device__ __forceinline__ int row_parts(int cost, int limit) { return cost > limit ? (cost + limit - 1) / limit : 1; }
+
 // Where a tile stands in its order (heaviest first, ties by index), and sums over the tiles before it.
-__device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cost, int first, int is_short, int rank, long long cost_before) {
+__device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cost, int first, int is_short, int parts, int rank,
+                                               long long cost_before, int parts_before) {
     const long long before = cost_before + (long long)rank * kRowItemOverhead;
     a.fwd_order[rank] = i;
     a.fwd_prefix[rank] = before;
-    reinterpret_cast<int4*>(a.row_item)[rank] = make_int4(i, first, first + cost, is_short);
-    if (rank == a.n_tiles - 1) a.fwd_prefix[a.n_tiles] = before + cost + kRowItemOverhead;
+    const int4 whole = make_int4(i, first, first + cost, is_short ? -2 : -1);
+    reinterpret_cast<int4*>(a.row_item)[rank] = whole;
+    int4* part = reinterpret_cast<int4*>(a.row_part) + parts_before;
+    if (parts == 1) part[0] = whole;
+    else
+        for (int k = 0; k < parts; ++k)        // divided tiles come first, so a part's index is its partial slot as well
+            part[k] = make_int4(i, first + (int)((long long)cost * k / parts), first + (int)((long long)cost * (k + 1) / parts),
+                                2 * (parts_before + k) + (k > 0));
+    a.row_part_base[rank] = parts_before;
+    if (rank == a.n_tiles - 1) {
+        a.fwd_prefix[a.n_tiles] = before + cost + kRowItemOverhead;
+        a.row_part_base[a.n_tiles] = parts_before + parts;
+    }
 }
 __device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 range, int ways, int rank, int items_before, int slots_before) {
     a.key_ways[i] = ways;
@@ -330,10 +364,10 @@ __device__ __forceinline__ void order_block(int n, int block, ItemOf item_of, Pu
         put(i, own, mine);
     }
 }
-struct RowCounts {                 // query tiles before this one, and their cost
-    int rank; long long cost;
-    __device__ __forceinline__ void add(int c, int) { rank += 1; cost += c; }
-    __device__ __forceinline__ void join(const RowCounts& o) { rank += o.rank; cost += o.cost; }
+struct RowCounts {                 // query tiles before this one, their cost and their parts
+    int rank, parts; long long cost;
+    __device__ __forceinline__ void add(int c, int n) { rank += 1; parts += n; cost += c; }
+    __device__ __forceinline__ void join(const RowCounts& o) { rank += o.rank; parts += o.parts; cost += o.cost; }
 };
 struct KeyCounts {                 // key tiles before this one, and their items and partial slots for one KV head
     int rank, items, slots;
@@ -341,13 +375,30 @@ struct KeyCounts {                 // key tiles before this one, and their items
     __device__ __forceinline__ void join(const KeyCounts& o) { rank += o.rank; items += o.items; slots += o.slots; }
 };
 
+// Sum over the elements of value_of, for every thread of a workgroup of 1024; s_total is shared.
+template <class ValueOf>
+__device__ __forceinline__ long long block_sum(int n, long long* s_total, ValueOf value_of) {
+    if (threadIdx.x == 0) *s_total = 0;
+    __syncthreads();
+    long long sum = 0;
+    for (int i = threadIdx.x; i < n; i += 1024) sum += value_of(i);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if ((threadIdx.x & 63) == 0 && sum) atomicAdd((unsigned long long*)s_total, (unsigned long long)sum);
+    __syncthreads();
+    return *s_total;
+}
+
 // Second launch: workgroups [0, order_blocks) order the query tiles; the others find, one wavefront per key tile,
 // the groups whose hull touches it.
 __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int order_blocks) {
+    __shared__ long long s_total;
     if ((int)blockIdx.x < order_blocks) {
-        order_block<RowCounts>(a.n_tiles, blockIdx.x, [&](int j) { return make_int2(a.fwd_cost[j], 0); },
+        const int limit = row_part_limit(block_sum(a.n_tiles, &s_total, [&](int t) { return a.fwd_cost[t]; }), a);
+        order_block<RowCounts>(a.n_tiles, blockIdx.x,
+                               [&](int j) { const int cost = a.fwd_cost[j]; return make_int2(cost, row_parts(cost, limit)); },
                                [&](int i, int2 own, const RowCounts& c) {
-                                   put_query_tile(a, i, own.x, a.tile_first[i], a.tile_short[i], c.rank, c.cost);
+                                   put_query_tile(a, i, own.x, a.tile_first[i], a.tile_short[i], own.y, c.rank, c.cost, c.parts);
                                });
         return;
     }
@@ -376,17 +427,9 @@ __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int
 // heads per item).
 __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) {
     __shared__ long long s_total;
-    if (threadIdx.x == 0) s_total = 0;
     if (blockIdx.x == 0 && threadIdx.x < kLists) a.dkv_counters[threadIdx.x] = 0;
-    __syncthreads();
-    long long sum = 0;
-    for (int kt = threadIdx.x; kt < a.n_key_tiles; kt += 1024) sum += a.key_span[kt];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if ((threadIdx.x & 63) == 0 && sum) atomicAdd((unsigned long long*)&s_total, (unsigned long long)sum);
-    __syncthreads();
     const int G = a.hq / a.hkv;
-    const int limit = item_limit(s_total, a.hq, a.n_slots);
+    const int limit = item_limit(block_sum(a.n_key_tiles, &s_total, [&](int kt) { return a.key_span[kt]; }), a.hq, a.n_slots);
     order_block<KeyCounts>(a.n_key_tiles, blockIdx.x, [&](int j) { return item_split(a.key_span[j], G, limit); },
                            [&](int i, int2 own, const KeyCounts& c) {
                                put_key_tile(a, i, make_int2(a.key_range[2 * i], a.key_range[2 * i + 1]), own.y, c.rank, c.items, c.slots);
@@ -460,18 +503,23 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
         static_assert(kSmallTiles == 32 && kGroupsPerTile == 2, "a lane of a half-wavefront per query tile");
         const TileCost own = cost_of(t), other = cost_of(j);
         const bool before = j < a.n_tiles && other.cost > own.cost - (j < t);
-        int rank = before, sum = before ? other.cost : 0;
+        int rank = before, sum = before ? other.cost : 0, total = j < a.n_tiles ? other.cost : 0;
 #pragma unroll
         for (int o = 16; o > 0; o >>= 1) {
             rank += __shfl_xor(rank, o);
             sum += __shfl_xor(sum, o);
+            total += __shfl_xor(total, o);
         }
+        const int limit = row_part_limit(total, a);
+        int parts = before ? row_parts(other.cost, limit) : 0;
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) parts += __shfl_xor(parts, o);
         if (j == 0 && t < a.n_tiles) {
             const int is_short = s_fits[kGroupsPerTile * t] & s_fits[kGroupsPerTile * t + 1];
             a.fwd_cost[t] = own.cost;
             a.tile_first[t] = own.first;
             a.tile_short[t] = is_short;
-            put_query_tile(a, t, own.cost, own.first, is_short, rank, sum);
+            put_query_tile(a, t, own.cost, own.first, is_short, row_parts(own.cost, limit), rank, sum, parts);
         }
     }
     if (a.forward_only) return;
@@ -506,7 +554,9 @@ wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_
     a.row_lo = at(L.off_row_lo); a.row_hi = at(L.off_row_hi);
     a.group = at(L.off_group); a.group_real = at(L.off_group_real); a.block_hull = at(L.off_block_hull);
     a.fwd_cost = at(L.off_fwd_cost); a.tile_first = at(L.off_tile_first); a.tile_short = at(L.off_tile_short);
-    a.fwd_order = at(L.off_fwd_order); a.row_item = at(L.off_row_item); a.fwd_prefix = (long long*)(ws + L.off_fwd_prefix);
+    a.fwd_order = at(L.off_fwd_order); a.row_item = at(L.off_row_item); a.row_part = at(L.off_row_part); a.row_part_base = at(L.off_row_part_base);
+    a.row_slots = std::max(1, row_parts_added(d, L) * d.hq);
+    a.fwd_prefix = (long long*)(ws + L.off_fwd_prefix);
     a.key_range = at(L.off_key_range); a.key_span = at(L.off_key_span); a.key_ways = at(L.off_key_ways);
     a.key_order = at(L.off_key_order); a.key_item_base = at(L.off_key_item_base); a.key_slot_base = at(L.off_key_slot_base);
     a.dkv_counters = at(L.off_dkv_counters); a.dkv_item = at(L.off_dkv_item);
@@ -530,8 +580,9 @@ wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_
 // process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the address
 // that call returns (kept per device) is what kernels and every other use of the memory get.
 // The stated limit counts the tables a schedule had to have when the limit was set (PlanLayout::static_bytes);
-// the tables added since (20 bytes per query tile, at most 2 MiB / 4 bytes per row of them) have room of their own.
-constexpr size_t kStaticExtraBytes = WLB_ATTN_FWD_STATIC_SCRATCH_BYTES / 8 / kFwdTileRows * 20 + 1024;
+// the tables added since (40 bytes per query tile of a schedule with at least 8 bytes per row, and 16 per part added, at most one per workgroup slot)
+// have room of their own.
+constexpr size_t kStaticExtraBytes = WLB_ATTN_FWD_STATIC_SCRATCH_BYTES / 8 / kFwdTileRows * 40 + 1024 * 16 + 2048;
 static __device__ __align__(256) unsigned char scratch[WLB_ATTN_FWD_STATIC_SCRATCH_BYTES + kStaticExtraBytes];
 
 constexpr int kMaxDevices = 64;

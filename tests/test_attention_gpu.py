@@ -183,6 +183,24 @@ def test_both_row_schedules_match_oracle(flag, hq, hkv, d):
         c.check_bwd(f" cp {cp} rank {r}")
 
 
+@pytest.mark.parametrize("docs,hq,hkv,d,cp", [
+    ([384, 385, 1], 2, 1, 128, 1),               # 6 key tiles: whole; 7: two parts, one key tile apart
+    ([5000], 4, 4, 64, 8),                       # rows of two chunks, tiles of 5 - 79 key tiles in many parts
+    ([2600, 3, 700], 6, 2, 128, 2),              # pads, three query heads per KV head
+    ([1500, 40, 9], 32, 8, 64, 1),               # more than one workgroup per compute unit: the second half reversed
+])
+def test_divided_query_tiles_match_oracle(docs, hq, hkv, d, cp):
+    """Launches with few items divide heavy query tiles along their keys and merge the parts (forward, dQ); the tables
+    of the schedule, and the results against the oracle, at the default schedule choice."""
+    w, tens = wl.small_case(78, docs, hq, hkv, d)
+    for r in sorted({0, cp - 1}):
+        sh = osh.shard(docs, cp, r, osh.PER_DOC_PADDED)
+        c = Case(tens, sh["q_idx"], sh["cu_seqlens_k"], hq, hkv, d, w.scale)
+        assert not B.wlb_attn_plan_layout(c.attn.desc).uses_gangs
+        c.check_fwd(f" cp {cp} rank {r}")
+        c.check_bwd(f" cp {cp} rank {r}")
+
+
 def test_gang_share_weights_change_the_cuts_not_the_result():
     """wlb_attn_set_gang_weights: very uneven weights (by half of the launch and by XCD) move the points where
     query tiles are cut between gangs; the results still match the oracle, and the defaults come back."""
