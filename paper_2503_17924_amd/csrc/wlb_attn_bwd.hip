@@ -17,6 +17,7 @@
 //   dkv_kernel        key-stationary: a work item owns 128 keys of one KV head and streams the row
 //                     groups that can see them through LDS for some or all query heads of the KV
 //                     group; dK^T, dV^T stay in registers until the single final store
+//   dkv_short_kernel  the same for key tiles that few rows can see (short documents)
 //   dkv_fixup_kernel  sums the fp32 partial results of key tiles whose heads were divided among
 //                     several work items (heavy tiles, so that no item is a straggler)
 // S and dP are recomputed in both dq_kernel and dkv_kernel (7 GEMMs for the 5 the derivative
@@ -40,6 +41,7 @@ struct BwdParams {
     __bf16* dq; __bf16* dk; __bf16* dv;
     const int32_t* row_lo; const int32_t* row_hi; const int32_t* group; const int32_t* group_real;
     const int32_t* key_order; const int32_t* key_ways; const int32_t* key_item_base; const int32_t* key_slot_base;
+    const int32_t* key_range; const int32_t* general_items;   // short dK/dV kernel (see dkv_short_kernel)
     const int32_t* dkv_item;   // two int4 per item (PlanLayout::off_dkv_item)
     int32_t* dkv_counters;     // [8]: items of each XCD's list handed out so far (zero before every dK/dV launch)
     float* partial;
@@ -50,7 +52,7 @@ struct BwdParams {
     int first_half;                   // see paired_index
     const int32_t* block_hull;   // short-hull path (see dq_short_unit)
     unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of dq_kernel's workgroup
-    int n_blocks32, use_short;
+    int n_blocks32, use_short, short_keys;
     int n_q, t_kv, hq, hkv, n_groups, n_tiles, n_key_tiles;
     float scale_log2e, scale;
 };
@@ -679,7 +681,9 @@ __global__ void __launch_bounds__(256) dq_merge_parts_kernel(const BwdParams p) 
 // A work item is a key tile with all query heads of one KV head, or - for a tile whose work
 // exceeds a threshold set by the schedule - a 1/2, 1/4 or 1/8 of those heads; such an item
 // writes its dK^T / dV^T as an unscaled fp32 partial result instead of the final bf16 rows.
-template <int D>
+// SHORT: the launch runs beside dkv_short_kernel and leaves that kernel's items out (a kernel of its own, because the
+// checks cost the long documents' launches 1 %).
+template <int D, bool SHORT>
 __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     constexpr int BNK = kBwdKeyTile, GR = kGroupRows, KS = D / 16, DB = D / 32, CPR = D / 8;
     constexpr int ROWB = D * 2, TILEB = GR * ROWB, NW = 8, NBUF = 3, PBYTES = 4 * 2 * 2 * 1024;
@@ -699,12 +703,12 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     // one workgroup per item the hardware hands every XCD the same number of them.  (A first item by
     // workgroup index and reading all counters at once near the end measured the same.)
     __shared__ int s_item;
-    const int n_items = ld_const(p.key_item_base + p.n_key_tiles);
+    const int n_items = ld_const(SHORT ? p.general_items : p.key_item_base + p.n_key_tiles);
   for (;;) {
     __syncthreads();              // every wavefront has left the LDS of the item before, and has read s_item
     if (threadIdx.x == 0) {
         int it = -1;
-        for (int k = 0; k < kLists && it < 0; ++k) {
+        for (int k = 0; k < kLists && it < 0 && (!SHORT || n_items > 0); ++k) {
             const int c = ((int)blockIdx.x + k) % kLists;
             const int cand = atomicAdd(p.dkv_counters + c, 1) * kLists + c;
             if (cand < n_items) it = cand;
@@ -717,6 +721,7 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     // one record per item: finding the tile by a search of the item bases and then its tables was a chain of a dozen
     // dependent loads in front of every item
     const int4 rec0 = ld_const4(p.dkv_item + 8 * item), rec1 = ld_const4(p.dkv_item + 8 * item + 4);
+    if (SHORT && rec1.w) continue;
     const int kt = rec0.x, hk = rec0.y, h_first = rec0.z, nh = rec0.w;   // query heads [h_first, h_first + nh)
     const int slot = rec1.x;
     const bool whole = slot < 0;
@@ -1071,6 +1076,216 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
   }   // next item
 }
 
+// dK/dV of key tiles that few rows can see (documents of a few dozen tokens).  There the general kernel walks whole
+// stages of 64 rows x 128 keys of which a third holds visible pairs, and waits for each at a barrier (2.5 us).  Here one
+// workgroup takes a key tile and KV head, and each of its four wavefronts works alone -- no barrier -- on 32 keys: it
+// holds K, V, dK^T and dV^T of them and walks (query head, 32-row block that can see them), the block's Q, dO and
+// per-row scalars copied into LDS of the wavefront's own.  S, P, dP and dS stay in its registers, so nothing is handed
+// over, and blocks without a visible pair are never touched.  Two wavefronts per SIMD (one set of tiles each) cover each
+// other's copies; one per SIMD with two sets measured slower (111 us for 104).  Bound: the copies alone take 72 us at
+// 32K tokens in 979 documents, 16/2 heads (67 at the rate of a large copy), the arithmetic alone 54, together 95; one
+// load per line a step ahead to warm L2 made it slower.  Workgroups are dealt so that neighbouring key tiles share an XCD.
+// With the (then empty) general launch 130 -> 105 us there, 89 -> 62 on one of four ranks, 43 -> 35 at 8K tokens.
+template <int D>
+struct ShortDkv {
+    static constexpr int NW = 4, ROWB = D * 2, TILE = 32 * ROWB;
+    static constexpr int SMALL = 4 * 64 * 4;                       // lse2 | delta | row_lo | row_hi, 64 entries each
+    static constexpr int WAVE = 2 * TILE + SMALL;              // Q tile | dO tile | scalars
+};
+
+template <int D>
+__global__ void __launch_bounds__(256, 2) dkv_short_kernel(const BwdParams p) {
+    using T = ShortDkv<D>;
+    constexpr int KS = D / 16, DB = D / 32, CPR = D / 8, ROWB = T::ROWB, TILE = T::TILE;
+    __shared__ __attribute__((aligned(1024))) char smem[T::NW * T::WAVE];
+    // XCD x (workgroups b with b % 8 == x) takes a contiguous run of (key tile, KV head)
+    const int jobs = p.n_key_tiles * p.hkv, per_xcd = (jobs + kLists - 1) / kLists;
+    const int job = ((int)blockIdx.x % kLists) * per_xcd + (int)blockIdx.x / kLists;
+    if ((int)blockIdx.x / kLists >= per_xcd || job >= jobs) return;
+    const int kt = job / p.hkv, hk = job % p.hkv;
+    const int g_first = ld_const(p.key_range + 2 * kt), span = ld_const(p.key_range + 2 * kt + 1) - g_first;
+    if (span > kShortSpan) return;
+
+    const int G = p.hq / p.hkv;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int j16 = lane & 15, gi = (lane >> 4) & 1;
+    const float cs = p.scale_log2e;
+    const int kw0 = kt * kBwdKeyTile + wave * 32, mykey = kw0 + l32;
+
+    // the 32-row blocks that can see one of the wavefront's keys
+    const int rb0 = g_first * (kGroupRows / kShortBlockRows), n_rb = span * (kGroupRows / kShortBlockRows);
+    static_assert(kShortSpan * (kGroupRows / kShortBlockRows) <= 32, "a lane per row block");
+    int b_lo = 0, b_hi = 0;
+    if (lane < n_rb) { b_lo = p.block_hull[2 * (rb0 + lane)]; b_hi = p.block_hull[2 * (rb0 + lane) + 1]; }
+    const uint32_t blocks = (uint32_t)__ballot(b_hi > b_lo && b_lo < kw0 + 32 && b_hi > kw0);
+    const int steps = __popc(blocks) * G;
+
+    const uint32_t base = uniform((uint32_t)(uintptr_t)(WLB_LDS char*)smem + (uint32_t)wave * T::WAVE);
+    const uint32_t q_row_bytes = (uint32_t)p.hq * D * 2u;
+    const uint32_t q_total = (uint32_t)p.n_q * q_row_bytes;
+    BufRsrc q_rs, do_rs, lo_rs, hi_rs, ls_rs, dl_rs;
+    q_rs.init(p.q, q_total);
+    do_rs.init(p.d_o, q_total);
+    lo_rs.init(p.row_lo, (uint32_t)p.n_q * 4u);
+    hi_rs.init(p.row_hi, (uint32_t)p.n_q * 4u);
+    // The swizzle is an XOR of chunk and row bits, tiles are 1 KiB aligned and rows 128 or 256 bytes: an instruction's
+    // lane offsets and an operand's addresses are one register each, XORed with a constant (with all of them in
+    // registers the kernel spills).
+    constexpr int RPI = 64 / CPR, NI = 32 / RPI;                   // rows per copy instruction, instructions per tile
+    int voff0 = (lane / CPR) * (int)q_row_bytes + swz<CPR>(lane / CPR, lane % CPR) * 16;
+    // the copies of one step: 32 rows of Q and dO of a head (rows past n_q read as zeros) and the rows' scalars
+    auto issue = [&](int rb, int h) __attribute__((always_inline)) {
+        const uint32_t so = uniform((uint32_t)rb * 32u * q_row_bytes + (uint32_t)h * ROWB);
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const int voff = voff0 ^ (swz<CPR>(n * RPI, 0) * 16);
+            const uint32_t off = (uint32_t)(n * RPI) * q_row_bytes;
+            dma_issue_1k(q_rs.r, uniform(base + n * 1024u), voff, uniform(so + off));
+            dma_issue_1k(do_rs.r, uniform(base + TILE + n * 1024u), voff, uniform(so + off));
+        }
+        const size_t ho = (size_t)h * p.n_q;
+        ls_rs.init(p.lse2 + ho, (uint32_t)p.n_q * 4u);             // per head: entries past n_q read as zeros
+        dl_rs.init(p.delta + ho, (uint32_t)p.n_q * 4u);
+        const uint32_t ro = uniform((uint32_t)rb * 128u), sm = uniform(base + 2 * TILE);
+        dma_issue_256(ls_rs.r, sm, lane * 4, ro);
+        dma_issue_256(dl_rs.r, uniform(sm + 256u), lane * 4, ro);
+        dma_issue_256(lo_rs.r, uniform(sm + 512u), lane * 4, ro);
+        dma_issue_256(hi_rs.r, uniform(sm + 768u), lane * 4, ro);
+    };
+    // query heads outermost: the wavefronts of a workgroup, whose keys the same rows see, then read those rows of a head
+    // close together in time and share them in L2 (row blocks outermost: 121 us for 59 at 32K tokens, 16/2 heads)
+    uint32_t left = blocks;
+    int rb_n = rb0 + __ffs((int)left) - 1, h_n = hk * G;
+    auto advance = [&] {
+        left &= left - 1;
+        if (left == 0) { left = blocks; ++h_n; }
+        rb_n = rb0 + __ffs((int)left) - 1;
+    };
+    if (steps > 0) { issue(rb_n, h_n); advance(); }
+
+    bf16x8 kop[KS], vop[KS];
+    {
+        const size_t row = ((size_t)min(mykey, p.t_kv - 1) * p.hkv + hk) * D + half * 8;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            kop[ks] = *reinterpret_cast<const bf16x8*>(p.k + row + ks * 16);
+            vop[ks] = *reinterpret_cast<const bf16x8*>(p.v + row + ks * 16);
+        }
+    }
+    f32x16 dk[DB], dv[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { dk[db][r] = 0.f; dv[db][r] = 0.f; }
+    // rows read as they lie: chunk 2 ks + half of row l32; read transposed: rows qq and, with bit 5 flipped, qq + 8 (see dkv_kernel)
+    uint32_t naddr = base + l32 * ROWB + swz<CPR>(l32, half) * 16;
+    const int qq = half * 4 + (j16 >> 2);
+    uint32_t taddr = base + qq * ROWB + swz<CPR>(qq, gi * 2 + ((j16 & 3) >> 1)) * 16 + (j16 & 1) * 8;
+    static_assert(TILE % 1024 == 0 && T::WAVE % 1024 == 0, "bit 5 of a tile's address is the swizzle's");
+    const uint32_t saddr = base + 2 * TILE + half * 16;
+    // the K / V operands have arrived: no compiler-visible vector load may be pending among the copies
+    wait_vmem();
+
+    auto fence = [] () __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
+    for (int s = 0; s < steps; ++s) {
+        wait_vmem();
+        asm volatile("" : "+v"(naddr), "+v"(taddr), "+v"(voff0) :: "memory");   // (keeps the XORs inside the loop)
+        // padding rows may hold anything: zero their Q and dO (rows past n_q are zeros already)
+        const int my_hi = *reinterpret_cast<const WLB_LDS int*>((uintptr_t)(base + 2 * TILE + 768 + l32 * 4));
+        if (__any(my_hi == 0)) {
+            if (my_hi == 0) {
+#pragma unroll
+                for (int i = 0; i < CPR / 2; ++i) {
+                    const uint32_t a = base + l32 * ROWB + (half * (CPR / 2) + i) * 16;
+                    *reinterpret_cast<WLB_LDS i32x4*>((uintptr_t)a) = i32x4{0, 0, 0, 0};
+                    *reinterpret_cast<WLB_LDS i32x4*>((uintptr_t)(a + TILE)) = i32x4{0, 0, 0, 0};
+                }
+            }
+            asm volatile("" ::: "memory");
+        }
+        bf16x8 pk[2], ds[2];
+        {
+            f32x16 sc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) sc = mfma32(*reinterpret_cast<const WLB_LDS bf16x8*>((uintptr_t)(naddr ^ (ks * 32))), kop[ks], sc);
+#pragma unroll
+            for (int cc = 0; cc < 2; ++cc) {
+                float pr[8];
+#pragma unroll
+                for (int r2 = 0; r2 < 2; ++r2) {
+                    const int off = (cc * 2 + r2) * 32;
+                    const f32x4 ls = *reinterpret_cast<const WLB_LDS f32x4*>((uintptr_t)(saddr + off));
+                    const i32x4 lo = *reinterpret_cast<const WLB_LDS i32x4*>((uintptr_t)(saddr + off + 512));
+                    const i32x4 hi = *reinterpret_cast<const WLB_LDS i32x4*>((uintptr_t)(saddr + off + 768));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float e = fast_exp2(fmaf(sc[(cc * 2 + r2) * 4 + i], cs, -ls[i]));
+                        pr[r2 * 4 + i] = (mykey >= lo[i] && mykey < hi[i]) ? e : 0.f;
+                    }
+                }
+                pk[cc] = pack8(pr[0], pr[1], pr[2], pr[3], pr[4], pr[5], pr[6], pr[7]);
+            }
+        }
+        fence();
+        {
+            f32x16 dp;
+#pragma unroll
+            for (int g8 = 0; g8 < 4; ++g8) {
+                const f32x4 x = *reinterpret_cast<const WLB_LDS f32x4*>((uintptr_t)(saddr + 256 + g8 * 32));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dp[g8 * 4 + i] = x[i];
+            }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) dp = mfma32(*reinterpret_cast<const WLB_LDS bf16x8*>((uintptr_t)((naddr ^ (ks * 32)) + TILE)), vop[ks], dp);
+#pragma unroll
+            for (int cc = 0; cc < 2; ++cc) {
+                float g[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) g[i] = (float)pk[cc][i] * dp[cc * 8 + i];
+                ds[cc] = pack8(g[0], g[1], g[2], g[3], g[4], g[5], g[6], g[7]);
+            }
+        }
+        fence();
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const uint32_t a0 = (taddr ^ (db * 64)) + cc * 16 * ROWB, a1 = (taddr ^ (db * 64 + 32)) + (cc * 16 + 8) * ROWB;
+                dv[db] = mfma32(cat4(lds_read_tr4_at(a0 + TILE), lds_read_tr4_at(a1 + TILE)), pk[cc], dv[db]);
+                dk[db] = mfma32(cat4(lds_read_tr4_at(a0), lds_read_tr4_at(a1)), ds[cc], dk[db]);
+            }
+        if (s + 1 < steps) {
+            wait_lds();                                            // the tiles have been read to the end
+            issue(rb_n, h_n);
+            advance();
+        }
+    }
+
+    // dK and dV leave as whole rows through the tiles; keys past t_kv are not stored
+    wait_lds();
+    asm volatile("" ::: "memory");
+    const uint32_t kv_row_bytes = (uint32_t)p.hkv * D * 2u, kv_total = (uint32_t)p.t_kv * kv_row_bytes;
+    const int voff = RowBlock<D>::lane_off(lane, kv_row_bytes);
+    const uint32_t soff = uniform((uint32_t)kw0 * kv_row_bytes + (uint32_t)hk * ROWB);
+    auto put = [&](const f32x16 (&acc)[DB], float f, __bf16* dst, uint32_t tile) __attribute__((always_inline)) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+                *reinterpret_cast<WLB_LDS bf16x4*>((uintptr_t)(tile + l32 * ROWB + swz<CPR>(l32, db * 4 + r4) * 16 + half * 8)) =
+                    pack4(acc[db][r4 * 4 + 0] * f, acc[db][r4 * 4 + 1] * f, acc[db][r4 * 4 + 2] * f, acc[db][r4 * 4 + 3] * f);
+        asm volatile("" ::: "memory");
+        RowBlock<D> rows;
+        rows.from_tile(tile, lane);
+        rows.store(make_buf(dst, kv_total), voff, soff, kv_row_bytes);
+    };
+    put(dk, p.scale, p.dk, base);
+    put(dv, 1.0f, p.dv, base + TILE);
+}
+
 // Sums the partial results of the key tiles that were split into several items.
 // One workgroup per (tile in order, KV head).
 template <int D>
@@ -1082,6 +1297,7 @@ __global__ void __launch_bounds__(256) dkv_fixup_kernel(const BwdParams p) {
     const int hk = job % p.hkv, r = job / p.hkv;
     const int kt = p.key_order[r];
     const int ways = p.key_ways[kt];
+    if (p.short_keys && p.key_range[2 * kt + 1] - p.key_range[2 * kt] <= kShortSpan) return;
     if (ways == 1) return;                      // one item did the whole tile and wrote dK/dV itself
     const int k0 = kt * BNK, nk = min(BNK, p.t_kv - k0);
     const float* src = p.partial + (size_t)(p.key_slot_base[r] + hk * ways) * (2 * BNK * D);
@@ -1143,6 +1359,8 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.group_real = (const int32_t*)(ws + L.off_group_real);
     p.key_order = (const int32_t*)(ws + L.off_key_order);
     p.dkv_item = (const int32_t*)(ws + L.off_dkv_item);
+    p.key_range = (const int32_t*)(ws + L.off_key_range);
+    p.general_items = (const int32_t*)(ws + L.off_general_items);
     p.key_ways = (const int32_t*)(ws + L.off_key_ways);
     p.key_item_base = (const int32_t*)(ws + L.off_key_item_base);
     p.key_slot_base = (const int32_t*)(ws + L.off_key_slot_base);
@@ -1181,6 +1399,8 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     const bool do_dq = !(d.flags & WLB_ATTN_BWD_SKIP_DQ);
     const bool do_dkv = !(d.flags & WLB_ATTN_BWD_SKIP_DKV);
     p.use_short = use_short_path(d, L) ? 1 : 0;
+    p.short_keys = use_short_keys(d, L) ? 1 : 0;
+    const unsigned grid_short = (unsigned)((L.n_key_tiles * d.hkv + kLists - 1) / kLists) * kLists;
     auto run = [&](auto dtag) {
         constexpr int D = decltype(dtag)::value;
         if (do_dq && gangs) {
@@ -1193,7 +1413,12 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
             delta_kernel<D><<<grid_delta, 256, 0, stream>>>(p);
         }
         if (do_dkv) {
-            dkv_kernel<D><<<grid_dkv, 512, 0, stream>>>(p);
+            if (p.short_keys) {
+                dkv_short_kernel<D><<<grid_short, 256, 0, stream>>>(p);
+                dkv_kernel<D, true><<<grid_dkv, 512, 0, stream>>>(p);
+            } else {
+                dkv_kernel<D, false><<<grid_dkv, 512, 0, stream>>>(p);
+            }
             dkv_fixup_kernel<D><<<grid_fix * kMergeSplit, 256, 0, stream>>>(p);
         }
     };

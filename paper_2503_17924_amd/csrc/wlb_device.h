@@ -371,6 +371,12 @@ struct RowBlock {
     __device__ __forceinline__ void store(buf_rsrc_t rs, int voff, uint32_t soff0, uint32_t row_bytes) const {
 #pragma unroll
         for (int i = 0; i < N; ++i) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, v[i]), rs, voff, (int)(soff0 + i * RPI * row_bytes), 0);
+        // A 128-bit buffer store reads its data registers after it has issued, and a vector instruction right behind it that
+        // writes one of them changes what is stored (seen in the last lanes of the first register); the compiler assumes
+        // that a store with a scalar offset has no such hazard.  The registers are kept until a wait state has passed.
+        asm volatile("s_nop 1" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < N; ++i) asm volatile("" :: "v"(v[i]));
     }
     __device__ __forceinline__ void to_tile(uint32_t tile, int lane) const {
 #pragma unroll

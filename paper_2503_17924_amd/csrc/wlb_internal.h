@@ -45,9 +45,10 @@ struct PlanLayout : wlb_plan_layout {
     size_t off_row_item;       // int32 [n_fwd_tiles][4], by order rank: whole tiles only
     size_t off_row_part;       // int32 [n_fwd_tiles + row_parts_added(..)][4]: heavy tiles divided into parts (row_part_limit), by rank, a tile's parts in turn
     size_t off_row_part_base;  // int32 [n_fwd_tiles + 1]: parts before the tile of order rank r
+    size_t off_general_items;  // int32: dK/dV items up to the last one of a key tile with a longer span than kShortSpan
     // Last, because a forward's schedule (wlb_attn_fwd_static) leaves it out.
     size_t off_dkv_item;       // int32 [dkv_max_items][8], by item: {key tile, KV head, first query head, query heads, partial slot or -1,
-                               // first row group, stages, 0}
+                               // first row group, stages, 1: a key tile of the short dK/dV kernel}
     size_t static_bytes;       // bytes counted against WLB_ATTN_FWD_STATIC_SCRATCH_BYTES
 };
 
@@ -97,6 +98,11 @@ bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L);
 inline size_t row_partial_floats(int head_dim) { return (size_t)kFwdTileRows * head_dim + 2 * kFwdTileRows; }
 // bytes of the partial results of the query tiles that are cut at a gang boundary: two per gang and member
 size_t row_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L);
+// Key tiles that at most this many 64-row groups can see go to dkv_short_kernel (4, 6 and 9 measured alike on documents
+// of 16 - 128 tokens: 119 - 121 us where the general kernel alone takes 149; 2: 171).
+constexpr int kShortSpan = 6;
+// whether this backward runs dkv_short_kernel for such tiles beside the general kernel for the others
+bool use_short_keys(const wlb_attn_desc& d, const PlanLayout& L);
 // bytes of the dK/dV partial results that follow delta / lse2 in the backward workspace
 size_t dkv_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L);
 

@@ -100,6 +100,12 @@ bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L) {
     return !(d.flags & WLB_ATTN_NO_SHORT_PATH) && !use_row_gangs(d, L);
 }
 
+// Documents of up to a key tile on average.  With longer ones few key tiles have a short span, and the launch for them
+// costs what it saves; the mean length the host knows, which tiles are short the schedule finds out.
+bool use_short_keys(const wlb_attn_desc& d, const PlanLayout& L) {
+    return use_short_path(d, L) && (long long)d.n_docs * kBwdKeyTile >= d.t_kv;
+}
+
 size_t row_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L) {
     return (size_t)2 * L.row_gangs * (d.hq / d.hkv) * row_partial_floats(d.head_dim) * sizeof(float);
 }
@@ -142,6 +148,7 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
     L->off_row_item = take(sizeof(int32_t) * 4 * L->n_fwd_tiles);
     L->off_row_part_base = take(sizeof(int32_t) * (L->n_fwd_tiles + 1));
     L->off_row_part = take(sizeof(int32_t) * 4 * (size_t)(L->n_fwd_tiles + row_parts_added(d, *L)));
+    L->off_general_items = take(sizeof(int32_t));
     L->off_dkv_item = take(sizeof(int32_t) * 8 * (size_t)L->dkv_max_items);
     L->plan_bytes = off;
 }
@@ -157,7 +164,7 @@ struct PlanArgs {
     int32_t* fwd_cost; int32_t* tile_first; int32_t* tile_short; int32_t* fwd_order; int32_t* row_item; int32_t* row_part; int32_t* row_part_base;
     long long* fwd_prefix;
     int32_t* key_range; int32_t* key_span; int32_t* key_ways; int32_t* key_order; int32_t* key_item_base; int32_t* key_slot_base;
-    int32_t* dkv_item; int32_t* dkv_counters;
+    int32_t* dkv_item; int32_t* dkv_counters; int32_t* general_items;
 };
 constexpr int kGroupsPerTile = kFwdTileRows / kGroupRows;
 // document starts are searched in LDS up to this many documents (a search is log2 dependent loads)
@@ -277,7 +284,8 @@ __device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cos
         a.row_part_base[a.n_tiles] = parts_before + parts;
     }
 }
-__device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 range, int ways, int rank, int items_before, int slots_before) {
+// Returns the end of its items if the tile is the general dK/dV kernel's in any case, else 0.
+__device__ __forceinline__ int put_key_tile(const PlanArgs& a, int i, int2 range, int ways, int rank, int items_before, int slots_before) {
     a.key_ways[i] = ways;
     a.key_order[rank] = i;
     a.key_item_base[rank] = items_before * a.hkv;
@@ -292,8 +300,9 @@ __device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 rang
         for (int part = 0; part < ways; ++part, ++j) {
             int4* rec = reinterpret_cast<int4*>(a.dkv_item) + 2 * (size_t)(item0 + j);
             rec[0] = make_int4(i, hk, hk * G + part * nh, nh);
-            rec[1] = make_int4(ways > 1 ? slot0 + j : -1, range.x, (range.y - range.x) * nh, 0);
+            rec[1] = make_int4(ways > 1 ? slot0 + j : -1, range.x, (range.y - range.x) * nh, range.y - range.x <= kShortSpan ? 1 : 0);
         }
+    return range.y - range.x > kShortSpan ? (items_before + ways) * a.hkv : 0;
 }
 
 // Schedule, first launch of three: a wavefront per group of 64 rows, and the two query tiles of the workgroup.
@@ -303,6 +312,7 @@ __device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 rang
 // work across workgroups inside one launch (the last to arrive goes on) costs more than a launch.
 __global__ void __launch_bounds__(256) plan_rows_kernel(const PlanArgs a) {
     __shared__ int s_cu[kCuLds], s_hull[4][3];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !a.forward_only) *a.general_items = 0;
     const int wave = threadIdx.x >> 6, g = (int)blockIdx.x * 4 + wave;
     int tok[1], hull[1][3];
     load_tokens<1>(a, g, 1, tok);
@@ -432,7 +442,8 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
     const int limit = item_limit(block_sum(a.n_key_tiles, &s_total, [&](int kt) { return a.key_span[kt]; }), a.hq, a.n_slots);
     order_block<KeyCounts>(a.n_key_tiles, blockIdx.x, [&](int j) { return item_split(a.key_span[j], G, limit); },
                            [&](int i, int2 own, const KeyCounts& c) {
-                               put_key_tile(a, i, make_int2(a.key_range[2 * i], a.key_range[2 * i + 1]), own.y, c.rank, c.items, c.slots);
+                               const int end = put_key_tile(a, i, make_int2(a.key_range[2 * i], a.key_range[2 * i + 1]), own.y, c.rank, c.items, c.slots);
+                               if (end) atomicMax(a.general_items, end);           // zeroed by the first launch
                            });
 }
 
@@ -441,7 +452,7 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
 // keys it takes 10.0 us (one launch per step: 17.0 in five), at 4095 rows and 16381 keys 12.5 us.
 constexpr int kSmallGroups = 64, kSmallTiles = kSmallGroups / kGroupsPerTile, kSmallKeyTiles = 256;
 __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
-    __shared__ int s_cu[kCuLds], s_total;
+    __shared__ int s_cu[kCuLds], s_total, s_general;
     __shared__ int2 s_hull[kSmallGroups];
     __shared__ int s_fits[kSmallGroups];
     __shared__ __attribute__((aligned(16))) int2 s_items[kSmallKeyTiles];
@@ -450,7 +461,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
     int tok[PER], hull[PER][3];
     load_tokens<PER>(a, wave, 16, tok);
     for (int i = tid; i < a.n_docs; i += 1024) s_cu[i] = a.cu[i];
-    if (tid == 0) s_total = 0;
+    if (tid == 0) { s_total = 0; s_general = 0; }
     if (tid < kLists) a.dkv_counters[tid] = 0;
     __syncthreads();
     plan_groups<PER>(a, s_cu, wave, 16, tok, hull);
@@ -539,8 +550,13 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             c.items += __shfl_xor(c.items, o);
             c.slots += __shfl_xor(c.slots, o);
         }
-        if ((tid & 3) == 0 && i < a.n_key_tiles) put_key_tile(a, i, range, s_items[i].y, c.rank, c.items, c.slots);
+        if ((tid & 3) == 0 && i < a.n_key_tiles) {
+            const int end = put_key_tile(a, i, range, s_items[i].y, c.rank, c.items, c.slots);
+            if (end) atomicMax(&s_general, end);
+        }
     }
+    __syncthreads();
+    if (tid == 0) *a.general_items = s_general;
 }
 
 wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_t* q_idx,
@@ -559,7 +575,7 @@ wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_
     a.fwd_prefix = (long long*)(ws + L.off_fwd_prefix);
     a.key_range = at(L.off_key_range); a.key_span = at(L.off_key_span); a.key_ways = at(L.off_key_ways);
     a.key_order = at(L.off_key_order); a.key_item_base = at(L.off_key_item_base); a.key_slot_base = at(L.off_key_slot_base);
-    a.dkv_counters = at(L.off_dkv_counters); a.dkv_item = at(L.off_dkv_item);
+    a.dkv_counters = at(L.off_dkv_counters); a.dkv_item = at(L.off_dkv_item); a.general_items = at(L.off_general_items);
     a.forward_only = forward_only ? 1 : 0;
     if (L.n_groups <= kSmallGroups && L.n_key_tiles <= kSmallKeyTiles && d.n_docs <= kCuLds) {
         plan_small_kernel<<<1, 1024, 0, stream>>>(a);

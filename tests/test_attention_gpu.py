@@ -343,6 +343,46 @@ def test_short_hull_path_matches_oracle(docs, hq, hkv, d, cp):
             check_close(f"{name} short vs general", a, b)
 
 
+@pytest.mark.parametrize("hq,hkv,d,cp", [(8, 1, 128, 1), (2, 2, 64, 1), (6, 2, 128, 2), (16, 2, 64, 4)])
+def test_short_key_tiles_match_oracle(hq, hkv, d, cp):
+    """Key tiles that up to six 64-row groups can see have a dK/dV kernel of their own where documents are short on
+    average; here beside longer documents (spans just below and above the limit, split tiles), pads whose Q and dO
+    are garbage, keys that no row sees, and a ragged last tile."""
+    docs = [1] * 40 + [384, 330, 450, 700] + [7, 64, 33, 2, 128, 90] * 6 + [5]
+    w, tens = wl.small_case(79, docs, hq, hkv, d)
+    for r in sorted({0, cp - 1}):
+        sh = osh.shard(docs, cp, r, osh.PER_DOC_PADDED)
+        c = Case(tens, sh["q_idx"], sh["cu_seqlens_k"], hq, hkv, d, w.scale)
+        c.flags = B.ATTN_SCHEDULE_ITEMS
+        pads = c.torch.from_numpy(c.q_idx < 0).cuda()
+        c.dev["q"][pads] = float("nan")
+        c.dev["do"][pads] = float("nan")
+        c.check_fwd(f" cp {cp} rank {r}")
+        c.check_bwd(f" cp {cp} rank {r}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_short_key_tiles_repeat_bit_for_bit(d):
+    """Thousands of short key tiles: repeated backward calls give the same bits, and what the general kernels give up to
+    rounding (a store whose data registers were written again too early showed in a few rows per call, not in every one)."""
+    import torch
+    rng = np.random.default_rng(12)
+    docs = rng.integers(1, 65, size=990)
+    cu = np.concatenate([[0], np.cumsum(docs)]).astype(np.int32)
+    t, hq, hkv = int(cu[-1]), 16, 2
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v, do = (torch.randn((t, h, d), device="cuda", generator=gen, dtype=torch.bfloat16) for h in (hq, hkv, hkv, hq))
+    attn = B.Attention(np.arange(t, dtype=np.int32), cu, t, hq, hkv, d, d ** -0.5)
+    o, lse = attn.forward(q, k, v)
+    first = [x.clone() for x in attn.backward(q, k, v, o, lse, do)]
+    general = attn.backward(q, k, v, o, lse, do, extra_flags=B.ATTN_NO_SHORT_PATH)
+    for a, b in zip(first, general):
+        # both round P and dS to bf16 (2^-9) and sum at most 64 of them per result in fp32
+        assert (a.float() - b.float()).abs().max() <= 2e-2 * b.float().abs().max()
+    for _ in range(6):
+        assert all(torch.equal(a, b) for a, b in zip(first, attn.backward(q, k, v, o, lse, do)))
+
+
 ROW_ITEM_OVERHEAD = 6     # units of fixed cost per query tile in the forward / dQ work line
 DKV_SPLIT = 6             # a dK/dV item is at most 1/DKV_SPLIT of a compute unit's mean load
 DKV_MIN_ITEM_STAGES = 32  # items this short are not split further
