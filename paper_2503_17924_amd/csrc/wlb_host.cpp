@@ -127,6 +127,19 @@ extern "C" wlb_status wlb_packer_pending(const wlb_packer* packer, int64_t* n_le
     return WLB_OK;
 }
 
+// index of the first least element (selects, no branches: which micro-batch is least loaded cannot be predicted)
+template <class T>
+static int first_least(const T* x, int n) {
+    T best = x[0];
+    int at = 0;
+    for (int j = 1; j < n; ++j) {
+        const bool less = x[j] < best;
+        best = less ? x[j] : best;
+        at = less ? j : at;
+    }
+    return at;
+}
+
 extern "C" wlb_status wlb_packer_step(wlb_packer* packer, const int32_t* doc_len, const int64_t* doc_id, int64_t n_docs,
                                       int64_t* out_doc_id, int32_t* out_doc_len, int32_t* out_mb, int64_t capacity,
                                       int64_t* n_out, int64_t* mb_len, uint64_t* mb_cost) {
@@ -163,15 +176,11 @@ extern "C" wlb_status wlb_packer_step(wlb_packer* packer, const int32_t* doc_len
     int64_t placed = 0;
     for (const Doc& doc : pending) {
         const uint64_t d = (uint64_t)doc.len;
-        int w = 0, l = 0;
-        for (int j = 1; j < n; ++j) {
-            if (mb_cost[j] < mb_cost[w]) w = j;
-            if (mb_len[j] < mb_len[l]) l = j;
+        int dst = first_least(mb_cost, n);
+        if (mb_len[dst] + (int64_t)d > packer->l_max) {
+            dst = first_least(mb_len, n);
+            if (mb_len[dst] + (int64_t)d > packer->l_max) { packer->left_over.push_back(doc); continue; }
         }
-        int dst;
-        if (mb_len[w] + (int64_t)d <= packer->l_max) dst = w;
-        else if (mb_len[l] + (int64_t)d <= packer->l_max) dst = l;
-        else { packer->left_over.push_back(doc); continue; }
         out_doc_id[placed] = doc.id;
         out_doc_len[placed] = doc.len;
         out_mb[placed] = dst;
