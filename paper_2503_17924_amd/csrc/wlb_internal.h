@@ -98,9 +98,12 @@ bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L);
 inline size_t row_partial_floats(int head_dim) { return (size_t)kFwdTileRows * head_dim + 2 * kFwdTileRows; }
 // bytes of the partial results of the query tiles that are cut at a gang boundary: two per gang and member
 size_t row_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L);
-// Key tiles that at most this many 64-row groups can see go to dkv_short_kernel (4, 6 and 9 measured alike on documents
-// of 16 - 128 tokens: 119 - 121 us where the general kernel alone takes 149; 2: 171).
-constexpr int kShortSpan = 6;
+// Key tiles that at most this many 64-row groups can see go to dkv_short_kernel (documents of 16 - 128 tokens: 121 us with
+// 4, 119 with 6, 171 with 2, 149 with the general kernel alone; one document of 2100 tokens beside short ones: with 6 its
+// last tiles, 48 steps one after another, made 138 us of 91).
+constexpr int kShortSpan = 4;
+// ... when documents average at most this many tokens (use_short_keys)
+constexpr int kShortMeanDoc = 96;
 // whether this backward runs dkv_short_kernel for such tiles beside the general kernel for the others
 bool use_short_keys(const wlb_attn_desc& d, const PlanLayout& L);
 // bytes of the dK/dV partial results that follow delta / lse2 in the backward workspace

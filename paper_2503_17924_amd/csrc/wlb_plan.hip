@@ -100,10 +100,10 @@ bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L) {
     return !(d.flags & WLB_ATTN_NO_SHORT_PATH) && !use_row_gangs(d, L);
 }
 
-// Documents of up to a key tile on average.  With longer ones few key tiles have a short span, and the launch for them
-// costs what it saves; the mean length the host knows, which tiles are short the schedule finds out.
+// With longer documents, or one long one that makes up most of the tokens, few key tiles have a short span, and the launch
+// for them costs what it saves; the mean length the host knows, which tiles are short the schedule finds out.
 bool use_short_keys(const wlb_attn_desc& d, const PlanLayout& L) {
-    return use_short_path(d, L) && (long long)d.n_docs * kBwdKeyTile >= d.t_kv;
+    return use_short_path(d, L) && (long long)d.n_docs * kShortMeanDoc >= d.t_kv;
 }
 
 size_t row_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L) {

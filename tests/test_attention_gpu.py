@@ -345,10 +345,10 @@ def test_short_hull_path_matches_oracle(docs, hq, hkv, d, cp):
 
 @pytest.mark.parametrize("hq,hkv,d,cp", [(8, 1, 128, 1), (2, 2, 64, 1), (6, 2, 128, 2), (16, 2, 64, 4)])
 def test_short_key_tiles_match_oracle(hq, hkv, d, cp):
-    """Key tiles that up to six 64-row groups can see have a dK/dV kernel of their own where documents are short on
+    """Key tiles that up to four 64-row groups can see have a dK/dV kernel of their own where documents are short on
     average; here beside longer documents (spans just below and above the limit, split tiles), pads whose Q and dO
     are garbage, keys that no row sees, and a ragged last tile."""
-    docs = [1] * 40 + [384, 330, 450, 700] + [7, 64, 33, 2, 128, 90] * 6 + [5]
+    docs = [1] * 40 + [128, 190, 256, 700] + [7, 64, 33, 2, 128, 90] * 6 + [5]
     w, tens = wl.small_case(79, docs, hq, hkv, d)
     for r in sorted({0, cp - 1}):
         sh = osh.shard(docs, cp, r, osh.PER_DOC_PADDED)
