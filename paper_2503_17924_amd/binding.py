@@ -34,7 +34,7 @@ STATUS_NAMES = {0: "WLB_OK", 1: "WLB_ERR_INVALID_ARG", 2: "WLB_ERR_BUFFER_TOO_SM
 
 EXPORTS = ["wlb_last_error", "wlb_pack", "wlb_pack_optimal", "wlb_packer_create", "wlb_packer_destroy", "wlb_packer_step",
            "wlb_packer_pending", "wlb_calib_mfma", "wlb_calib_atomic_add", "wlb_predict_latency", "wlb_select_sharding", "wlb_shard_size", "wlb_shard", "wlb_attn_workspace_size",
-           "wlb_attn_plan", "wlb_attn_plan_layout", "wlb_attn_set_gang_weights", "wlb_attn_get_gang_weights", "wlb_attn_fwd", "wlb_attn_fwd_static", "wlb_attn_bwd"]
+           "wlb_attn_plan", "wlb_attn_plan_layout", "wlb_attn_plan_records", "wlb_attn_set_gang_weights", "wlb_attn_get_gang_weights", "wlb_attn_fwd", "wlb_attn_fwd_static", "wlb_attn_bwd"]
 
 
 class WlbError(RuntimeError):
@@ -60,6 +60,13 @@ class PlanLayout(C.Structure):
                 ("n_blocks32", C.c_int32), ("off_block_hull", C.c_size_t), ("off_tile_short", C.c_size_t),
                 ("off_gang_clock", C.c_size_t),
                 ("plan_bytes", C.c_size_t)]
+
+
+class PlanRecords(C.Structure):
+    _fields_ = [("uses_parts", C.c_int32), ("max_parts", C.c_int32), ("uses_short_keys", C.c_int32), ("short_span", C.c_int32),
+                ("off_row_item", C.c_size_t), ("off_row_part", C.c_size_t), ("off_row_part_base", C.c_size_t),
+                ("off_dkv_item", C.c_size_t), ("off_general_items", C.c_size_t), ("row_partial_bytes", C.c_size_t),
+                ("row_partials_bytes", C.c_size_t)]
 
 
 _lib = None
@@ -298,6 +305,12 @@ def wlb_attn_plan_layout(desc: AttnDesc) -> PlanLayout:
     return lay
 
 
+def wlb_attn_plan_records(desc: AttnDesc) -> PlanRecords:
+    rec = PlanRecords()
+    _check(lib().wlb_attn_plan_records(C.byref(desc), C.byref(rec)))
+    return rec
+
+
 def _dev_ptr(t, dtype=None):
     import torch
     if t is None:
@@ -419,13 +432,18 @@ def plan_tables(attn: "Attention") -> dict:
     visible key range of each 64-row group); fwd_cost [n_fwd_tiles] (64-key tiles a query tile visits), fwd_order
     (heaviest first), fwd_prefix [n_fwd_tiles + 1] (running cost in that order, fixed cost per tile included);
     tile_short; key_range [n_key_tiles][2] (row groups a key tile is visible to), key_ways (items a key tile is
-    split into), key_order, key_item_base; layout (the PlanLayout)."""
+    split into), key_order, key_item_base, key_slot_base; the work records row_item [n_fwd_tiles][4], row_part
+    [parts][4], row_part_base [n_fwd_tiles + 1], dkv_item [items][8] and general_items; block_hull [n_blocks32][2]; layout
+    (the PlanLayout) and records (the PlanRecords)."""
     lay = wlb_attn_plan_layout(attn.desc)
+    rec = wlb_attn_plan_records(attn.desc)
     ws = attn.workspace[:lay.plan_bytes].cpu().numpy()
     i32 = lambda off, n: ws[off:off + 4 * n].view(np.int32).copy()
     n_q = attn.shape[0]
+    part_base = i32(rec.off_row_part_base, lay.n_fwd_tiles + 1)
+    item_base = i32(lay.off_key_item_base, lay.n_key_tiles + 1)
     return {
-        "layout": lay,
+        "layout": lay, "records": rec,
         "row_lo": i32(lay.off_row_lo, n_q), "row_hi": i32(lay.off_row_hi, n_q),
         "group": i32(lay.off_group, 4 * lay.n_groups).reshape(-1, 4),
         "fwd_cost": i32(lay.off_fwd_cost, lay.n_fwd_tiles), "fwd_order": i32(lay.off_fwd_order, lay.n_fwd_tiles),
@@ -433,7 +451,12 @@ def plan_tables(attn: "Attention") -> dict:
         "tile_short": i32(lay.off_tile_short, lay.n_fwd_tiles),
         "key_range": i32(lay.off_key_range, 2 * lay.n_key_tiles).reshape(-1, 2),
         "key_ways": i32(lay.off_key_ways, lay.n_key_tiles), "key_order": i32(lay.off_key_order, lay.n_key_tiles),
-        "key_item_base": i32(lay.off_key_item_base, lay.n_key_tiles + 1),
+        "key_item_base": item_base, "key_slot_base": i32(lay.off_key_slot_base, lay.n_key_tiles + 1),
+        "row_item": i32(rec.off_row_item, 4 * lay.n_fwd_tiles).reshape(-1, 4),
+        "row_part": i32(rec.off_row_part, 4 * int(part_base[-1])).reshape(-1, 4), "row_part_base": part_base,
+        "dkv_item": i32(rec.off_dkv_item, 8 * int(item_base[-1])).reshape(-1, 8),
+        "general_items": int(i32(rec.off_general_items, 1)[0]),
+        "block_hull": i32(lay.off_block_hull, 2 * lay.n_blocks32).reshape(-1, 2),
     }
 
 
@@ -460,6 +483,11 @@ def plan_report(attn: "Attention", name: str = "") -> str:
         share = np.diff(begin)
         lines.append(f"  forward work line: {total} units (tile cost + fixed part, x KV heads) over {ng} gangs of {hq // hkv} "
                      f"workgroups: share {q(share)}")
+    elif t["records"].uses_parts:
+        part = t["row_part"]
+        divided = np.diff(t["row_part_base"]) > 1
+        lines.append(f"  forward / dQ items: {len(part) * hq} (tile or part of one, head), key tiles {q(part[:, 2] - part[:, 1])}; "
+                     f"{int(divided.sum())} tiles divided into {int(np.diff(t['row_part_base'])[divided].sum())} parts")
     else:
         lines.append(f"  forward / dQ items: {lay.n_fwd_tiles * hq} (tile, head), cost with fixed part {q(per)}")
     kr = t["key_range"]

@@ -669,6 +669,25 @@ extern "C" wlb_status wlb_attn_plan_layout(const wlb_attn_desc* desc, wlb_plan_l
     return WLB_OK;
 }
 
+extern "C" wlb_status wlb_attn_plan_records(const wlb_attn_desc* desc, wlb_plan_records* records) {
+    if (wlb_status st = check_desc(desc)) return st;
+    if (!records) return fail(WLB_ERR_INVALID_ARG, "wlb_attn_plan_records: null output");
+    PlanLayout L;
+    plan_layout(*desc, &L);
+    records->uses_parts = use_row_parts(*desc, L) ? 1 : 0;
+    records->max_parts = L.n_fwd_tiles + row_parts_added(*desc, L);
+    records->uses_short_keys = use_short_keys(*desc, L) ? 1 : 0;
+    records->short_span = kShortSpan;
+    records->off_row_item = L.off_row_item;
+    records->off_row_part = L.off_row_part;
+    records->off_row_part_base = L.off_row_part_base;
+    records->off_dkv_item = L.off_dkv_item;
+    records->off_general_items = L.off_general_items;
+    records->row_partial_bytes = row_partial_floats(desc->head_dim) * sizeof(float);
+    records->row_partials_bytes = row_partial_bytes(*desc, L);
+    return WLB_OK;
+}
+
 extern "C" wlb_status wlb_attn_plan(const wlb_attn_desc* desc, const int32_t* q_idx, const int32_t* cu_seqlens_k,
                                     void* workspace, size_t workspace_bytes, void* stream) {
     if (wlb_status st = check_desc(desc)) return st;

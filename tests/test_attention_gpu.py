@@ -183,6 +183,58 @@ def test_both_row_schedules_match_oracle(flag, hq, hkv, d):
         c.check_bwd(f" cp {cp} rank {r}")
 
 
+def check_work_records(attn):
+    """The records that the kernels start from, against the schedule's tables: whole tiles; parts that cover their tile's
+    key tiles without a gap, with partial results of their own inside the workspace; dK/dV items.  Returns the tables."""
+    t = B.plan_tables(attn)
+    lay, rec = t["layout"], t["records"]
+    hq, hkv = attn.shape[3], attn.shape[4]
+    G = hq // hkv
+    order, cost = t["fwd_order"], t["fwd_cost"]
+    item, part, base = t["row_item"], t["row_part"], t["row_part_base"]
+    assert (item[:, 0] == order).all() and (item[:, 2] - item[:, 1] == cost[order]).all()
+    assert (item[:, 3] == np.where(t["tile_short"][order] == 1, -2, -1)).all()
+    group = t["group"]
+    for tile in range(lay.n_fwd_tiles):
+        g = group[2 * tile:2 * tile + 2]
+        g = g[g[:, 1] > g[:, 0]]
+        r = int(np.nonzero(order == tile)[0][0])
+        assert item[r, 1] == (g[:, 0].min() // 64 if len(g) else 0)
+    assert base[0] == 0 and (np.diff(base) >= 1).all() and base[-1] <= rec.max_parts
+    partials = []
+    for r in range(lay.n_fwd_tiles):
+        mine = part[base[r]:base[r + 1]]
+        if len(mine) == 1:
+            assert (mine[0] == item[r]).all()
+            continue
+        assert (mine[:, 0] == order[r]).all()
+        assert mine[0, 1] == item[r, 1] and mine[-1, 2] == item[r, 2] and (mine[1:, 1] == mine[:-1, 2]).all()
+        size = mine[:, 2] - mine[:, 1]
+        assert size.min() >= 1 and size.max() - size.min() <= 1
+        assert (mine[:, 3] >= 0).all() and ((mine[:, 3] & 1) == (np.arange(len(mine)) > 0)).all()
+        slots = mine[:, 3] >> 1
+        assert (np.diff(slots) == 1).all()           # the merge kernel steps from one to the next
+        partials += slots.tolist()
+    assert len(set(partials)) == len(partials)
+    if partials:
+        assert (max(partials) + 1) * hq * rec.row_partial_bytes <= rec.row_partials_bytes
+    want, end = [], 0
+    for r, kt in enumerate(t["key_order"]):
+        first, last = t["key_range"][kt]
+        ways = int(t["key_ways"][kt])
+        nh = G // ways
+        for hk in range(hkv):
+            for p in range(ways):
+                slot = t["key_slot_base"][r] + hk * ways + p if ways > 1 else -1
+                want.append([kt, hk, hk * G + p * nh, nh, slot, first, (last - first) * nh])
+    assert (t["dkv_item"][:, :7] == np.asarray(want)).all()
+    short = t["dkv_item"][:, 7] == 1
+    assert ((t["key_range"][:, 1] - t["key_range"][:, 0])[t["dkv_item"][short, 0]] <= rec.short_span).all()
+    general = np.nonzero(~short)[0]
+    assert t["general_items"] == (general[-1] + 1 if len(general) else 0)
+    return t
+
+
 @pytest.mark.parametrize("docs,hq,hkv,d,cp", [
     ([384, 385, 1], 2, 1, 128, 1),               # 6 key tiles: whole; 7: two parts, one key tile apart
     ([5000], 4, 4, 64, 8),                       # rows of two chunks, tiles of 5 - 79 key tiles in many parts
@@ -199,6 +251,41 @@ def test_divided_query_tiles_match_oracle(docs, hq, hkv, d, cp):
         assert not B.wlb_attn_plan_layout(c.attn.desc).uses_gangs
         c.check_fwd(f" cp {cp} rank {r}")
         c.check_bwd(f" cp {cp} rank {r}")
+        check_work_records(c.attn)
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,cp,mode", [
+    ([384, 385, 1, 3000], 2, 1, 128, 1, 0),      # a tile of 6 key tiles whole, one of 7 in two parts
+    ([5000, 500], 4, 4, 64, 8, 0),               # rows of two chunks, tiles of up to 79 key tiles in many parts
+    ([2600, 3, 700], 6, 2, 128, 2, 0),           # pads, three query heads per KV head
+    ([8000], 2, 1, 64, 1, 0),                    # more than 4096 rows: the schedule's three launches
+    ([300, 4600, 3, 300], 4, 2, 128, 1, 0),      # the same with more than 128 items
+    ([9000, 40, 3000], 1, 1, 64, 2, 1),          # and with rows of two distant places in one tile
+])
+def test_divided_query_tiles_and_their_records(docs, hq, hkv, d, cp, mode):
+    """Query tiles divided along their keys at the default schedule choice, by the one-launch and the three-launch
+    schedule: the limit, the records, and the merged results against the oracle."""
+    import torch
+    if mode == osh.PER_SEQ:
+        docs = docs + [2 * cp - sum(docs) % (2 * cp)]
+    w, tens = wl.small_case(78, docs, hq, hkv, d)
+    for r in sorted({0, cp - 1}):
+        sh = osh.shard(docs, cp, r, mode)
+        c = Case(tens, sh["q_idx"], sh["cu_seqlens_k"], hq, hkv, d, w.scale)
+        c.attn.visible_pairs = int(sh["useful_pairs"])
+        c.attn.desc, c.attn.desc_reuse = c.attn.make_desc(0), c.attn.make_desc(B.ATTN_REUSE_PLAN)
+        assert B.wlb_attn_plan_records(c.attn.desc).uses_parts
+        c.check_fwd(f" cp {cp} rank {r}")
+        c.check_bwd(f" cp {cp} rank {r}")
+        t = check_work_records(c.attn)
+        # a part holds at most 6 key tiles, or 6 / 4 of the mean work of a workgroup slot
+        lay = t["layout"]
+        slots = lay.row_gangs * (hq // hkv) // hq * hq
+        units = int(t["fwd_prefix"][-1]) * hq
+        limit = max(6, -(-(units * 6 // 4) // slots))
+        parts = np.diff(t["row_part_base"])
+        assert (parts == np.where(t["tile_short"][t["fwd_order"]] == 1, 1, np.maximum(1, -(-t["fwd_cost"][t["fwd_order"]] // limit)))).all()
+        assert parts.max() > 1
 
 
 def test_gang_share_weights_change_the_cuts_not_the_result():
@@ -461,6 +548,82 @@ def test_schedule_tables():
         # no item is heavier than the threshold unless it is already a single head
         total = int(span.sum()) * c.hq
         assert (icost[ways < g_heads] <= max(DKV_MIN_ITEM_STAGES, -(-total // (DKV_SPLIT * n_cu)))).all()
+        check_work_records(c.attn)
+
+
+@pytest.mark.parametrize("docs,hq,hkv", [
+    ([1700, 2, 900, 64, 1600], 4, 2),                                                       # just above 4096 rows
+    (np.random.default_rng(4).integers(1, 33, size=2500).tolist() + [700], 8, 1),           # more documents than LDS holds
+])
+@pytest.mark.parametrize("shuffled", [False, True])
+def test_schedule_tables_of_larger_calls(docs, hq, hkv, shuffled):
+    """The tables of the three-launch schedule against their definitions, with the document starts searched in LDS and
+    in global memory, rows in order and shuffled with padding in between."""
+    import torch
+    cu = _cu(docs)
+    t_kv = int(cu[-1])
+    q_idx = np.arange(t_kv, dtype=np.int32)
+    if shuffled:
+        q_idx = np.random.default_rng(3).permutation(q_idx)
+        q_idx[::11] = -1
+    assert len(q_idx) > 4096
+    attn = B.Attention(q_idx, cu, t_kv, hq, hkv, 64, 0.125)
+    attn.plan()
+    torch.cuda.synchronize()
+    t = check_work_records(attn)
+    lay = t["layout"]
+    lo, hi = t["row_lo"], t["row_hi"]
+    real = q_idx >= 0
+    start = cu[np.searchsorted(cu, np.maximum(q_idx, 0), side="right") - 1]
+    assert (lo[real] == start[real]).all() and (hi[real] == q_idx[real] + 1).all() and (lo[~real] > hi[~real]).all()
+
+    def hulls(n, rows):
+        pad = np.full(n * rows - len(q_idx), -1)
+        q = np.concatenate([q_idx, pad]).reshape(n, rows)
+        l = np.concatenate([start, pad]).reshape(n, rows)
+        return [(l[i][q[i] >= 0], q[i][q[i] >= 0] + 1) for i in range(n)]
+
+    for want, got in zip(hulls(lay.n_groups, lay.group_rows), t["group"]):
+        if len(want[0]):
+            assert got.tolist() == [want[0].min(), want[1].max(), want[0].max(), want[1].min()]
+        else:
+            assert got[1] <= got[0]
+    fits = []
+    for want, got in zip(hulls(lay.n_blocks32, 32), t["block_hull"]):
+        if len(want[0]):
+            assert got.tolist() == [want[0].min(), want[1].max()]
+        else:
+            assert got[1] <= got[0]
+        fits.append(not len(want[0]) or want[1].max() - want[0].min() // 32 * 32 <= 96)
+    fits = np.asarray(fits + [True] * (4 * lay.n_fwd_tiles - len(fits))).reshape(-1, 4).all(axis=1)
+    assert (t["tile_short"] == fits).all()
+    tile = hulls(lay.n_fwd_tiles, lay.fwd_tile_rows)
+    cost = np.asarray([-(-h.max() // 64) - l.min() // 64 if len(l) else 0 for l, h in tile])
+    assert (t["fwd_cost"] == cost).all()
+    assert (t["fwd_order"] == np.lexsort((np.arange(len(cost)), -cost))).all()
+    prefix = t["fwd_prefix"]
+    assert prefix[0] == 0 and (np.diff(prefix) == cost[t["fwd_order"]] + ROW_ITEM_OVERHEAD).all()
+    g = t["group"]
+    for kt in range(lay.n_key_tiles):
+        k0, k1 = kt * lay.bwd_key_tile, min((kt + 1) * lay.bwd_key_tile, t_kv)
+        sees = np.nonzero((g[:, 1] > g[:, 0]) & (g[:, 0] < k1) & (g[:, 1] > k0))[0]
+        first, last = t["key_range"][kt]
+        assert (first, last) == (sees[0], sees[-1] + 1) if len(sees) else first == last
+    G, ways = hq // hkv, t["key_ways"]
+    span = t["key_range"][:, 1] - t["key_range"][:, 0]
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    limit = max(DKV_MIN_ITEM_STAGES, -(-int(span.sum()) * hq // (DKV_SPLIT * n_cu)))
+    for kt in range(lay.n_key_tiles):
+        w = 1
+        while (G // w) % 2 == 0 and span[kt] * (G // w) > limit:
+            w *= 2
+        assert ways[kt] == w
+    icost = span * (G // ways)
+    assert (t["key_order"] == np.lexsort((np.arange(len(icost)), -icost))).all()
+    in_order = ways[t["key_order"]]
+    assert (np.diff(t["key_item_base"]) == in_order * hkv).all() and t["key_item_base"][0] == 0
+    assert (np.diff(t["key_slot_base"]) == np.where(in_order > 1, in_order * hkv, 0)).all() and t["key_slot_base"][0] == 0
+    assert t["key_item_base"][-1] <= lay.dkv_max_items and t["key_slot_base"][-1] <= lay.dkv_max_partials
 
 
 def test_schedule_orders_with_thousands_of_tiles():
