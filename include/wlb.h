@@ -275,18 +275,18 @@ wlb_status wlb_attn_plan_layout(const wlb_attn_desc* desc, wlb_plan_layout* layo
  * and tests).  Row records are int32[4]: {query tile, first, one-past-last 64-key tile, code}; code = -1: a whole
  * tile, -2: a whole tile of the short-hull path, else 2 * partial result (before the query head) + (1: not the
  * tile's first part).  dK/dV records are int32[8]: {key tile, KV head, first query head, query heads, partial slot or
- * -1, first row group, stages, 1: left to the kernel of short key tiles}. */
+ * -1, first row group, stages, 0}. */
 typedef struct {
     int32_t uses_parts;                  /* 1: forward and dQ of this desc (its flags included) divide heavy query tiles along
                                             their keys and take the part records, else one record per whole tile */
     int32_t max_parts;                   /* room for part records; partial results are those of divided tiles only */
-    int32_t uses_short_keys;             /* 1: the backward of this desc (its flags included) launches the kernel of short key tiles */
-    int32_t short_span;                  /* ... which takes key tiles that at most this many row groups can see */
+    int32_t uses_short_keys;             /* 1: the backward of this desc (its flags included) launches the dK/dV kernel of short key tiles */
+    int32_t short_span;                  /* ... which can do the work if no key tile is seen by more row groups than this */
     size_t  off_row_item;                /* int32 [n_fwd_tiles][4], by order rank */
     size_t  off_row_part;                /* int32 [max_parts][4], by order rank, a tile's parts in turn */
     size_t  off_row_part_base;           /* int32 [n_fwd_tiles + 1]: parts before the tile of order rank r */
     size_t  off_dkv_item;                /* int32 [dkv_max_items][8], by item */
-    size_t  off_general_items;           /* int32: items up to the last one that is not a short key tile's */
+    size_t  off_short_on;                /* int32: 1: that kernel does the work, 0: the general one */
     size_t  row_partial_bytes;           /* bytes of one partial result of a query tile and head */
     size_t  row_partials_bytes;          /* bytes the workspace holds for them */
 } wlb_plan_records;

@@ -65,7 +65,7 @@ class PlanLayout(C.Structure):
 class PlanRecords(C.Structure):
     _fields_ = [("uses_parts", C.c_int32), ("max_parts", C.c_int32), ("uses_short_keys", C.c_int32), ("short_span", C.c_int32),
                 ("off_row_item", C.c_size_t), ("off_row_part", C.c_size_t), ("off_row_part_base", C.c_size_t),
-                ("off_dkv_item", C.c_size_t), ("off_general_items", C.c_size_t), ("row_partial_bytes", C.c_size_t),
+                ("off_dkv_item", C.c_size_t), ("off_short_on", C.c_size_t), ("row_partial_bytes", C.c_size_t),
                 ("row_partials_bytes", C.c_size_t)]
 
 
@@ -433,7 +433,7 @@ def plan_tables(attn: "Attention") -> dict:
     (heaviest first), fwd_prefix [n_fwd_tiles + 1] (running cost in that order, fixed cost per tile included);
     tile_short; key_range [n_key_tiles][2] (row groups a key tile is visible to), key_ways (items a key tile is
     split into), key_order, key_item_base, key_slot_base; the work records row_item [n_fwd_tiles][4], row_part
-    [parts][4], row_part_base [n_fwd_tiles + 1], dkv_item [items][8] and general_items; block_hull [n_blocks32][2]; layout
+    [parts][4], row_part_base [n_fwd_tiles + 1], dkv_item [items][8]; short_keys_on; block_hull [n_blocks32][2]; layout
     (the PlanLayout) and records (the PlanRecords)."""
     lay = wlb_attn_plan_layout(attn.desc)
     rec = wlb_attn_plan_records(attn.desc)
@@ -455,7 +455,7 @@ def plan_tables(attn: "Attention") -> dict:
         "row_item": i32(rec.off_row_item, 4 * lay.n_fwd_tiles).reshape(-1, 4),
         "row_part": i32(rec.off_row_part, 4 * int(part_base[-1])).reshape(-1, 4), "row_part_base": part_base,
         "dkv_item": i32(rec.off_dkv_item, 8 * int(item_base[-1])).reshape(-1, 8),
-        "general_items": int(i32(rec.off_general_items, 1)[0]),
+        "short_keys_on": bool(i32(rec.off_short_on, 1)[0]),
         "block_hull": i32(lay.off_block_hull, 2 * lay.n_blocks32).reshape(-1, 2),
     }
 

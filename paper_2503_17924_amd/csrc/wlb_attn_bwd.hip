@@ -41,7 +41,7 @@ struct BwdParams {
     __bf16* dq; __bf16* dk; __bf16* dv;
     const int32_t* row_lo; const int32_t* row_hi; const int32_t* group; const int32_t* group_real;
     const int32_t* key_order; const int32_t* key_ways; const int32_t* key_item_base; const int32_t* key_slot_base;
-    const int32_t* key_range; const int32_t* general_items;   // short dK/dV kernel (see dkv_short_kernel)
+    const int32_t* key_range; const int32_t* short_on;   // dkv_short_kernel; null: not launched
     const int32_t* dkv_item;   // two int4 per item (PlanLayout::off_dkv_item)
     int32_t* dkv_counters;     // [8]: items of each XCD's list handed out so far (zero before every dK/dV launch)
     float* partial;
@@ -52,7 +52,7 @@ struct BwdParams {
     int first_half;                   // see paired_index
     const int32_t* block_hull;   // short-hull path (see dq_short_unit)
     unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of dq_kernel's workgroup
-    int n_blocks32, use_short, short_keys;
+    int n_blocks32, use_short;
     int n_q, t_kv, hq, hkv, n_groups, n_tiles, n_key_tiles;
     float scale_log2e, scale;
 };
@@ -681,9 +681,7 @@ __global__ void __launch_bounds__(256) dq_merge_parts_kernel(const BwdParams p) 
 // A work item is a key tile with all query heads of one KV head, or - for a tile whose work
 // exceeds a threshold set by the schedule - a 1/2, 1/4 or 1/8 of those heads; such an item
 // writes its dK^T / dV^T as an unscaled fp32 partial result instead of the final bf16 rows.
-// SHORT: the launch runs beside dkv_short_kernel and leaves that kernel's items out (a kernel of its own, because the
-// checks cost the long documents' launches 1 %).
-template <int D, bool SHORT>
+template <int D>
 __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     constexpr int BNK = kBwdKeyTile, GR = kGroupRows, KS = D / 16, DB = D / 32, CPR = D / 8;
     constexpr int ROWB = D * 2, TILEB = GR * ROWB, NW = 8, NBUF = 3, PBYTES = 4 * 2 * 2 * 1024;
@@ -703,12 +701,13 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     // one workgroup per item the hardware hands every XCD the same number of them.  (A first item by
     // workgroup index and reading all counters at once near the end measured the same.)
     __shared__ int s_item;
-    const int n_items = ld_const(SHORT ? p.general_items : p.key_item_base + p.n_key_tiles);
+    if (p.short_on && ld_const(p.short_on)) return;              // dkv_short_kernel has done it
+    const int n_items = ld_const(p.key_item_base + p.n_key_tiles);
   for (;;) {
     __syncthreads();              // every wavefront has left the LDS of the item before, and has read s_item
     if (threadIdx.x == 0) {
         int it = -1;
-        for (int k = 0; k < kLists && it < 0 && (!SHORT || n_items > 0); ++k) {
+        for (int k = 0; k < kLists && it < 0; ++k) {
             const int c = ((int)blockIdx.x + k) % kLists;
             const int cand = atomicAdd(p.dkv_counters + c, 1) * kLists + c;
             if (cand < n_items) it = cand;
@@ -721,7 +720,6 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     // one record per item: finding the tile by a search of the item bases and then its tables was a chain of a dozen
     // dependent loads in front of every item
     const int4 rec0 = ld_const4(p.dkv_item + 8 * item), rec1 = ld_const4(p.dkv_item + 8 * item + 4);
-    if (SHORT && rec1.w) continue;
     const int kt = rec0.x, hk = rec0.y, h_first = rec0.z, nh = rec0.w;   // query heads [h_first, h_first + nh)
     const int slot = rec1.x;
     const bool whole = slot < 0;
@@ -1102,9 +1100,9 @@ __global__ void __launch_bounds__(256, 2) dkv_short_kernel(const BwdParams p) {
     const int jobs = p.n_key_tiles * p.hkv, per_xcd = (jobs + kLists - 1) / kLists;
     const int job = ((int)blockIdx.x % kLists) * per_xcd + (int)blockIdx.x / kLists;
     if ((int)blockIdx.x / kLists >= per_xcd || job >= jobs) return;
+    if (!ld_const(p.short_on)) return;                           // the general kernel does it (short_keys_pay)
     const int kt = job / p.hkv, hk = job % p.hkv;
     const int g_first = ld_const(p.key_range + 2 * kt), span = ld_const(p.key_range + 2 * kt + 1) - g_first;
-    if (span > kShortSpan) return;
 
     const int G = p.hq / p.hkv;
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
@@ -1297,7 +1295,7 @@ __global__ void __launch_bounds__(256) dkv_fixup_kernel(const BwdParams p) {
     const int hk = job % p.hkv, r = job / p.hkv;
     const int kt = p.key_order[r];
     const int ways = p.key_ways[kt];
-    if (p.short_keys && p.key_range[2 * kt + 1] - p.key_range[2 * kt] <= kShortSpan) return;
+    if (p.short_on && *p.short_on) return;
     if (ways == 1) return;                      // one item did the whole tile and wrote dK/dV itself
     const int k0 = kt * BNK, nk = min(BNK, p.t_kv - k0);
     const float* src = p.partial + (size_t)(p.key_slot_base[r] + hk * ways) * (2 * BNK * D);
@@ -1360,7 +1358,7 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.key_order = (const int32_t*)(ws + L.off_key_order);
     p.dkv_item = (const int32_t*)(ws + L.off_dkv_item);
     p.key_range = (const int32_t*)(ws + L.off_key_range);
-    p.general_items = (const int32_t*)(ws + L.off_general_items);
+    p.short_on = use_short_keys(d, L) ? (const int32_t*)(ws + L.off_short_on) : nullptr;
     p.key_ways = (const int32_t*)(ws + L.off_key_ways);
     p.key_item_base = (const int32_t*)(ws + L.off_key_item_base);
     p.key_slot_base = (const int32_t*)(ws + L.off_key_slot_base);
@@ -1399,7 +1397,6 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     const bool do_dq = !(d.flags & WLB_ATTN_BWD_SKIP_DQ);
     const bool do_dkv = !(d.flags & WLB_ATTN_BWD_SKIP_DKV);
     p.use_short = use_short_path(d, L) ? 1 : 0;
-    p.short_keys = use_short_keys(d, L) ? 1 : 0;
     const unsigned grid_short = (unsigned)((L.n_key_tiles * d.hkv + kLists - 1) / kLists) * kLists;
     auto run = [&](auto dtag) {
         constexpr int D = decltype(dtag)::value;
@@ -1413,12 +1410,8 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
             delta_kernel<D><<<grid_delta, 256, 0, stream>>>(p);
         }
         if (do_dkv) {
-            if (p.short_keys) {
-                dkv_short_kernel<D><<<grid_short, 256, 0, stream>>>(p);
-                dkv_kernel<D, true><<<grid_dkv, 512, 0, stream>>>(p);
-            } else {
-                dkv_kernel<D, false><<<grid_dkv, 512, 0, stream>>>(p);
-            }
+            if (p.short_on) dkv_short_kernel<D><<<grid_short, 256, 0, stream>>>(p);
+            dkv_kernel<D><<<grid_dkv, 512, 0, stream>>>(p);
             dkv_fixup_kernel<D><<<grid_fix * kMergeSplit, 256, 0, stream>>>(p);
         }
     };

@@ -45,10 +45,11 @@ struct PlanLayout : wlb_plan_layout {
     size_t off_row_item;       // int32 [n_fwd_tiles][4], by order rank: whole tiles only
     size_t off_row_part;       // int32 [n_fwd_tiles + row_parts_added(..)][4]: heavy tiles divided into parts (row_part_limit), by rank, a tile's parts in turn
     size_t off_row_part_base;  // int32 [n_fwd_tiles + 1]: parts before the tile of order rank r
-    size_t off_general_items;  // int32: dK/dV items up to the last one of a key tile with a longer span than kShortSpan
-    // Last, because a forward's schedule (wlb_attn_fwd_static) leaves it out.
+    size_t off_short_on;       // int32: 1: dkv_short_kernel does dK/dV, 0: the general kernel
+    // Last, because a forward's schedule (wlb_attn_fwd_static) leaves them out.
     size_t off_dkv_item;       // int32 [dkv_max_items][8], by item: {key tile, KV head, first query head, query heads, partial slot or -1,
-                               // first row group, stages, 1: a key tile of the short dK/dV kernel}
+                               // first row group, stages, 0}
+    size_t off_key_steps;      // int32 [n_key_tiles]: row blocks that see 32 keys of a tile of a short span: most | all four sums << 8
     size_t static_bytes;       // bytes counted against WLB_ATTN_FWD_STATIC_SCRATCH_BYTES
 };
 
@@ -98,14 +99,23 @@ bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L);
 inline size_t row_partial_floats(int head_dim) { return (size_t)kFwdTileRows * head_dim + 2 * kFwdTileRows; }
 // bytes of the partial results of the query tiles that are cut at a gang boundary: two per gang and member
 size_t row_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L);
-// Key tiles that at most this many 64-row groups can see go to dkv_short_kernel (documents of 16 - 128 tokens: 121 us with
-// 4, 119 with 6, 171 with 2, 149 with the general kernel alone; one document of 2100 tokens beside short ones: with 6 its
-// last tiles, 48 steps one after another, made 138 us of 91).
+// dkv_short_kernel does dK/dV where no key tile is seen by more than this many 64-row groups (documents of 16 - 128 tokens:
+// 121 us with 4, 119 with 6, 171 with 2, 149 with the general kernel).
 constexpr int kShortSpan = 4;
-// ... when documents average at most this many tokens (use_short_keys)
-constexpr int kShortMeanDoc = 96;
-// whether this backward runs dkv_short_kernel for such tiles beside the general kernel for the others
+// It is launched, beside the general kernel, when documents average at most kShortMeanDoc tokens and a tile of 128 keys and
+// the longest documents that shape the work (2 * pairs / rows, where the pair count is known) are seen by about
+// kShortSpan groups: an empty launch costs 1.5 us of a backward that may take 30.
+constexpr int kShortMeanDoc = 96, kShortReach = 224;      // kShortReach = 64 * (kShortSpan - 1/2)
+bool short_documents(const wlb_attn_desc& d);
 bool use_short_keys(const wlb_attn_desc& d, const PlanLayout& L);
+// Which of the two then does the work the schedule decides (short_keys_pay), from estimates in stages of the general kernel
+// (1.2 us at D = 64, 1.7 at 128) that were fitted to 1542 random calls: the general kernel takes kGeneralStart and its longest
+// item or kGeneralLoad of the mean load of a compute unit (all of them copying at once), the short one kShortStart and, at
+// kShortStep.. a step, its longest wavefront or kShortLoad of a compute unit's steps.  26 of those calls run more than 3 %
+// (and at most 9 %, 4 us) slower than with the general kernel alone; always taking the short kernel for tiles of a short span
+// beside the general one for the others was slower in a third of them, by up to a factor of five.
+constexpr float kGeneralStart = 18.f, kGeneralLoad = 1.45f, kEmptyLaunch = 2.f, kFixup = 2.f;
+constexpr float kShortStart = 7.f, kShortStep64 = 1.0f, kShortStep128 = 1.3f, kShortLoad = 0.35f;
 // bytes of the dK/dV partial results that follow delta / lse2 in the backward workspace
 size_t dkv_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L);
 

@@ -100,11 +100,12 @@ bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L) {
     return !(d.flags & WLB_ATTN_NO_SHORT_PATH) && !use_row_gangs(d, L);
 }
 
-// With longer documents, or one long one that makes up most of the tokens, few key tiles have a short span, and the launch
-// for them costs what it saves; the mean length the host knows, which tiles are short the schedule finds out.
-bool use_short_keys(const wlb_attn_desc& d, const PlanLayout& L) {
-    return use_short_path(d, L) && (long long)d.n_docs * kShortMeanDoc >= d.t_kv;
+bool short_documents(const wlb_attn_desc& d) {
+    if ((long long)d.n_docs * kShortMeanDoc < d.t_kv) return false;
+    const long long length = d.visible_pairs > 0 ? std::min<long long>(2 * (d.visible_pairs / d.n_q), d.t_kv) : d.t_kv / d.n_docs;
+    return (kBwdKeyTile + length) * d.n_q <= (long long)kShortReach * d.t_kv;
 }
+bool use_short_keys(const wlb_attn_desc& d, const PlanLayout& L) { return use_short_path(d, L) && short_documents(d); }
 
 size_t row_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L) {
     return (size_t)2 * L.row_gangs * (d.hq / d.hkv) * row_partial_floats(d.head_dim) * sizeof(float);
@@ -148,8 +149,9 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
     L->off_row_item = take(sizeof(int32_t) * 4 * L->n_fwd_tiles);
     L->off_row_part_base = take(sizeof(int32_t) * (L->n_fwd_tiles + 1));
     L->off_row_part = take(sizeof(int32_t) * 4 * (size_t)(L->n_fwd_tiles + row_parts_added(d, *L)));
-    L->off_general_items = take(sizeof(int32_t));
+    L->off_short_on = take(sizeof(int32_t));
     L->off_dkv_item = take(sizeof(int32_t) * 8 * (size_t)L->dkv_max_items);
+    L->off_key_steps = take(sizeof(int32_t) * L->n_key_tiles);
     L->plan_bytes = off;
 }
 
@@ -159,12 +161,13 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
 // Everything the schedule kernels read and write.
 struct PlanArgs {
     const int32_t* q_idx; const int32_t* cu;
-    int n_q, t_kv, n_docs, n_groups, n_tiles, n_key_tiles, hq, hkv, n_slots, row_slots, forward_only;
+    int n_q, t_kv, n_docs, n_groups, n_tiles, n_key_tiles, hq, hkv, n_slots, row_slots, forward_only, short_keys, key_run;
+    float short_step, per_cu;
     int32_t* row_lo; int32_t* row_hi; int32_t* group; int32_t* group_real; int32_t* block_hull;
     int32_t* fwd_cost; int32_t* tile_first; int32_t* tile_short; int32_t* fwd_order; int32_t* row_item; int32_t* row_part; int32_t* row_part_base;
     long long* fwd_prefix;
     int32_t* key_range; int32_t* key_span; int32_t* key_ways; int32_t* key_order; int32_t* key_item_base; int32_t* key_slot_base;
-    int32_t* dkv_item; int32_t* dkv_counters; int32_t* general_items;
+    int32_t* dkv_item; int32_t* dkv_counters; int32_t* short_on; int32_t* key_steps;
 };
 constexpr int kGroupsPerTile = kFwdTileRows / kGroupRows;
 // document starts are searched in LDS up to this many documents (a search is log2 dependent loads)
@@ -182,10 +185,10 @@ __device__ __forceinline__ void load_tokens(const PlanArgs& a, int g0, int step,
 
 // The groups g0, g0 + step, ... (N of them, one wavefront): per-row [lo, hi), the hulls of the two 32-row blocks, the
 // group's {k_lo, k_hi, max_lo, min_hi} and its number of real rows.  hull[i] = {k_lo, k_hi, both blocks fit the
-// short-hull window}; {kPadLo, 0, 1} for a group without a real row or past the end.  The N groups' searches and
-// reductions are independent chains.
+// short-hull window}; {kPadLo, 0, 1} for a group without a real row or past the end; block[i]: hull of the lane's block.
+// The N groups' searches and reductions are independent chains.
 template <int N>
-__device__ __forceinline__ void plan_groups(const PlanArgs& a, const int32_t* cu, int g0, int step, const int (&tok)[N], int (&hull)[N][3]) {
+__device__ __forceinline__ void plan_groups(const PlanArgs& a, const int32_t* cu, int g0, int step, const int (&tok)[N], int (&hull)[N][3], int2 (&block)[N]) {
     const int lane = threadIdx.x & 63;
     int d[N] = {}, lo[N], hi[N];
     // last document start <= tok (cu[0] = 0 <= tok); the step count is the same for every row
@@ -223,11 +226,12 @@ __device__ __forceinline__ void plan_groups(const PlanArgs& a, const int32_t* cu
         const bool fits = b_hi == 0 || b_hi - (b_lo & ~31) <= kShortHullKeys;
         hull[i][0] = k_lo; hull[i][1] = k_hi; hull[i][2] = __all(fits) ? 1 : 0;
         const int n_real = __popcll(__ballot(real));
+        block[i] = make_int2(b_hi > 0 ? b_lo : 0, b_hi);
         if (g < a.n_groups) {
             if ((lane & 31) == 0) {
                 const int b = g * (kGroupRows / kShortBlockRows) + (lane >> 5);
-                a.block_hull[2 * b] = b_hi > 0 ? b_lo : 0;
-                a.block_hull[2 * b + 1] = b_hi;
+                a.block_hull[2 * b] = block[i].x;
+                a.block_hull[2 * b + 1] = block[i].y;
             }
             if (lane == 0) {
                 reinterpret_cast<int4*>(a.group)[g] = k_hi == 0 ? make_int4(0, 0, 0, 0) : make_int4(k_lo, k_hi, max_lo, min_hi);
@@ -264,6 +268,34 @@ __device__ __forceinline__ int row_part_limit(long long total_cost, const PlanAr
 }
 __device__ __forceinline__ int row_parts(int cost, int limit) { return cost > limit ? (cost + limit - 1) / limit : 1; }
 
+// What dK/dV would have to do: the sum of the key tiles' spans and the longest, and the row blocks that see 32 of a tile's
+// keys (the most, and the sum over each XCD's run of tiles).
+struct KeyWork { int span, chain, load[kLists]; unsigned long long total; };
+__device__ __forceinline__ void clear(KeyWork& w) {
+    w.span = w.chain = 0;
+    w.total = 0;
+#pragma unroll
+    for (int x = 0; x < kLists; ++x) w.load[x] = 0;
+}
+// Whether dkv_short_kernel does dK/dV.  Its wavefronts walk (row blocks x query heads of a KV head) one after another, where
+// the general kernel divides a tile's heads among items; and tiles of a longer span would need the general kernel's launch
+// after its own.  1024 tokens in documents of 1 - 64, dK/dV with 8 / 16 / 32 / 64 query heads on one KV head: 52 / 93 / 176 /
+// 377 us there, 63 / 81 / 88 / 98 in the general kernel; 32K tokens, 16/2 heads: 108 and 136; 4096 tokens, one document of
+// 1500, 8/1 heads: 176 (both launches) and 94.
+__device__ __forceinline__ bool short_keys_pay(const PlanArgs& a, const KeyWork& w, int limit) {
+    int load = 0;
+#pragma unroll
+    for (int x = 0; x < kLists; ++x) load = max(load, w.load[x]);
+    const int G = a.hq / a.hkv;
+    const int2 item = item_split(w.span, G, limit);              // the longest, or half of it
+    const float general = kGeneralStart + fmaxf((float)item.x, kGeneralLoad * (float)w.total * a.per_cu) + (item.y > 1 ? kFixup : 0.f);
+    const float steps = fmaxf((float)(w.chain * G), kShortLoad * kLists * (float)load * a.per_cu);
+    return w.span <= kShortSpan && kShortStart + a.short_step * steps + kEmptyLaunch <= general;
+}
+// Row blocks that see a key tile's 32 keys kw0 ..: lane = 8 * (32 keys) + row block, of at most 8 from group `first` on.
+static_assert(2 * kShortSpan <= 8 && kGroupRows == 2 * kShortBlockRows && kBwdKeyTile == 128, "a lane per 32 keys and row block");
+__device__ __forceinline__ bool block_sees(int2 hull, int kw0) { return hull.y > hull.x && hull.x < kw0 + 32 && hull.y > kw0; }
+
 // Where a tile stands in its order (heaviest first, ties by index), and sums over the tiles before it.
 __device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cost, int first, int is_short, int parts, int rank,
                                                long long cost_before, int parts_before) {
@@ -284,8 +316,7 @@ __device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cos
         a.row_part_base[a.n_tiles] = parts_before + parts;
     }
 }
-// Returns the end of its items if the tile is the general dK/dV kernel's in any case, else 0.
-__device__ __forceinline__ int put_key_tile(const PlanArgs& a, int i, int2 range, int ways, int rank, int items_before, int slots_before) {
+__device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 range, int ways, int rank, int items_before, int slots_before) {
     a.key_ways[i] = ways;
     a.key_order[rank] = i;
     a.key_item_base[rank] = items_before * a.hkv;
@@ -300,9 +331,8 @@ __device__ __forceinline__ int put_key_tile(const PlanArgs& a, int i, int2 range
         for (int part = 0; part < ways; ++part, ++j) {
             int4* rec = reinterpret_cast<int4*>(a.dkv_item) + 2 * (size_t)(item0 + j);
             rec[0] = make_int4(i, hk, hk * G + part * nh, nh);
-            rec[1] = make_int4(ways > 1 ? slot0 + j : -1, range.x, (range.y - range.x) * nh, range.y - range.x <= kShortSpan ? 1 : 0);
+            rec[1] = make_int4(ways > 1 ? slot0 + j : -1, range.x, (range.y - range.x) * nh, 0);
         }
-    return range.y - range.x > kShortSpan ? (items_before + ways) * a.hkv : 0;
 }
 
 // Schedule, first launch of three: a wavefront per group of 64 rows, and the two query tiles of the workgroup.
@@ -312,17 +342,17 @@ __device__ __forceinline__ int put_key_tile(const PlanArgs& a, int i, int2 range
 // work across workgroups inside one launch (the last to arrive goes on) costs more than a launch.
 __global__ void __launch_bounds__(256) plan_rows_kernel(const PlanArgs a) {
     __shared__ int s_cu[kCuLds], s_hull[4][3];
-    if (blockIdx.x == 0 && threadIdx.x == 0 && !a.forward_only) *a.general_items = 0;
     const int wave = threadIdx.x >> 6, g = (int)blockIdx.x * 4 + wave;
     int tok[1], hull[1][3];
+    int2 block[1];
     load_tokens<1>(a, g, 1, tok);
     const bool in_lds = a.n_docs <= kCuLds;
     if (in_lds) {
         for (int i = threadIdx.x; i < a.n_docs; i += 256) s_cu[i] = a.cu[i];
         __syncthreads();
     }
-    if (in_lds) plan_groups<1>(a, s_cu, g, 1, tok, hull);
-    else plan_groups<1>(a, a.cu, g, 1, tok, hull);
+    if (in_lds) plan_groups<1>(a, s_cu, g, 1, tok, hull, block);
+    else plan_groups<1>(a, a.cu, g, 1, tok, hull, block);
     if ((threadIdx.x & 63) == 0)
         for (int i = 0; i < 3; ++i) s_hull[wave][i] = hull[0][i];
     __syncthreads();
@@ -426,6 +456,14 @@ __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int
         first = min(first, __shfl_xor(first, o));
         last = max(last, __shfl_xor(last, o));
     }
+    if (a.short_keys) {
+        int2 h = make_int2(0, 0);
+        const bool is_short = last && last - first <= kShortSpan;
+        if (is_short && lane < 32 && (lane & 7) < 2 * (last - first)) h = reinterpret_cast<const int2*>(a.block_hull)[2 * first + (lane & 7)];
+        const uint32_t seen = (uint32_t)__ballot(block_sees(h, k0 + (lane >> 3) * 32));
+        const int most = max(max(__popc(seen & 0xff), __popc(seen & 0xff00)), max(__popc(seen & 0xff0000), __popc(seen & 0xff000000)));
+        if (lane == 0) a.key_steps[kt] = most | __popc(seen) << 8;
+    }
     if (lane == 0) {
         a.key_range[2 * kt] = last ? first : 0;
         a.key_range[2 * kt + 1] = last;
@@ -436,14 +474,48 @@ __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int
 // Third launch: how many items each key tile is split into, and the key tiles ordered by item cost (groups in range x
 // heads per item).
 __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) {
-    __shared__ long long s_total;
+    __shared__ KeyWork s_work;
     if (blockIdx.x == 0 && threadIdx.x < kLists) a.dkv_counters[threadIdx.x] = 0;
+    if (threadIdx.x == 0) clear(s_work);
+    __syncthreads();
     const int G = a.hq / a.hkv;
-    const int limit = item_limit(block_sum(a.n_key_tiles, &s_total, [&](int kt) { return a.key_span[kt]; }), a.hq, a.n_slots);
+    {   // two wavefronts per XCD's run of key tiles
+        static_assert(1024 / 64 == 2 * kLists, "wavefronts");
+        const int x = (int)threadIdx.x >> 7, per = a.key_run, end = min(a.n_key_tiles, (x + 1) * per);
+        int most = 0, chain = 0, load = 0;
+        long long total = 0;
+#pragma unroll 2
+        for (int kt = x * per + (int)(threadIdx.x & 127); kt < end; kt += 128) {
+            const int span = a.key_span[kt], steps = a.short_keys ? a.key_steps[kt] : 0;
+            total += span;
+            most = max(most, span);
+            chain = max(chain, steps & 255);
+            load += steps >> 8;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&s_work.total, (unsigned long long)total);
+        if (a.short_keys) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                most = max(most, __shfl_xor(most, o));
+                chain = max(chain, __shfl_xor(chain, o));
+                load += __shfl_xor(load, o);
+            }
+            if ((threadIdx.x & 63) == 0) {
+                atomicMax(&s_work.span, most);
+                atomicMax(&s_work.chain, chain);
+                atomicAdd(&s_work.load[x], load);
+            }
+        }
+        __syncthreads();
+    }
+    const int limit = item_limit((long long)s_work.total, a.hq, a.n_slots);
+    const bool short_on = a.short_keys && short_keys_pay(a, s_work, limit);        // every workgroup comes to the same result
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.short_on = short_on ? 1 : 0;
     order_block<KeyCounts>(a.n_key_tiles, blockIdx.x, [&](int j) { return item_split(a.key_span[j], G, limit); },
                            [&](int i, int2 own, const KeyCounts& c) {
-                               const int end = put_key_tile(a, i, make_int2(a.key_range[2 * i], a.key_range[2 * i + 1]), own.y, c.rank, c.items, c.slots);
-                               if (end) atomicMax(a.general_items, end);           // zeroed by the first launch
+                               put_key_tile(a, i, make_int2(a.key_range[2 * i], a.key_range[2 * i + 1]), own.y, c.rank, c.items, c.slots);
                            });
 }
 
@@ -452,19 +524,24 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
 // keys it takes 10.0 us (one launch per step: 17.0 in five), at 4095 rows and 16381 keys 12.5 us.
 constexpr int kSmallGroups = 64, kSmallTiles = kSmallGroups / kGroupsPerTile, kSmallKeyTiles = 256;
 __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
-    __shared__ int s_cu[kCuLds], s_total, s_general;
-    __shared__ int2 s_hull[kSmallGroups];
+    __shared__ int s_cu[kCuLds];
+    __shared__ int2 s_hull[kSmallGroups], s_block[2 * kSmallGroups];
+    __shared__ KeyWork s_work;
     __shared__ int s_fits[kSmallGroups];
     __shared__ __attribute__((aligned(16))) int2 s_items[kSmallKeyTiles];
     const int tid = threadIdx.x, wave = tid >> 6;
     constexpr int PER = kSmallGroups / 16;
     int tok[PER], hull[PER][3];
+    int2 block[PER];
     load_tokens<PER>(a, wave, 16, tok);
     for (int i = tid; i < a.n_docs; i += 1024) s_cu[i] = a.cu[i];
-    if (tid == 0) { s_total = 0; s_general = 0; }
+    if (tid == 0) clear(s_work);
     if (tid < kLists) a.dkv_counters[tid] = 0;
     __syncthreads();
-    plan_groups<PER>(a, s_cu, wave, 16, tok, hull);
+    plan_groups<PER>(a, s_cu, wave, 16, tok, hull, block);
+    if ((tid & 31) == 0)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) s_block[2 * (wave + i * 16) + ((tid >> 5) & 1)] = block[i];
     if ((tid & 63) == 0)
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
@@ -490,14 +567,36 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
         }
         if (last && kt < a.n_key_tiles) range = make_int2(first, last);
         const int span = range.y - range.x;
-        int sum = (tid & 3) == 0 ? span : 0;
+        int seen = 0;
+        if (a.short_keys && span <= kShortSpan) {                // a thread per 32 keys
+#pragma unroll
+            for (int j = 0; j < 2 * kShortSpan; ++j)
+                seen += j < 2 * span && block_sees(s_block[min(2 * range.x + j, 2 * kSmallGroups - 1)], k0 + (tid & 3) * 32);
+        }
+        int chain = seen, most = span, sum = (tid & 3) == 0 ? span : 0;
+        if (a.short_keys) {
+            seen += __shfl_xor(seen, 1);
+            seen += __shfl_xor(seen, 2);
+            if ((tid & 3) == 0 && seen) atomicAdd(&s_work.load[kt / a.key_run], seen);
+        }
 #pragma unroll
         for (int o = 32; o > 1; o >>= 1) sum += __shfl_xor(sum, o);
-        if ((tid & 63) == 0 && sum) atomicAdd(&s_total, sum);
+        if ((tid & 63) == 0 && sum) atomicAdd(&s_work.total, (unsigned long long)sum);
+        if (a.short_keys) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                most = max(most, __shfl_xor(most, o));
+                chain = max(chain, __shfl_xor(chain, o));
+            }
+            if ((tid & 63) == 0 && sum) {
+                atomicMax(&s_work.span, most);
+                atomicMax(&s_work.chain, chain);
+            }
+        }
         __syncthreads();
         if ((tid & 3) == 0) {
             // past the end: a cost below every real one
-            s_items[kt] = kt < a.n_key_tiles ? item_split(span, G, item_limit(s_total, a.hq, a.n_slots)) : make_int2(-1, 0);
+            s_items[kt] = kt < a.n_key_tiles ? item_split(span, G, item_limit((long long)s_work.total, a.hq, a.n_slots)) : make_int2(-1, 0);
             if (kt < a.n_key_tiles) {
                 a.key_range[2 * kt] = range.x;
                 a.key_range[2 * kt + 1] = range.y;
@@ -535,6 +634,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
     }
     if (a.forward_only) return;
     __syncthreads();
+    if (tid == 0) *a.short_on = a.short_keys && short_keys_pay(a, s_work, item_limit((long long)s_work.total, a.hq, a.n_slots)) ? 1 : 0;
     {   // the key tiles' order: four threads per tile, each a quarter of the comparisons
         const int i = tid >> 2, cost = s_items[i].x;
         KeyCounts c{};
@@ -550,13 +650,8 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             c.items += __shfl_xor(c.items, o);
             c.slots += __shfl_xor(c.slots, o);
         }
-        if ((tid & 3) == 0 && i < a.n_key_tiles) {
-            const int end = put_key_tile(a, i, range, s_items[i].y, c.rank, c.items, c.slots);
-            if (end) atomicMax(&s_general, end);
-        }
+        if ((tid & 3) == 0 && i < a.n_key_tiles) put_key_tile(a, i, range, s_items[i].y, c.rank, c.items, c.slots);
     }
-    __syncthreads();
-    if (tid == 0) *a.general_items = s_general;
 }
 
 wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_t* q_idx,
@@ -575,8 +670,13 @@ wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_
     a.fwd_prefix = (long long*)(ws + L.off_fwd_prefix);
     a.key_range = at(L.off_key_range); a.key_span = at(L.off_key_span); a.key_ways = at(L.off_key_ways);
     a.key_order = at(L.off_key_order); a.key_item_base = at(L.off_key_item_base); a.key_slot_base = at(L.off_key_slot_base);
-    a.dkv_counters = at(L.off_dkv_counters); a.dkv_item = at(L.off_dkv_item); a.general_items = at(L.off_general_items);
+    a.dkv_counters = at(L.off_dkv_counters); a.dkv_item = at(L.off_dkv_item); a.short_on = at(L.off_short_on);
+    a.key_steps = at(L.off_key_steps);
     a.forward_only = forward_only ? 1 : 0;
+    a.short_keys = !forward_only && short_documents(d) ? 1 : 0;
+    a.key_run = (L.n_key_tiles + kLists - 1) / kLists;
+    a.per_cu = (float)d.hq / (float)a.n_slots;
+    a.short_step = d.head_dim == 64 ? kShortStep64 : kShortStep128;
     if (L.n_groups <= kSmallGroups && L.n_key_tiles <= kSmallKeyTiles && d.n_docs <= kCuLds) {
         plan_small_kernel<<<1, 1024, 0, stream>>>(a);
     } else {
@@ -682,7 +782,7 @@ extern "C" wlb_status wlb_attn_plan_records(const wlb_attn_desc* desc, wlb_plan_
     records->off_row_part = L.off_row_part;
     records->off_row_part_base = L.off_row_part_base;
     records->off_dkv_item = L.off_dkv_item;
-    records->off_general_items = L.off_general_items;
+    records->off_short_on = L.off_short_on;
     records->row_partial_bytes = row_partial_floats(desc->head_dim) * sizeof(float);
     records->row_partials_bytes = row_partial_bytes(*desc, L);
     return WLB_OK;

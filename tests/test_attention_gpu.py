@@ -228,10 +228,8 @@ def check_work_records(attn):
                 slot = t["key_slot_base"][r] + hk * ways + p if ways > 1 else -1
                 want.append([kt, hk, hk * G + p * nh, nh, slot, first, (last - first) * nh])
     assert (t["dkv_item"][:, :7] == np.asarray(want)).all()
-    short = t["dkv_item"][:, 7] == 1
-    assert ((t["key_range"][:, 1] - t["key_range"][:, 0])[t["dkv_item"][short, 0]] <= rec.short_span).all()
-    general = np.nonzero(~short)[0]
-    assert t["general_items"] == (general[-1] + 1 if len(general) else 0)
+    longest = (t["key_range"][:, 1] - t["key_range"][:, 0]).max()
+    assert not t["short_keys_on"] or longest <= rec.short_span
     return t
 
 
@@ -432,9 +430,9 @@ def test_short_hull_path_matches_oracle(docs, hq, hkv, d, cp):
 
 @pytest.mark.parametrize("hq,hkv,d,cp", [(8, 1, 128, 1), (2, 2, 64, 1), (6, 2, 128, 2), (16, 2, 64, 4)])
 def test_short_key_tiles_match_oracle(hq, hkv, d, cp):
-    """Key tiles that up to four 64-row groups can see have a dK/dV kernel of their own where documents are short on
-    average; here beside longer documents (spans just below and above the limit, split tiles), pads whose Q and dO
-    are garbage, keys that no row sees, and a ragged last tile."""
+    """Short documents beside longer ones: spans just below and above the limit of the dK/dV kernel of short key tiles (which
+    then leaves them all to the general one), split tiles, pads whose Q and dO are garbage, keys that no row sees, and a
+    ragged last tile."""
     docs = [1] * 40 + [128, 190, 256, 700] + [7, 64, 33, 2, 128, 90] * 6 + [5]
     w, tens = wl.small_case(79, docs, hq, hkv, d)
     for r in sorted({0, cp - 1}):
@@ -446,6 +444,63 @@ def test_short_key_tiles_match_oracle(hq, hkv, d, cp):
         c.dev["do"][pads] = float("nan")
         c.check_fwd(f" cp {cp} rank {r}")
         c.check_bwd(f" cp {cp} rank {r}")
+
+
+def short_keys_estimate(t, hq, hkv, d):
+    """Estimated times of dK/dV in the general kernel and in the kernel of short key tiles, in stages of the general one:
+    from the schedule's tables, as the schedule's rule is stated."""
+    import torch
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    G, ways = hq // hkv, t["key_ways"]
+    first, last = t["key_range"].T
+    span = last - first
+    top = span.argmax()
+    general = 18 + max(span[top] * (G // ways[top]), 1.45 * span.sum() * hq / n_cu) + 2 * (ways[top] > 1)
+    if span[top] > t["records"].short_span:
+        return general, np.inf
+    hull = t["block_hull"]
+    seen = np.zeros((len(span), 4), dtype=np.int64)
+    for kt in range(len(span)):
+        h = hull[2 * first[kt]:2 * last[kt]]
+        for w in range(4):
+            seen[kt, w] = ((h[:, 1] > h[:, 0]) & (h[:, 0] < kt * 128 + w * 32 + 32) & (h[:, 1] > kt * 128 + w * 32)).sum()
+    run = np.arange(len(span)) // -(-len(span) // 8)
+    load = max(seen[run == x].sum() for x in range(8))
+    return general, 7 + (1.0 if d == 64 else 1.3) * max(seen.max() * G, 0.35 * load * hq * 8 / n_cu) + 2
+
+
+@pytest.mark.parametrize("tokens,long,hq,hkv,d,cp,takes", [
+    (1024, 0, 4, 1, 64, 1, True),
+    (1024, 0, 16, 1, 128, 1, False),       # 48 steps one after another, where the general kernel divides the heads
+    (1024, 0, 32, 1, 128, 1, False),
+    (4096, 700, 8, 1, 128, 1, False),      # the long document's tiles would need the general launch as well
+    (4400, 0, 4, 2, 128, 1, True),         # the three-launch schedule
+    (4400, 0, 32, 1, 64, 1, False),
+    (9000, 700, 16, 2, 128, 1, False),
+    (3000, 190, 6, 2, 128, 2, True),       # pads, whose Q and dO are garbage, and keys that no row sees
+    (16800, 0, 4, 4, 64, 3, True),
+])
+def test_short_key_tiles_are_taken_where_that_is_shorter(tokens, long, hq, hkv, d, cp, takes):
+    """dK/dV is left to the kernel of short key tiles only where no tile has a long span and the schedule's estimate of it is
+    the shorter one; the results are the oracle's either way."""
+    rng = np.random.default_rng(tokens + hq)
+    docs = [long] if long else []
+    while sum(docs) < tokens:
+        docs.append(min(int(rng.integers(1, 65)), tokens - sum(docs)))
+    docs = rng.permutation(docs).tolist()
+    w, tens = wl.small_case(80, docs, hq, hkv, d)
+    sh = osh.shard(docs, cp, 0, osh.PER_DOC_PADDED)
+    c = Case(tens, sh["q_idx"], sh["cu_seqlens_k"], hq, hkv, d, w.scale)
+    pads = c.torch.from_numpy(c.q_idx < 0).cuda()
+    c.dev["q"][pads] = float("nan")
+    c.dev["do"][pads] = float("nan")
+    c.check_fwd()
+    t = check_work_records(c.attn)
+    assert t["records"].uses_short_keys
+    general, short = short_keys_estimate(t, hq, hkv, d)
+    assert (short <= general) == takes and abs(short - general) > 0.5       # far enough from the rounding of an estimate
+    assert t["short_keys_on"] == takes
+    c.check_bwd()
 
 
 @pytest.mark.parametrize("d", [64, 128])
