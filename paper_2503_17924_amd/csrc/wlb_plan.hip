@@ -75,13 +75,15 @@ bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L) {
     return items * mean_item_units(d, L) >= (long long)kRowGangMinUnitsPerSlot * slots;
 }
 
-// Parts of tiles, in launches with few items per slot whose shares are too short for the gangs: when the items fill at
-// most a quarter of the slots, or when they are long enough for the merge launch to pay off.
+// Parts of tiles, in launches with few items per slot whose shares are too short for the gangs (kRowPartMeanUnits,
+// kRowPartKeys).
 bool use_row_parts(const wlb_attn_desc& d, const PlanLayout& L) {
     if ((d.flags & WLB_ATTN_SCHEDULE_ITEMS) || use_row_gangs(d, L) || row_parts_added(d, L) < 1) return false;
     const long long items = (long long)L.n_fwd_tiles * d.hq, slots = 2LL * compute_units();
     if (items >= (long long)kRowGangMaxItemsPerSlot * slots) return false;
-    return items * 4 <= slots || mean_item_units(d, L) >= kRowPartMeanUnits;
+    if (items * 4 > slots) return mean_item_units(d, L) >= kRowPartMeanUnits;
+    const long long length = d.visible_pairs > 0 ? std::min<long long>(2 * (d.visible_pairs / d.n_q), d.t_kv) : d.t_kv / d.n_docs;
+    return std::min<long long>(length + (long long)kFwdTileRows * d.t_kv / d.n_q, d.t_kv) > kRowPartKeys;
 }
 
 // gang share weights: process-wide, set by wlb_attn_set_gang_weights (0 = not set: the defaults)

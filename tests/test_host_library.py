@@ -136,6 +136,29 @@ def test_schedule_choice_uses_the_pair_count_when_given():
         B.wlb_attn_plan_layout(B._desc(n_q, 131072, len(docs), 8, 1, 128, 0.1, visible_pairs=-1))
 
 
+@pytest.mark.parametrize("docs,hq,hkv,cp,parts", [
+    ([32] * 32, 8, 2, 1, 0),                 # 1024 tokens: no tile has more key tiles than a part may hold
+    ([384] * 2 + [256], 8, 2, 1, 0),
+    ([64] * 64, 4, 4, 1, 0),
+    ([500], 16, 2, 1, 0),
+    ([1536] * 2, 4, 4, 1, 1),
+    ([700, 100, 1300, 90, 1906], 4, 4, 2, 1),
+    ([40] * 100, 8, 1, 8, 1),                # 128 rows of one of eight ranks reach over 1024 tokens
+    ([5000], 4, 2, 1, 1),                    # more items than a quarter of the slots: by their mean work
+    ([512] * 16, 8, 2, 1, 0),
+])
+def test_query_tiles_are_divided_where_one_is_heavy(docs, hq, hkv, cp, parts):
+    """Dividing heavy query tiles costs a launch that merges the parts; calls whose tiles are all light do without it,
+    whether the descriptor has the pair count or not."""
+    sh = B.wlb_shard(docs, cp, cp - 1, B.SHARD_PER_DOC_PADDED)
+    for pairs in (sh["useful_pairs"], 0):
+        d = B._desc(len(sh["q_idx"]), sum(docs), len(docs), hq, hkv, 64, 0.125, visible_pairs=pairs)
+        assert not B.wlb_attn_plan_layout(d).uses_gangs
+        assert B.wlb_attn_plan_records(d).uses_parts == parts
+        d.flags = B.ATTN_SCHEDULE_ITEMS
+        assert B.wlb_attn_plan_records(d).uses_parts == 0
+
+
 def test_attention_argument_checks_need_no_gpu():
     d = B._desc(128, 128, 1, 4, 3, 128, 0.1)
     with pytest.raises(B.WlbError) as e:
