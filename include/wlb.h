@@ -283,8 +283,9 @@ typedef struct {
     int32_t uses_short_keys;             /* 1: the backward of this desc (its flags included) launches the dK/dV kernel of short key tiles */
     int32_t short_span;                  /* ... which can do the work if no key tile is seen by more row groups than this */
     size_t  off_row_item;                /* int32 [n_fwd_tiles][4], by order rank */
-    size_t  off_row_part;                /* int32 [max_parts][4], by order rank, a tile's parts in turn */
-    size_t  off_row_part_base;           /* int32 [n_fwd_tiles + 1]: parts before the tile of order rank r */
+    size_t  off_row_part;                /* int32 [max_parts][4], longest part first, a tile's parts in turn */
+    size_t  off_row_part_base;           /* int32 [n_fwd_tiles + 1][4]: of the tile of order rank r {first record, records, first
+                                            partial result (if more than one record), 0}; last: {records in all, 0, 0, 0} */
     size_t  off_dkv_item;                /* int32 [dkv_max_items][8], by item */
     size_t  off_short_on;                /* int32: 1: that kernel does the work, 0: the general one */
     size_t  row_partial_bytes;           /* bytes of one partial result of a query tile and head */

@@ -433,14 +433,14 @@ def plan_tables(attn: "Attention") -> dict:
     (heaviest first), fwd_prefix [n_fwd_tiles + 1] (running cost in that order, fixed cost per tile included);
     tile_short; key_range [n_key_tiles][2] (row groups a key tile is visible to), key_ways (items a key tile is
     split into), key_order, key_item_base, key_slot_base; the work records row_item [n_fwd_tiles][4], row_part
-    [parts][4], row_part_base [n_fwd_tiles + 1], dkv_item [items][8]; short_keys_on; block_hull [n_blocks32][2]; layout
+    [parts][4], row_part_base [n_fwd_tiles + 1][4], dkv_item [items][8]; short_keys_on; block_hull [n_blocks32][2]; layout
     (the PlanLayout) and records (the PlanRecords)."""
     lay = wlb_attn_plan_layout(attn.desc)
     rec = wlb_attn_plan_records(attn.desc)
     ws = attn.workspace[:lay.plan_bytes].cpu().numpy()
     i32 = lambda off, n: ws[off:off + 4 * n].view(np.int32).copy()
     n_q = attn.shape[0]
-    part_base = i32(rec.off_row_part_base, lay.n_fwd_tiles + 1)
+    part_base = i32(rec.off_row_part_base, 4 * (lay.n_fwd_tiles + 1)).reshape(-1, 4)
     item_base = i32(lay.off_key_item_base, lay.n_key_tiles + 1)
     return {
         "layout": lay, "records": rec,
@@ -453,7 +453,7 @@ def plan_tables(attn: "Attention") -> dict:
         "key_ways": i32(lay.off_key_ways, lay.n_key_tiles), "key_order": i32(lay.off_key_order, lay.n_key_tiles),
         "key_item_base": item_base, "key_slot_base": i32(lay.off_key_slot_base, lay.n_key_tiles + 1),
         "row_item": i32(rec.off_row_item, 4 * lay.n_fwd_tiles).reshape(-1, 4),
-        "row_part": i32(rec.off_row_part, 4 * int(part_base[-1])).reshape(-1, 4), "row_part_base": part_base,
+        "row_part": i32(rec.off_row_part, 4 * int(part_base[-1, 0])).reshape(-1, 4), "row_part_base": part_base,
         "dkv_item": i32(rec.off_dkv_item, 8 * int(item_base[-1])).reshape(-1, 8),
         "short_keys_on": bool(i32(rec.off_short_on, 1)[0]),
         "block_hull": i32(lay.off_block_hull, 2 * lay.n_blocks32).reshape(-1, 2),
@@ -485,9 +485,9 @@ def plan_report(attn: "Attention", name: str = "") -> str:
                      f"workgroups: share {q(share)}")
     elif t["records"].uses_parts:
         part = t["row_part"]
-        divided = np.diff(t["row_part_base"]) > 1
+        count = t["row_part_base"][:-1, 1]
         lines.append(f"  forward / dQ items: {len(part) * hq} (tile or part of one, head), key tiles {q(part[:, 2] - part[:, 1])}; "
-                     f"{int(divided.sum())} tiles divided into {int(np.diff(t['row_part_base'])[divided].sum())} parts")
+                     f"{int((count > 1).sum())} tiles divided into {int(count[count > 1].sum())} parts")
     else:
         lines.append(f"  forward / dQ items: {lay.n_fwd_tiles * hq} (tile, head), cost with fixed part {q(per)}")
     kr = t["key_range"]

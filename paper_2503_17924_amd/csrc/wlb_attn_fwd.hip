@@ -539,7 +539,7 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
     RowPiece pc;
     pc.member = y % G; y /= G;
     pc.hk = y % p.hkv;
-    const int n_items = p.row_part_base ? ld_const(p.row_part_base + p.n_tiles) : p.n_tiles;
+    const int n_items = p.row_part_base ? ld_const(p.row_part_base + 4 * p.n_tiles) : p.n_tiles;
     int index = (y / p.hkv) * 8 + x;
     if (index >= n_items) return;
     index = paired_index(index, n_items, p.first_half);
@@ -644,9 +644,10 @@ __global__ void __launch_bounds__(256) fwd_merge_parts_kernel(const FwdParams p)
     constexpr int PF = kFwdTileRows * D + 2 * kFwdTileRows;
     const int job = (int)blockIdx.x / kMergeSplit, which = (int)blockIdx.x % kMergeSplit;
     const int rank = job / p.hq, h = job % p.hq;
-    const int base = ld_const(p.row_part_base + rank), n = ld_const(p.row_part_base + rank + 1) - base;
+    const int4 base = ld_const4(p.row_part_base + 4 * rank);     // first record, records, first partial result
+    const int n = base.y;
     if (n < 2) return;
-    const float* first = p.partial + ((size_t)base * p.hq + h) * PF;
+    const float* first = p.partial + ((size_t)base.z * p.hq + h) * PF;
     fwd_merge_rows<D, kMergeSplit>(p, ld_const(p.sched.order + rank), h, which, n, [&](int i) __attribute__((always_inline)) {
         return first + (size_t)i * p.hq * PF;
     });

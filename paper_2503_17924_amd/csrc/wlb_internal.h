@@ -43,8 +43,8 @@ struct PlanLayout : wlb_plan_layout {
     // Work records of the one-workgroup-per-item launches: {query tile, first, one-past-last 64-key tile, code}, code = -1:
     // a whole tile, -2: a whole short-hull tile, else 2 * partial slot + (1: not the tile's first part)
     size_t off_row_item;       // int32 [n_fwd_tiles][4], by order rank: whole tiles only
-    size_t off_row_part;       // int32 [n_fwd_tiles + row_parts_added(..)][4]: heavy tiles divided into parts (row_part_limit), by rank, a tile's parts in turn
-    size_t off_row_part_base;  // int32 [n_fwd_tiles + 1]: parts before the tile of order rank r
+    size_t off_row_part;       // int32 [n_fwd_tiles + row_parts_added(..)][4]: heavy tiles divided into parts (row_part_limit), longest part first, a tile's parts in turn
+    size_t off_row_part_base;  // int32 [n_fwd_tiles + 1][4]: of the tile of order rank r {first record, records, first partial result, 0}; last: {records in all}
     size_t off_short_on;       // int32: 1: dkv_short_kernel does dK/dV, 0: the general kernel
     // Last, because a forward's schedule (wlb_attn_fwd_static) leaves them out.
     size_t off_dkv_item;       // int32 [dkv_max_items][8], by item: {key tile, KV head, first query head, query heads, partial slot or -1,

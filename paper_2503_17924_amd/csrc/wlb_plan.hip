@@ -149,7 +149,7 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
     L->static_bytes = off;
     L->off_tile_first = take(sizeof(int32_t) * L->n_fwd_tiles);
     L->off_row_item = take(sizeof(int32_t) * 4 * L->n_fwd_tiles);
-    L->off_row_part_base = take(sizeof(int32_t) * (L->n_fwd_tiles + 1));
+    L->off_row_part_base = take(sizeof(int32_t) * 4 * (L->n_fwd_tiles + 1));
     L->off_row_part = take(sizeof(int32_t) * 4 * (size_t)(L->n_fwd_tiles + row_parts_added(d, *L)));
     L->off_short_on = take(sizeof(int32_t));
     L->off_dkv_item = take(sizeof(int32_t) * 8 * (size_t)L->dkv_max_items);
@@ -298,25 +298,27 @@ __device__ __forceinline__ bool short_keys_pay(const PlanArgs& a, const KeyWork&
 static_assert(2 * kShortSpan <= 8 && kGroupRows == 2 * kShortBlockRows && kBwdKeyTile == 128, "a lane per 32 keys and row block");
 __device__ __forceinline__ bool block_sees(int2 hull, int kw0) { return hull.y > hull.x && hull.x < kw0 + 32 && hull.y > kw0; }
 
-// Where a tile stands in its order (heaviest first, ties by index), and sums over the tiles before it.
-__device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cost, int first, int is_short, int parts, int rank,
-                                               long long cost_before, int parts_before) {
-    const long long before = cost_before + (long long)rank * kRowItemOverhead;
-    a.fwd_order[rank] = i;
-    a.fwd_prefix[rank] = before;
+// Sums over the tiles before a query tile: in the tiles' order (heaviest first, ties by index), and in the order of the part
+// records, longest part first.  (Records in the tiles' order put halves of heavy tiles before heavier whole ones: three of 15
+// tiles of a 3808-token document on one of two ranks divided, 32 heads, forward 79 -> 98 us.)
+struct RowPlace { int rank; long long cost; int part_rank, records, partials; };
+__device__ __forceinline__ int part_length(int cost, int parts) { return parts == 1 ? cost : (cost + parts - 1) / parts; }
+__device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cost, int first, int is_short, int parts, const RowPlace& at) {
+    const long long before = at.cost + (long long)at.rank * kRowItemOverhead;
+    a.fwd_order[at.rank] = i;
+    a.fwd_prefix[at.rank] = before;
     const int4 whole = make_int4(i, first, first + cost, is_short ? -2 : -1);
-    reinterpret_cast<int4*>(a.row_item)[rank] = whole;
-    int4* part = reinterpret_cast<int4*>(a.row_part) + parts_before;
+    reinterpret_cast<int4*>(a.row_item)[at.rank] = whole;
+    int4* part = reinterpret_cast<int4*>(a.row_part) + at.records;
     if (parts == 1) part[0] = whole;
     else
-        for (int k = 0; k < parts; ++k)        // divided tiles come first, so a part's index is its partial slot as well
+        for (int k = 0; k < parts; ++k)
             part[k] = make_int4(i, first + (int)((long long)cost * k / parts), first + (int)((long long)cost * (k + 1) / parts),
-                                2 * (parts_before + k) + (k > 0));
-    a.row_part_base[rank] = parts_before;
-    if (rank == a.n_tiles - 1) {
-        a.fwd_prefix[a.n_tiles] = before + cost + kRowItemOverhead;
-        a.row_part_base[a.n_tiles] = parts_before + parts;
-    }
+                                2 * (at.partials + k) + (k > 0));
+    int4* base = reinterpret_cast<int4*>(a.row_part_base);
+    base[at.rank] = make_int4(at.records, parts, at.partials, 0);
+    if (at.rank == a.n_tiles - 1) a.fwd_prefix[a.n_tiles] = before + cost + kRowItemOverhead;
+    if (at.part_rank == a.n_tiles - 1) base[a.n_tiles] = make_int4(at.records + parts, 0, 0, 0);
 }
 __device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 range, int ways, int rank, int items_before, int slots_before) {
     a.key_ways[i] = ways;
@@ -373,8 +375,8 @@ __global__ void __launch_bounds__(256) plan_rows_kernel(const PlanArgs a) {
 // Orders by a counting rank (n is at most a few thousand).  A workgroup of 1024 ranks kOrderPerBlock elements: wavefront
 // w compares them with every (waves)th pair of elements, which pass through LDS in chunks, and the partial counts are
 // summed in LDS.  (One element per thread kept the n^2 comparisons on very few compute units: 40 us for 1024 key
-// tiles.)  item_of(j) gives an element's cost (>= 0) and a number of its own; Counts sums over the elements before
-// this one; put(i, item, counts) receives the result.
+// tiles.)  item_of(j) gives an element's cost (>= 0) and a number of its own; Counts::see decides whether another one comes
+// before it (ties: an earlier index) and sums; put(i, item, counts) receives the result.
 constexpr int kOrderPerBlock = 64, kOrderChunk = 2048;
 template <class Counts, class ItemOf, class Put>
 __device__ __forceinline__ void order_block(int n, int block, ItemOf item_of, Put put) {
@@ -388,15 +390,14 @@ __device__ __forceinline__ void order_block(int n, int block, ItemOf item_of, Pu
     for (int j0 = 0; j0 < n; j0 += kOrderChunk) {
         const int m = min(kOrderChunk, n - j0), m2 = (m + 1) & ~1;
         __syncthreads();
-        // past the end: a cost below every real one, so it never counts
-        for (int j = threadIdx.x; j < m2; j += 1024) s_item[j] = j < m ? item_of(j0 + j) : make_int2(-1, 0);
+        // past the end: below every real one, so it never counts
+        for (int j = threadIdx.x; j < m2; j += 1024) s_item[j] = j < m ? item_of(j0 + j) : make_int2(-1, -1);
         __syncthreads();
 #pragma unroll 2
         for (int j = 2 * seg; j < m; j += 2 * n_seg) {
             const int4 two = *reinterpret_cast<const int4*>(&s_item[j]);
-            // entries before i win ties: an entry counts if its cost exceeds own - 1 before i, own from i on
-            if (two.x > own.x - (j0 + j < i)) mine.add(two.x, two.y);
-            if (two.z > own.x - (j0 + j + 1 < i)) mine.add(two.z, two.w);
+            mine.see(make_int2(two.x, two.y), own, j0 + j < i);
+            mine.see(make_int2(two.z, two.w), own, j0 + j + 1 < i);
         }
     }
     s_part[seg][e] = mine;
@@ -406,14 +407,29 @@ __device__ __forceinline__ void order_block(int n, int block, ItemOf item_of, Pu
         put(i, own, mine);
     }
 }
-struct RowCounts {                 // query tiles before this one, their cost and their parts
-    int rank, parts; long long cost;
-    __device__ __forceinline__ void add(int c, int n) { rank += 1; parts += n; cost += c; }
-    __device__ __forceinline__ void join(const RowCounts& o) { rank += o.rank; parts += o.parts; cost += o.cost; }
+// query tiles: cost, and the length of its longest part << kPartBits | parts (the length of a sequence with a K of less than
+// 4 GiB has 19 bits in key tiles)
+constexpr int kPartBits = 11;
+struct RowCounts {
+    RowPlace at;
+    __device__ __forceinline__ void see(int2 o, int2 own, int earlier) {
+        if (o.x > own.x - earlier) { at.rank += 1; at.cost += o.x; }
+        if ((o.y >> kPartBits) > (own.y >> kPartBits) - earlier) {
+            const int parts = o.y & ((1 << kPartBits) - 1);
+            at.part_rank += 1;
+            at.records += parts;
+            at.partials += parts > 1 ? parts : 0;
+        }
+    }
+    __device__ __forceinline__ void join(const RowCounts& o) {
+        at.rank += o.at.rank; at.cost += o.at.cost; at.part_rank += o.at.part_rank; at.records += o.at.records; at.partials += o.at.partials;
+    }
 };
 struct KeyCounts {                 // key tiles before this one, and their items and partial slots for one KV head
     int rank, items, slots;
-    __device__ __forceinline__ void add(int, int ways) { rank += 1; items += ways; slots += ways > 1 ? ways : 0; }
+    __device__ __forceinline__ void see(int2 o, int2 own, int earlier) {
+        if (o.x > own.x - earlier) { rank += 1; items += o.y; slots += o.y > 1 ? o.y : 0; }
+    }
     __device__ __forceinline__ void join(const KeyCounts& o) { rank += o.rank; items += o.items; slots += o.slots; }
 };
 
@@ -438,9 +454,12 @@ __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int
     if ((int)blockIdx.x < order_blocks) {
         const int limit = row_part_limit(block_sum(a.n_tiles, &s_total, [&](int t) { return a.fwd_cost[t]; }), a);
         order_block<RowCounts>(a.n_tiles, blockIdx.x,
-                               [&](int j) { const int cost = a.fwd_cost[j]; return make_int2(cost, row_parts(cost, limit)); },
+                               [&](int j) {
+                                   const int cost = a.fwd_cost[j], parts = row_parts(cost, limit);
+                                   return make_int2(cost, part_length(cost, parts) << kPartBits | parts);
+                               },
                                [&](int i, int2 own, const RowCounts& c) {
-                                   put_query_tile(a, i, own.x, a.tile_first[i], a.tile_short[i], own.y, c.rank, c.cost, c.parts);
+                                   put_query_tile(a, i, own.x, a.tile_first[i], a.tile_short[i], own.y & ((1 << kPartBits) - 1), c.at);
                                });
         return;
     }
@@ -623,28 +642,32 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             total += __shfl_xor(total, o);
         }
         const int limit = row_part_limit(total, a);
-        int parts = before ? row_parts(other.cost, limit) : 0;
+        const int parts = row_parts(own.cost, limit), other_parts = row_parts(other.cost, limit);
+        const bool part_before = j < a.n_tiles && part_length(other.cost, other_parts) > part_length(own.cost, parts) - (j < t);
+        // records, partial results and tiles before it: at most 32 tiles and the parts added to them, in 10, 10 and 6 bits
+        int places = part_before ? other_parts | (other_parts > 1 ? other_parts << 10 : 0) | 1 << 20 : 0;
 #pragma unroll
-        for (int o = 16; o > 0; o >>= 1) parts += __shfl_xor(parts, o);
+        for (int o = 16; o > 0; o >>= 1) places += __shfl_xor(places, o);
         if (j == 0 && t < a.n_tiles) {
             const int is_short = s_fits[kGroupsPerTile * t] & s_fits[kGroupsPerTile * t + 1];
             a.fwd_cost[t] = own.cost;
             a.tile_first[t] = own.first;
             a.tile_short[t] = is_short;
-            put_query_tile(a, t, own.cost, own.first, is_short, row_parts(own.cost, limit), rank, sum, parts);
+            put_query_tile(a, t, own.cost, own.first, is_short, parts, RowPlace{rank, sum, places >> 20, places & 1023, (places >> 10) & 1023});
         }
     }
     if (a.forward_only) return;
     __syncthreads();
     if (tid == 0) *a.short_on = a.short_keys && short_keys_pay(a, s_work, item_limit((long long)s_work.total, a.hq, a.n_slots)) ? 1 : 0;
     {   // the key tiles' order: four threads per tile, each a quarter of the comparisons
-        const int i = tid >> 2, cost = s_items[i].x;
+        const int i = tid >> 2;
+        const int2 own = s_items[i];
         KeyCounts c{};
 #pragma unroll 4
         for (int j = 2 * (tid & 3); j < a.n_key_tiles; j += 8) {
             const int4 two = *reinterpret_cast<const int4*>(&s_items[j]);
-            if (two.x > cost - (j < i)) c.add(two.x, two.y);
-            if (two.z > cost - (j + 1 < i)) c.add(two.z, two.w);
+            c.see(make_int2(two.x, two.y), own, j < i);
+            c.see(make_int2(two.z, two.w), own, j + 1 < i);
         }
 #pragma unroll
         for (int o = 2; o > 0; o >>= 1) {
@@ -652,7 +675,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             c.items += __shfl_xor(c.items, o);
             c.slots += __shfl_xor(c.slots, o);
         }
-        if ((tid & 3) == 0 && i < a.n_key_tiles) put_key_tile(a, i, range, s_items[i].y, c.rank, c.items, c.slots);
+        if ((tid & 3) == 0 && i < a.n_key_tiles) put_key_tile(a, i, range, own.y, c.rank, c.items, c.slots);
     }
 }
 
@@ -698,9 +721,9 @@ wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_
 // process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the address
 // that call returns (kept per device) is what kernels and every other use of the memory get.
 // The stated limit counts the tables a schedule had to have when the limit was set (PlanLayout::static_bytes);
-// the tables added since (40 bytes per query tile of a schedule with at least 8 bytes per row, and 16 per part added, at most one per workgroup slot)
+// the tables added since (52 bytes per query tile of a schedule with at least 8 bytes per row, and 16 per part added, at most one per workgroup slot)
 // have room of their own.
-constexpr size_t kStaticExtraBytes = WLB_ATTN_FWD_STATIC_SCRATCH_BYTES / 8 / kFwdTileRows * 40 + 1024 * 16 + 2048;
+constexpr size_t kStaticExtraBytes = WLB_ATTN_FWD_STATIC_SCRATCH_BYTES / 8 / kFwdTileRows * 52 + 1024 * 16 + 2048;
 static __device__ __align__(256) unsigned char scratch[WLB_ATTN_FWD_STATIC_SCRATCH_BYTES + kStaticExtraBytes];
 
 constexpr int kMaxDevices = 64;

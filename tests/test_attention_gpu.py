@@ -200,10 +200,13 @@ def check_work_records(attn):
         g = g[g[:, 1] > g[:, 0]]
         r = int(np.nonzero(order == tile)[0][0])
         assert item[r, 1] == (g[:, 0].min() // 64 if len(g) else 0)
-    assert base[0] == 0 and (np.diff(base) >= 1).all() and base[-1] <= rec.max_parts
-    partials = []
+    count = base[:-1, 1]
+    assert (count >= 1).all() and base[-1, 0] == count.sum() == len(part) <= rec.max_parts
+    partials, at, longest = [], [], []
     for r in range(lay.n_fwd_tiles):
-        mine = part[base[r]:base[r + 1]]
+        mine = part[base[r, 0]:base[r, 0] + count[r]]
+        at += range(base[r, 0], base[r, 0] + count[r])
+        longest.append((-(mine[:, 2] - mine[:, 1]).max(), order[r], base[r, 0]))
         if len(mine) == 1:
             assert (mine[0] == item[r]).all()
             continue
@@ -213,8 +216,10 @@ def check_work_records(attn):
         assert size.min() >= 1 and size.max() - size.min() <= 1
         assert (mine[:, 3] >= 0).all() and ((mine[:, 3] & 1) == (np.arange(len(mine)) > 0)).all()
         slots = mine[:, 3] >> 1
-        assert (np.diff(slots) == 1).all()           # the merge kernel steps from one to the next
+        assert (slots == base[r, 2] + np.arange(len(mine))).all()
         partials += slots.tolist()
+    assert sorted(at) == list(range(len(part)))
+    assert [x[2] for x in sorted(longest)] == sorted(x[2] for x in longest)         # longest part first, ties by tile
     assert len(set(partials)) == len(partials)
     if partials:
         assert (max(partials) + 1) * hq * rec.row_partial_bytes <= rec.row_partials_bytes
@@ -281,7 +286,7 @@ def test_divided_query_tiles_and_their_records(docs, hq, hkv, d, cp, mode):
         slots = lay.row_gangs * (hq // hkv) // hq * hq
         units = int(t["fwd_prefix"][-1]) * hq
         limit = max(6, -(-(units * 6 // 4) // slots))
-        parts = np.diff(t["row_part_base"])
+        parts = t["row_part_base"][:-1, 1]
         assert (parts == np.where(t["tile_short"][t["fwd_order"]] == 1, 1, np.maximum(1, -(-t["fwd_cost"][t["fwd_order"]] // limit)))).all()
         assert parts.max() > 1
 
