@@ -691,7 +691,7 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     } else {
         const int items = L.n_fwd_tiles + (parts ? row_parts_added(d, L) : 0);
         const unsigned grid = (unsigned)((items + 7) / 8) * 8u * (unsigned)d.hq;
-        const unsigned grid_merge = (unsigned)std::min(L.n_fwd_tiles, row_parts_added(d, L)) * (unsigned)d.hq * kMergeSplit;
+        const unsigned grid_merge = (unsigned)row_tiles_divided(d, L) * (unsigned)d.hq * kMergeSplit;
         if (d.head_dim == 128) {
             fwd_items_kernel<128><<<grid, 256, 0, stream>>>(p);
             if (parts) fwd_merge_parts_kernel<128><<<grid_merge, 256, 0, stream>>>(p);

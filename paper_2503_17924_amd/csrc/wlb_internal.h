@@ -66,9 +66,17 @@ inline int row_gangs(int hq, int hkv, int cus) {
 // of the mean work of a workgroup slot (4 / 4, 6 / 4, 8 / 4 measured at 4095 rows, 16 heads: forward + dQ 218, 203 and
 // 229 us; undivided 247) and at most kRowPartMin key tiles where that is less (4 - 12: within 1 us at 2052 rows).
 constexpr int kRowPartMin = 6, kRowPartMean = 6;
+// None is divided unless the heaviest has kRowPartHeavy / 10 of the mean work of a compute unit: below that the launch is
+// balanced as it is, heavy tiles beside light ones (one of two ranks of a 3808-token document, 32 heads: forward 80 us whole,
+// 98 divided; 26624 tokens in documents of 3396, one of four ranks, 8 heads: 88 and 114).
+constexpr int kRowPartHeavy = 11;
 bool use_row_parts(const wlb_attn_desc& d, const PlanLayout& L);
-// upper bound of the number of divided tiles, and of the parts they add (each is at least a slot's mean work)
+// upper bound of the parts that divided tiles add (each is at least a slot's mean work), and of the number of divided tiles
 inline int row_parts_added(const wlb_attn_desc& d, const PlanLayout& L) { return L.row_gangs * (d.hq / d.hkv) / d.hq; }
+inline int row_tiles_divided(const wlb_attn_desc& d, const PlanLayout& L) {
+    const int most = row_parts_added(d, L) * 4 / kRowPartMean;
+    return most < L.n_fwd_tiles ? most : L.n_fwd_tiles;
+}
 // fixed cost of a query tile (loading Q, the first copies, the output) in units of one key tile's work
 constexpr int kRowItemOverhead = 6;
 // Default relative work share (percent) of a gang of the first half of a launch; a gang of the second half

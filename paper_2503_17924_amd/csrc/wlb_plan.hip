@@ -78,7 +78,7 @@ bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L) {
 // Parts of tiles, in launches with few items per slot whose shares are too short for the gangs (kRowPartMeanUnits,
 // kRowPartKeys).
 bool use_row_parts(const wlb_attn_desc& d, const PlanLayout& L) {
-    if ((d.flags & WLB_ATTN_SCHEDULE_ITEMS) || use_row_gangs(d, L) || row_parts_added(d, L) < 1) return false;
+    if ((d.flags & WLB_ATTN_SCHEDULE_ITEMS) || use_row_gangs(d, L) || row_tiles_divided(d, L) < 1) return false;
     const long long items = (long long)L.n_fwd_tiles * d.hq, slots = 2LL * compute_units();
     if (items >= (long long)kRowGangMaxItemsPerSlot * slots) return false;
     if (items * 4 > slots) return mean_item_units(d, L) >= kRowPartMeanUnits;
@@ -264,7 +264,8 @@ __device__ __forceinline__ int2 item_split(int span, int G, int limit) {
 }
 
 // A query tile with more key tiles than this is divided (equally) among parts that have at most as many.
-__device__ __forceinline__ int row_part_limit(long long total_cost, const PlanArgs& a) {
+__device__ __forceinline__ int row_part_limit(long long total_cost, int top_cost, const PlanArgs& a) {
+    if ((long long)top_cost * 10 * a.n_slots < total_cost * kRowPartHeavy * a.hq) return 0x7fffffff;
     const unsigned long long units = ((unsigned long long)total_cost + (unsigned long long)a.n_tiles * kRowItemOverhead) * a.hq;
     return (int)min(max((unsigned long long)kRowPartMin, (units * kRowPartMean / 4 + a.row_slots - 1) / a.row_slots), 0x7fffffffull);
 }
@@ -433,26 +434,28 @@ struct KeyCounts {                 // key tiles before this one, and their items
     __device__ __forceinline__ void join(const KeyCounts& o) { rank += o.rank; items += o.items; slots += o.slots; }
 };
 
-// Sum over the elements of value_of, for every thread of a workgroup of 1024; s_total is shared.
-template <class ValueOf>
-__device__ __forceinline__ long long block_sum(int n, long long* s_total, ValueOf value_of) {
-    if (threadIdx.x == 0) *s_total = 0;
-    __syncthreads();
-    long long sum = 0;
-    for (int i = threadIdx.x; i < n; i += 1024) sum += value_of(i);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if ((threadIdx.x & 63) == 0 && sum) atomicAdd((unsigned long long*)s_total, (unsigned long long)sum);
-    __syncthreads();
-    return *s_total;
-}
-
 // Second launch: workgroups [0, order_blocks) order the query tiles; the others find, one wavefront per key tile,
 // the groups whose hull touches it.
 __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int order_blocks) {
-    __shared__ long long s_total;
+    __shared__ unsigned long long s_total;
+    __shared__ int s_top;
     if ((int)blockIdx.x < order_blocks) {
-        const int limit = row_part_limit(block_sum(a.n_tiles, &s_total, [&](int t) { return a.fwd_cost[t]; }), a);
+        if (threadIdx.x == 0) { s_total = 0; s_top = 0; }
+        __syncthreads();
+        long long sum = 0;
+        int top = 0;
+        for (int t = threadIdx.x; t < a.n_tiles; t += 1024) { sum += a.fwd_cost[t]; top = max(top, a.fwd_cost[t]); }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            sum += __shfl_xor(sum, o);
+            top = max(top, __shfl_xor(top, o));
+        }
+        if ((threadIdx.x & 63) == 0 && sum) {
+            atomicAdd(&s_total, (unsigned long long)sum);
+            atomicMax(&s_top, top);
+        }
+        __syncthreads();
+        const int limit = row_part_limit((long long)s_total, s_top, a);
         order_block<RowCounts>(a.n_tiles, blockIdx.x,
                                [&](int j) {
                                    const int cost = a.fwd_cost[j], parts = row_parts(cost, limit);
@@ -634,14 +637,15 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
         static_assert(kSmallTiles == 32 && kGroupsPerTile == 2, "a lane of a half-wavefront per query tile");
         const TileCost own = cost_of(t), other = cost_of(j);
         const bool before = j < a.n_tiles && other.cost > own.cost - (j < t);
-        int rank = before, sum = before ? other.cost : 0, total = j < a.n_tiles ? other.cost : 0;
+        int rank = before, sum = before ? other.cost : 0, total = j < a.n_tiles ? other.cost : 0, top = total;
 #pragma unroll
         for (int o = 16; o > 0; o >>= 1) {
+            top = max(top, __shfl_xor(top, o));
             rank += __shfl_xor(rank, o);
             sum += __shfl_xor(sum, o);
             total += __shfl_xor(total, o);
         }
-        const int limit = row_part_limit(total, a);
+        const int limit = row_part_limit(total, top, a);
         const int parts = row_parts(own.cost, limit), other_parts = row_parts(other.cost, limit);
         const bool part_before = j < a.n_tiles && part_length(other.cost, other_parts) > part_length(own.cost, parts) - (j < t);
         // records, partial results and tiles before it: at most 32 tiles and the parts added to them, in 10, 10 and 6 bits

@@ -281,7 +281,10 @@ def test_divided_query_tiles_and_their_records(docs, hq, hkv, d, cp, mode):
         c.check_fwd(f" cp {cp} rank {r}")
         c.check_bwd(f" cp {cp} rank {r}")
         t = check_work_records(c.attn)
-        # a part holds at most 6 key tiles, or 6 / 4 of the mean work of a workgroup slot
+        # a part holds at most 6 key tiles, or 6 / 4 of the mean work of a workgroup slot; more than a compute unit's mean
+        # work in one tile
+        n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+        assert t["fwd_cost"].max() >= 1.1 * t["fwd_cost"].sum() * hq / n_cu
         lay = t["layout"]
         slots = lay.row_gangs * (hq // hkv) // hq * hq
         units = int(t["fwd_prefix"][-1]) * hq
@@ -289,6 +292,25 @@ def test_divided_query_tiles_and_their_records(docs, hq, hkv, d, cp, mode):
         parts = t["row_part_base"][:-1, 1]
         assert (parts == np.where(t["tile_short"][t["fwd_order"]] == 1, 1, np.maximum(1, -(-t["fwd_cost"][t["fwd_order"]] // limit)))).all()
         assert parts.max() > 1
+
+
+@pytest.mark.parametrize("docs,hq,hkv,cp,divided", [
+    ([3808], 32, 4, 2, False),             # the heaviest tile has the mean work of a compute unit
+    ([3328] * 8, 8, 8, 4, False),          # the same with the three-launch schedule
+    ([8144], 16, 2, 4, True),
+    ([12000], 4, 4, 2, True),
+])
+def test_query_tiles_stay_whole_where_the_launch_is_balanced(docs, hq, hkv, cp, divided):
+    import torch
+    sh = osh.shard(docs, cp, 0, osh.PER_DOC_PADDED)
+    attn = B.Attention(sh["q_idx"], sh["cu_seqlens_k"], sum(docs), hq, hkv, 128, 0.09, visible_pairs=int(sh["useful_pairs"]))
+    assert B.wlb_attn_plan_records(attn.desc).uses_parts
+    attn.plan()
+    torch.cuda.synchronize()
+    t = check_work_records(attn)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert (t["fwd_cost"].max() >= 1.1 * t["fwd_cost"].sum() * hq / n_cu) == divided
+    assert (t["row_part_base"][:-1, 1].max() > 1) == divided
 
 
 def test_gang_share_weights_change_the_cuts_not_the_result():
