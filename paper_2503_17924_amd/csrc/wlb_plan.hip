@@ -263,7 +263,8 @@ __device__ __forceinline__ int2 item_split(int span, int G, int limit) {
     return make_int2(span * heads, w);
 }
 
-// A query tile with more key tiles than this is divided (equally) among parts that have at most as many.
+// A query tile with more key tiles than this is divided (equally) among parts that have at most as many.  A short-hull tile
+// counts as one without key tiles: its blocks' windows are all it reads, however far apart they lie.
 __device__ __forceinline__ int row_part_limit(long long total_cost, int top_cost, const PlanArgs& a) {
     if ((long long)top_cost * 10 * a.n_slots < total_cost * kRowPartHeavy * a.hq) return 0x7fffffff;
     const unsigned long long units = ((unsigned long long)total_cost + (unsigned long long)a.n_tiles * kRowItemOverhead) * a.hq;
@@ -300,7 +301,7 @@ static_assert(2 * kShortSpan <= 8 && kGroupRows == 2 * kShortBlockRows && kBwdKe
 __device__ __forceinline__ bool block_sees(int2 hull, int kw0) { return hull.y > hull.x && hull.x < kw0 + 32 && hull.y > kw0; }
 
 // Sums over the tiles before a query tile: in the tiles' order (heaviest first, ties by index), and in the order of the part
-// records, longest part first.  (Records in the tiles' order put halves of heavy tiles before heavier whole ones: three of 15
+// records, longest part first (short-hull tiles last).  (Records in the tiles' order put halves of heavy tiles before heavier whole ones: three of 15
 // tiles of a 3808-token document on one of two ranks divided, 32 heads, forward 79 -> 98 us.)
 struct RowPlace { int rank; long long cost; int part_rank, records, partials; };
 __device__ __forceinline__ int part_length(int cost, int parts) { return parts == 1 ? cost : (cost + parts - 1) / parts; }
@@ -444,7 +445,11 @@ __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int
         __syncthreads();
         long long sum = 0;
         int top = 0;
-        for (int t = threadIdx.x; t < a.n_tiles; t += 1024) { sum += a.fwd_cost[t]; top = max(top, a.fwd_cost[t]); }
+        for (int t = threadIdx.x; t < a.n_tiles; t += 1024) {
+            const int cost = a.tile_short[t] ? 0 : a.fwd_cost[t];
+            sum += cost;
+            top = max(top, cost);
+        }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             sum += __shfl_xor(sum, o);
@@ -458,8 +463,8 @@ __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int
         const int limit = row_part_limit((long long)s_total, s_top, a);
         order_block<RowCounts>(a.n_tiles, blockIdx.x,
                                [&](int j) {
-                                   const int cost = a.fwd_cost[j], parts = row_parts(cost, limit);
-                                   return make_int2(cost, part_length(cost, parts) << kPartBits | parts);
+                                   const int cost = a.fwd_cost[j], work = a.tile_short[j] ? 0 : cost, parts = row_parts(work, limit);
+                                   return make_int2(cost, part_length(work, parts) << kPartBits | parts);
                                },
                                [&](int i, int2 own, const RowCounts& c) {
                                    put_query_tile(a, i, own.x, a.tile_first[i], a.tile_short[i], own.y & ((1 << kPartBits) - 1), c.at);
@@ -636,8 +641,11 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
         };
         static_assert(kSmallTiles == 32 && kGroupsPerTile == 2, "a lane of a half-wavefront per query tile");
         const TileCost own = cost_of(t), other = cost_of(j);
+        const int is_short = s_fits[kGroupsPerTile * t] & s_fits[kGroupsPerTile * t + 1];
+        const int other_short = s_fits[kGroupsPerTile * j] & s_fits[kGroupsPerTile * j + 1];
+        const int work = is_short ? 0 : own.cost, other_work = other_short ? 0 : other.cost;
         const bool before = j < a.n_tiles && other.cost > own.cost - (j < t);
-        int rank = before, sum = before ? other.cost : 0, total = j < a.n_tiles ? other.cost : 0, top = total;
+        int rank = before, sum = before ? other.cost : 0, total = j < a.n_tiles ? other_work : 0, top = total;
 #pragma unroll
         for (int o = 16; o > 0; o >>= 1) {
             top = max(top, __shfl_xor(top, o));
@@ -646,14 +654,13 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             total += __shfl_xor(total, o);
         }
         const int limit = row_part_limit(total, top, a);
-        const int parts = row_parts(own.cost, limit), other_parts = row_parts(other.cost, limit);
-        const bool part_before = j < a.n_tiles && part_length(other.cost, other_parts) > part_length(own.cost, parts) - (j < t);
+        const int parts = row_parts(work, limit), other_parts = row_parts(other_work, limit);
+        const bool part_before = j < a.n_tiles && part_length(other_work, other_parts) > part_length(work, parts) - (j < t);
         // records, partial results and tiles before it: at most 32 tiles and the parts added to them, in 10, 10 and 6 bits
         int places = part_before ? other_parts | (other_parts > 1 ? other_parts << 10 : 0) | 1 << 20 : 0;
 #pragma unroll
         for (int o = 16; o > 0; o >>= 1) places += __shfl_xor(places, o);
         if (j == 0 && t < a.n_tiles) {
-            const int is_short = s_fits[kGroupsPerTile * t] & s_fits[kGroupsPerTile * t + 1];
             a.fwd_cost[t] = own.cost;
             a.tile_first[t] = own.first;
             a.tile_short[t] = is_short;

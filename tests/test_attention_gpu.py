@@ -206,7 +206,9 @@ def check_work_records(attn):
     for r in range(lay.n_fwd_tiles):
         mine = part[base[r, 0]:base[r, 0] + count[r]]
         at += range(base[r, 0], base[r, 0] + count[r])
-        longest.append((-(mine[:, 2] - mine[:, 1]).max(), order[r], base[r, 0]))
+        is_short = t["tile_short"][order[r]]
+        assert not is_short or len(mine) == 1
+        longest.append((0 if is_short else -(mine[:, 2] - mine[:, 1]).max(), order[r], base[r, 0]))
         if len(mine) == 1:
             assert (mine[0] == item[r]).all()
             continue
@@ -219,7 +221,7 @@ def check_work_records(attn):
         assert (slots == base[r, 2] + np.arange(len(mine))).all()
         partials += slots.tolist()
     assert sorted(at) == list(range(len(part)))
-    assert [x[2] for x in sorted(longest)] == sorted(x[2] for x in longest)         # longest part first, ties by tile
+    assert [x[2] for x in sorted(longest)] == sorted(x[2] for x in longest)         # longest part first (short-hull: last), ties by tile
     assert len(set(partials)) == len(partials)
     if partials:
         assert (max(partials) + 1) * hq * rec.row_partial_bytes <= rec.row_partials_bytes
@@ -282,16 +284,38 @@ def test_divided_query_tiles_and_their_records(docs, hq, hkv, d, cp, mode):
         c.check_bwd(f" cp {cp} rank {r}")
         t = check_work_records(c.attn)
         # a part holds at most 6 key tiles, or 6 / 4 of the mean work of a workgroup slot; more than a compute unit's mean
-        # work in one tile
+        # work in one tile; short-hull tiles count as none
         n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-        assert t["fwd_cost"].max() >= 1.1 * t["fwd_cost"].sum() * hq / n_cu
         lay = t["layout"]
+        work = np.where(t["tile_short"] == 1, 0, t["fwd_cost"]).astype(np.int64)
+        assert work.max() >= 1.1 * work.sum() * hq / n_cu
         slots = lay.row_gangs * (hq // hkv) // hq * hq
-        units = int(t["fwd_prefix"][-1]) * hq
+        units = (int(work.sum()) + ROW_ITEM_OVERHEAD * lay.n_fwd_tiles) * hq
         limit = max(6, -(-(units * 6 // 4) // slots))
         parts = t["row_part_base"][:-1, 1]
-        assert (parts == np.where(t["tile_short"][t["fwd_order"]] == 1, 1, np.maximum(1, -(-t["fwd_cost"][t["fwd_order"]] // limit)))).all()
+        assert (parts == np.maximum(1, -(-work[t["fwd_order"]] // limit))).all()
         assert parts.max() > 1
+
+
+@pytest.mark.parametrize("long,hq,hkv,d", [(2000, 4, 4, 64), (4000, 2, 1, 128)])       # one and three launches of the schedule
+def test_short_hull_tiles_of_distant_blocks_stay_whole(long, hq, hkv, d):
+    """Blocks of 32 rows from documents all over the sequence side by side in a query tile: each fits the short-hull window,
+    the tile's hull is wide.  Beside divided tiles of a long document they stay whole short-hull tiles."""
+    docs = [64] * 32 + [long]
+    t_kv = sum(docs)
+    blocks = np.random.default_rng(6).permutation(64).repeat(32) * 32 + np.tile(np.arange(32), 64)
+    q_idx = np.concatenate([blocks, np.arange(2048, t_kv)])
+    w, tens = wl.small_case(83, docs, hq, hkv, d)
+    c = Case(tens, q_idx, _cu(docs), hq, hkv, d, w.scale)
+    c.attn.visible_pairs = sum(n * (n + 1) // 2 for n in docs)
+    c.attn.desc, c.attn.desc_reuse = c.attn.make_desc(0), c.attn.make_desc(B.ATTN_REUSE_PLAN)
+    c.check_fwd()
+    t = check_work_records(c.attn)
+    assert t["records"].uses_parts and t["row_part_base"][:-1, 1].max() > 1
+    wide = (t["tile_short"] == 1) & (t["fwd_cost"] > 12)
+    assert wide.sum() > 8
+    assert (t["row_part"][np.isin(t["row_part"][:, 0], np.nonzero(wide)[0]), 3] == -2).all()
+    c.check_bwd()
 
 
 @pytest.mark.parametrize("docs,hq,hkv,cp,divided", [
