@@ -163,7 +163,7 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
 // Everything the schedule kernels read and write.
 struct PlanArgs {
     const int32_t* q_idx; const int32_t* cu;
-    int n_q, t_kv, n_docs, n_groups, n_tiles, n_key_tiles, hq, hkv, n_slots, row_slots, forward_only, short_keys, key_run;
+    int n_q, t_kv, n_docs, n_groups, n_tiles, n_key_tiles, hq, hkv, n_slots, row_slots, forward_only, parts, short_keys, key_run;
     float short_step, per_cu;
     int32_t* row_lo; int32_t* row_hi; int32_t* group; int32_t* group_real; int32_t* block_hull;
     int32_t* fwd_cost; int32_t* tile_first; int32_t* tile_short; int32_t* fwd_order; int32_t* row_item; int32_t* row_part; int32_t* row_part_base;
@@ -305,24 +305,35 @@ __device__ __forceinline__ bool block_sees(int2 hull, int kw0) { return hull.y >
 // tiles of a 3808-token document on one of two ranks divided, 32 heads, forward 79 -> 98 us.)
 struct RowPlace { int rank; long long cost; int part_rank, records, partials; };
 __device__ __forceinline__ int part_length(int cost, int parts) { return parts == 1 ? cost : (cost + parts - 1) / parts; }
-__device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cost, int first, int is_short, int parts, const RowPlace& at) {
+// (Each of the tile's `workers` threads calls it; they share its part records.)
+__device__ __forceinline__ void put_query_tile(const PlanArgs& a, int i, int cost, int first, int is_short, int parts, const RowPlace& at, int worker, int workers) {
+    int4* part = reinterpret_cast<int4*>(a.row_part) + at.records;
+    for (int k = worker; parts > 1 && k < parts; k += workers)
+        part[k] = make_int4(i, first + (int)((long long)cost * k / parts), first + (int)((long long)cost * (k + 1) / parts),
+                            2 * (at.partials + k) + (k > 0));
+    if (worker > 0) return;
     const long long before = at.cost + (long long)at.rank * kRowItemOverhead;
     a.fwd_order[at.rank] = i;
     a.fwd_prefix[at.rank] = before;
     const int4 whole = make_int4(i, first, first + cost, is_short ? -2 : -1);
     reinterpret_cast<int4*>(a.row_item)[at.rank] = whole;
-    int4* part = reinterpret_cast<int4*>(a.row_part) + at.records;
     if (parts == 1) part[0] = whole;
-    else
-        for (int k = 0; k < parts; ++k)
-            part[k] = make_int4(i, first + (int)((long long)cost * k / parts), first + (int)((long long)cost * (k + 1) / parts),
-                                2 * (at.partials + k) + (k > 0));
     int4* base = reinterpret_cast<int4*>(a.row_part_base);
     base[at.rank] = make_int4(at.records, parts, at.partials, 0);
     if (at.rank == a.n_tiles - 1) a.fwd_prefix[a.n_tiles] = before + cost + kRowItemOverhead;
     if (at.part_rank == a.n_tiles - 1) base[a.n_tiles] = make_int4(at.records + parts, 0, 0, 0);
 }
-__device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 range, int ways, int rank, int items_before, int slots_before) {
+// One record per item, KV head major, head part minor: what a workgroup needs to begin.  (With one thread per tile they
+// made the schedule of 64 KV heads 2 - 3 us longer.)
+__device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 range, int ways, int rank, int items_before, int slots_before, int worker, int workers) {
+    const int shift = 31 - __clz(ways), G = a.hq / a.hkv, nh = G >> shift, item0 = items_before * a.hkv, slot0 = slots_before * a.hkv;
+    for (int j = worker; j < a.hkv << shift; j += workers) {         // ways: a power of two
+        const int hk = j >> shift, part = j & (ways - 1);
+        int4* rec = reinterpret_cast<int4*>(a.dkv_item) + 2 * (size_t)(item0 + j);
+        rec[0] = make_int4(i, hk, hk * G + part * nh, nh);
+        rec[1] = make_int4(ways > 1 ? slot0 + j : -1, range.x, (range.y - range.x) * nh, 0);
+    }
+    if (worker > 0) return;
     a.key_ways[i] = ways;
     a.key_order[rank] = i;
     a.key_item_base[rank] = items_before * a.hkv;
@@ -331,14 +342,6 @@ __device__ __forceinline__ void put_key_tile(const PlanArgs& a, int i, int2 rang
         a.key_item_base[a.n_key_tiles] = (items_before + ways) * a.hkv;
         a.key_slot_base[a.n_key_tiles] = (slots_before + (ways > 1 ? ways : 0)) * a.hkv;
     }
-    // one record per item, KV head major, head part minor: what a workgroup needs to begin
-    const int G = a.hq / a.hkv, nh = G / ways, item0 = items_before * a.hkv, slot0 = slots_before * a.hkv;
-    for (int hk = 0, j = 0; hk < a.hkv; ++hk)
-        for (int part = 0; part < ways; ++part, ++j) {
-            int4* rec = reinterpret_cast<int4*>(a.dkv_item) + 2 * (size_t)(item0 + j);
-            rec[0] = make_int4(i, hk, hk * G + part * nh, nh);
-            rec[1] = make_int4(ways > 1 ? slot0 + j : -1, range.x, (range.y - range.x) * nh, 0);
-        }
 }
 
 // Schedule, first launch of three: a wavefront per group of 64 rows, and the two query tiles of the workgroup.
@@ -378,13 +381,15 @@ __global__ void __launch_bounds__(256) plan_rows_kernel(const PlanArgs a) {
 // w compares them with every (waves)th pair of elements, which pass through LDS in chunks, and the partial counts are
 // summed in LDS.  (One element per thread kept the n^2 comparisons on very few compute units: 40 us for 1024 key
 // tiles.)  item_of(j) gives an element's cost (>= 0) and a number of its own; Counts::see decides whether another one comes
-// before it (ties: an earlier index) and sums; put(i, item, counts) receives the result.
+// before it (ties: an earlier index) and sums; put(i, item, counts, worker, workers) receives the result: in one thread per
+// element or, where much follows for an element (`shared`), in a wavefront.
 constexpr int kOrderPerBlock = 64, kOrderChunk = 2048;
 template <class Counts, class ItemOf, class Put>
-__device__ __forceinline__ void order_block(int n, int block, ItemOf item_of, Put put) {
+__device__ __forceinline__ void order_block(int n, int block, bool shared, ItemOf item_of, Put put) {
     constexpr int n_seg = 1024 / kOrderPerBlock;
     __shared__ __attribute__((aligned(16))) int2 s_item[kOrderChunk];
     __shared__ Counts s_part[n_seg][kOrderPerBlock];
+    __shared__ int2 s_own[kOrderPerBlock];
     const int e = threadIdx.x % kOrderPerBlock, seg = threadIdx.x / kOrderPerBlock;
     const int i = block * kOrderPerBlock + e;
     const int2 own = i < n ? item_of(i) : make_int2(0, 0);
@@ -404,10 +409,16 @@ __device__ __forceinline__ void order_block(int n, int block, ItemOf item_of, Pu
     }
     s_part[seg][e] = mine;
     __syncthreads();
-    if (seg == 0 && i < n) {
+    if (seg == 0) {
         for (int s = 1; s < n_seg; ++s) mine.join(s_part[s][e]);
-        put(i, own, mine);
+        if (!shared && i < n) put(i, own, mine, 0, 1);
+        s_part[0][e] = mine;
+        s_own[e] = own;
     }
+    if (!shared) return;
+    __syncthreads();
+    for (int k = threadIdx.x >> 6; k < kOrderPerBlock; k += 1024 / 64)
+        if (block * kOrderPerBlock + k < n) put(block * kOrderPerBlock + k, s_own[k], s_part[0][k], threadIdx.x & 63, 64);
 }
 // query tiles: cost, and the length of its longest part << kPartBits | parts (the length of a sequence with a K of less than
 // 4 GiB has 19 bits in key tiles)
@@ -441,33 +452,38 @@ __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int
     __shared__ unsigned long long s_total;
     __shared__ int s_top;
     if ((int)blockIdx.x < order_blocks) {
-        if (threadIdx.x == 0) { s_total = 0; s_top = 0; }
-        __syncthreads();
-        long long sum = 0;
-        int top = 0;
-        for (int t = threadIdx.x; t < a.n_tiles; t += 1024) {
-            const int cost = a.tile_short[t] ? 0 : a.fwd_cost[t];
-            sum += cost;
-            top = max(top, cost);
-        }
+        int limit = 0x7fffffff;
+        bool many = false;             // a tile of many parts
+        if (a.parts) {
+            if (threadIdx.x == 0) { s_total = 0; s_top = 0; }
+            __syncthreads();
+            long long sum = 0;
+            int top = 0;
+            for (int t = threadIdx.x; t < a.n_tiles; t += 1024) {
+                const int work = a.tile_short[t] ? 0 : a.fwd_cost[t];
+                sum += work;
+                top = max(top, work);
+            }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            sum += __shfl_xor(sum, o);
-            top = max(top, __shfl_xor(top, o));
+            for (int o = 32; o > 0; o >>= 1) {
+                sum += __shfl_xor(sum, o);
+                top = max(top, __shfl_xor(top, o));
+            }
+            if ((threadIdx.x & 63) == 0 && sum) {
+                atomicAdd(&s_total, (unsigned long long)sum);
+                atomicMax(&s_top, top);
+            }
+            __syncthreads();
+            limit = row_part_limit((long long)s_total, s_top, a);
+            many = s_top / 16 > limit;
         }
-        if ((threadIdx.x & 63) == 0 && sum) {
-            atomicAdd(&s_total, (unsigned long long)sum);
-            atomicMax(&s_top, top);
-        }
-        __syncthreads();
-        const int limit = row_part_limit((long long)s_total, s_top, a);
-        order_block<RowCounts>(a.n_tiles, blockIdx.x,
+        order_block<RowCounts>(a.n_tiles, blockIdx.x, many,
                                [&](int j) {
-                                   const int cost = a.fwd_cost[j], work = a.tile_short[j] ? 0 : cost, parts = row_parts(work, limit);
+                                   const int cost = a.fwd_cost[j], work = a.parts && a.tile_short[j] ? 0 : cost, parts = row_parts(work, limit);
                                    return make_int2(cost, part_length(work, parts) << kPartBits | parts);
                                },
-                               [&](int i, int2 own, const RowCounts& c) {
-                                   put_query_tile(a, i, own.x, a.tile_first[i], a.tile_short[i], own.y & ((1 << kPartBits) - 1), c.at);
+                               [&](int i, int2 own, const RowCounts& c, int worker, int workers) {
+                                   put_query_tile(a, i, own.x, a.tile_first[i], a.tile_short[i], own.y & ((1 << kPartBits) - 1), c.at, worker, workers);
                                });
         return;
     }
@@ -542,9 +558,9 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
     const int limit = item_limit((long long)s_work.total, a.hq, a.n_slots);
     const bool short_on = a.short_keys && short_keys_pay(a, s_work, limit);        // every workgroup comes to the same result
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.short_on = short_on ? 1 : 0;
-    order_block<KeyCounts>(a.n_key_tiles, blockIdx.x, [&](int j) { return item_split(a.key_span[j], G, limit); },
-                           [&](int i, int2 own, const KeyCounts& c) {
-                               put_key_tile(a, i, make_int2(a.key_range[2 * i], a.key_range[2 * i + 1]), own.y, c.rank, c.items, c.slots);
+    order_block<KeyCounts>(a.n_key_tiles, blockIdx.x, a.hkv > 8, [&](int j) { return item_split(a.key_span[j], G, limit); },
+                           [&](int i, int2 own, const KeyCounts& c, int worker, int workers) {
+                               put_key_tile(a, i, make_int2(a.key_range[2 * i], a.key_range[2 * i + 1]), own.y, c.rank, c.items, c.slots, worker, workers);
                            });
 }
 
@@ -643,7 +659,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
         const TileCost own = cost_of(t), other = cost_of(j);
         const int is_short = s_fits[kGroupsPerTile * t] & s_fits[kGroupsPerTile * t + 1];
         const int other_short = s_fits[kGroupsPerTile * j] & s_fits[kGroupsPerTile * j + 1];
-        const int work = is_short ? 0 : own.cost, other_work = other_short ? 0 : other.cost;
+        const int work = a.parts && is_short ? 0 : own.cost, other_work = a.parts && other_short ? 0 : other.cost;
         const bool before = j < a.n_tiles && other.cost > own.cost - (j < t);
         int rank = before, sum = before ? other.cost : 0, total = j < a.n_tiles ? other_work : 0, top = total;
 #pragma unroll
@@ -653,18 +669,20 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             sum += __shfl_xor(sum, o);
             total += __shfl_xor(total, o);
         }
-        const int limit = row_part_limit(total, top, a);
+        const int limit = a.parts ? row_part_limit(total, top, a) : 0x7fffffff;
         const int parts = row_parts(work, limit), other_parts = row_parts(other_work, limit);
         const bool part_before = j < a.n_tiles && part_length(other_work, other_parts) > part_length(work, parts) - (j < t);
         // records, partial results and tiles before it: at most 32 tiles and the parts added to them, in 10, 10 and 6 bits
         int places = part_before ? other_parts | (other_parts > 1 ? other_parts << 10 : 0) | 1 << 20 : 0;
 #pragma unroll
         for (int o = 16; o > 0; o >>= 1) places += __shfl_xor(places, o);
-        if (j == 0 && t < a.n_tiles) {
-            a.fwd_cost[t] = own.cost;
-            a.tile_first[t] = own.first;
-            a.tile_short[t] = is_short;
-            put_query_tile(a, t, own.cost, own.first, is_short, parts, RowPlace{rank, sum, places >> 20, places & 1023, (places >> 10) & 1023});
+        if (t < a.n_tiles) {
+            if (j == 0) {
+                a.fwd_cost[t] = own.cost;
+                a.tile_first[t] = own.first;
+                a.tile_short[t] = is_short;
+            }
+            put_query_tile(a, t, own.cost, own.first, is_short, parts, RowPlace{rank, sum, places >> 20, places & 1023, (places >> 10) & 1023}, j, 32);
         }
     }
     if (a.forward_only) return;
@@ -686,7 +704,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             c.items += __shfl_xor(c.items, o);
             c.slots += __shfl_xor(c.slots, o);
         }
-        if ((tid & 3) == 0 && i < a.n_key_tiles) put_key_tile(a, i, range, own.y, c.rank, c.items, c.slots);
+        if (i < a.n_key_tiles) put_key_tile(a, i, range, own.y, c.rank, c.items, c.slots, tid & 3, 4);
     }
 }
 
@@ -703,6 +721,9 @@ wlb_status launch_plan(const wlb_attn_desc& d, const PlanLayout& L, const int32_
     a.fwd_cost = at(L.off_fwd_cost); a.tile_first = at(L.off_tile_first); a.tile_short = at(L.off_tile_short);
     a.fwd_order = at(L.off_fwd_order); a.row_item = at(L.off_row_item); a.row_part = at(L.off_row_part); a.row_part_base = at(L.off_row_part_base);
     a.row_slots = std::max(1, row_parts_added(d, L) * d.hq);
+    wlb_attn_desc unforced = d;        // the tables do not depend on flags that force a schedule
+    unforced.flags = 0;
+    a.parts = use_row_parts(unforced, L) ? 1 : 0;
     a.fwd_prefix = (long long*)(ws + L.off_fwd_prefix);
     a.key_range = at(L.off_key_range); a.key_span = at(L.off_key_span); a.key_ways = at(L.off_key_ways);
     a.key_order = at(L.off_key_order); a.key_item_base = at(L.off_key_item_base); a.key_slot_base = at(L.off_key_slot_base);

@@ -208,7 +208,7 @@ def check_work_records(attn):
         at += range(base[r, 0], base[r, 0] + count[r])
         is_short = t["tile_short"][order[r]]
         assert not is_short or len(mine) == 1
-        longest.append((0 if is_short else -(mine[:, 2] - mine[:, 1]).max(), order[r], base[r, 0]))
+        longest.append((0 if is_short and rec.uses_parts else -(mine[:, 2] - mine[:, 1]).max(), order[r], base[r, 0]))
         if len(mine) == 1:
             assert (mine[0] == item[r]).all()
             continue
@@ -316,6 +316,17 @@ def test_short_hull_tiles_of_distant_blocks_stay_whole(long, hq, hkv, d):
     assert wide.sum() > 8
     assert (t["row_part"][np.isin(t["row_part"][:, 0], np.nonzero(wide)[0]), 3] == -2).all()
     c.check_bwd()
+
+
+@pytest.mark.parametrize("t_kv,n_q,hq,hkv", [(40000, 200, 1, 1), (20000, 300, 2, 1)])      # three launches of the schedule, one
+def test_query_tiles_of_hundreds_of_parts(t_kv, n_q, hq, hkv):
+    """The last rows of a long document: two or three query tiles, each in as many parts as fill the GPU."""
+    w, tens = wl.small_case(84, [t_kv], hq, hkv, 64)
+    c = Case(tens, np.arange(t_kv - n_q, t_kv), _cu([t_kv]), hq, hkv, 64, w.scale)
+    c.check_fwd()
+    c.check_bwd()
+    t = check_work_records(c.attn)
+    assert t["row_part_base"][:-1, 1].max() > 50
 
 
 @pytest.mark.parametrize("docs,hq,hkv,cp,divided", [
@@ -660,6 +671,7 @@ def test_schedule_tables():
 @pytest.mark.parametrize("docs,hq,hkv", [
     ([1700, 2, 900, 64, 1600], 4, 2),                                                       # just above 4096 rows
     (np.random.default_rng(4).integers(1, 33, size=2500).tolist() + [700], 8, 1),           # more documents than LDS holds
+    ([700] * 13 + [77], 36, 18),                                                            # records of a tile shared by a wavefront
 ])
 @pytest.mark.parametrize("shuffled", [False, True])
 def test_schedule_tables_of_larger_calls(docs, hq, hkv, shuffled):
