@@ -600,36 +600,27 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
     dq_piece<D>(p, smem, pc);
 }
 
-// Sums the partial dQ of a query tile that was cut at gang boundaries.  One workgroup per
-// (gang, member): it acts if its gang's last piece is the first part of a tile, and then takes
-// that part and the first piece of every later gang whose (non-empty) share begins inside the tile.
-template <int D, int SPLIT, class PartOf>
-__device__ __forceinline__ void dq_merge_rows(const BwdParams& p, int tile, int h, int which, int n, PartOf part_of) {
+// dQ rows of 1 / SPLIT of a query tile and head; sum_of(offset) adds up the four elements at an offset of the tile's partial results.
+template <int D, int SPLIT, class SumOf>
+__device__ __forceinline__ void dq_merge_rows(const BwdParams& p, int tile, int h, int which, SumOf sum_of) {
     constexpr int BM = kFwdTileRows, V4 = D / 4;
     constexpr int PER = BM * V4 / SPLIT;
-    static_assert(PER % 256 == 0, "whole passes");
-#pragma unroll
-    for (int k = 0; k < PER / 256; ++k) {
-        const int e = which * PER + k * 256 + (int)threadIdx.x;
+    for (int e = which * PER + (int)threadIdx.x; e < (which + 1) * PER; e += 256) {
         const int rl = e / V4, d4 = e % V4;
         const int row = tile * BM + rl;
         if (row >= p.n_q) continue;
-        const size_t at = (size_t)rl * D + d4 * 4;
-        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-        for (int i0 = 0; i0 < n; i0 += 4) {                      // the loads of four parts together
-            f32x4 x[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(part_of(min(i0 + i, n - 1)) + at);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (i0 + i < n) sum += x[i];
-        }
+        const f32x4 sum = sum_of((size_t)rl * D + d4 * 4);
         const bool real = p.row_hi[row] > 0;
         *reinterpret_cast<bf16x4*>(p.dq + ((size_t)row * p.hq + h) * D + d4 * 4) =
             real ? pack4(sum[0] * p.scale, sum[1] * p.scale, sum[2] * p.scale, sum[3] * p.scale) : pack4(0.f, 0.f, 0.f, 0.f);
     }
 }
 
+// Sums the partial dQ of a query tile that was cut at gang boundaries.  kGangMergeSplit workgroups per
+// (gang, member): they act if the gang's last piece is the first part of a tile, and then take
+// that part and the first piece of every later gang whose (non-empty) share begins inside the tile.  Most have two parts:
+// one load after the other, where requesting four together costs registers and repeats loads (21 us against 30, 128K tokens
+// on one of eight ranks).
 template <int D>
 __global__ void __launch_bounds__(256) dq_merge_kernel(const BwdParams p) {
     constexpr int BM = kFwdTileRows, PF = BM * D + 2 * BM;
@@ -639,14 +630,18 @@ __global__ void __launch_bounds__(256) dq_merge_kernel(const BwdParams p) {
     RowCut cut;
     if (!cut.find(s, gang)) return;
     auto part = [&](int slot) { return p.row_partial + ((size_t)slot * s.G + member) * PF; };
+    const float* first = part(cut.first_slot());
     constexpr int CAP = 32;
     __shared__ int s_slots[CAP], s_count;
     const int n_later = gather_later_parts<CAP>(cut, s_slots, &s_count);
-    dq_merge_rows<D, kGangMergeSplit>(p, cut.tile, cut.hk * s.G + member, which, n_later + 1, [&](int i) __attribute__((always_inline)) {
-        int slot = cut.first_slot();
-        if (i > 0 && n_later <= CAP) slot = s_slots[i - 1];
-        else if (i > 0) cut.later_parts([&](int later) { if (--i == 0) slot = later; });
-        return part(slot);
+    dq_merge_rows<D, kGangMergeSplit>(p, cut.tile, cut.hk * s.G + member, which, [&](size_t at) __attribute__((always_inline)) {
+        f32x4 sum = *reinterpret_cast<const f32x4*>(first + at);
+        if (n_later <= CAP) {
+            for (int i = 0; i < n_later; ++i) sum += *reinterpret_cast<const f32x4*>(part(s_slots[i]) + at);
+        } else {
+            cut.later_parts([&](int slot) { sum += *reinterpret_cast<const f32x4*>(part(slot) + at); });
+        }
+        return sum;
     });
 }
 
@@ -660,8 +655,18 @@ __global__ void __launch_bounds__(256) dq_merge_parts_kernel(const BwdParams p) 
     const int n = base.y;
     if (n < 2) return;
     const float* first = p.row_partial + ((size_t)base.z * p.hq + h) * PF;
-    dq_merge_rows<D, kMergeSplit>(p, ld_const(p.sched.order + rank), h, which, n, [&](int i) __attribute__((always_inline)) {
-        return first + (size_t)i * p.hq * PF;
+    const size_t step = (size_t)p.hq * PF;
+    dq_merge_rows<D, kMergeSplit>(p, ld_const(p.sched.order + rank), h, which, [&](size_t at) __attribute__((always_inline)) {
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+        for (int i0 = 0; i0 < n; i0 += 4) {                      // the loads of four parts together
+            f32x4 x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(first + min(i0 + i, n - 1) * step + at);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (i0 + i < n) sum += x[i];
+        }
+        return sum;
     });
 }
 
