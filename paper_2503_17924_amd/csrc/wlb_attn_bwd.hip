@@ -1374,7 +1374,7 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.sched.order = (const int32_t*)(ws + L.off_fwd_order);
     p.sched.tile_first = (const int32_t*)(ws + L.off_tile_first);
     const bool parts = use_row_parts(d, L);
-    p.first_half = compute_units() / d.hq;
+    p.first_half = row_first_half(d);
     p.row_item = (const int32_t*)(ws + (parts ? L.off_row_part : L.off_row_item));
     p.row_part_base = parts ? (const int32_t*)(ws + L.off_row_part_base) : nullptr;
     p.sched.n_tiles = L.n_fwd_tiles; p.sched.hkv = d.hkv; p.sched.G = d.hq / d.hkv; p.sched.n_gangs = L.row_gangs;

@@ -77,6 +77,9 @@ inline int row_tiles_divided(const wlb_attn_desc& d, const PlanLayout& L) {
     const int most = row_parts_added(d, L) * 4 / kRowPartMean;
     return most < L.n_fwd_tiles ? most : L.n_fwd_tiles;
 }
+// positions of a one-workgroup-per-item launch whose workgroups fill the compute units once (see paired_index); 0: a position's
+// workgroups, one per query head, fill more than the compute units of an XCD
+inline int row_first_half(const wlb_attn_desc& d) { return d.hq * kLists <= compute_units() ? compute_units() / d.hq : 0; }
 // fixed cost of a query tile (loading Q, the first copies, the output) in units of one key tile's work
 constexpr int kRowItemOverhead = 6;
 // Default relative work share (percent) of a gang of the first half of a launch; a gang of the second half
