@@ -687,7 +687,9 @@ __global__ void __launch_bounds__(256) dq_merge_parts_kernel(const BwdParams p) 
 // A work item is a key tile with all query heads of one KV head, or - for a tile whose work
 // exceeds a threshold set by the schedule - a 1/2, 1/4 or 1/8 of those heads; such an item
 // writes its dK^T / dV^T as an unscaled fp32 partial result instead of the final bf16 rows.
-template <int D>
+// SHORT: launched beside dkv_short_kernel, one of the two does the work (a kernel of its own, because the look at which one
+// costs the long documents' launches 1 %).
+template <int D, bool SHORT>
 __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     constexpr int BNK = kBwdKeyTile, GR = kGroupRows, KS = D / 16, DB = D / 32, CPR = D / 8;
     constexpr int ROWB = D * 2, TILEB = GR * ROWB, NW = 8, NBUF = 3, PBYTES = 4 * 2 * 2 * 1024;
@@ -707,7 +709,7 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
     // one workgroup per item the hardware hands every XCD the same number of them.  (A first item by
     // workgroup index and reading all counters at once near the end measured the same.)
     __shared__ int s_item;
-    if (p.short_on && ld_const(p.short_on)) return;              // dkv_short_kernel has done it
+    if (SHORT && ld_const(p.short_on)) return;                   // dkv_short_kernel has done it
     const int n_items = ld_const(p.key_item_base + p.n_key_tiles);
   for (;;) {
     __syncthreads();              // every wavefront has left the LDS of the item before, and has read s_item
@@ -1301,8 +1303,8 @@ __global__ void __launch_bounds__(256) dkv_fixup_kernel(const BwdParams p) {
     const int hk = job % p.hkv, r = job / p.hkv;
     const int kt = p.key_order[r];
     const int ways = p.key_ways[kt];
-    if (p.short_on && *p.short_on) return;
     if (ways == 1) return;                      // one item did the whole tile and wrote dK/dV itself
+    if (p.short_on && *p.short_on) return;      // dkv_short_kernel did
     const int k0 = kt * BNK, nk = min(BNK, p.t_kv - k0);
     const float* src = p.partial + (size_t)(p.key_slot_base[r] + hk * ways) * (2 * BNK * D);
     constexpr int V4 = D / 4;                   // float4 per row
@@ -1416,8 +1418,12 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
             delta_kernel<D><<<grid_delta, 256, 0, stream>>>(p);
         }
         if (do_dkv) {
-            if (p.short_on) dkv_short_kernel<D><<<grid_short, 256, 0, stream>>>(p);
-            dkv_kernel<D><<<grid_dkv, 512, 0, stream>>>(p);
+            if (p.short_on) {
+                dkv_short_kernel<D><<<grid_short, 256, 0, stream>>>(p);
+                dkv_kernel<D, true><<<grid_dkv, 512, 0, stream>>>(p);
+            } else {
+                dkv_kernel<D, false><<<grid_dkv, 512, 0, stream>>>(p);
+            }
             dkv_fixup_kernel<D><<<grid_fix * kMergeSplit, 256, 0, stream>>>(p);
         }
     };

@@ -127,11 +127,12 @@ bool use_short_keys(const wlb_attn_desc& d, const PlanLayout& L);
 // Which of the two then does the work the schedule decides (short_keys_pay), from estimates in stages of the general kernel
 // (1.2 us at D = 64, 1.7 at 128) that were fitted to 1542 random calls: the general kernel takes kGeneralStart and its longest
 // item or kGeneralLoad of the mean load of a compute unit (all of them copying at once), the short one kShortStart and, at
-// kShortStep.. a step, its longest wavefront or kShortLoad of a compute unit's steps.  26 of those calls run more than 3 %
-// (and at most 9 %, 4 us) slower than with the general kernel alone; always taking the short kernel for tiles of a short span
-// beside the general one for the others was slower in a third of them, by up to a factor of five.
+// kShortStep.. a step, its longest wavefront or kShortLoad of a compute unit's steps.  Of 678 other random calls 24 run more
+// than 3 % slower than before there was a short kernel, most by an empty launch (2 - 3 us), one by a wrong choice (49 -> 57);
+// always taking the short kernel for tiles of a short span beside the general one for the others was slower in a third of
+// them, by up to a factor of five.
 constexpr float kGeneralStart = 18.f, kGeneralLoad = 1.45f, kEmptyLaunch = 2.f, kFixup = 2.f;
-constexpr float kShortStart = 7.f, kShortStep64 = 1.0f, kShortStep128 = 1.3f, kShortLoad = 0.35f;
+constexpr float kShortStart = 7.f, kShortStep64 = 1.0f, kShortStep128 = 1.3f, kShortLoad = 0.25f;
 // bytes of the dK/dV partial results that follow delta / lse2 in the backward workspace
 size_t dkv_partial_bytes(const wlb_attn_desc& d, const PlanLayout& L);
 

@@ -528,7 +528,7 @@ def short_keys_estimate(t, hq, hkv, d):
             seen[kt, w] = ((h[:, 1] > h[:, 0]) & (h[:, 0] < kt * 128 + w * 32 + 32) & (h[:, 1] > kt * 128 + w * 32)).sum()
     run = np.arange(len(span)) // -(-len(span) // 8)
     load = max(seen[run == x].sum() for x in range(8))
-    return general, 7 + (1.0 if d == 64 else 1.3) * max(seen.max() * G, 0.35 * load * hq * 8 / n_cu) + 2
+    return general, 7 + (1.0 if d == 64 else 1.3) * max(seen.max() * G, 0.25 * load * hq * 8 / n_cu) + 2
 
 
 @pytest.mark.parametrize("tokens,long,hq,hkv,d,cp,takes", [
