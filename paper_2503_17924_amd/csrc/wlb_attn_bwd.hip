@@ -580,7 +580,7 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
     const int n_items = p.row_part_base ? ld_const(p.row_part_base + 4 * p.n_tiles) : p.n_tiles;
     int index = (y / p.hkv) * 8 + x;
     if (index >= n_items) return;
-    index = paired_index(index, n_items, p.first_half);
+    index = paired_index(index, n_items, p.first_half, p.row_part_base != nullptr);
     // one record holds what the workgroup needs before its first copy: order, hull and flag through separate
     // tables are three dependent loads
     const int4 item = ld_const4(p.row_item + 4 * index);

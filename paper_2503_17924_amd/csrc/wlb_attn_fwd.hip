@@ -37,7 +37,7 @@ struct FwdParams {
     float scale_log2e, scale;
 };
 
-// One piece of work: key tiles [pc.a, pc.b) of the pc.c the query tile pc.tile sees, for query head
+// One piece of work: the 64-key tiles [pc.jb, pc.je) of those the query tile pc.tile sees, for query head
 // pc.hk * G + pc.member.  A whole tile (pc.slot < 0) writes O and LSE; a part writes its
 // unnormalised accumulator, row sums and reference exponents as a partial result.
 template <int D>
@@ -542,7 +542,7 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
     const int n_items = p.row_part_base ? ld_const(p.row_part_base + 4 * p.n_tiles) : p.n_tiles;
     int index = (y / p.hkv) * 8 + x;
     if (index >= n_items) return;
-    index = paired_index(index, n_items, p.first_half);
+    index = paired_index(index, n_items, p.first_half, p.row_part_base != nullptr);
     // one record holds what the workgroup needs before its first copy: order, hull and flag through separate
     // tables are three dependent loads
     const int4 item = ld_const4(p.row_item + 4 * index);

@@ -234,12 +234,14 @@ __device__ __forceinline__ int gather_later_parts(const RowCut& cut, int* s_slot
 
 // One-workgroup-per-item launches: which of the n work records (heaviest first) the launch position `pos` takes.
 // first_half = positions whose workgroups (one per query head) fill the compute units once.  When the launch is
-// resident as a whole or nearly so, two workgroups per compute unit, its second half goes lightest first: the compute unit
-// with the heaviest record then gets the lightest beside it (8191 tokens, 8 heads: forward 42 -> 38 us, dQ 55 -> 51 us); what
-// is left over goes where a unit is done first.
-__device__ __forceinline__ int paired_index(int pos, int n, int first_half) {
+// resident as a whole, two workgroups per compute unit, its second half goes lightest first: the compute unit
+// with the heaviest record then gets the lightest beside it (8191 tokens, 8 heads: forward 42 -> 38 us, dQ 55 -> 51 us).  So
+// it does with up to half as many records more where heavy tiles are divided; what is left over goes where a unit is done
+// first.  (With whole tiles only, one of them far heavier than the rest, that made the forward 3 % longer.)
+__device__ __forceinline__ int paired_index(int pos, int n, int first_half, bool divided) {
     const int resident = min(n, 2 * first_half);
-    return n < 3 * first_half && pos >= first_half && pos < resident ? resident - 1 - (pos - first_half) : pos;
+    const bool paired = n <= resident || (divided && n < 3 * first_half);
+    return paired && pos >= first_half && pos < resident ? resident - 1 - (pos - first_half) : pos;
 }
 
 // XOR swizzle of the 16-byte chunks of an unpadded row-major LDS tile whose rows hold CPR

@@ -100,11 +100,12 @@ constexpr int kRowGangMinUnitsPerSlot = 64;
 // the parts takes 5 us, which at 18 units per item (8191 tokens, 8 heads: forward 43 us) is more than the better balance
 // returns (47 us), at 39 (4095 rows of a 16K-token micro-batch, 16 heads) a third of it (106 -> 89 us).  Or when they fill at
 // most a quarter of the workgroup slots, if the heaviest tile probably sees more than kRowPartKeys keys: twice what its rows
-// see on average (a document's length, weighted by tokens) and the 128 rows' own share of the sequence.  With less there is
+// see on average (a document's length, weighted by tokens) and kRowPartReach for the 128 rows' own share of the sequence (a
+// tile's rows lie in several documents and, context-parallel, in distant places).  With less there is
 // little or nothing to divide, and the merge launch alone costs 1.4 us (1024 tokens in documents of 1 - 64, 8/2 heads:
-// forward 7.4 -> 8.8; of 64 - 384: 16.1 -> 17.5).  Of 887 random calls, forward and dQ: 704 keys leaves 7 slower by more than
-// 3 % and 0.5 us than undivided ones, no limit 220; both kernels together take 0.826 and 0.843 of the undivided time.
-constexpr int kRowPartKeys = 704;
+// forward 7.4 -> 8.8; of 64 - 384: 16.1 -> 17.5).  Of 887 random calls, forward and dQ: these leave 8 slower by more than
+// 3 % and 0.5 us than undivided ones, dividing always 220; the mean time is 0.822 of the undivided one, 0.843 dividing always.
+constexpr int kRowPartKeys = 704, kRowPartReach = 224;
 constexpr int kRowPartMeanUnits = 24;
 bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L);
 // whether this launch sends short-hull query tiles to the short-hull kernels (only in the

@@ -83,7 +83,7 @@ bool use_row_parts(const wlb_attn_desc& d, const PlanLayout& L) {
     if (items >= (long long)kRowGangMaxItemsPerSlot * slots) return false;
     if (items * 4 > slots) return mean_item_units(d, L) >= kRowPartMeanUnits;
     const long long length = d.visible_pairs > 0 ? std::min<long long>(2 * (d.visible_pairs / d.n_q), d.t_kv) : d.t_kv / d.n_docs;
-    return std::min<long long>(length + (long long)kFwdTileRows * d.t_kv / d.n_q, d.t_kv) > kRowPartKeys;
+    return std::min<long long>(length + (long long)kRowPartReach * d.t_kv / d.n_q, d.t_kv) > kRowPartKeys;
 }
 
 // gang share weights: process-wide, set by wlb_attn_set_gang_weights (0 = not set: the defaults)
