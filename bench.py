@@ -462,8 +462,7 @@ def main():
         if w.backward:
             bw = lambda fl: st.attn.backward(st.q, full["k"], full["v"], st.o, st.lse, st.do, st.dq, st.dk, st.dv,
                                              extra_flags=fl)
-            add("delta_ms", time_call(lambda: bw(B.ATTN_BWD_SKIP_DQ | B.ATTN_BWD_SKIP_DKV)))
-            add("dq_ms", time_call(lambda: bw(B.ATTN_BWD_SKIP_DELTA | B.ATTN_BWD_SKIP_DKV)))
+            add("dq_ms", time_call(lambda: bw(B.ATTN_BWD_SKIP_DKV)))              # forms delta and leaves it for the next
             add("dkv_ms", time_call(lambda: bw(B.ATTN_BWD_SKIP_DELTA | B.ATTN_BWD_SKIP_DQ)))
     kern = {k: float(np.mean(v)) for k, v in kern.items()}
     # algorithmic flops per launch (mean over ranks): forward 4*D per pair and head; the dK/dV

@@ -72,8 +72,8 @@ def main():
     # kernel, launch, executed flops per launch (recomputed products included), launches
     phases = [
         ("forward", lambda: attn.forward(q, full["k"], full["v"], o, lse), 4.0 * d * hq * pairs, 1000),
-        ("dQ (+ delta pass)", lambda: attn.backward(q, full["k"], full["v"], o, lse, do, dq, dk, dv,
-                                                     extra_flags=B.ATTN_BWD_SKIP_DKV), 6.0 * d * hq * pairs, 800),
+        ("dQ (forms delta)", lambda: attn.backward(q, full["k"], full["v"], o, lse, do, dq, dk, dv,
+                                                    extra_flags=B.ATTN_BWD_SKIP_DKV), 6.0 * d * hq * pairs, 800),
         ("dK/dV (+ delta pass, fix-up)", lambda: attn.backward(q, full["k"], full["v"], o, lse, do, dq, dk, dv,
                                                                 extra_flags=B.ATTN_BWD_SKIP_DQ), 8.0 * d * hq * pairs, 500),
         ("MFMA only, random operands", lambda: mfma(1), flops.value, 600),
@@ -101,7 +101,7 @@ def main():
         print(f"{name:30s} {ms:10.3f} {str(clk):>28s} {tf:17.1f} {tf / PEAK_TFLOPS:19.3f} {at}")
         ns_per_mfma[name] = ms * 1e6 * N_SIMD / (fl / MFMA_FLOPS)
     print("executed flops: 4*D per visible pair and head forward, 6*D in the dQ kernel and 8*D in the dK/dV kernel (S and dP are")
-    print("computed in both); the delta pass and the fix-up are included in the times.  'of peak at sclk' divides by 2.5 PFLOP/s x sclk / 2.4 GHz.")
+    print("computed in both); the dK/dV time includes the delta pass of a call without dQ and the fix-up.  'of peak at sclk' divides by 2.5 PFLOP/s x sclk / 2.4 GHz.")
 
     # ---- the same kernels on uniform, unmasked work
     del attn, q, do, o, lse, dq, dk, dv
@@ -127,7 +127,7 @@ def main():
         return float(np.median(out))
     pairs_u = float(nq_u) * t_u
     rows = [("forward", lambda: attn.forward(q, k, v, o, lse), 4.0),
-            ("dQ (+ delta pass)", lambda: attn.backward(q, k, v, o, lse, do, dq, dk, dv, extra_flags=B.ATTN_BWD_SKIP_DKV), 6.0),
+            ("dQ (forms delta)", lambda: attn.backward(q, k, v, o, lse, do, dq, dk, dv, extra_flags=B.ATTN_BWD_SKIP_DKV), 6.0),
             ("dK/dV (+ delta pass, fix-up)", lambda: attn.backward(q, k, v, o, lse, do, dq, dk, dv, extra_flags=B.ATTN_BWD_SKIP_DQ), 8.0)]
     print()
     print(f"uniform problem: {nq_u} rows x one document of {t_u} keys, heads {hq}/{hkv}, D {d}; ns per MFMA and SIMD ({MFMA_FLOPS} flops per MFMA, {N_SIMD} SIMDs)")

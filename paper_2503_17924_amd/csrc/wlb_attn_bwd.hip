@@ -17,7 +17,7 @@
 //   dkv_kernel        key-stationary: a work item owns 128 keys of one KV head and streams the row
 //                     groups that can see them through LDS for some or all query heads of the KV
 //                     group; dK^T, dV^T stay in registers until the single final store
-//   dkv_short_kernel  the same for key tiles that few rows can see (short documents)
+//   dkv_short_kernel  the same for calls in which few rows can see any one key tile (short documents)
 //   dkv_fixup_kernel  sums the fp32 partial results of key tiles whose heads were divided among
 //                     several work items (heavy tiles, so that no item is a straggler)
 // S and dP are recomputed in both dq_kernel and dkv_kernel (7 GEMMs for the 5 the derivative
@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(256, 2) dq_kernel(const BwdParams p) {
 // P and dP and forms delta itself as sum_j P_ij dP_ij (equal to <dO_i, O_i> since O = P V), without
 // reading O: first pass per 32-key block S^T, dP^T, P and X = P o dP (both kept as bf16), then
 // dS^T = X - delta P and dQ^T += K^T dS^T.  delta (negated) and the log2-scaled LSE copy are left
-// for the dK/dV kernel, which runs after this one; the separate delta pass skips these rows.
+// for the dK/dV kernel, which runs after this one.
 template <int D>
 struct ShortDq {
     static constexpr int NW = 4, ROWB = D * 2, HULL = kShortHullKeys, STAGE = kShortBlockRows * ROWB;
@@ -1082,14 +1082,15 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
   }   // next item
 }
 
-// dK/dV of key tiles that few rows can see (documents of a few dozen tokens).  There the general kernel walks whole
+// dK/dV of calls in which few rows can see any one key tile (documents of a few dozen tokens); the schedule decides
+// between this kernel and the general one for the call as a whole.  There the general kernel walks whole
 // stages of 64 rows x 128 keys of which a third holds visible pairs, and waits for each at a barrier (2.5 us).  Here one
 // workgroup takes a key tile and KV head, and each of its four wavefronts works alone -- no barrier -- on 32 keys: it
 // holds K, V, dK^T and dV^T of them and walks (query head, 32-row block that can see them), the block's Q, dO and
 // per-row scalars copied into LDS of the wavefront's own.  S, P, dP and dS stay in its registers, so nothing is handed
 // over, and blocks without a visible pair are never touched.  Two wavefronts per SIMD (one set of tiles each) cover each
 // other's copies; one per SIMD with two sets measured slower (111 us for 104).  Bound: the copies alone take 72 us at
-// 32K tokens in 979 documents, 16/2 heads (67 at the rate of a large copy), the arithmetic alone 54, together 95; one
+// 32K tokens in 979 documents, 16/2 heads (67 at the rate of a large copy), the arithmetic alone 54, the kernel 104; one
 // load per line a step ahead to warm L2 made it slower.  Workgroups are dealt so that neighbouring key tiles share an XCD.
 // With the (then empty) general launch 130 -> 105 us there, 89 -> 62 on one of four ranks, 43 -> 35 at 8K tokens.
 template <int D>
@@ -1160,7 +1161,7 @@ __global__ void __launch_bounds__(256, 2) dkv_short_kernel(const BwdParams p) {
         dma_issue_256(hi_rs.r, uniform(sm + 768u), lane * 4, ro);
     };
     // query heads outermost: the wavefronts of a workgroup, whose keys the same rows see, then read those rows of a head
-    // close together in time and share them in L2 (row blocks outermost: 121 us for 59 at 32K tokens, 16/2 heads)
+    // close together in time and share them in L2 (row blocks outermost: 121 us against 104 at 32K tokens, 16/2 heads)
     uint32_t left = blocks;
     int rb_n = rb0 + __ffs((int)left) - 1, h_n = hk * G;
     auto advance = [&] {
