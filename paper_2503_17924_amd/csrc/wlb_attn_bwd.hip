@@ -1090,8 +1090,9 @@ __global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
 // per-row scalars copied into LDS of the wavefront's own.  S, P, dP and dS stay in its registers, so nothing is handed
 // over, and blocks without a visible pair are never touched.  Two wavefronts per SIMD (one set of tiles each) cover each
 // other's copies; one per SIMD with two sets measured slower (111 us for 104).  Bound: the copies alone take 72 us at
-// 32K tokens in 979 documents, 16/2 heads (67 at the rate of a large copy), the arithmetic alone 54, the kernel 104; one
-// load per line a step ahead to warm L2 made it slower.  Workgroups are dealt so that neighbouring key tiles share an XCD.
+// 32K tokens in 979 documents, 16/2 heads (67 for the operands once at the rate of a large copy; 528 MiB are fetched past
+// L2 where Q, dO, K and V have 288), the arithmetic alone 54, the kernel 104; one load per line a step ahead to warm L2 made
+// it slower.  Workgroups are dealt so that neighbouring key tiles share an XCD.
 // With the (then empty) general launch 130 -> 105 us there, 89 -> 62 on one of four ranks, 43 -> 35 at 8K tokens.
 template <int D>
 struct ShortDkv {
