@@ -6,6 +6,7 @@ hipcc cross-compiles, so no GPU is needed to build.
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -14,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libwlb.so")
-SOURCES = ["wlb_host.cpp", "wlb_plan.hip", "wlb_attn_fwd.hip", "wlb_attn_bwd.hip", "wlb_calib.hip"]
+SOURCES = ["wlb_host.cpp", "wlb_plan.hip", "wlb_attn_fwd.hip", "wlb_attn_bwd.hip", "wlb_attn_dkv.hip", "wlb_calib.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -22,6 +23,20 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]
+
+
+# Sources whose kernels use the accumulation registers by number, in statements marked "; acc"
+OWN_ACC_REGISTERS = ["wlb_attn_dkv.hip"]
+
+
+def check_acc_registers(asm: str) -> None:
+    """Refuses code in which the compiler itself uses an accumulation register (as a place to spill to, for
+    instance): it does not know that they hold values between the statements that name them."""
+    with open(asm) as fh:
+        for number, line in enumerate(fh, 1):
+            code, _, comment = line.partition(";")
+            if re.search(r"(^|[\s,])a(\[|\d)", code) and not code.lstrip().startswith(".") and comment.strip() != "acc":
+                raise RuntimeError(f"{asm}:{number}: accumulation register used by the compiler: {line.strip()}")
 
 
 def build(verbose: bool = False, keep_asm: bool = False, lib_out: str | None = None) -> str:
@@ -45,8 +60,12 @@ def build(verbose: bool = False, keep_asm: bool = False, lib_out: str | None = N
             # kernels only: lets max() compile to bare v_max3 (no NaN quieting); the host-side
             # argument checks live in other files and keep full NaN semantics
             cmd += ["-fno-honor-nans"]
+        if src in OWN_ACC_REGISTERS:
+            # results of MFMAs that the vector ALU reads stay out of the accumulation registers, which the kernels
+            # of this file number themselves (check_acc_registers)
+            cmd += ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, cwd=bdir)))
-        if keep_asm and src.endswith(".hip"):
+        if (keep_asm or src in OWN_ACC_REGISTERS) and src.endswith(".hip"):
             asm = [c for c in cmd if c != "-c"]
             asm[asm.index("-o") + 1] = os.path.join(bdir, os.path.splitext(src)[0] + ".s")
             asm += ["-S", "--cuda-device-only"]
@@ -59,6 +78,8 @@ def build(verbose: bool = False, keep_asm: bool = False, lib_out: str | None = N
             raise RuntimeError(f"hipcc failed on {src}:\n{out}")
         if verbose and out.strip():
             print(out)
+    for src in OWN_ACC_REGISTERS:
+        check_acc_registers(os.path.join(bdir, os.path.splitext(src)[0] + ".s"))
     tmp = lib_out + ".tmp"
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

@@ -14,7 +14,7 @@
 //                     copy (0 / +inf for padding rows) for the dK/dV kernel, which runs after it
 //   delta_kernel      the same for a call that leaves dQ out (WLB_ATTN_BWD_SKIP_DQ)
 //   dq_merge_kernel   sums the fp32 partial dQ of query tiles cut at a gang boundary
-//   dkv_kernel        key-stationary: a work item owns 128 keys of one KV head and streams the row
+//   dkv_kernel        (wlb_attn_dkv.hip) key-stationary: a work item owns 128 keys of one KV head and streams the row
 //                     groups that can see them through LDS for some or all query heads of the KV
 //                     group; dK^T, dV^T stay in registers until the single final store
 //   dkv_short_kernel  the same for calls in which few rows can see any one key tile (short documents)
@@ -27,6 +27,7 @@
 // bank-conflict free; all tiles arrive by asynchronous global->LDS copies.
 #include <hip/hip_runtime.h>
 
+#include "wlb_attn_bwd.h"
 #include "wlb_device.h"
 #include <algorithm>
 #include <type_traits>
@@ -34,28 +35,6 @@
 #include "wlb_internal.h"
 
 namespace wlb {
-
-struct BwdParams {
-    const __bf16* q; const __bf16* k; const __bf16* v; const __bf16* o; const __bf16* d_o;
-    const float* lse; float* delta; float* lse2;
-    __bf16* dq; __bf16* dk; __bf16* dv;
-    const int32_t* row_lo; const int32_t* row_hi; const int32_t* group; const int32_t* group_real;
-    const int32_t* key_order; const int32_t* key_ways; const int32_t* key_item_base; const int32_t* key_slot_base;
-    const int32_t* key_range; const int32_t* short_on;   // dkv_short_kernel; null: not launched
-    const int32_t* dkv_item;   // two int4 per item (PlanLayout::off_dkv_item)
-    int32_t* dkv_counters;     // [8]: items of each XCD's list handed out so far (zero before every dK/dV launch)
-    float* partial;
-    RowSched sched;            // dQ: which query tiles, heads and key ranges a workgroup works on
-    float* row_partial;        // dQ: partial results of the tiles cut at a gang boundary
-    const int32_t* row_item;   // one workgroup per item: records (PlanLayout::off_row_item, or off_row_part with row_part_base)
-    const int32_t* row_part_base;     // null: whole tiles only
-    int first_half;                   // see paired_index
-    const int32_t* block_hull;   // short-hull path (see dq_short_unit)
-    unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of dq_kernel's workgroup
-    int n_blocks32, use_short;
-    int n_q, t_kv, hq, hkv, n_groups, n_tiles, n_key_tiles;
-    float scale_log2e, scale;
-};
 
 // ------------------------------------------------------------------------------------------
 template <int D>
@@ -670,421 +649,9 @@ __global__ void __launch_bounds__(256) dq_merge_parts_kernel(const BwdParams p) 
     });
 }
 
-// ------------------------------------------------------------------------------------------
-// dK/dV with role-split wavefronts: one workgroup = 128 keys x one KV head, eight wavefronts.
-// Wavefronts 0-3 ("score" role) hold the K operands of 32 keys each: they compute
-// S = Q K^T, P = exp(scale*S - LSE) (masked), hand P (bf16) to their partner through LDS and
-// accumulate dV^T += dO^T P.  Wavefronts 4-7 ("gradient" role) hold the V operands of the same
-// keys: they compute dP = dO V^T, take P from the partner, form dS = P o (dP - delta) and
-// accumulate dK^T += Q^T dS.  A wavefront that held K, V, dK^T and dV^T together would need
-// more than 256 registers, i.e. one wavefront per SIMD, which measured slower here: splitting
-// halves the register need, so two wavefronts share a SIMD and hide each other's LDS latencies.
-// Stages (row group, query head) stream through three LDS buffers.  The gradient role works one
-// stage behind the score role: between two workgroup barriers the score wavefronts run stage t
-// (S, P, dV) while the gradient wavefronts run stage t-1 (dP, dS, dK) with the P that was
-// written before the barrier.  One barrier per stage, and both roles carry the same load
-// (32 MFMAs plus the exponentials resp. the dS products), so neither waits for the other.
-// A work item is a key tile with all query heads of one KV head, or - for a tile whose work
-// exceeds a threshold set by the schedule - a 1/2, 1/4 or 1/8 of those heads; such an item
-// writes its dK^T / dV^T as an unscaled fp32 partial result instead of the final bf16 rows.
-// SHORT: launched beside dkv_short_kernel, one of the two does the work (a kernel of its own, because the look at which one
-// costs the long documents' launches 1 %).
-template <int D, bool SHORT>
-__global__ void __launch_bounds__(512) dkv_kernel(const BwdParams p) {
-    constexpr int BNK = kBwdKeyTile, GR = kGroupRows, KS = D / 16, DB = D / 32, CPR = D / 8;
-    constexpr int ROWB = D * 2, TILEB = GR * ROWB, NW = 8, NBUF = 3, PBYTES = 4 * 2 * 2 * 1024;
-    static_assert(BNK == 128 && GR == 64, "tiling");
-
-    __shared__ __attribute__((aligned(1024))) char smem[NBUF * 2 * TILEB];   // per stage buffer: Q tile | dO tile, swizzled
-    // P of two stages (aligned so that one XOR switches stage): [key block][row block][half of 16 rows][lane] x 16 B
-    __shared__ __attribute__((aligned(2 * PBYTES))) char pbuf[2 * PBYTES];
-    __shared__ __attribute__((aligned(256))) int small_s[NBUF][4][GR];       // per stage buffer: lse2 | delta | row_lo | row_hi
-
-    // Work items: tiles in order (heaviest item first), a tile's items consecutive: KV head major, head
-    // part minor.  The launch is one workgroup per compute unit, and each takes item after item until
-    // none is left.  Item i belongs to XCD i % 8 (workgroup b runs on XCD b % 8): the same head part of
-    // neighbouring tiles then shares an XCD and its L2 copy of the Q / dO tiles.  A workgroup takes its own
-    // XCD's items first, through one counter per XCD, and the other XCDs' once those are gone: the XCDs
-    // of one GPU differ in speed by several percent (the same ones are slower in every launch), and with
-    // one workgroup per item the hardware hands every XCD the same number of them.  (A first item by
-    // workgroup index and reading all counters at once near the end measured the same.)
-    __shared__ int s_item;
-    if (SHORT && ld_const(p.short_on)) return;                   // dkv_short_kernel has done it
-    const int n_items = ld_const(p.key_item_base + p.n_key_tiles);
-  for (;;) {
-    __syncthreads();              // every wavefront has left the LDS of the item before, and has read s_item
-    if (threadIdx.x == 0) {
-        int it = -1;
-        for (int k = 0; k < kLists && it < 0; ++k) {
-            const int c = ((int)blockIdx.x + k) % kLists;
-            const int cand = atomicAdd(p.dkv_counters + c, 1) * kLists + c;
-            if (cand < n_items) it = cand;
-        }
-        s_item = it;
-    }
-    __syncthreads();
-    const int item = uniform(s_item);
-    if (item < 0) break;
-    // one record per item: finding the tile by a search of the item bases and then its tables was a chain of a dozen
-    // dependent loads in front of every item
-    const int4 rec0 = ld_const4(p.dkv_item + 8 * item), rec1 = ld_const4(p.dkv_item + 8 * item + 4);
-    const int kt = rec0.x, hk = rec0.y, h_first = rec0.z, nh = rec0.w;   // query heads [h_first, h_first + nh)
-    const int slot = rec1.x;
-    const bool whole = slot < 0;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
-    // role and key block are left as per-lane values: as scalars they raise the register pressure
-    // of the two role branches past 256 (spills)
-    const int role = tid >> 8, kblk = (tid >> 6) & 3;
-    const int l32 = lane & 31, half = lane >> 5;
-    const int j16 = lane & 15, gi = (lane >> 4) & 1;
-    const float cs = p.scale_log2e;
-    const int k0 = kt * BNK;
-    const int kw0 = k0 + kblk * 32;
-    const int mykey = kw0 + l32;
-
-    const uint32_t q_row = (uint32_t)p.hq * D;
-    const uint32_t q_total = (uint32_t)p.n_q * q_row * 2u;
-    TileDma<D, GR, NW> dma;
-    dma.init(wave, lane, q_row);
-    const uint32_t smem_base = (uint32_t)(uintptr_t)(WLB_LDS char*)smem;
-    const uint32_t small_base = (uint32_t)(uintptr_t)(WLB_LDS char*)&small_s[0][0][0];
-    // The copies of a stage are issued with as little scalar work as possible (it sits between the
-    // barrier and the stage's first MFMA): the Q and dO descriptors span the whole tensors and the
-    // stage's row group and head go into the scalar offset (an address at or past the tensor's end
-    // still reads as zeros: the hardware compares offset + scalar offset with the size); everything
-    // that depends only on the wavefront is computed here.
-    BufRsrc q_rs, do_rs;
-    q_rs.init(p.q, q_total);
-    do_rs.init(p.d_o, q_total);
-    uint32_t dma_soff[TileDma<D, GR, NW>::PER], dma_lds[TileDma<D, GR, NW>::PER];
-#pragma unroll
-    for (int n = 0; n < TileDma<D, GR, NW>::PER; ++n) {
-        const uint32_t blk = (uint32_t)(wave * TileDma<D, GR, NW>::PER + n);
-        dma_soff[n] = uniform(blk * TileDma<D, GR, NW>::RPI * q_row * 2u);
-        dma_lds[n] = uniform(smem_base + blk * 1024u);
-    }
-    const uint32_t group_bytes = (uint32_t)GR * q_row * 2u;
-    auto issue_stage = [&](int g, int h, int b) {
-        const uint32_t so = uniform((uint32_t)g * group_bytes + (uint32_t)h * ROWB);
-        const uint32_t lo = uniform((uint32_t)b * (2 * TILEB));
-#pragma unroll
-        for (int n = 0; n < TileDma<D, GR, NW>::PER; ++n) {
-            dma_issue_1k(q_rs.r, dma_lds[n] + lo, dma.voff[n], so + dma_soff[n]);
-            dma_issue_1k(do_rs.r, dma_lds[n] + lo + TILEB, dma.voff[n], so + dma_soff[n]);
-        }
-    };
-    // Per-row scalars of a stage (visible key interval, log2-scaled LSE, delta) are copied
-    // global->LDS asynchronously as well, by wavefront 0: no register load sits between the copies
-    // and the compute, so nothing makes the compiler wait on vector memory while they are in
-    // flight.  Rows past n_q read as zeros (row_hi = 0: no visible key; their Q/dO rows are zero);
-    // the LSE and delta descriptors are therefore per head (base + h * n_q, n_q entries).
-    BufRsrc lo_rs, hi_rs, ls_rs, dl_rs;
-    lo_rs.init(p.row_lo, (uint32_t)p.n_q * 4u);
-    hi_rs.init(p.row_hi, (uint32_t)p.n_q * 4u);
-    ls_rs.init(p.lse2, (uint32_t)p.n_q * 4u);
-    dl_rs.init(p.delta, (uint32_t)p.n_q * 4u);
-    const uint64_t lse_addr = (uint64_t)(uintptr_t)p.lse2, delta_addr = (uint64_t)(uintptr_t)p.delta;
-    auto load_small = [&](int g, int h, int b) {
-        if (wave == 0) {
-            const uint64_t ho = (uint64_t)(uint32_t)h * (uint32_t)p.n_q * 4u;
-            const uint64_t la = lse_addr + ho, da = delta_addr + ho;
-            ls_rs.r[0] = (int)(uint32_t)la; ls_rs.r[1] = (int)(uint32_t)((la >> 32) & 0xffffu);
-            dl_rs.r[0] = (int)(uint32_t)da; dl_rs.r[1] = (int)(uint32_t)((da >> 32) & 0xffffu);
-            const uint32_t soff = uniform((uint32_t)(g * GR) * 4u);
-            const uint32_t sl = uniform(small_base + (uint32_t)b * (4 * GR * 4));
-            dma_issue_256(ls_rs.r, sl, lane * 4, soff);
-            dma_issue_256(dl_rs.r, sl + GR * 4, lane * 4, soff);
-            dma_issue_256(lo_rs.r, sl + 2 * GR * 4, lane * 4, soff);
-            dma_issue_256(hi_rs.r, sl + 3 * GR * 4, lane * 4, soff);
-        }
-    };
-
-    // LDS addresses, absolute and per role, rotated through the three stage buffers by one add per
-    // stage so that every access in the regions is register + immediate:
-    //   naddr: rows of the tile read row-wise      (score role: Q of its stage, gradient role: dO of its stage)
-    //   taddr: rows of the tile read transposed    (score role: dO,             gradient role: Q)
-    //   saddr: this lane's 4 rows of the per-row scalars;  paddr: this lane's slot of the P buffer
-    // The score role starts at buffer 0 (stage 0); the gradient role works one stage behind and
-    // starts at the last buffer.
-    const int rot0 = role == 0 ? 0 : NBUF - 1;
-    const uint32_t stage_base = smem_base + (uint32_t)rot0 * (2 * TILEB);
-    uint32_t naddr[KS], taddr[DB];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-        naddr[ks] = stage_base + (role == 0 ? 0 : TILEB) + l32 * ROWB + swz<CPR>(l32, ks * 2 + half) * 16;
-    // transposed reads: rows qq and qq+8 of a 16-row step; the swizzle of row qq+8 is that of row
-    // qq with bit 1 flipped, and tiles are 1 KiB aligned, so the second address is the first
-    // with address bit 5 flipped plus 8 rows
-    static_assert(swz<CPR>(8, 0) == (swz<CPR>(0, 0) ^ 2) && swz<CPR>(13, 5) == (swz<CPR>(5, 5) ^ 2), "row+8 flips swizzle bit 1");
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-        const int qq = half * 4 + (j16 >> 2);
-        const int dch = db * 4 + gi * 2 + ((j16 & 3) >> 1);
-        taddr[db] = stage_base + (role == 0 ? TILEB : 0) + qq * ROWB + swz<CPR>(qq, dch) * 16 + (j16 & 1) * 8;
-    }
-    uint32_t saddr = small_base + (uint32_t)rot0 * (4 * GR * 4) + half * 16;
-    // score role: P buffer of its stage, gradient role: of the stage before
-    uint32_t paddr = ((uint32_t)(uintptr_t)(WLB_LDS char*)pbuf + kblk * 4096 + lane * 16) ^ (role == 0 ? 0u : (uint32_t)PBYTES);
-    // b = buffer of the stage the score role just ran
-    auto rotate = [&](int b) __attribute__((always_inline)) {
-        const bool wrap = role == 0 ? b == NBUF - 1 : b == 0;
-        const int dt = wrap ? -(NBUF - 1) * 2 * TILEB : 2 * TILEB;
-        const int dsm = wrap ? -(NBUF - 1) * 4 * GR * 4 : 4 * GR * 4;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) naddr[ks] += dt;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) taddr[db] += dt;
-        saddr += dsm;
-        paddr ^= (uint32_t)PBYTES;
-    };
-    auto lds_f4 = [&](uint32_t a) __attribute__((always_inline)) { return *reinterpret_cast<const WLB_LDS f32x4*>((uintptr_t)a); };
-    auto lds_i4 = [&](uint32_t a) __attribute__((always_inline)) { return *reinterpret_cast<const WLB_LDS i32x4*>((uintptr_t)a); };
-
-    // this wavefront's B operands: K rows (score role) or V rows (gradient role) of its 32 keys
-    bf16x8 bop[KS];
-    {
-        const int kr = min(mykey, p.t_kv - 1);
-        const __bf16* src = (role == 0 ? p.k : p.v) + ((size_t)kr * p.hkv + hk) * D + half * 8;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) bop[ks] = *reinterpret_cast<const bf16x8*>(src + ks * 16);
-    }
-    f32x16 acc[DB];     // dV^T (score role) or dK^T (gradient role)
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
-
-    // ---- pieces of a role's work on one stage
-    // A stage is eight units of four (D/32) MFMAs; the operands of unit u+1 are requested from LDS
-    // before the MFMAs of unit u are issued (two operand register sets), so that a wavefront by
-    // itself can keep MFMAs flowing and only the first unit of a stage waits for an LDS round trip.
-    struct RowOps { bf16x8 a[KS / 2]; };       // half the head dimension of 32 rows, read row-wise
-    struct ColOps { bf16x4 t[DB][2]; };        // 16 rows, read transposed
-    auto load_rows = [&](RowOps& o, int qb, int kh) __attribute__((always_inline)) {
-#pragma unroll
-        for (int ks = 0; ks < KS / 2; ++ks)
-            o.a[ks] = *reinterpret_cast<const WLB_LDS bf16x8*>((uintptr_t)(naddr[kh * (KS / 2) + ks] + qb * 32 * ROWB));
-    };
-    auto load_cols = [&](ColOps& o, int st) __attribute__((always_inline)) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int t = 0; t < 2; ++t) o.t[db][t] = lds_read_tr4_at((t ? taddr[db] ^ 32u : taddr[db]) + (st * 16 + t * 8) * ROWB);
-    };
-    // S or dP of a 32-row block, half the head dimension: B operand = K or V
-    auto mfma_rows = [&](f32x16& sc, const RowOps& o, int kh) __attribute__((always_inline)) {
-#pragma unroll
-        for (int ks = 0; ks < KS / 2; ++ks) sc = mfma32(o.a[ks], bop[kh * (KS / 2) + ks], sc);
-    };
-    // 16 rows: acc += tile^T x b  (score role: dV from dO^T, gradient role: dK from Q^T)
-    auto mfma_cols = [&](const ColOps& o, const bf16x8& b) __attribute__((always_inline)) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db) acc[db] = mfma32(cat4(o.t[db][0], o.t[db][1]), b, acc[db]);
-    };
-    // Per-row scalars of 16 rows (8-row groups 2cc, 2cc+1 of row block qb; this lane's 4 rows of each):
-    // requested one unit ahead like the MFMA operands
-    struct RowVals { f32x4 v[2]; };
-    auto load_vals = [&](RowVals& o, int which, int qb, int cc) __attribute__((always_inline)) {
-#pragma unroll
-        for (int r2 = 0; r2 < 2; ++r2) o.v[r2] = lds_f4(saddr + which * GR * 4 + (qb * 32 + (cc * 2 + r2) * 8) * 4);
-    };
-    // P of those 16 rows: exponentials, mask, bf16; returned as this wavefront's B operand and
-    // handed to the partner through LDS.  The mask is needed only on a document's diagonal or edge
-    // (uniform branch).
-    auto probs_half = [&](const f32x16& sc, const RowVals& ls, int qb, int cc, bool masked) __attribute__((always_inline)) {
-        float pr[8];
-#pragma unroll
-        for (int r2 = 0; r2 < 2; ++r2)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) pr[r2 * 4 + i] = fast_exp2(fmaf(sc[(cc * 2 + r2) * 4 + i], cs, -ls.v[r2][i]));
-        if (masked) {
-#pragma unroll
-            for (int r2 = 0; r2 < 2; ++r2) {
-                const int roff = (qb * 32 + (cc * 2 + r2) * 8) * 4;
-                const i32x4 l4 = lds_i4(saddr + 2 * GR * 4 + roff);
-                const i32x4 h4 = lds_i4(saddr + 3 * GR * 4 + roff);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    pr[r2 * 4 + i] = (mykey >= l4[i] && mykey < h4[i]) ? pr[r2 * 4 + i] : 0.f;
-            }
-        }
-        const bf16x8 pk = pack8(pr[0], pr[1], pr[2], pr[3], pr[4], pr[5], pr[6], pr[7]);
-        *reinterpret_cast<WLB_LDS bf16x8*>((uintptr_t)(paddr + (qb * 2 + cc) * 1024)) = pk;
-        return pk;
-    };
-    // dS of 16 rows: P (from the partner) x (dP - delta); the dP accumulators start from -delta
-    auto load_p = [&](int qb, int cc) __attribute__((always_inline)) {
-        return *reinterpret_cast<const WLB_LDS bf16x8*>((uintptr_t)(paddr + (qb * 2 + cc) * 1024));
-    };
-    auto ds_half = [&](const f32x16& dn, const bf16x8& pv, int cc) __attribute__((always_inline)) {
-        float ds[8];
-#pragma unroll
-        for (int r2 = 0; r2 < 2; ++r2)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) ds[r2 * 4 + i] = (float)pv[r2 * 4 + i] * dn[(cc * 2 + r2) * 4 + i];
-        return pack8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
-    };
-    // -delta of the 32 rows of block qb, in accumulator order
-    auto load_neg_delta = [&](f32x16& o, int qb) __attribute__((always_inline)) {
-#pragma unroll
-        for (int g8 = 0; g8 < 4; ++g8) {
-            const f32x4 x = lds_f4(saddr + GR * 4 + (qb * 32 + g8 * 8) * 4);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[g8 * 4 + i] = x[i];
-        }
-    };
-    // The fences pin the order "request unit u+1, run unit u"; the exponentials / dS products of
-    // one row block are placed beside the MFMAs of the units that do not depend on them.
-    auto fence = [] () __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
-    auto score_stage = [&](bool masked) __attribute__((always_inline)) {
-        f32x16 s0, s1;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { s0[r] = 0.f; s1[r] = 0.f; }
-        RowOps ra, rb;
-        ColOps ca, cb;
-        RowVals la, lb;
-        load_rows(ra, 0, 0);
-        load_rows(rb, 0, 1);                          fence();  mfma_rows(s0, ra, 0);  fence();
-        load_rows(ra, 1, 0);  load_vals(la, 0, 0, 0); fence();  mfma_rows(s0, rb, 1);  fence();
-        load_rows(rb, 1, 1);  load_vals(lb, 0, 0, 1); fence();  mfma_rows(s1, ra, 0);
-        const bf16x8 p00 = probs_half(s0, la, 0, 0, masked);
-        fence();
-        load_cols(ca, 0);     load_vals(la, 0, 1, 0); fence();  mfma_rows(s1, rb, 1);
-        const bf16x8 p01 = probs_half(s0, lb, 0, 1, masked);
-        fence();
-        load_cols(cb, 1);     load_vals(lb, 0, 1, 1); fence();  mfma_cols(ca, p00);
-        const bf16x8 p10 = probs_half(s1, la, 1, 0, masked);
-        fence();
-        load_cols(ca, 2);                             fence();  mfma_cols(cb, p01);
-        const bf16x8 p11 = probs_half(s1, lb, 1, 1, masked);
-        fence();
-        load_cols(cb, 3);                             fence();  mfma_cols(ca, p10);  fence();
-        mfma_cols(cb, p11);
-    };
-    auto grad_stage = [&]() __attribute__((always_inline)) {
-        f32x16 d0, d1;
-        RowOps ra, rb;
-        ColOps ca, cb;
-        bf16x8 pa, pb;
-        load_rows(ra, 0, 0);  load_neg_delta(d0, 0);
-        load_rows(rb, 0, 1);                           fence();  mfma_rows(d0, ra, 0);  fence();
-        load_rows(ra, 1, 0);  load_neg_delta(d1, 1);  pa = load_p(0, 0);  fence();  mfma_rows(d0, rb, 1);  fence();
-        load_rows(rb, 1, 1);  pb = load_p(0, 1);      fence();  mfma_rows(d1, ra, 0);
-        const bf16x8 e00 = ds_half(d0, pa, 0);
-        fence();
-        load_cols(ca, 0);     pa = load_p(1, 0);      fence();  mfma_rows(d1, rb, 1);
-        const bf16x8 e01 = ds_half(d0, pb, 1);
-        fence();
-        load_cols(cb, 1);     pb = load_p(1, 1);      fence();  mfma_cols(ca, e00);
-        const bf16x8 e10 = ds_half(d1, pa, 0);
-        fence();
-        load_cols(ca, 2);                             fence();  mfma_cols(cb, e01);
-        const bf16x8 e11 = ds_half(d1, pb, 1);
-        fence();
-        load_cols(cb, 3);                             fence();  mfma_cols(ca, e10);  fence();
-        mfma_cols(cb, e11);
-    };
-
-    // stage t of the item is row group g_first + t / nh with query head h_first + t % nh; every
-    // group of the tile's range is a stage (one whose hull misses the tile, rare, costs a copy and no math)
-    const int g_first = rec1.y, t1 = rec1.z;
-
-    // The schedule data of a stage (its group's hull, fully visible range and real-row count) comes
-    // by scalar loads issued right after the barrier of the stage before and is turned into flags
-    // at that stage's end: a load at the top of a stage would put its latency in front of the barrier.
-    struct Flags { bool full, live, pads; };
-    auto flags_of = [&](const int4& gd, int real, int g) {
-        Flags f;
-        f.full = (gd.z <= k0) && (k0 + BNK <= gd.w);
-        f.live = (gd.x < kw0 + 32) && (gd.y > kw0);
-        f.pads = real < min(GR, p.n_q - g * GR);
-        return f;
-    };
-    Flags cur_f{false, false, false};
-    if (t1 > 0) {
-        cur_f = flags_of(ld_const4(p.group + 4 * g_first), ld_const(p.group_real + g_first), g_first);
-        issue_stage(g_first, h_first, 0);
-        load_small(g_first, h_first, 0);
-    }
-    // no compiler-visible vector load may be pending inside the stage loop (it would wait for the copies too)
-    wait_vmem();
-    int g = g_first, hh = 0, b = 0;      // the score role's stage t = (g, hh) in buffer b
-    bool live_prev = false;
-    for (int t = 0; t <= t1 && t1 > 0; ++t) {
-        const bool have = t < t1, have_next = t + 1 < t1;
-        const bool full = cur_f.full, live = have && cur_f.live, has_pads = have && cur_f.pads;
-        int gn = g, hn = hh + 1;
-        if (hn == nh) { hn = 0; gn = g + 1; }
-        const int bn = b == NBUF - 1 ? 0 : b + 1;
-
-        wait_vmem();
-        if (has_pads) {
-            __syncthreads();      // stage t's tiles and row scalars are in LDS
-            const int r = tid >> 3, part = tid & 7;       // 512 threads: 8 per row
-            if (small_s[b][3][r] == 0) {
-                const i32x4 z = {0, 0, 0, 0};
-#pragma unroll
-                for (int i = 0; i < CPR / 8; ++i) {
-                    *reinterpret_cast<i32x4*>(smem + (2 * b) * TILEB + r * ROWB + (part * (CPR / 8) + i) * 16) = z;
-                    *reinterpret_cast<i32x4*>(smem + (2 * b + 1) * TILEB + r * ROWB + (part * (CPR / 8) + i) * 16) = z;
-                }
-            }
-        }
-        __syncthreads();          // stage t is in LDS, P of stage t-1 is visible, everyone has left
-                                  // the buffer of stage t-2 and the P buffer of stage t-2
-        if (have_next) {
-            issue_stage(gn, h_first + hn, bn);
-            load_small(gn, h_first + hn, bn);
-        }
-        int4 gd_n = int4{0, 0, 0, 0};
-        int real_n = 0;
-        const bool new_group = have_next && gn != g;
-        if (new_group) { gd_n = ld_const4(p.group + 4 * gn); real_n = ld_const(p.group_real + gn); }
-
-        if (role == 0) {
-            if (live) score_stage(!full);
-        } else {
-            if (live_prev) grad_stage();
-        }
-
-        if (new_group) cur_f = flags_of(gd_n, real_n, gn);
-        live_prev = live;
-        rotate(b);
-        g = gn; hh = hn; b = bn;
-    }
-
-    if (whole) {
-        if (mykey < p.t_kv) {
-            __bf16* op = (role == 0 ? p.dv : p.dk) + ((size_t)mykey * p.hkv + hk) * D;
-            const float f = role == 0 ? 1.0f : p.scale;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const int d = db * 32 + r4 * 8 + half * 4;
-                    *reinterpret_cast<bf16x4*>(op + d) = pack4(acc[db][r4 * 4 + 0] * f, acc[db][r4 * 4 + 1] * f,
-                                                               acc[db][r4 * 4 + 2] * f, acc[db][r4 * 4 + 3] * f);
-                }
-        }
-    } else {
-        // part of a key tile's work: unscaled fp32 partial [dK | dV][key][d], summed by dkv_fixup_kernel
-        float* op = p.partial + (size_t)slot * (2 * BNK * D) + (role == 0 ? BNK * D : 0) + (size_t)(kblk * 32 + l32) * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int d = db * 32 + r4 * 8 + half * 4;
-                *reinterpret_cast<f32x4*>(op + d) = f32x4{acc[db][r4 * 4 + 0], acc[db][r4 * 4 + 1],
-                                                          acc[db][r4 * 4 + 2], acc[db][r4 * 4 + 3]};
-            }
-    }
-  }   // next item
-}
-
 // dK/dV of calls in which few rows can see any one key tile (documents of a few dozen tokens); the schedule decides
 // between this kernel and the general one for the call as a whole.  There the general kernel walks whole
-// stages of 64 rows x 128 keys of which a third holds visible pairs, and waits for each at a barrier (2.5 us).  Here one
+// stages of 64 rows x 128 keys of which a third holds visible pairs, and waits for each at a barrier.  Here one
 // workgroup takes a key tile and KV head, and each of its four wavefronts works alone -- no barrier -- on 32 keys: it
 // holds K, V, dK^T and dV^T of them and walks (query head, 32-row block that can see them), the block's Q, dO and
 // per-row scalars copied into LDS of the wavefront's own.  S, P, dP and dS stay in its registers, so nothing is handed
@@ -1186,7 +753,7 @@ __global__ void __launch_bounds__(256, 2) dkv_short_kernel(const BwdParams p) {
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) { dk[db][r] = 0.f; dv[db][r] = 0.f; }
-    // rows read as they lie: chunk 2 ks + half of row l32; read transposed: rows qq and, with bit 5 flipped, qq + 8 (see dkv_kernel)
+    // rows read as they lie: chunk 2 ks + half of row l32; read transposed: rows qq and, with bit 5 flipped, qq + 8 (whose swizzle differs in bit 1)
     uint32_t naddr = base + l32 * ROWB + swz<CPR>(l32, half) * 16;
     const int qq = half * 4 + (j16 >> 2);
     uint32_t taddr = base + qq * ROWB + swz<CPR>(qq, gi * 2 + ((j16 & 3) >> 1)) * 16 + (j16 & 1) * 8;
@@ -1422,9 +989,9 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
         if (do_dkv) {
             if (p.short_on) {
                 dkv_short_kernel<D><<<grid_short, 256, 0, stream>>>(p);
-                dkv_kernel<D, true><<<grid_dkv, 512, 0, stream>>>(p);
+                launch_dkv_general(p, D, true, grid_dkv, stream);
             } else {
-                dkv_kernel<D, false><<<grid_dkv, 512, 0, stream>>>(p);
+                launch_dkv_general(p, D, false, grid_dkv, stream);
             }
             dkv_fixup_kernel<D><<<grid_fix * kMergeSplit, 256, 0, stream>>>(p);
         }

@@ -836,6 +836,29 @@ def test_backward_rows_in_arbitrary_order_with_garbage_in_padding():
     c.check_bwd()
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(1, 1, 128), (3, 1, 128), (4, 4, 64), (8, 1, 64), (8, 2, 128)])
+@pytest.mark.parametrize("docs", [[1], [33], [64, 64], [63, 1, 65, 127], [129, 31, 96, 700], [300, 5, 2100]], ids=str)
+def test_general_key_tiles_at_their_edges(docs, hq, hkv, d):
+    """The general dK/dV kernel where documents begin and end at, before and after a wavefront's 64 keys and 32 rows: a last tile
+    that ends in either half of its keys, items of one stage to dozens, stages that only some of the wavefronts see (between
+    stages that they do), a wavefront without a visible pair, and padding rows that hold NaN and Inf among them."""
+    import torch
+    w, tens = wl.small_case(63, docs, hq, hkv, d)
+    q_idx = np.arange(sum(docs), dtype=np.int32)
+    q_idx = np.insert(q_idx, np.arange(0, len(q_idx), 37), -1)
+    if len(docs) == 3:
+        q_idx = np.concatenate([q_idx[1000:], np.full(70, -1, dtype=np.int32), q_idx[:700]])      # late rows first, a group of padding
+    c = Case(tens, q_idx, _cu(docs), hq, hkv, d, w.scale)
+    c.flags = B.ATTN_NO_SHORT_PATH
+    pad = np.nonzero(q_idx < 0)[0]
+    for name in ("q", "do"):
+        t = c.dev[name].view(dtype=torch.int16)
+        t[pad[0::2]] = 0x7FC0          # NaN
+        t[pad[1::2]] = 0x7F80          # +Inf
+    c.check_fwd()
+    c.check_bwd()
+
+
 def test_backward_is_deterministic():
     c = _small(62, [900, 50, 400], 4, 2, 128)
     c.run_fwd()

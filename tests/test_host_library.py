@@ -324,3 +324,17 @@ def test_missing_library_is_an_error_not_a_fallback(tmp_path):
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, env=env,
                        cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     assert r.returncode == 0 and "ok" in r.stdout, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("line,fine", [("v_mfma_f32_32x32x16_bf16 a[0:15], v[2:5], v[6:9], a[0:15] ; acc", True), ("v_add_u32 v1, s2, v3 ; a[0:3]", True),
+                                       ("scratch_load_dwordx4 a[0:3], off, off offset:4 ; 16-byte Folded Reload", False),
+                                       ("v_accvgpr_write_b32 a17, v3", False)])
+def test_build_refuses_accumulation_registers_used_by_the_compiler(tmp_path, line, fine):
+    from paper_2503_17924_amd import build
+    asm = tmp_path / "kernel.s"
+    asm.write_text("\t.amdhsa_accum_offset 256\n\t" + line + "\n")
+    if fine:
+        build.check_acc_registers(str(asm))
+    else:
+        with pytest.raises(RuntimeError, match="accumulation register"):
+            build.check_acc_registers(str(asm))
