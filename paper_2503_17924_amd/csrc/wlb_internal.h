@@ -24,14 +24,18 @@ constexpr int kLists = 8;         // XCDs: workgroup b runs on XCD b % 8
 // takes this path when each of its four blocks qualifies.
 constexpr int kShortBlockRows = 32;
 constexpr int kShortHullKeys = 96;
-#ifndef WLB_DKV_SPLIT
-#define WLB_DKV_SPLIT 6
-#endif
-constexpr int kDkvSplit = WLB_DKV_SPLIT;      // a dK/dV item is at most 1/kDkvSplit of the mean load of a compute unit
-#ifndef WLB_DKV_MIN_ITEM_STAGES
-#define WLB_DKV_MIN_ITEM_STAGES 32
-#endif
-constexpr int kDkvMinItemStages = WLB_DKV_MIN_ITEM_STAGES;   // items this short are never split further
+// A dK/dV item is at most 1/kDkvSplit of the mean load of a compute unit, or kDkvMinItemStages stages where that is more: items
+// this short are never split further.  Each split costs an item more to start and two partial results that are written and
+// summed, so the items are coarse (kDkvCoarseSplit, kDkvCoarseStages) where the longest ones still leave the compute units
+// evenly loaded: for q = 1 .. kDkvBalance at most q - 1 per compute unit are longer than 1/q of 17/16 of its mean load and
+// kDkvCoarseSlack stages (what the partial results of one cost).  Only from one (key tile, KV head) per compute unit on: below
+// that the splits are what fills the chip.  Fine and coarse, dK/dV: 32K tokens in documents of 8K - 32K, 32/8 heads 2245 and
+// 2139 us; one of four ranks of 16K, 16/4 heads, 159 and 144; 13860 in documents of 64 - 1536, 16/4 heads, 183 and 149; and where
+// the rule stays with fine items: one of eight ranks of 128K, 8/1 heads, 5456 and 5652 us, with head dimension 64 3534 and 3785;
+// one document of 13719, 8/1 heads, 514 and 541.  Of 196 random calls three are more than 2 % slower than with fine items (3.5
+// at most), 50 more than 2 % faster (up to 18); without the slack 43.
+constexpr int kDkvSplit = 6, kDkvMinItemStages = 32;
+constexpr int kDkvCoarseSplit = 2, kDkvCoarseStages = 64, kDkvCoarseSlack = 16, kDkvBalance = 8;
 // workgroups per cut query tile and head in the merge kernels, and per key tile and KV head in the dK/dV fix-up (rows
 // split evenly); the gangs' merges, where finding a tile's parts costs more than summing them, take fewer
 constexpr int kMergeSplit = 8, kGangMergeSplit = 4;

@@ -249,12 +249,11 @@ __device__ __forceinline__ TileCost tile_cost(int k_lo, int k_hi) {
     return k_hi > k_lo ? TileCost{k_lo / 64, (k_hi + 63) / 64 - k_lo / 64} : TileCost{0, 0};
 }
 
-// A dK/dV item is at most this many stages (row groups x heads) unless it is a single head's.  An item of a few dozen
-// stages is not worth splitting: its partial results and the fix-up pass cost more than the shorter tail saves
-// (small-document inputs: 0.55 -> 0.48 ms with the minimum).
-__device__ __forceinline__ int item_limit(long long total_span, int hq, int n_slots) {
-    const unsigned long long per = (unsigned long long)n_slots * kDkvSplit;
-    return (int)min(max((unsigned long long)kDkvMinItemStages, ((unsigned long long)total_span * hq + per - 1) / per), 0x7fffffffull);
+// A dK/dV item is at most this many stages (row groups x heads) unless it is a single head's.
+__device__ __forceinline__ int item_limit(unsigned long long total_span, const PlanArgs& a, bool coarse) {
+    const unsigned long long per = (unsigned long long)a.n_slots * (coarse ? kDkvCoarseSplit : kDkvSplit);
+    const unsigned long long least = coarse ? kDkvCoarseStages : kDkvMinItemStages;
+    return (int)min(max(least, (total_span * a.hq + per - 1) / per), 0x7fffffffull);
 }
 // Items per (key tile, KV head), the smallest power of two that brings an item under the limit, and an item's stages.
 __device__ __forceinline__ int2 item_split(int span, int G, int limit) {
@@ -272,14 +271,34 @@ __device__ __forceinline__ int row_part_limit(long long total_cost, int top_cost
 }
 __device__ __forceinline__ int row_parts(int cost, int limit) { return cost > limit ? (cost + limit - 1) / limit : 1; }
 
-// What dK/dV would have to do: the sum of the key tiles' spans and the longest, and the row blocks that see 32 of a tile's
-// keys (the most, and the sum over each XCD's run of tiles).
-struct KeyWork { int span, chain, load[kLists]; unsigned long long total; };
+// What dK/dV would have to do: the sum of the key tiles' spans and the longest, the row blocks that see 32 of a tile's keys
+// (the most, and the sum over each XCD's run of tiles), and the coarse items too long for more than
+// q on a compute unit.
+struct KeyWork { int span, chain, load[kLists], longer[kDkvBalance]; unsigned long long total; };
 __device__ __forceinline__ void clear(KeyWork& w) {
     w.span = w.chain = 0;
     w.total = 0;
 #pragma unroll
+    for (int q = 0; q < kDkvBalance; ++q) w.longer[q] = 0;
+#pragma unroll
     for (int x = 0; x < kLists; ++x) w.load[x] = 0;
+}
+// Whether the items may be coarse (kDkvCoarseSplit), and then whether they are, once `longer` is filled.
+__device__ __forceinline__ bool coarse_items_possible(const PlanArgs& a) {
+    return ((a.hq / a.hkv) & 1) == 0 && (long long)a.n_key_tiles * a.hkv >= a.n_slots;
+}
+__device__ __forceinline__ bool items_split(const PlanArgs& a, const KeyWork& w) {
+    return (long long)w.span * (a.hq / a.hkv) > item_limit(w.total, a, false);
+}
+__device__ __forceinline__ int longer_items(const PlanArgs& a, const KeyWork& w, int span, int limit, int q) {
+    const int2 item = item_split(span, a.hq / a.hkv, limit);
+    return 16ull * (q + 1) * a.n_slots * item.x > 17ull * w.total * a.hq + 16ull * kDkvCoarseSlack * a.n_slots ? item.y * a.hkv : 0;
+}
+__device__ __forceinline__ bool coarse_items(const PlanArgs& a, const KeyWork& w) {
+    bool even = true;
+#pragma unroll
+    for (int q = 0; q < kDkvBalance; ++q) even &= w.longer[q] <= q * a.n_slots;
+    return even;
 }
 // Whether dkv_short_kernel does dK/dV.  Its wavefronts walk (row blocks x query heads of a KV head) one after another, where
 // the general kernel divides a tile's heads among items; and tiles of a longer span would need the general kernel's launch
@@ -538,24 +557,41 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
             load += steps >> 8;
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
-        if ((threadIdx.x & 63) == 0) atomicAdd(&s_work.total, (unsigned long long)total);
+        for (int o = 32; o > 0; o >>= 1) {
+            total += __shfl_xor(total, o);
+            most = max(most, __shfl_xor(most, o));
+        }
+        if ((threadIdx.x & 63) == 0) {
+            atomicAdd(&s_work.total, (unsigned long long)total);
+            atomicMax(&s_work.span, most);
+        }
         if (a.short_keys) {
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) {
-                most = max(most, __shfl_xor(most, o));
                 chain = max(chain, __shfl_xor(chain, o));
                 load += __shfl_xor(load, o);
             }
             if ((threadIdx.x & 63) == 0) {
-                atomicMax(&s_work.span, most);
                 atomicMax(&s_work.chain, chain);
                 atomicAdd(&s_work.load[x], load);
             }
         }
         __syncthreads();
     }
-    const int limit = item_limit((long long)s_work.total, a.hq, a.n_slots);
+    bool coarse = coarse_items_possible(a) && items_split(a, s_work);
+    if (coarse) {                                                // two wavefronts per q
+        static_assert(kDkvBalance == kLists, "wavefronts");
+        const int q = (int)threadIdx.x >> 7, most = item_limit(s_work.total, a, true);
+        int longer = 0;
+#pragma unroll 4
+        for (int kt = (int)(threadIdx.x & 127); kt < a.n_key_tiles; kt += 128) longer += longer_items(a, s_work, a.key_span[kt], most, q);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) longer += __shfl_xor(longer, o);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&s_work.longer[q], longer);
+        __syncthreads();
+        coarse = coarse_items(a, s_work);
+    }
+    const int limit = item_limit(s_work.total, a, coarse);
     const bool short_on = a.short_keys && short_keys_pay(a, s_work, limit);        // every workgroup comes to the same result
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.short_on = short_on ? 1 : 0;
     order_block<KeyCounts>(a.n_key_tiles, blockIdx.x, a.hkv > 8, [&](int j) { return item_split(a.key_span[j], G, limit); },
@@ -596,6 +632,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
     __syncthreads();
     const int G = a.hq / a.hkv;
     int2 range = make_int2(0, 0);      // of key tile tid / 4
+    int key_limit;
     {   // key tiles: four threads each
         const int kt = tid >> 2, k0 = kt * kBwdKeyTile, k1 = min(k0 + kBwdKeyTile, a.t_kv);
         int first = kPadLo, last = 0;
@@ -625,23 +662,38 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             if ((tid & 3) == 0 && seen) atomicAdd(&s_work.load[kt / a.key_run], seen);
         }
 #pragma unroll
-        for (int o = 32; o > 1; o >>= 1) sum += __shfl_xor(sum, o);
-        if ((tid & 63) == 0 && sum) atomicAdd(&s_work.total, (unsigned long long)sum);
+        for (int o = 32; o > 1; o >>= 1) {
+            sum += __shfl_xor(sum, o);
+            most = max(most, __shfl_xor(most, o));
+        }
+        if ((tid & 63) == 0 && sum) {
+            atomicAdd(&s_work.total, (unsigned long long)sum);
+            atomicMax(&s_work.span, most);
+        }
         if (a.short_keys) {
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                most = max(most, __shfl_xor(most, o));
-                chain = max(chain, __shfl_xor(chain, o));
-            }
-            if ((tid & 63) == 0 && sum) {
-                atomicMax(&s_work.span, most);
-                atomicMax(&s_work.chain, chain);
-            }
+            for (int o = 32; o > 0; o >>= 1) chain = max(chain, __shfl_xor(chain, o));
+            if ((tid & 63) == 0 && sum) atomicMax(&s_work.chain, chain);
         }
         __syncthreads();
+        bool coarse = coarse_items_possible(a) && items_split(a, s_work);
+        if (coarse) {                                            // a thread per tile and every fourth q
+            static_assert(kDkvBalance % 4 == 0, "four threads per key tile");
+            const int most = item_limit(s_work.total, a, true);
+#pragma unroll
+            for (int q = tid & 3; q < kDkvBalance; q += 4) {
+                int longer = kt < a.n_key_tiles ? longer_items(a, s_work, span, most, q) : 0;
+#pragma unroll
+                for (int o = 32; o > 2; o >>= 1) longer += __shfl_xor(longer, o);
+                if ((tid & 63) < 4 && longer) atomicAdd(&s_work.longer[q], longer);
+            }
+            __syncthreads();
+            coarse = coarse_items(a, s_work);
+        }
+        key_limit = item_limit(s_work.total, a, coarse);
         if ((tid & 3) == 0) {
             // past the end: a cost below every real one
-            s_items[kt] = kt < a.n_key_tiles ? item_split(span, G, item_limit((long long)s_work.total, a.hq, a.n_slots)) : make_int2(-1, 0);
+            s_items[kt] = kt < a.n_key_tiles ? item_split(span, G, key_limit) : make_int2(-1, 0);
             if (kt < a.n_key_tiles) {
                 a.key_range[2 * kt] = range.x;
                 a.key_range[2 * kt + 1] = range.y;
@@ -687,7 +739,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
     }
     if (a.forward_only) return;
     __syncthreads();
-    if (tid == 0) *a.short_on = a.short_keys && short_keys_pay(a, s_work, item_limit((long long)s_work.total, a.hq, a.n_slots)) ? 1 : 0;
+    if (tid == 0) *a.short_on = a.short_keys && short_keys_pay(a, s_work, key_limit) ? 1 : 0;
     {   // the key tiles' order: four threads per tile, each a quarter of the comparisons
         const int i = tid >> 2;
         const int2 own = s_items[i];

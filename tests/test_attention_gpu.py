@@ -791,6 +791,44 @@ BWD_CASES = [
 ]
 
 
+@pytest.mark.parametrize("docs,rows,hq,hkv,coarse", [
+    ([1024] * 16, range(16384), 32, 8, True),                          # documents of one length, three launches
+    ([18432], range(10240, 18432), 8, 2, False),                       # too many long items
+    ([16384], range(8192, 16384), 10, 5, True),
+    ([18432], range(14336, 18432), 8, 2, True),                        # the single launch
+    ([900, 3000, 77] * 4 + [384], range(1, 16276, 4), 16, 4, True),
+    ([16384], range(12288, 16384), 16, 2, False),                      # too many long items
+    ([1024] * 15 + [1000], range(0, 16360, 3), 6, 1, False),           # fewer key tiles and KV heads than compute units
+    ([1024] * 16, range(16384), 6, 2, False),                          # three heads are never split
+])
+def test_dkv_items_are_coarse_where_they_balance(docs, rows, hq, hkv, coarse):
+    """The limit of a dK/dV item in both schedules against its rule."""
+    import torch
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    cu = _cu(docs)
+    attn = B.Attention(np.asarray(rows, dtype=np.int32), cu, int(cu[-1]), hq, hkv, 64, 0.125)
+    attn.plan()
+    torch.cuda.synchronize()
+    t = check_work_records(attn)
+    G, span = hq // hkv, t["key_range"][:, 1] - t["key_range"][:, 0]
+    total = int(span.sum()) * hq
+
+    def ways_of(limit):
+        ways = np.ones(len(span), dtype=np.int64)
+        while (more := ((G // ways) % 2 == 0) & (span * (G // ways) > limit)).any():
+            ways[more] *= 2
+        return ways
+
+    want = ways_of(max(64, -(-total // (2 * n_cu))))
+    even = all((want * hkv)[span * (G // want) * 16 * q * n_cu > 17 * total + 256 * n_cu].sum() <= (q - 1) * n_cu for q in range(1, 9))
+    takes = G % 2 == 0 and len(span) * hkv >= n_cu and even
+    assert takes == coarse or n_cu != 256
+    if not takes:
+        want = ways_of(max(DKV_MIN_ITEM_STAGES, -(-total // (DKV_SPLIT * n_cu))))
+    assert (t["key_ways"] == want).all()
+    assert t["key_slot_base"][-1] <= t["layout"].dkv_max_partials
+
+
 @pytest.mark.parametrize("docs,hq,hkv,d,cp", BWD_CASES)
 def test_backward_matches_oracle(docs, hq, hkv, d, cp):
     for r in range(cp):
