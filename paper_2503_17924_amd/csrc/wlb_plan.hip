@@ -287,6 +287,8 @@ __device__ __forceinline__ void clear(KeyWork& w) {
 __device__ __forceinline__ bool coarse_items_possible(const PlanArgs& a) {
     return ((a.hq / a.hkv) & 1) == 0 && (long long)a.n_key_tiles * a.hkv >= a.n_slots;
 }
+// Whether anything asks for the longest span.
+__device__ __forceinline__ bool need_span(const PlanArgs& a) { return a.short_keys || coarse_items_possible(a); }
 __device__ __forceinline__ bool items_split(const PlanArgs& a, const KeyWork& w) {
     return (long long)w.span * (a.hq / a.hkv) > item_limit(w.total, a, false);
 }
@@ -557,13 +559,12 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
             load += steps >> 8;
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            total += __shfl_xor(total, o);
-            most = max(most, __shfl_xor(most, o));
-        }
-        if ((threadIdx.x & 63) == 0) {
-            atomicAdd(&s_work.total, (unsigned long long)total);
-            atomicMax(&s_work.span, most);
+        for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&s_work.total, (unsigned long long)total);
+        if (need_span(a)) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
+            if ((threadIdx.x & 63) == 0) atomicMax(&s_work.span, most);
         }
         if (a.short_keys) {
 #pragma unroll
@@ -603,6 +604,7 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
 // The whole schedule in one launch of one workgroup, for calls that one workgroup handles faster than three launches
 // follow each other: up to 4096 rows (four groups per wavefront), 256 key tiles (32768 keys) and the documents the LDS holds.  At 2052 rows and 4096
 // keys it takes 10.0 us (one launch per step: 17.0 in five), at 4095 rows and 16381 keys 12.5 us.
+// A forward alone has no dK/dV items to order: 1031 rows with their schedule 33.1 -> 31.6 us without the key tiles, 4096 34.6 -> 32.9.
 constexpr int kSmallGroups = 64, kSmallTiles = kSmallGroups / kGroupsPerTile, kSmallKeyTiles = 256;
 __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
     __shared__ int s_cu[kCuLds];
@@ -632,8 +634,8 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
     __syncthreads();
     const int G = a.hq / a.hkv;
     int2 range = make_int2(0, 0);      // of key tile tid / 4
-    int key_limit;
-    {   // key tiles: four threads each
+    int key_limit = 0;
+    if (!a.forward_only) {             // key tiles: four threads each
         const int kt = tid >> 2, k0 = kt * kBwdKeyTile, k1 = min(k0 + kBwdKeyTile, a.t_kv);
         int first = kPadLo, last = 0;
 #pragma unroll
@@ -662,13 +664,12 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             if ((tid & 3) == 0 && seen) atomicAdd(&s_work.load[kt / a.key_run], seen);
         }
 #pragma unroll
-        for (int o = 32; o > 1; o >>= 1) {
-            sum += __shfl_xor(sum, o);
-            most = max(most, __shfl_xor(most, o));
-        }
-        if ((tid & 63) == 0 && sum) {
-            atomicAdd(&s_work.total, (unsigned long long)sum);
-            atomicMax(&s_work.span, most);
+        for (int o = 32; o > 1; o >>= 1) sum += __shfl_xor(sum, o);
+        if ((tid & 63) == 0 && sum) atomicAdd(&s_work.total, (unsigned long long)sum);
+        if (need_span(a)) {
+#pragma unroll
+            for (int o = 32; o > 1; o >>= 1) most = max(most, __shfl_xor(most, o));
+            if ((tid & 63) == 0 && sum) atomicMax(&s_work.span, most);
         }
         if (a.short_keys) {
 #pragma unroll
