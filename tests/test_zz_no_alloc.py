@@ -57,6 +57,13 @@ def test_two_calls_in_a_row_second_one_smaller():
     _run_both(303, [5], 2, 1, 128, 1, 0)                                  # smaller again: less than one tile
 
 
+@pytest.mark.parametrize("docs,hq,hkv,d", [([3000, 1095, 1], 4, 2, 64), ([3000, 1096, 1], 4, 2, 64), ([4096], 2, 1, 128), ([33] * 124, 8, 1, 128)])
+def test_schedule_of_a_forward_alone(docs, hq, hkv, d):
+    """The last number of rows that one workgroup schedules and the first that takes three launches, one long
+    document, many short ones: without the key tiles as with them."""
+    _run_both(305, docs, hq, hkv, d, 1, 0)
+
+
 def test_limits_and_flags():
     import torch
     docs = [64]
