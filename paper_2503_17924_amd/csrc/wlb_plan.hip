@@ -275,13 +275,9 @@ __device__ __forceinline__ int row_parts(int cost, int limit) { return cost > li
 // (the most, and the sum over each XCD's run of tiles), and the coarse items too long for more than
 // q on a compute unit.
 struct KeyWork { int span, chain, load[kLists], longer[kDkvBalance]; unsigned long long total; };
-__device__ __forceinline__ void clear(KeyWork& w) {
-    w.span = w.chain = 0;
-    w.total = 0;
-#pragma unroll
-    for (int q = 0; q < kDkvBalance; ++q) w.longer[q] = 0;
-#pragma unroll
-    for (int x = 0; x < kLists; ++x) w.load[x] = 0;
+__device__ __forceinline__ void clear(KeyWork& w) {              // by the threads of a workgroup
+    static_assert(sizeof(KeyWork) % 4 == 0 && sizeof(KeyWork) / 4 <= 1024, "a thread per word");
+    if (threadIdx.x < sizeof(KeyWork) / 4) reinterpret_cast<int*>(&w)[threadIdx.x] = 0;
 }
 // Whether the items may be coarse (kDkvCoarseSplit), and then whether they are, once `longer` is filled.
 __device__ __forceinline__ bool coarse_items_possible(const PlanArgs& a) {
@@ -289,9 +285,6 @@ __device__ __forceinline__ bool coarse_items_possible(const PlanArgs& a) {
 }
 // Whether anything asks for the longest span.
 __device__ __forceinline__ bool need_span(const PlanArgs& a) { return a.short_keys || coarse_items_possible(a); }
-__device__ __forceinline__ bool items_split(const PlanArgs& a, const KeyWork& w) {
-    return (long long)w.span * (a.hq / a.hkv) > item_limit(w.total, a, false);
-}
 __device__ __forceinline__ int longer_items(const PlanArgs& a, const KeyWork& w, int span, int limit, int q) {
     const int2 item = item_split(span, a.hq / a.hkv, limit);
     return 16ull * (q + 1) * a.n_slots * item.x > 17ull * w.total * a.hq + 16ull * kDkvCoarseSlack * a.n_slots ? item.y * a.hkv : 0;
@@ -542,7 +535,7 @@ __global__ void __launch_bounds__(1024) plan_ranges_kernel(const PlanArgs a, int
 __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) {
     __shared__ KeyWork s_work;
     if (blockIdx.x == 0 && threadIdx.x < kLists) a.dkv_counters[threadIdx.x] = 0;
-    if (threadIdx.x == 0) clear(s_work);
+    clear(s_work);
     __syncthreads();
     const int G = a.hq / a.hkv;
     {   // two wavefronts per XCD's run of key tiles
@@ -579,8 +572,8 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
         }
         __syncthreads();
     }
-    bool coarse = coarse_items_possible(a) && items_split(a, s_work);
-    if (coarse) {                                                // two wavefronts per q
+    int limit = item_limit(s_work.total, a, false);
+    if (coarse_items_possible(a) && (long long)s_work.span * G > limit) {        // two wavefronts per q
         static_assert(kDkvBalance == kLists, "wavefronts");
         const int q = (int)threadIdx.x >> 7, most = item_limit(s_work.total, a, true);
         int longer = 0;
@@ -590,9 +583,8 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
         for (int o = 32; o > 0; o >>= 1) longer += __shfl_xor(longer, o);
         if ((threadIdx.x & 63) == 0) atomicAdd(&s_work.longer[q], longer);
         __syncthreads();
-        coarse = coarse_items(a, s_work);
+        if (coarse_items(a, s_work)) limit = most;
     }
-    const int limit = item_limit(s_work.total, a, coarse);
     const bool short_on = a.short_keys && short_keys_pay(a, s_work, limit);        // every workgroup comes to the same result
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.short_on = short_on ? 1 : 0;
     order_block<KeyCounts>(a.n_key_tiles, blockIdx.x, a.hkv > 8, [&](int j) { return item_split(a.key_span[j], G, limit); },
@@ -618,7 +610,7 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
     int2 block[PER];
     load_tokens<PER>(a, wave, 16, tok);
     for (int i = tid; i < a.n_docs; i += 1024) s_cu[i] = a.cu[i];
-    if (tid == 0) clear(s_work);
+    clear(s_work);
     if (tid < kLists) a.dkv_counters[tid] = 0;
     __syncthreads();
     plan_groups<PER>(a, s_cu, wave, 16, tok, hull, block);
@@ -677,8 +669,8 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             if ((tid & 63) == 0 && sum) atomicMax(&s_work.chain, chain);
         }
         __syncthreads();
-        bool coarse = coarse_items_possible(a) && items_split(a, s_work);
-        if (coarse) {                                            // a thread per tile and every fourth q
+        key_limit = item_limit(s_work.total, a, false);
+        if (coarse_items_possible(a) && (long long)s_work.span * G > key_limit) {        // a thread per tile and every fourth q
             static_assert(kDkvBalance % 4 == 0, "four threads per key tile");
             const int most = item_limit(s_work.total, a, true);
 #pragma unroll
@@ -689,9 +681,8 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
                 if ((tid & 63) < 4 && longer) atomicAdd(&s_work.longer[q], longer);
             }
             __syncthreads();
-            coarse = coarse_items(a, s_work);
+            if (coarse_items(a, s_work)) key_limit = most;
         }
-        key_limit = item_limit(s_work.total, a, coarse);
         if ((tid & 3) == 0) {
             // past the end: a cost below every real one
             s_items[kt] = kt < a.n_key_tiles ? item_split(span, G, key_limit) : make_int2(-1, 0);
