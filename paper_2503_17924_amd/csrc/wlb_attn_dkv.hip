@@ -131,16 +131,20 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
 
     __shared__ __attribute__((aligned(1024))) char smem[NBUF * 2 * TILEB];   // per stage buffer: Q tile | dO tile, swizzled
     __shared__ __attribute__((aligned(1024))) char small_s[NBUF * SMALL];    // per stage buffer: lse2 | delta | row_lo | row_hi
+    __shared__ __attribute__((aligned(1024))) char zero_s[TILEB];            // columns of zeros, in place of a stage that the wavefront leaves out
     __shared__ int s_item;
     if (SHORT && ld_const(p.short_on)) return;                   // dkv_short_kernel has done it
     const int n_items = ld_const(p.key_item_base + p.n_key_tiles);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    for (int i = tid; i < TILEB / 16; i += 256) reinterpret_cast<u32x4*>(zero_s)[i] = u32x4{0, 0, 0, 0};
+    wait_lds();                                                   // (in front of an item's first barrier)
     const int kb = wave & 1, rh = wave >> 1;                      // the wavefront's 64 keys and 32 rows
     const int l32 = lane & 31, half = lane >> 5, j16 = lane & 15, gi = (lane >> 4) & 1;
     const float cs = p.scale_log2e;
     const uint32_t q_row_bytes = (uint32_t)p.hq * (D * 2u), q_total = (uint32_t)p.n_q * q_row_bytes;
     const uint32_t smem_base = (uint32_t)(uintptr_t)(WLB_LDS char*)smem, small_base = (uint32_t)(uintptr_t)(WLB_LDS char*)small_s;
+    const uint32_t zero_at = (uint32_t)(uintptr_t)(WLB_LDS char*)zero_s - smem_base;
     auto lds_f4 = [](uint32_t a) __attribute__((always_inline)) { return *reinterpret_cast<const WLB_LDS f32x4*>((uintptr_t)a); };
     auto lds_i4 = [](uint32_t a) __attribute__((always_inline)) { return *reinterpret_cast<const WLB_LDS i32x4*>((uintptr_t)a); };
     auto lds_i = [](uint32_t a) __attribute__((always_inline)) { return *reinterpret_cast<const WLB_LDS int*>((uintptr_t)a); };
@@ -361,6 +365,13 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         f.pads = __any(!real);
         return f;
     };
+    // Whether a row's LSE or delta is Inf or NaN, as they are where its Q or dO is, or a K or V that it sees.  0 x Inf is not 0, so
+    // such rows may meet only keys that they see: odd_stage.
+    auto odd_row = [&](uint32_t small_at) __attribute__((always_inline)) {
+        const uint32_t a = row_at(small_at);
+        const uint32_t x = (uint32_t)lds_i(a) & 0x7f800000u, y = (uint32_t)lds_i(a + GR * 4) & 0x7f800000u;
+        return max(x, y) == 0x7f800000u;
+    };
     // Scores of invisible pairs become -inf, rows of padding (which may hold anything) zero.  Both wavefronts of the same rows write the
     // zeros, so none waits for the other.
     auto mask = [&](uint32_t small_at) __attribute__((always_inline)) {
@@ -413,9 +424,51 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         }
     };
     const f32x16 zero16 = {};
+    // All of a stage after its scores, without anything beside it: P and dS of invisible pairs are zeros whatever the rows hold, and of the two
+    // sets of 32 keys only those that one of the rows sees are added to.
+    auto odd_stage = [&](Pair x_row, Pair x_col, uint32_t small_at) __attribute__((always_inline)) {
+        const uint32_t a = vals_at(small_at), ra = row_at(small_at);
+        const int lo = lds_i(ra + 2 * GR * 4), hi = lds_i(ra + 3 * GR * 4), my = kw0 + ((int)opaque((uint32_t)tid) & 31);
+        for_all<2>([&](auto i_tag) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_tag)::value;
+            if (!__any(hi > 0 && lo < kw0 + i * 32 + 32 && hi > kw0 + i * 32)) return;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) dp[i][e] = __builtin_bit_cast(float, lds_i(a + GR * 4 + (e >> 2) * 32 + (e & 3) * 4));
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                dp[i] = mfma32(rd_row(x_row, u, TILEB), vop[i][u], dp[i]);
+                fence();
+            }
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+                float pe[2], de[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const uint32_t at = a + ((e + j) >> 2) * 32 + ((e + j) & 3) * 4;
+                    const int l = lds_i(at + 2 * GR * 4), w = lds_i(at + 3 * GR * 4) - l;
+                    const bool seen = (uint32_t)(my + i * 32 - l) < (uint32_t)w;
+                    const float pv = fast_exp2(fmaf(s[i][e + j], cs, -__builtin_bit_cast(float, lds_i(at))));
+                    pe[j] = seen ? pv : 0.f;
+                    de[j] = seen ? pv * dp[i][e + j] : 0.f;
+                }
+                pk[i][e >> 3][(e & 7) >> 1] = pack2(pe[0], pe[1]);
+                ds[i][e >> 3][(e & 7) >> 1] = pack2(de[0], de[1]);
+                fence();
+            }
+            asm volatile("s_nop 1");
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                acc_mfma(ACC_DV + i * DB + u % DB, rd_col(x_col, u, TILEB), pk[i][u / DB]);
+                fence();
+                acc_mfma(ACC_DK + i * DB + u % DB, rd_col(x_col, u, 0), ds[i][u / DB]);
+                fence();
+            }
+        });
+    };
 
     // first stage: scores
     Flags f;
+    bool odd = false;
     Pair a_row = rows_of(0), a_dk = cols_of(0);     // of the stage's buffer; of the buffer of the stage whose dK is pending
     bool pending = false;                           // (none is: dS = 0, of any buffer)
     {
@@ -430,6 +483,7 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         f = flags(lo, hi);
         if (!f.full) {
             asm volatile("");
+            odd = __any(hi > 0 && odd_row(0));
             mask(0);
             if (f.pads) zero_pads(hi, 0);
         }
@@ -442,8 +496,8 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
     uint32_t buf = 0, small_at = 0;
     int hh = 0;
     for (int t = 0; t < t1; ++t) {
-        const bool live = f.live;
-        const Pair a_col = cols_of(buf);
+        const bool live = f.live && !odd;
+        Pair a_col = cols_of(buf);
         if (live) {
             const uint32_t a_s = vals_at(small_at);
             f32x16 dl;
@@ -488,8 +542,13 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
                 }
             }
         } else {
-            // none of the wavefront's pairs is visible here: the pending dK while its rows are still in LDS, then zeros
+            // none of the wavefront's pairs is visible here, or rows are odd: the pending dK while its rows are still in LDS, then zeros
+            // times zeros (the rows of a stage that the wavefront does not see may hold anything)
             if (pending) flush_dk(a_dk);
+            if (f.live) {
+                asm volatile("");
+                odd_stage(a_row, a_col, small_at);
+            }
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 ds[i][0] = ds[i][1] = pk[i][0] = pk[i][1] = u32x4{0, 0, 0, 0};
@@ -497,7 +556,8 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
             }
             carry = 0.f;
 #pragma unroll
-            for (int u = SY; u < SY + 3; ++u) ring[u & 3] = rd_col(a_col, u, TILEB);
+            for (int u = SY; u < SY + 3; ++u) ring[u & 3] = bf16x8{};
+            a_col = cols_of(zero_at - TILEB);
         }
         // The next stage's copies are complete (issued in front of the latest ones), and every wavefront has left the buffer of the
         // stage before this one.
@@ -522,7 +582,7 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
                 fence();
             }
         }
-        a_dk = a_col;                               // (dS = 0 after a stage without visible pairs: of any buffer that holds numbers)
+        a_dk = cols_of(live ? buf : zero_at);
         pending = live;
         const uint32_t a_sn = vals_at(small_n);
 #pragma unroll
@@ -539,8 +599,10 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         }
         if (++hh == nh) hh = 0;
         if (hh == 0) f = flags(lo, hi);             // other rows
+        odd = false;
         if (!f.full) {
             asm volatile("");
+            odd = __any(hi > 0 && odd_row(small_n));
             mask(small_n);
             if (f.pads) zero_pads(hi, buf_n);
         }

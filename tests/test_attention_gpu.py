@@ -897,6 +897,50 @@ def test_general_key_tiles_at_their_edges(docs, hq, hkv, d):
     c.check_bwd()
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(2, 1, 128), (4, 4, 64), (8, 2, 128)])
+@pytest.mark.parametrize("docs,bad,cp", [([32, 300], 100, 1), ([64, 300], 200, 1), ([96, 40, 300], 250, 1), ([200, 300, 64], 400, 1),
+                                         ([16, 700, 33], 300, 1), ([32, 600, 40, 90], 200, 2)], ids=str)
+@pytest.mark.parametrize("where", ["q", "do", "lse"])
+def test_non_finite_rows_stay_with_the_keys_that_see_them(docs, bad, cp, where, hq, hkv, d):
+    """Inf or NaN in a row of Q or dO: dK and dV of other documents stay as they are, at least in the aligned blocks of 32 keys that none
+    of the same 64 rows sees (0 x Inf inside such a block is NaN).  In a row's LSE: those of every key that the row does not see."""
+    import torch
+    w, tens = wl.small_case(64, docs, hq, hkv, d)
+    cu = _cu(docs)
+    q_idx = np.arange(int(cu[-1]), dtype=np.int32) if cp == 1 else B.wlb_shard(docs, cp, 1, B.SHARD_PER_DOC_NOPAD)["q_idx"]
+    c = Case(tens, q_idx, cu, hq, hkv, d, w.scale)
+    c.flags = B.ATTN_NO_SHORT_PATH
+    c.run_fwd()
+    _, dk0, dv0 = c.run_bwd()
+
+    doc_of = np.searchsorted(cu, q_idx, side="right") - 1
+    seen = np.arange(int(cu[doc_of[bad]]), int(q_idx[bad]) + 1)
+    apart = np.ones(len(dk0), dtype=bool)
+    if where == "lse":
+        apart[seen] = False
+        c.lse[0::2, bad] = float("nan")
+        c.lse[1::2, bad] = float("-inf")
+    else:
+        t = c.dev[where].view(dtype=torch.int16)
+        t[bad, :, 3] = 0x7F80              # +Inf
+        t[bad, :, d - 1] = 0x7FC0          # NaN
+        c.run_fwd()
+        group = np.arange(bad // 64 * 64, min(bad // 64 * 64 + 64, len(q_idx)))
+        lo, hi = int(cu[doc_of[group]].min()), int(q_idx[group].max()) + 1
+        apart[lo // 32 * 32:-(-hi // 32) * 32] = False
+    assert apart.any()
+    _, dk1, dv1 = c.run_bwd()
+    for name, was, now, keys in [("dK", dk0, dk1, apart), ("dV", dv0, dv1, apart)]:
+        assert np.isfinite(now[keys]).all(), f"{name}: {np.nonzero(~np.isfinite(now).all(axis=(1, 2)) & keys)[0]}"
+        assert (np.abs(now[keys] - was[keys]) <= 2e-2 * np.abs(was).max()).all(), name
+    if where == "do":
+        assert not np.isfinite(dv1[seen][:, :, [3, d - 1]]).any()
+    if where == "q":
+        assert not np.isfinite(dk1[seen][:, :, [3, d - 1]]).any()
+    if where == "lse":
+        assert not np.isfinite(dv1[seen]).any()
+
+
 def test_backward_is_deterministic():
     c = _small(62, [900, 50, 400], 4, 2, 128)
     c.run_fwd()
