@@ -39,6 +39,14 @@ def check_acc_registers(asm: str) -> None:
                 raise RuntimeError(f"{asm}:{number}: accumulation register used by the compiler: {line.strip()}")
 
 
+def check_scratch(asm: str) -> None:
+    """Refuses code that keeps registers in memory: these kernels count the copies that are under way, and a load among them waits for all of those."""
+    with open(asm) as fh:
+        for number, line in enumerate(fh, 1):
+            if line.lstrip().startswith("scratch_"):
+                raise RuntimeError(f"{asm}:{number}: register kept in memory: {line.strip()}")
+
+
 def build(verbose: bool = False, keep_asm: bool = False, lib_out: str | None = None) -> str:
     """Compiles every source and links the library (to `lib_out`, default in-tree libwlb.so).
     WLB_HIPCC_EXTRA adds compiler flags (space separated) to every compile line."""
@@ -79,7 +87,9 @@ def build(verbose: bool = False, keep_asm: bool = False, lib_out: str | None = N
         if verbose and out.strip():
             print(out)
     for src in OWN_ACC_REGISTERS:
-        check_acc_registers(os.path.join(bdir, os.path.splitext(src)[0] + ".s"))
+        asm = os.path.join(bdir, os.path.splitext(src)[0] + ".s")
+        check_acc_registers(asm)
+        check_scratch(asm)
     tmp = lib_out + ".tmp"
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

@@ -170,7 +170,9 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
     const uint32_t voff0 = (uint32_t)((lane & 7) ^ ((lane >> 4 & 1) * 4)) * q_row_bytes + (uint32_t)(lane >> 3) * 16u, voff1 = voff0 ^ 16u;
     const uint64_t sm_array = (uint64_t)(uintptr_t)(wave == 0 ? (const void*)p.lse2 : wave == 1 ? (const void*)p.delta : wave == 2 ? (const void*)p.row_lo : (const void*)p.row_hi);
     const uint32_t sm_head = wave < 2 ? (uint32_t)p.n_q * 4u : 0u;
-    const uint32_t wave_lds = uniform(smem_base + (uint32_t)(wave * PER) * 1024u), wave_small = uniform(small_base + (uint32_t)wave * (GR * 4));
+    // (left to the compiler as what they are: told once more that they are uniform it kept them in vector registers, one of which went to memory, and
+    // the load of it waited for every copy under way)
+    const uint32_t wave_lds = smem_base + (uint32_t)(wave * PER) * 1024u, wave_small = small_base + (uint32_t)wave * (GR * 4);
 
     // Operands: rows as they lie (row rh * 32 + l32, chunk 2 u + half), for even and odd u; read transposed, rows qq and qq + 8 of 16 and
     // 4 columns of 32 db (lds_read_tr4)
@@ -224,7 +226,7 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         if constexpr (k < 2 * PER) {
             if (k == 0) {
                 at_so = uniform(nx_left > 0 ? nx_so : q_total);
-                at_lds = uniform(wave_lds + nx_b * (2 * TILEB));
+                at_lds = wave_lds + nx_b * (2 * TILEB);
             }
             const int voff = (int)(n / CH ? voff1 : voff0);
             if constexpr (k & 1) dma_issue_at<TILEB + n * 1024>(do_rs.r, at_lds, voff, at_so);
@@ -234,7 +236,7 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
             sm_rs.r[0] = (int)(uint32_t)nx_sm;
             sm_rs.r[1] = (int)(uint32_t)((nx_sm >> 32) & 0xffffu);
             sm_rs.make_uniform();
-            dma_issue_256(sm_rs.r, uniform(wave_small + nx_b * SMALL), (int)((opaque((uint32_t)tid) & 63) * 4), uniform(nx_left > 0 ? nx_row : n_q_bytes));
+            dma_issue_256(sm_rs.r, wave_small + nx_b * SMALL, (int)((opaque((uint32_t)tid) & 63) * 4), uniform(nx_left > 0 ? nx_row : n_q_bytes));
             // the next stage (no branch: this sits between MFMAs)
             --nx_left;
             nx_b = (nx_b + 1) & (NBUF - 1);
@@ -273,7 +275,7 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         BufRsrc kv_rs;
         kv_rs.init(p.k, kv_total);
         uint32_t so = uniform((uint32_t)(kt * BNK + wave * 16) * kv_row + (uint32_t)hk * ROWB);
-        const uint32_t at = uniform(wave_lds + 4 * TILEB), kv_rows8 = 8u * kv_row;
+        const uint32_t at = wave_lds + 4 * TILEB, kv_rows8 = 8u * kv_row;
         for_all<4>([&](auto tile) __attribute__((always_inline)) {                  // 64 rows of K, 64 more, V
             if (tile == 2) kv_rs.init(p.v, kv_total);
             uint32_t block = uniform(so + (tile & 1) * 64u * kv_row);

@@ -338,3 +338,13 @@ def test_build_refuses_accumulation_registers_used_by_the_compiler(tmp_path, lin
     else:
         with pytest.raises(RuntimeError, match="accumulation register"):
             build.check_acc_registers(str(asm))
+
+
+def test_build_refuses_registers_kept_in_memory(tmp_path):
+    from paper_2503_17924_amd import build
+    asm = tmp_path / "kernel.s"
+    asm.write_text("\tds_read_b32 v2, v1 ; scratch_\n")
+    build.check_scratch(str(asm))
+    asm.write_text("\tscratch_load_dword v2, off, off\t; 4-byte Folded Reload\n")
+    with pytest.raises(RuntimeError, match="kept in memory"):
+        build.check_scratch(str(asm))
