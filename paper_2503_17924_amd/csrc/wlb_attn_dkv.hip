@@ -33,6 +33,8 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
     "a208", "a209", "a210", "a211", "a212", "a213", "a214", "a215", "a216", "a217", "a218", "a219", "a220", "a221", "a222", "a223", \
     "a224", "a225", "a226", "a227", "a228", "a229", "a230", "a231", "a232", "a233", "a234", "a235", "a236", "a237", "a238", "a239", \
     "a240", "a241", "a242", "a243", "a244", "a245", "a246", "a247", "a248", "a249", "a250", "a251", "a252", "a253", "a254", "a255"
+// Two wait states must lie between a vector instruction and an MFMA that reads what it wrote, and the compiler does not put them in front of a
+// statement of ours.  As built, operands come from LDS or were packed some instructions before; build.py refuses code in which that is not so.
 template <int I>
 __device__ __forceinline__ void acc_mfma(bf16x8 a, u32x4 b) {
     asm volatile("v_mfma_f32_32x32x16_bf16 a[%0:%1], %2, %3, a[%0:%1] ; acc" ::"n"(I * 16), "n"(I * 16 + 15), "v"(a), "v"(b) : WLB_ACC_ALL);

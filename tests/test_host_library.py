@@ -348,3 +348,37 @@ def test_build_refuses_registers_kept_in_memory(tmp_path):
     asm.write_text("\tscratch_load_dword v2, off, off\t; 4-byte Folded Reload\n")
     with pytest.raises(RuntimeError, match="kept in memory"):
         build.check_scratch(str(asm))
+
+
+BY_HAND = "\t;;#ASMSTART\n\t%s\n\t;;#ASMEND\n"
+MFMA = BY_HAND % "v_mfma_f32_32x32x16_bf16 a[0:15], v[68:71], v[0x48:0x4b], a[0:15] ; acc"
+COPY = BY_HAND % "s_mov_b32 m0, s75\n\ts_nop 0\n\tbuffer_load_dword v3, s[40:43], s72 offen lds"
+
+
+@pytest.mark.parametrize("code,fine", [
+    ("\tv_mov_b32_e32 v75, v3\n\ts_nop 1\n" + MFMA, True),
+    ("\tv_mov_b32_e32 v75, v3\n\ts_nop 0\n" + MFMA, False),
+    ("\tv_mov_b32_e32 v76, v3\n" + MFMA, True),                                           # not an operand
+    ("\ts_nop 7\n\tv_mov_b32_e32 v68, v3\n\ts_cbranch_scc0 .LBB0_1\n\ts_nop 1\n.LBB0_1:\n" + MFMA, False),     # over a branch
+    ("\tv_mov_b32_e32 v68, v3\n\ts_branch .LBB0_1\n.LBB0_0:\n" + MFMA + "\ts_nop 1\n.LBB0_1:\n\ts_nop 1\n\ts_branch .LBB0_0\n", True),
+    ("\tv_mfma_f32_32x32x16_bf16 v[64:79], v[0:3], v[4:7], 0\n\ts_nop 15\n" + MFMA, False),
+    (MFMA + MFMA, True),                                                                     # one sum after the other
+    (MFMA + BY_HAND % "ds_write_b128 v2, a[0:3] ; acc", False),
+    (MFMA + BY_HAND % "s_nop 15\n\ts_nop 15" + BY_HAND % "ds_write_b128 v2, a[0:3] ; acc", True),
+    ("\tv_readfirstlane_b32 s43, v1\n\ts_nop 2\n" + COPY, True),
+    ("\tv_readfirstlane_b32 s43, v1\n\ts_nop 1\n" + COPY, False),
+    ("\tv_cmp_eq_u32_e64 s[72:73], 0, v0\n" + COPY, False),
+    (BY_HAND % "s_mov_b32 m0, s75\n\tbuffer_load_dword v3, s[40:43], s72 offen lds", False),
+    ("\tv_readfirstlane_b32 s4, v1\n\ts_nop 0\n" + BY_HAND % "v_add_u32 v2, s4, v3", False),
+    (BY_HAND % "v_add_u32 v2, s4, v3" + "\tv_readfirstlane_b32 s5, v2\n", False),
+    ("\tv_mov_b32_e32 v68, v3\n\tv_mfma_f32_32x32x16_bf16 a[0:15], v[68:71], v[72:75], 0\n", True),      # the compiler's own: it sees to them
+])
+def test_build_refuses_missing_wait_states(tmp_path, code, fine):
+    from paper_2503_17924_amd import build
+    asm = tmp_path / "kernel.s"
+    asm.write_text("kernel:\n" + code)
+    if fine:
+        build.check_wait_states(str(asm))
+    else:
+        with pytest.raises(RuntimeError, match="wait states"):
+            build.check_wait_states(str(asm))
