@@ -243,17 +243,36 @@ __device__ __forceinline__ void plan_groups(const PlanArgs& a, const int32_t* cu
     }
 }
 
+// Sum and largest (of numbers >= 0) over a wavefront, in every lane.  Between registers: exchanges through LDS by 16 wavefronts cost the one
+// workgroup that waits for them 0.1 us a step.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int from_lane(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }     // 0 where there is none
+template <class Op>
+__device__ __forceinline__ int over_lanes(int v, Op op) {
+    v = op(v, from_lane<0x111, 0xf>(v));       // row_shr:1, 2, 4, 8
+    v = op(v, from_lane<0x112, 0xf>(v));
+    v = op(v, from_lane<0x114, 0xf>(v));
+    v = op(v, from_lane<0x118, 0xf>(v));
+    v = op(v, from_lane<0x142, 0xa>(v));       // row_bcast:15, 31
+    v = op(v, from_lane<0x143, 0xc>(v));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ __forceinline__ int lanes_sum(int v) { return over_lanes(v, [](int x, int y) { return x + y; }); }
+__device__ __forceinline__ int lanes_max(int v) { return over_lanes(v, [](int x, int y) { return max(x, y); }); }
+
 // A query tile's cost: the 64-key tiles between the ends of its hull.
 struct TileCost { int first, cost; };
 __device__ __forceinline__ TileCost tile_cost(int k_lo, int k_hi) {
     return k_hi > k_lo ? TileCost{k_lo / 64, (k_hi + 63) / 64 - k_lo / 64} : TileCost{0, 0};
 }
 
+// (a 64-bit division takes a third of a microsecond, and every dividend but those of enormous calls has 32 bits)
+__device__ __forceinline__ unsigned long long quotient(unsigned long long x, uint32_t d) { return x >> 32 ? x / d : (uint32_t)x / d; }
 // A dK/dV item is at most this many stages (row groups x heads) unless it is a single head's.
 __device__ __forceinline__ int item_limit(unsigned long long total_span, const PlanArgs& a, bool coarse) {
-    const unsigned long long per = (unsigned long long)a.n_slots * (coarse ? kDkvCoarseSplit : kDkvSplit);
+    const uint32_t per = (uint32_t)a.n_slots * (coarse ? kDkvCoarseSplit : kDkvSplit);
     const unsigned long long least = coarse ? kDkvCoarseStages : kDkvMinItemStages;
-    return (int)min(max(least, (total_span * a.hq + per - 1) / per), 0x7fffffffull);
+    return (int)min(max(least, quotient(total_span * a.hq + per - 1, per)), 0x7fffffffull);
 }
 // Items per (key tile, KV head), the smallest power of two that brings an item under the limit, and an item's stages.
 __device__ __forceinline__ int2 item_split(int span, int G, int limit) {
@@ -283,11 +302,10 @@ __device__ __forceinline__ void clear(KeyWork& w) {              // by the threa
 __device__ __forceinline__ bool coarse_items_possible(const PlanArgs& a) {
     return ((a.hq / a.hkv) & 1) == 0 && (long long)a.n_key_tiles * a.hkv >= a.n_slots;
 }
-// Whether anything asks for the longest span.
-__device__ __forceinline__ bool need_span(const PlanArgs& a) { return a.short_keys || coarse_items_possible(a); }
-__device__ __forceinline__ int longer_items(const PlanArgs& a, const KeyWork& w, int span, int limit, int q) {
-    const int2 item = item_split(span, a.hq / a.hkv, limit);
-    return 16ull * (q + 1) * a.n_slots * item.x > 17ull * w.total * a.hq + 16ull * kDkvCoarseSlack * a.n_slots ? item.y * a.hkv : 0;
+// 17/16 of a compute unit's mean load and the slack, in stages: an item of x counts among the longer ones for q if (q + 1) x is more.  (Q has less than
+// 4 GiB, so rows x query heads have at most 25 bits, and the stages of an item 20.)
+__device__ __forceinline__ int coarse_load(const PlanArgs& a, const KeyWork& w) {
+    return (int)min(quotient(17ull * w.total * a.hq, 16u * (uint32_t)a.n_slots) + kDkvCoarseSlack, 0x7fffffffull);
 }
 __device__ __forceinline__ bool coarse_items(const PlanArgs& a, const KeyWork& w) {
     bool even = true;
@@ -551,21 +569,16 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
             chain = max(chain, steps & 255);
             load += steps >> 8;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
-        if ((threadIdx.x & 63) == 0) atomicAdd(&s_work.total, (unsigned long long)total);
-        if (need_span(a)) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
-            if ((threadIdx.x & 63) == 0) atomicMax(&s_work.span, most);
-        }
+        const int low = lanes_sum((int)(total & 0xffff)), high = lanes_sum((int)(total >> 16));
+        most = lanes_max(most);
         if (a.short_keys) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                chain = max(chain, __shfl_xor(chain, o));
-                load += __shfl_xor(load, o);
-            }
-            if ((threadIdx.x & 63) == 0) {
+            chain = lanes_max(chain);
+            load = lanes_sum(load);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            atomicAdd(&s_work.total, ((unsigned long long)high << 16) + low);
+            atomicMax(&s_work.span, most);
+            if (a.short_keys) {
                 atomicMax(&s_work.chain, chain);
                 atomicAdd(&s_work.load[x], load);
             }
@@ -573,15 +586,21 @@ __global__ void __launch_bounds__(1024) plan_key_items_kernel(const PlanArgs a) 
         __syncthreads();
     }
     int limit = item_limit(s_work.total, a, false);
-    if (coarse_items_possible(a) && (long long)s_work.span * G > limit) {        // two wavefronts per q
-        static_assert(kDkvBalance == kLists, "wavefronts");
-        const int q = (int)threadIdx.x >> 7, most = item_limit(s_work.total, a, true);
-        int longer = 0;
-#pragma unroll 4
-        for (int kt = (int)(threadIdx.x & 127); kt < a.n_key_tiles; kt += 128) longer += longer_items(a, s_work, a.key_span[kt], most, q);
+    if (coarse_items_possible(a) && (long long)s_work.span * G > limit) {        // a thread per tile
+        const int most = item_limit(s_work.total, a, true);
+        const int load = coarse_load(a, s_work), lane = (int)threadIdx.x & 63;
+        int longer[kDkvBalance] = {}, sum = 0;
+        for (int kt = (int)threadIdx.x; kt < a.n_key_tiles; kt += 1024) {
+            const int2 item = item_split(a.key_span[kt], G, most);
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) longer += __shfl_xor(longer, o);
-        if ((threadIdx.x & 63) == 0) atomicAdd(&s_work.longer[q], longer);
+            for (int q = 0; q < kDkvBalance; ++q) longer[q] += item.x * (q + 1) > load ? item.y * a.hkv : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < kDkvBalance; ++q) {
+            const int all = lanes_sum(longer[q]);
+            sum = lane == q ? all : sum;
+        }
+        if (lane < kDkvBalance) atomicAdd(&s_work.longer[lane], sum);
         __syncthreads();
         if (coarse_items(a, s_work)) limit = most;
     }
@@ -655,27 +674,24 @@ __global__ void __launch_bounds__(1024) plan_small_kernel(const PlanArgs a) {
             seen += __shfl_xor(seen, 2);
             if ((tid & 3) == 0 && seen) atomicAdd(&s_work.load[kt / a.key_run], seen);
         }
-#pragma unroll
-        for (int o = 32; o > 1; o >>= 1) sum += __shfl_xor(sum, o);
-        if ((tid & 63) == 0 && sum) atomicAdd(&s_work.total, (unsigned long long)sum);
-        if (need_span(a)) {
-#pragma unroll
-            for (int o = 32; o > 1; o >>= 1) most = max(most, __shfl_xor(most, o));
-            if ((tid & 63) == 0 && sum) atomicMax(&s_work.span, most);
-        }
-        if (a.short_keys) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) chain = max(chain, __shfl_xor(chain, o));
-            if ((tid & 63) == 0 && sum) atomicMax(&s_work.chain, chain);
+        sum = lanes_sum(sum);
+        most = lanes_max(most);
+        if (a.short_keys) chain = lanes_max(chain);
+        if ((tid & 63) == 0 && sum) {
+            atomicAdd(&s_work.total, (unsigned long long)sum);
+            atomicMax(&s_work.span, most);
+            if (a.short_keys) atomicMax(&s_work.chain, chain);
         }
         __syncthreads();
         key_limit = item_limit(s_work.total, a, false);
         if (coarse_items_possible(a) && (long long)s_work.span * G > key_limit) {        // a thread per tile and every fourth q
             static_assert(kDkvBalance % 4 == 0, "four threads per key tile");
             const int most = item_limit(s_work.total, a, true);
+            const int load = coarse_load(a, s_work);
+            const int2 item = kt < a.n_key_tiles ? item_split(span, G, most) : make_int2(0, 0);
 #pragma unroll
             for (int q = tid & 3; q < kDkvBalance; q += 4) {
-                int longer = kt < a.n_key_tiles ? longer_items(a, s_work, span, most, q) : 0;
+                int longer = item.x * (q + 1) > load ? item.y * a.hkv : 0;
 #pragma unroll
                 for (int o = 32; o > 2; o >>= 1) longer += __shfl_xor(longer, o);
                 if ((tid & 63) < 4 && longer) atomicAdd(&s_work.longer[q], longer);
