@@ -237,7 +237,7 @@ typedef struct {
     int32_t bwd_key_tile, n_key_tiles;
     size_t  off_row_lo, off_row_hi;      /* int32 [n_q]: visible keys are [lo, hi); pads: lo > hi */
     size_t  off_group;                   /* int32 [n_groups][4] */
-    size_t  off_group_real;              /* int32 [n_groups]: real (non-padding, in-range) rows in the group */
+    size_t  off_group_real;              /* int32 [n_groups]: real (non-padding, in-range) rows in the group; no launch reads it */
     size_t  off_fwd_order;               /* int32 [n_fwd_tiles] */
     size_t  off_fwd_cost;                /* int32 [n_fwd_tiles]: key tiles each query tile visits */
     size_t  off_key_order;               /* int32 [n_key_tiles] */
@@ -249,7 +249,7 @@ typedef struct {
     size_t  off_key_ways;                /* int32 [n_key_tiles]: items per (key tile, KV head), by key tile */
     size_t  off_key_item_base;           /* int32 [n_key_tiles + 1]: first item of the tile of order rank r */
     size_t  off_key_slot_base;           /* int32 [n_key_tiles + 1]: first partial slot of the tile of rank r */
-    size_t  off_dkv_counters;            /* int32 [8]: dK/dV items handed out per XCD list; zero between launches */
+    size_t  off_dkv_counters;            /* int32 [8]: dK/dV items handed out per XCD list beyond the first of each workgroup; zero between launches */
     /* forward / dQ work: the query tiles in order, each repeated for every KV head, form one line of
        work measured in key tiles (plus a fixed per-tile cost); row_gangs gangs of hq/hkv workgroups
        take consecutive shares of it (the first half of the gangs, whose workgroups run faster, a

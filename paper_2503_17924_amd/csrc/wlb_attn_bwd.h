@@ -8,11 +8,11 @@ struct BwdParams {
     const __bf16* q; const __bf16* k; const __bf16* v; const __bf16* o; const __bf16* d_o;
     const float* lse; float* delta; float* lse2;
     __bf16* dq; __bf16* dk; __bf16* dv;
-    const int32_t* row_lo; const int32_t* row_hi; const int32_t* group; const int32_t* group_real;
+    const int32_t* row_lo; const int32_t* row_hi;
     const int32_t* key_order; const int32_t* key_ways; const int32_t* key_item_base; const int32_t* key_slot_base;
     const int32_t* key_range; const int32_t* short_on;   // dkv_short_kernel; null: not launched
     const int32_t* dkv_item;   // two int4 per item (PlanLayout::off_dkv_item)
-    int32_t* dkv_counters;     // [8]: items of each XCD's list handed out so far (zero before every dK/dV launch)
+    int32_t* dkv_counters;     // [8]: items of each XCD's list handed out beyond the first of every workgroup (zero before every dK/dV launch)
     float* partial;
     RowSched sched;            // dQ: which query tiles, heads and key ranges a workgroup works on
     float* row_partial;        // dQ: partial results of the tiles cut at a gang boundary

@@ -930,8 +930,6 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.dq = (__bf16*)dq; p.dk = (__bf16*)dk; p.dv = (__bf16*)dv;
     p.row_lo = (const int32_t*)(ws + L.off_row_lo);
     p.row_hi = (const int32_t*)(ws + L.off_row_hi);
-    p.group = (const int32_t*)(ws + L.off_group);
-    p.group_real = (const int32_t*)(ws + L.off_group_real);
     p.key_order = (const int32_t*)(ws + L.off_key_order);
     p.dkv_item = (const int32_t*)(ws + L.off_dkv_item);
     p.key_range = (const int32_t*)(ws + L.off_key_range);

@@ -127,7 +127,7 @@ __device__ __forceinline__ const BwdParams& params_here() {
 template <int D, bool SHORT>
 __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
     const BwdParams& p = args;
-    constexpr int BNK = kBwdKeyTile, GR = kGroupRows, NU = D / 16, DB = D / 32, CPR = D / 8;
+    constexpr int BNK = kBwdKeyTile, GR = kGroupRows, NU = D / 16, DB = D / 32;
     constexpr int ROWB = D * 2, TILEB = GR * ROWB, NW = 4, NBUF = 4, SMALL = 4 * GR * 4;
     static_assert(BNK == 128 && GR == 64, "tiling");
 
