@@ -371,10 +371,8 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
     };
     // Whether a row's LSE or delta is Inf or NaN, as they are where its Q or dO is, or a K or V that it sees.  0 x Inf is not 0, so
     // such rows may meet only keys that they see: odd_stage.
-    auto odd_row = [&](uint32_t small_at) __attribute__((always_inline)) {
-        const uint32_t a = row_at(small_at);
-        const uint32_t x = (uint32_t)lds_i(a) & 0x7f800000u, y = (uint32_t)lds_i(a + GR * 4) & 0x7f800000u;
-        return max(x, y) == 0x7f800000u;
+    auto odd_rows = [&](int hi, int lse, int delta) __attribute__((always_inline)) {
+        return (bool)__any(hi > 0 && max((uint32_t)lse & 0x7f800000u, (uint32_t)delta & 0x7f800000u) == 0x7f800000u);
     };
     // Scores of invisible pairs become -inf, rows of padding (which may hold anything) zero.  Both wavefronts of the same rows write the
     // zeros, so none waits for the other.
@@ -487,8 +485,9 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         f = flags(lo, hi);
         if (!f.full) {
             asm volatile("");
-            odd = __any(hi > 0 && odd_row(0));
+            const int lse = lds_i(a), delta = lds_i(a + GR * 4);
             mask(0);
+            odd = odd_rows(hi, lse, delta);
             if (f.pads) zero_pads(hi, 0);
         }
 #pragma unroll
@@ -606,8 +605,10 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         odd = false;
         if (!f.full) {
             asm volatile("");
-            odd = __any(hi > 0 && odd_row(small_n));
+            const uint32_t a = row_at(small_n);
+            const int lse = lds_i(a), delta = lds_i(a + GR * 4);
             mask(small_n);
+            odd = odd_rows(hi, lse, delta);
             if (f.pads) zero_pads(hi, buf_n);
         }
         buf = buf_n;
