@@ -115,7 +115,9 @@ __device__ __forceinline__ const BwdParams& params_here() {
 // the vector work of one stage spread over the MFMAs that do not depend on it:
 //   dK of the stage before | exponentials of the first 16 rows       dP | exponentials of the other 16
 //   dV | dS       S of the next stage | the copies three stages ahead
-// and each operand is requested three units (of two MFMAs) ahead.  The stage's one barrier lies inside dV, in front of the
+// and each operand is requested three units (of two MFMAs) ahead, right behind a unit's first MFMA: a stream of this mix takes 36 cycles an
+// MFMA so, and 41 with the requests behind the exponentials, which hold LDS requests up (5326 -> 5210 us in the first call below, 2203 ->
+// 2166 in the third; the clock gives back half of the cycles).  The stage's one barrier lies inside dV, in front of the
 // first read of the next stage's tiles.  Per launch, before -> after: 131072 tokens on one of 8 ranks, 8/1 heads 6293 -> 5460 us, at D = 64
 // 4306 -> 3492; 32768 tokens, 32/8 heads 2475 -> 2263; 65536 tokens, 8/8 heads, one of 2 ranks 1262 -> 1158; at 24 - 32 stages a
 // compute unit, where loading K, V and the first stages (7 us) and adding up count as much as the stages, 80 -> 80.
@@ -506,40 +508,49 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
             f32x16 dl;
 #pragma unroll
             for (int u = 0; u < NU; ++u) {          // dK of the stage before
-                ring[(u + 3) & 3] = u + 3 < NU ? rd_col(a_dk, u + 3, 0) : rd_row(a_row, u + 3 - NU, TILEB);
-                if (u < 2) ls[2 + u] = lds_f4(a_s + (2 + u) * 32);
-                if (u >= NU - 4) {
-                    const int g8 = u - (NU - 4);
-                    const f32x4 x = lds_f4(a_s + GR * 4 + g8 * 32);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) dl[g8 * 4 + e] = x[e];
-                }
-                fence();
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     acc_mfma(ACC_DK + i * DB + u % DB, ring[u & 3], ds[i][u / DB]);
+                    fence();
+                    if (i == 0) {
+                        ring[(u + 3) & 3] = u + 3 < NU ? rd_col(a_dk, u + 3, 0) : rd_row(a_row, u + 3 - NU, TILEB);
+                        if (u < 2) ls[2 + u] = lds_f4(a_s + (2 + u) * 32);
+                        if (u >= NU - 4) {
+                            const int g8 = u - (NU - 4);
+                            const f32x4 x = lds_f4(a_s + GR * 4 + g8 * 32);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) dl[g8 * 4 + e] = x[e];
+                        }
+                        fence();
+                    }
                     exp_slot(0, 2 * u + i);
                     fence();
                 }
             }
 #pragma unroll
             for (int u = 0; u < NU; ++u) {          // dP - delta
-                ring[(u + 3) & 3] = u + 3 < NU ? rd_row(a_row, u + 3, TILEB) : rd_col(a_col, u + 3 - NU, TILEB);
-                fence();
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     dp[i] = mfma32(ring[u & 3], vop[i][u], u == 0 ? dl : dp[i]);
+                    fence();
+                    if (i == 0) {
+                        ring[(u + 3) & 3] = u + 3 < NU ? rd_row(a_row, u + 3, TILEB) : rd_col(a_col, u + 3 - NU, TILEB);
+                        fence();
+                    }
                     exp_slot(1, 2 * u + i);
                     fence();
                 }
             }
 #pragma unroll
             for (int u = 0; u < SY; ++u) {          // dV, first part
-                ring[(u + 3) & 3] = rd_col(a_col, u + 3, TILEB);
-                fence();
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     acc_mfma(ACC_DV + i * DB + u % DB, ring[u & 3], pk[i][u / DB]);
+                    fence();
+                    if (i == 0) {
+                        ring[(u + 3) & 3] = rd_col(a_col, u + 3, TILEB);
+                        fence();
+                    }
                     ds_slot(2 * u + i);
                     fence();
                 }
@@ -575,13 +586,18 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         }
 #pragma unroll
         for (int u = SY; u < NU; ++u) {             // dV, second part
-            ring[(u + 3) & 3] = u + 3 < NU ? rd_col(a_col, u + 3, TILEB) : rd_row(a_row, u + 3 - NU, 0);
-            fence();
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 acc_mfma(ACC_DV + i * DB + u % DB, ring[u & 3], pk[i][u / DB]);
+                fence();
+                if (i == 0) {
+                    ring[(u + 3) & 3] = u + 3 < NU ? rd_col(a_col, u + 3, TILEB) : rd_row(a_row, u + 3 - NU, 0);
+                    fence();
+                } else {
+                    issue_at(u - SY);                 // the copies of the stage after the next two, a piece per unit
+                    fence();
+                }
                 ds_slot(2 * u + i);
-                if (i == 0) issue_at(u - SY);         // the copies of the stage after the next two, a piece per unit
                 fence();
             }
         }
@@ -590,13 +606,14 @@ __global__ void __launch_bounds__(256, 1) dkv_kernel(const BwdParams args) {
         const uint32_t a_sn = vals_at(small_n);
 #pragma unroll
         for (int u = 0; u < NU; ++u) {              // the next stage's scores (after the last stage: of zeros, not used)
-            ring[(u + 3) & 3] = u + 3 < NU ? rd_row(a_row, u + 3, 0) : rd_col(a_dk, u + 3 - NU, 0);
-            if (u == 1 || u == 2) ls[u - 1] = lds_f4(a_sn + (u - 1) * 32);
-            fence();
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 s[i] = mfma32(ring[u & 3], kop[i][u], u == 0 ? zero16 : s[i]);
-                if (i == 0 && u + (NU - SY) < PIECES) issue_at(u + (NU - SY));
+                fence();
+                if (i == 0) {
+                    ring[(u + 3) & 3] = u + 3 < NU ? rd_row(a_row, u + 3, 0) : rd_col(a_dk, u + 3 - NU, 0);
+                    if (u == 1 || u == 2) ls[u - 1] = lds_f4(a_sn + (u - 1) * 32);
+                } else if (u + (NU - SY) < PIECES) issue_at(u + (NU - SY));
                 fence();
             }
         }
