@@ -115,16 +115,16 @@ __device__ __forceinline__ void dq_piece(const BwdParams& p, char* smem, const R
     const int row = tile * BM + wave * 32 + l32;
     const bool in = row < p.n_q;
     const int rc = in ? row : p.n_q - 1;
-    const int lo = in ? p.row_lo[rc] : kPadLo;
-    const int hi = in ? p.row_hi[rc] : 0;
+    const int row_lo[1] = {in ? p.row_lo[rc] : kPadLo}, row_hi[1] = {in ? p.row_hi[rc] : 0};
+    const int lo = row_lo[0], hi = row_hi[0];
     const bool real = hi > 0;
     // key tiles this wavefront needs no element-wise mask for: only outside [fb, fe) it masks.  Inside, the
     // rows of the wavefront's first document see every key and the rows of later documents none.
-    bool other_doc;
-    unmasked_tiles<BN>(lo, hi, real, fb, fe, other_doc);
+    bool other_doc[1];
+    unmasked_tiles<BN>(row_lo, row_hi, fb, fe, other_doc);
     // padding rows: zero operands and LSE = +inf make P, dS and dQ exactly 0
     const float lsec = real ? p.lse[(size_t)h * p.n_q + rc] * 1.4426950408889634f : INFINITY;
-    float lsec_unmasked = other_doc ? INFINITY : lsec;           // inside [fb, fe): +inf switches the lane off
+    float lsec_unmasked = other_doc[0] ? INFINITY : lsec;           // inside [fb, fe): +inf switches the lane off
     float dl = 0.f;                    // -delta
     bf16x8 qf[KS], dof[KS];
     {

@@ -17,25 +17,11 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "wlb_attn_fwd.h"
 #include "wlb_device.h"
 #include "wlb_internal.h"
 
 namespace wlb {
-
-struct FwdParams {
-    const __bf16* q; const __bf16* k; const __bf16* v;
-    __bf16* o; float* lse;
-    const int32_t* row_lo; const int32_t* row_hi;
-    RowSched sched;            // which query tiles, heads and key ranges a workgroup works on
-    float* partial;            // partial results of the tiles cut at a gang boundary
-    const int32_t* row_item;   // one workgroup per item: records (PlanLayout::off_row_item, or off_row_part with row_part_base)
-    const int32_t* row_part_base;     // null: whole tiles only
-    int first_half;                   // see paired_index
-    const int32_t* block_hull;   // short-hull path (see fwd_short_unit)
-    unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of a gang kernel's workgroup
-    int n_q, t_kv, hq, hkv, n_tiles, n_blocks32, use_short;
-    float scale_log2e, scale;
-};
 
 // One piece of work: the 64-key tiles [pc.jb, pc.je) of those the query tile pc.tile sees, for query head
 // pc.hk * G + pc.member.  A whole tile (pc.slot < 0) writes O and LSE; a part writes its
@@ -77,14 +63,15 @@ __device__ __forceinline__ void fwd_piece(const FwdParams& p, char* smem, const 
     const int row = tile * BM + wave * 32 + l32;
     const bool in = row < p.n_q;
     const int rc = in ? row : p.n_q - 1;
-    const int lo = in ? p.row_lo[rc] : kPadLo;
-    const int hi = in ? p.row_hi[rc] : 0;
+    const int row_lo[1] = {in ? p.row_lo[rc] : kPadLo}, row_hi[1] = {in ? p.row_hi[rc] : 0};
+    const int lo = row_lo[0], hi = row_hi[0];
     // Key tiles this wavefront needs no element-wise mask for: only outside [fb, fe) does it mask.  Inside,
     // the rows of the wavefront's first document see every key; rows of later documents in the same
     // wavefront (a tile that straddles a document boundary has one such wavefront) see none of them and
     // stay switched off as whole lanes until the range ends (`parked`).
-    bool parked;
-    unmasked_tiles<BN>(lo, hi, hi > 0, fb, fe, parked);
+    bool other_doc[1];
+    unmasked_tiles<BN>(row_lo, row_hi, fb, fe, other_doc);
+    bool parked = other_doc[0];
     bf16x8 qf[KS];
     {
         const __bf16* qp = p.q + ((size_t)rc * p.hq + h) * D + half * 8;
@@ -679,9 +666,15 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.gang_clock = (unsigned long long*)(ws + L.off_gang_clock);
     p.scale = d.scale;
     p.scale_log2e = d.scale * 1.4426950408889634f;
-    if (use_row_gangs(d, L)) {
+    const bool gangs = use_row_gangs(d, L), pairs = use_row_pairs(d, L);
+    if (gangs && pairs) pair_weights(p.sched.weight);
+    if (gangs) {
         const unsigned grid = (unsigned)L.row_gangs * (unsigned)(d.hq / d.hkv);
-        if (d.head_dim == 128) {
+        if (pairs) {
+            launch_fwd_pair(p, d.head_dim, true, grid / 2, stream);
+            if (d.head_dim == 128) fwd_merge_kernel<128><<<grid * kGangMergeSplit, 256, 0, stream>>>(p);
+            else fwd_merge_kernel<64><<<grid * kGangMergeSplit, 256, 0, stream>>>(p);
+        } else if (d.head_dim == 128) {
             fwd_kernel<128><<<grid, 256, 0, stream>>>(p);
             fwd_merge_kernel<128><<<grid * kGangMergeSplit, 256, 0, stream>>>(p);
         } else {
@@ -692,7 +685,9 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
         const int items = L.n_fwd_tiles + (parts ? row_parts_added(d, L) : 0);
         const unsigned grid = (unsigned)((items + 7) / 8) * 8u * (unsigned)d.hq;
         const unsigned grid_merge = (unsigned)row_tiles_divided(d, L) * (unsigned)d.hq * kMergeSplit;
-        if (d.head_dim == 128) {
+        if (pairs) {
+            launch_fwd_pair(p, d.head_dim, false, grid / 2, stream);       // (no parts)
+        } else if (d.head_dim == 128) {
             fwd_items_kernel<128><<<grid, 256, 0, stream>>>(p);
             if (parts) fwd_merge_parts_kernel<128><<<grid_merge, 256, 0, stream>>>(p);
         } else {

@@ -134,10 +134,12 @@ struct RowPiece {
 struct RowWalk {
     long long pos, end;
     int r, hk, gang, member;
-    __device__ __forceinline__ void start(const RowSched& s, int block) {
+    __device__ __forceinline__ void start(const RowSched& s, int block) { start(s, block, s.G); }
+    // members: workgroups to a gang
+    __device__ __forceinline__ void start(const RowSched& s, int block, int members) {
         const int x = block & 7, i = block >> 3;
-        member = i % s.G;
-        gang = (i / s.G) * 8 + x;
+        member = i % members;
+        gang = (i / members) * 8 + x;
         const long long W = s.hkv * ld_const64(s.prefix + s.n_tiles);
         pos = s.share_begin(W, gang);
         end = s.share_begin(W, gang + 1);
@@ -400,28 +402,36 @@ struct RowBlock {
 
 constexpr int kPadLo = 0x7fffffff;  // row_lo of a padding row (row_hi = 0): no key satisfies lo <= k < hi
 
-// Key tiles (of BN keys) a wavefront of 32 rows needs no element-wise mask for.  The rows are split by the
+// Key tiles (of BN keys) a wavefront of 32 N rows needs no element-wise mask for.  The rows are split by the
 // start of their key interval [lo, hi): the rows that share the smallest start (the first document in the
 // wavefront) see every key of the tiles [fb, fe); the other real rows (`other`: rows of later documents
 // that share the wavefront) see none of them and are switched off as whole lanes there.  A wavefront of one
 // document gets the range all its rows see in full and no lane with `other` set; neither does one whose
 // range is empty.  Both halves of the
-// wavefront hold the same 32 rows, so the reductions run over the 32 lanes of a half.
-template <int BN>
-__device__ __forceinline__ void unmasked_tiles(int lo, int hi, bool real, int& fb, int& fe, bool& other) {
-    int lo_min = real ? lo : kPadLo;
+// wavefront hold the same rows (N of them in a lane), so the reductions run over the 32 lanes of a half.
+template <int BN, int N>
+__device__ __forceinline__ void unmasked_tiles(const int (&lo)[N], const int (&hi)[N], int& fb, int& fe, bool (&other)[N]) {
+    int lo_min = kPadLo, end = kPadLo;
+#pragma unroll
+    for (int i = 0; i < N; ++i) lo_min = min(lo_min, hi[i] > 0 ? lo[i] : kPadLo);
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) lo_min = min(lo_min, __shfl_xor(lo_min, o));
-    const bool first = real && lo == lo_min;
-    other = real && !first;
-    int end = first ? hi : (other ? lo : kPadLo);      // the range ends where a first-document row stops seeing keys
-#pragma unroll                                         // or another document's keys begin
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const bool real = hi[i] > 0, first = real && lo[i] == lo_min;
+        other[i] = real && !first;
+        end = min(end, first ? hi[i] : (other[i] ? lo[i] : kPadLo));      // the range ends where a first-document row stops seeing keys
+    }                                                                     // or another document's keys begin
+#pragma unroll
     for (int o = 16; o > 0; o >>= 1) end = min(end, __shfl_xor(end, o));
     const int b = lo_min == kPadLo ? 0 : (lo_min + BN - 1) / BN;
     const int e = end == kPadLo ? 0 : end / BN;
     fb = __builtin_amdgcn_readfirstlane(b);
     fe = __builtin_amdgcn_readfirstlane(e < b ? b : e);
-    if (fe == fb) other = false;       // no such tile: every block is classified on its own
+    if (fe == fb) {                    // no such tile: every block is classified on its own
+#pragma unroll
+        for (int i = 0; i < N; ++i) other[i] = false;
+    }
 }
 
 }  // namespace wlb

@@ -75,6 +75,17 @@ bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L) {
     return items * mean_item_units(d, L) >= (long long)kRowGangMinUnitsPerSlot * slots;
 }
 
+bool use_row_pairs(const wlb_attn_desc& d, const PlanLayout& L) {
+    if ((d.hq / d.hkv) % 2 != 0) return false;
+    const long long items = (long long)L.n_fwd_tiles * d.hq, slots = 2LL * compute_units(), units = mean_item_units(d, L);
+    if (use_row_gangs(d, L)) return items * units >= (long long)kRowPairMinUnitsPerSlot * slots;
+    return d.head_dim == 128 && items >= (long long)kRowGangMaxItemsPerSlot * slots && units >= kRowPairMinItemUnits;
+}
+
+void pair_weights(int (&weight)[2][8]) {
+    for (int x = 0; x < 8; ++x) weight[0][x] = weight[1][x] = weight[0][x] + weight[1][x];
+}
+
 // Parts of tiles, in launches with few items per slot whose shares are too short for the gangs (kRowPartMeanUnits,
 // kRowPartKeys).
 bool use_row_parts(const wlb_attn_desc& d, const PlanLayout& L) {

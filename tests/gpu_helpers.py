@@ -66,7 +66,7 @@ class Case:
     the library writes (O, LSE, dQ, dK, dV, the workspace) sits between guard bands that are checked
     after each call."""
 
-    def __init__(self, tens, q_idx, cu_k, hq, hkv, d, scale, device="cuda:0"):
+    def __init__(self, tens, q_idx, cu_k, hq, hkv, d, scale, device="cuda:0", visible_pairs=0):
         import torch
         self.torch = torch
         self.q_idx = np.asarray(q_idx, dtype=np.int32)
@@ -78,7 +78,7 @@ class Case:
         if "do" in tens:
             self.bits["do"] = gather_rows(tens["do"], self.q_idx)
         self.dev = {n: B.bf16_bits_to_tensor(a, device) for n, a in self.bits.items()}
-        self.attn = B.Attention(self.q_idx, self.cu_k, self.t_kv, hq, hkv, d, scale, device)
+        self.attn = B.Attention(self.q_idx, self.cu_k, self.t_kv, hq, hkv, d, scale, device, visible_pairs)
         self.flags = 0          # extra descriptor flags for every call (e.g. a forced work schedule)
         n_q = len(self.q_idx)
         bf, f32, u8 = torch.bfloat16, torch.float32, torch.uint8

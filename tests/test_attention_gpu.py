@@ -348,6 +348,33 @@ def test_query_tiles_stay_whole_where_the_launch_is_balanced(docs, hq, hkv, cp, 
     assert (t["row_part_base"][:-1, 1].max() > 1) == divided
 
 
+@pytest.mark.parametrize("hq,hkv,d,cp,rank,mode,docs", [
+    # shares of a gang: tiles cut anywhere, pieces of a few keys, a last tile of 5 rows, padding, two heads and eight to a KV head
+    (8, 1, 128, 2, 1, osh.PER_DOC_PADDED, [2600, 1, 37, 900, 130, 64, 705]),
+    (4, 2, 128, 1, 0, osh.PER_DOC_PADDED, [1, 128, 129, 63, 1000, 2, 700]),
+    (8, 1, 64, 2, 0, osh.PER_DOC_NOPAD, [2600, 1, 37, 900, 130, 64, 705]),
+    (6, 1, 64, 1, 0, osh.PER_DOC_PADDED, [300]),
+    # items: 1536 and more
+    (64, 2, 128, 1, 0, osh.PER_DOC_PADDED, [5, 1500, 64, 31, 1, 33, 90, 1349]),
+    (128, 64, 128, 4, 3, osh.PER_DOC_PADDED, [3, 4000, 1700, 7, 290])])
+def test_forward_of_two_heads_to_a_workgroup(hq, hkv, d, cp, rank, mode, docs):
+    """Launches that take two query heads to a workgroup (chosen by the pair count that the caller states, here far more than there are)."""
+    w, tens = wl.small_case(91, docs, hq, hkv, d)
+    sh = osh.shard(docs, cp, rank, mode)
+    c = Case(tens, sh["q_idx"], sh["cu_seqlens_k"], hq, hkv, d, w.scale, visible_pairs=10 ** 12)
+    lay = B.wlb_attn_plan_layout(c.attn.desc)
+    assert bool(lay.uses_gangs) == (hq < 64)
+    c.check_fwd(f" pairs {hq}/{hkv} d{d}")
+    # a maximum that rises along the keys, so that what is accumulated is rescaled again and again
+    ramp = c.torch.linspace(0.2, 4.0, c.t_kv, device="cuda")[:, None, None]
+    q0, k0 = c.dev["q"], c.dev["k"]
+    c.dev["k"] = (k0.float().abs() * ramp).bfloat16()
+    c.dev["q"] = (q0.float().abs() * 3).bfloat16()
+    for name in ("q", "k"):
+        c.bits[name] = c.dev[name].view(c.torch.int16).cpu().numpy().view(np.uint16)
+    c.check_fwd(f" rising maxima {hq}/{hkv} d{d}")
+
+
 def test_gang_share_weights_change_the_cuts_not_the_result():
     """wlb_attn_set_gang_weights: very uneven weights (by half of the launch and by XCD) move the points where
     query tiles are cut between gangs; the results still match the oracle, and the defaults come back."""
