@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libwlb.so")
-SOURCES = ["wlb_host.cpp", "wlb_plan.hip", "wlb_attn_fwd.hip", "wlb_attn_fwd_pair.hip", "wlb_attn_bwd.hip", "wlb_attn_dkv.hip", "wlb_calib.hip"]
+SOURCES = ["wlb_host.cpp", "wlb_plan.hip", "wlb_attn_fwd.hip", "wlb_attn_fwd_pair.hip", "wlb_attn_bwd.hip", "wlb_attn_dq_pair.hip", "wlb_attn_dkv.hip", "wlb_calib.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -26,7 +26,7 @@ FLAGS = [
 
 
 # Sources whose kernels use the accumulation registers by number, in statements marked "; acc"
-OWN_ACC_REGISTERS = ["wlb_attn_dkv.hip", "wlb_attn_fwd_pair.hip"]
+OWN_ACC_REGISTERS = ["wlb_attn_dkv.hip", "wlb_attn_fwd_pair.hip", "wlb_attn_dq_pair.hip"]
 
 
 def check_acc_registers(asm: str) -> None:
@@ -67,6 +67,8 @@ def _wait_states(producer: tuple, consumer: tuple) -> int:
         return set().union(*(_registers(x, kind) for x in written)) & set().union(*(_registers(x, kind) for x in reads))
 
     if op.startswith("v_mfma"):
+        if use.startswith("v_mfma") and src[-1] == src[0] == dst[0]:
+            src = src[:-1]          # the sum that the next MFMA continues: the hardware orders it
         return _MFMA_RESULT if both("v", dst[:1]) or not use.startswith("v_mfma") and both("a", dst[:1]) else 0
     written = dst[:2] if re.search(r"_co_|_swap|div_scale|mad_[ui]64", op) else dst[:1]
     if op.startswith("v_cmp") and len(dst) == 2:

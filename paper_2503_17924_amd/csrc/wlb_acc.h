@@ -110,6 +110,11 @@ __device__ __forceinline__ void acc_scale(float f) {
     float x;
     asm volatile("v_accvgpr_read_b32 %0, a[%2] ; acc\n\tv_mul_f32 %0, %0, %1\n\tv_accvgpr_write_b32 a[%2], %0 ; acc" : "=&v"(x) : "v"(f), "n"(N) : WLB_ACC_ALL);
 }
+// in front of the first MFMA that reads it by some instructions
+template <int N>
+__device__ __forceinline__ void acc_write(uint32_t x) {
+    asm volatile("v_accvgpr_write_b32 a[%0], %1 ; acc" ::"n"(N), "v"(x) : WLB_ACC_ALL);
+}
 __device__ __forceinline__ void acc_written() { asm volatile("s_nop 3" ::: "memory"); }
 
 // Tiles of rows x D that operands are read from both row-wise and transposed lie in LDS as blocks of 1 KiB: 8 rows x 64 columns, block

@@ -26,6 +26,9 @@ struct BwdParams {
     float scale_log2e, scale;
 };
 
+// dQ with two query heads of a KV head to a workgroup (wlb_attn_dq_pair.hip); hq / hkv is even, head dimension 128.
+void launch_dq_pair(const BwdParams& p, bool gangs, unsigned grid, hipStream_t stream);
+
 // The dK/dV launch (wlb_attn_dkv.hip).
 void launch_dkv_general(const BwdParams& p, int head_dim, bool beside_short, unsigned grid, hipStream_t stream);
 

@@ -13,6 +13,7 @@
 //                     kernel starts its dP accumulators from it) and leaves it and a log2-scaled LSE
 //                     copy (0 / +inf for padding rows) for the dK/dV kernel, which runs after it
 //   delta_kernel      the same for a call that leaves dQ out (WLB_ATTN_BWD_SKIP_DQ)
+//   dq_pair_kernel    (wlb_attn_dq_pair.hip) the same for two query heads at a time, in launches of long items
 //   dq_merge_kernel   sums the fp32 partial dQ of query tiles cut at a gang boundary
 //   dkv_kernel        (wlb_attn_dkv.hip) key-stationary: a work item owns 128 keys of one KV head and streams the row
 //                     groups that can see them through LDS for some or all query heads of the KV
@@ -579,6 +580,26 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
     dq_piece<D>(p, smem, pc);
 }
 
+// The short-hull tiles of a launch whose other tiles dq_pair_items_kernel takes.  There may be none, so 64 of a workgroup's units are looked at
+// together: (order rank, KV head, block of 32 rows), a launch's workgroups one after another.
+template <int D>
+__global__ void __launch_bounds__(256, 2) dq_short_tiles_kernel(const BwdParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[ShortDq<D>::LDS_BYTES];
+    constexpr int per_tile = kFwdTileRows / kShortBlockRows;
+    const int n = p.n_tiles * p.hkv * per_tile, step = (int)gridDim.x, lane = threadIdx.x & 63;
+    for (int u0 = (int)blockIdx.x; u0 < n; u0 += 64 * step) {
+        const int u = min(u0 + lane * step, n - 1), rank = u / (p.hkv * per_tile);
+        const int tile = p.row_item[4 * rank], code = p.row_item[4 * rank + 3];
+        const int blk = tile * per_tile + u % per_tile;
+        unsigned long long todo = __ballot(u0 + lane * step < n && code == -2 && blk < p.n_blocks32);
+        while (todo) {
+            const int i = __ffsll(todo) - 1;
+            todo &= todo - 1;
+            dq_short_unit<D>(p, smem, __builtin_amdgcn_readlane(blk, i), __builtin_amdgcn_readlane(u / per_tile % p.hkv, i));
+        }
+    }
+}
+
 // dQ rows of 1 / SPLIT of a query tile and head; sum_of(offset) adds up the four elements at an offset of the tile's partial results.
 template <int D, int SPLIT, class SumOf>
 __device__ __forceinline__ void dq_merge_rows(const BwdParams& p, int tile, int h, int which, SumOf sum_of) {
@@ -964,7 +985,8 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     const unsigned grid_dq = (unsigned)L.row_gangs * (unsigned)(d.hq / d.hkv);
     const unsigned grid_dq_items = (unsigned)((L.n_fwd_tiles + (parts ? row_parts_added(d, L) : 0) + 7) / 8) * 8u * (unsigned)d.hq;
     const unsigned grid_dq_parts = (unsigned)row_tiles_divided(d, L) * (unsigned)d.hq * kMergeSplit;
-    const bool gangs = use_row_gangs(d, L);
+    const bool gangs = use_row_gangs(d, L), pairs = use_row_pairs(d, L) && d.head_dim == 128;     // (64: 2546 and 2527 us as gangs)
+    if (gangs && pairs) pair_weights(p.sched.weight);
     // one workgroup per compute unit, each taking item after item
     const unsigned grid_dkv = (unsigned)std::min(L.dkv_max_items, compute_units());   // one workgroup per compute unit, each taking item after item
     const unsigned grid_fix = (unsigned)(L.n_key_tiles * d.hkv);
@@ -976,8 +998,12 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     auto run = [&](auto dtag) {
         constexpr int D = decltype(dtag)::value;
         if (do_dq && gangs) {
-            dq_kernel<D><<<grid_dq, 256, 0, stream>>>(p);
+            if (pairs) launch_dq_pair(p, true, grid_dq / 2, stream);
+            else dq_kernel<D><<<grid_dq, 256, 0, stream>>>(p);
             dq_merge_kernel<D><<<grid_dq * kGangMergeSplit, 256, 0, stream>>>(p);
+        } else if (do_dq && pairs) {
+            launch_dq_pair(p, false, grid_dq_items / 2, stream);           // (no parts)
+            if (p.use_short) dq_short_tiles_kernel<D><<<2 * compute_units(), 256, 0, stream>>>(p);
         } else if (do_dq) {
             dq_items_kernel<D><<<grid_dq_items, 256, 0, stream>>>(p);
             if (parts) dq_merge_parts_kernel<D><<<grid_dq_parts, 256, 0, stream>>>(p);

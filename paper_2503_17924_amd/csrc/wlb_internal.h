@@ -112,12 +112,13 @@ constexpr int kRowGangMinUnitsPerSlot = 64;
 constexpr int kRowPartKeys = 704, kRowPartReach = 224;
 constexpr int kRowPartMeanUnits = 24;
 bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L);
-// Whether the forward takes two query heads to a workgroup, one workgroup to a compute unit (wlb_attn_fwd_pair.hip).  Its loop is faster (3 - 7 %),
-// but nothing runs beside the start and the end of an item, so items must be long: head dimension 128, at
-// least as many items as keep gangs away, and kRowPairMinItemUnits on average (old / new at 34 - 73 units 1.02 - 1.07, at 20 - 26 0.99 - 1.05,
-// at 13 0.88 - 1.0; at head dimension 64 0.80 - 0.93 up to 58 units).  Or shares of kRowPairMinUnitsPerSlot units in a gang launch (both head
-// dimensions): a share's fixed part and the rows of short documents weigh more than in launches of two workgroups (1620 units: 1.06 and 1.035 at
-// head dimension 64; 650: 0.96 - 0.995; 70 - 300: 0.73 - 0.99).
+// Whether forward and dQ take two query heads to a workgroup, one workgroup to a compute unit (wlb_attn_fwd_pair.hip, wlb_attn_dq_pair.hip).  Their
+// loops are faster (3 - 11 %), but nothing runs beside the start and the end of an item, so items must be long: head dimension 128, at
+// least as many items as keep gangs away, and kRowPairMinItemUnits on average (forward, old / new at 34 - 73 units 1.02 - 1.07, at 20 - 26 0.99 - 1.05,
+// at 13 0.88 - 1.0; at head dimension 64 0.80 - 0.93 up to 58 units; dQ at 33 - 58 units 1.025 - 1.08, at 20 - 26 0.98 - 1.08, at 13
+// 0.92 - 0.98).  Or shares of kRowPairMinUnitsPerSlot units in a gang launch: a share's fixed part and the rows of short documents weigh more than in
+// launches of two workgroups (1620 units: forward 1.06, at head dimension 64 1.035, dQ 1.08 and 1.01; 650: 0.96 - 0.995 and 0.93 - 0.98; 70 - 300:
+// 0.73 - 0.99 and 0.85 - 0.99).
 constexpr int kRowPairMinItemUnits = 30, kRowPairMinUnitsPerSlot = 1000;
 bool use_row_pairs(const wlb_attn_desc& d, const PlanLayout& L);
 // share weights of its gangs: with one workgroup to a compute unit no half of the launch is slower than the other
