@@ -580,24 +580,11 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
     dq_piece<D>(p, smem, pc);
 }
 
-// The short-hull tiles of a launch whose other tiles dq_pair_items_kernel takes.  There may be none, so 64 of a workgroup's units are looked at
-// together: (order rank, KV head, block of 32 rows), a launch's workgroups one after another.
+// The short-hull tiles of a launch whose other tiles dq_pair_items_kernel takes.
 template <int D>
 __global__ void __launch_bounds__(256, 2) dq_short_tiles_kernel(const BwdParams p) {
     __shared__ __attribute__((aligned(1024))) char smem[ShortDq<D>::LDS_BYTES];
-    constexpr int per_tile = kFwdTileRows / kShortBlockRows;
-    const int n = p.n_tiles * p.hkv * per_tile, step = (int)gridDim.x, lane = threadIdx.x & 63;
-    for (int u0 = (int)blockIdx.x; u0 < n; u0 += 64 * step) {
-        const int u = min(u0 + lane * step, n - 1), rank = u / (p.hkv * per_tile);
-        const int tile = p.row_item[4 * rank], code = p.row_item[4 * rank + 3];
-        const int blk = tile * per_tile + u % per_tile;
-        unsigned long long todo = __ballot(u0 + lane * step < n && code == -2 && blk < p.n_blocks32);
-        while (todo) {
-            const int i = __ffsll(todo) - 1;
-            todo &= todo - 1;
-            dq_short_unit<D>(p, smem, __builtin_amdgcn_readlane(blk, i), __builtin_amdgcn_readlane(u / per_tile % p.hkv, i));
-        }
-    }
+    for_short_tiles(p.row_item, p.n_tiles, p.hkv, p.n_blocks32, [&](int blk, int hk) __attribute__((always_inline)) { dq_short_unit<D>(p, smem, blk, hk); });
 }
 
 // dQ rows of 1 / SPLIT of a query tile and head; sum_of(offset) adds up the four elements at an offset of the tile's partial results.

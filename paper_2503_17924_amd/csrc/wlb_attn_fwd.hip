@@ -550,6 +550,13 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
     fwd_piece<D>(p, smem, pc);
 }
 
+// The short-hull tiles of a launch whose other tiles fwd_pair_items_kernel takes.
+template <int D>
+__global__ void __launch_bounds__(256, 2) fwd_short_tiles_kernel(const FwdParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[ShortTile<D>::LDS_BYTES];
+    for_short_tiles(p.row_item, p.n_tiles, p.hkv, p.n_blocks32, [&](int blk, int hk) __attribute__((always_inline)) { fwd_short_unit<D>(p, smem, blk, hk); });
+}
+
 // Combines the partial results of a query tile that was cut at gang boundaries.  One workgroup per
 // (gang, member): it acts if its gang's last piece is the first part of a tile, and then takes
 // that part and the following gangs' first pieces.  With reference exponents e_i (log2 units), row
@@ -686,7 +693,8 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
         const unsigned grid = (unsigned)((items + 7) / 8) * 8u * (unsigned)d.hq;
         const unsigned grid_merge = (unsigned)row_tiles_divided(d, L) * (unsigned)d.hq * kMergeSplit;
         if (pairs) {
-            launch_fwd_pair(p, d.head_dim, false, grid / 2, stream);       // (no parts)
+            launch_fwd_pair(p, d.head_dim, false, grid / 2, stream);       // (no parts, head dimension 128)
+            if (p.use_short) fwd_short_tiles_kernel<128><<<2 * compute_units(), 256, 0, stream>>>(p);
         } else if (d.head_dim == 128) {
             fwd_items_kernel<128><<<grid, 256, 0, stream>>>(p);
             if (parts) fwd_merge_parts_kernel<128><<<grid_merge, 256, 0, stream>>>(p);

@@ -400,6 +400,24 @@ struct RowBlock {
     }
 };
 
+// The short-hull tiles of a launch whose other tiles another kernel takes: f(block of 32 rows, KV head).  There may be none, so 64 of a
+// workgroup's units are looked at together: (order rank, KV head, block of 32 rows), a launch's workgroups one after another.
+template <class F>
+__device__ __forceinline__ void for_short_tiles(const int32_t* row_item, int n_tiles, int hkv, int n_blocks32, F f) {
+    constexpr int per_tile = kFwdTileRows / kShortBlockRows;
+    const int n = n_tiles * hkv * per_tile, step = (int)gridDim.x, lane = threadIdx.x & 63;
+    for (int u0 = (int)blockIdx.x; u0 < n; u0 += 64 * step) {
+        const int u = min(u0 + lane * step, n - 1), rank = u / (hkv * per_tile);
+        const int blk = row_item[4 * rank] * per_tile + u % per_tile;
+        unsigned long long todo = __ballot(u0 + lane * step < n && row_item[4 * rank + 3] == -2 && blk < n_blocks32);
+        while (todo) {
+            const int i = __ffsll(todo) - 1;
+            todo &= todo - 1;
+            f(__builtin_amdgcn_readlane(blk, i), __builtin_amdgcn_readlane(u / per_tile % hkv, i));
+        }
+    }
+}
+
 constexpr int kPadLo = 0x7fffffff;  // row_lo of a padding row (row_hi = 0): no key satisfies lo <= k < hi
 
 // Key tiles (of BN keys) a wavefront of 32 N rows needs no element-wise mask for.  The rows are split by the
