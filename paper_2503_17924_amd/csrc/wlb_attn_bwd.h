@@ -20,6 +20,7 @@ struct BwdParams {
     const int32_t* row_part_base;     // null: whole tiles only
     int first_half;                   // see paired_index
     const int32_t* block_hull;   // short-hull path (see dq_short_unit)
+    const int32_t* tile_short;   // by query tile: a short-hull tile
     unsigned long long* gang_clock;   // [workgroup][2]: real-time counter at the start / end of dq_kernel's workgroup
     int n_blocks32, use_short;
     int n_q, t_kv, hq, hkv, n_groups, n_tiles, n_key_tiles;
@@ -28,6 +29,9 @@ struct BwdParams {
 
 // dQ with two query heads of a KV head to a workgroup (wlb_attn_dq_pair.hip); hq / hkv is even, head dimension 128.
 void launch_dq_pair(const BwdParams& p, bool gangs, unsigned grid, hipStream_t stream);
+
+// Short documents divided among ranks (wlb_attn_span.hip).
+void launch_dq_span(const BwdParams& p, int head_dim, hipStream_t stream);
 
 // The dK/dV launch (wlb_attn_dkv.hip).
 void launch_dkv_general(const BwdParams& p, int head_dim, bool beside_short, unsigned grid, hipStream_t stream);

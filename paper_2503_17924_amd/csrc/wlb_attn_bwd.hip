@@ -580,7 +580,7 @@ __global__ void __launch_bounds__(256, 2) dq_items_kernel(const BwdParams p) {
     dq_piece<D>(p, smem, pc);
 }
 
-// The short-hull tiles of a launch whose other tiles dq_pair_items_kernel takes.
+// The short-hull tiles of a launch whose other tiles dq_pair_items_kernel or dq_span_kernel takes.
 template <int D>
 __global__ void __launch_bounds__(256, 2) dq_short_tiles_kernel(const BwdParams p) {
     __shared__ __attribute__((aligned(1024))) char smem[ShortDq<D>::LDS_BYTES];
@@ -958,6 +958,7 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     gang_weights(1, p.sched.weight);
     p.row_partial = (float*)((char*)p.partial + dkv_partial_bytes(d, L));
     p.block_hull = (const int32_t*)(ws + L.off_block_hull);
+    p.tile_short = (const int32_t*)(ws + L.off_tile_short);
     p.n_blocks32 = L.n_blocks32;
     p.gang_clock = (unsigned long long*)(ws + L.off_gang_clock) + 2 * (size_t)L.row_gangs * (d.hq / d.hkv);
     p.n_q = d.n_q; p.t_kv = d.t_kv; p.hq = d.hq; p.hkv = d.hkv;
@@ -984,13 +985,17 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     const unsigned grid_short = (unsigned)((L.n_key_tiles * d.hkv + kLists - 1) / kLists) * kLists;
     auto run = [&](auto dtag) {
         constexpr int D = decltype(dtag)::value;
-        if (do_dq && gangs) {
+        if (do_dq && use_span(d, L)) {
+            launch_dq_span(p, D, stream);
+            p.row_item = (const int32_t*)(ws + L.off_row_item);
+            dq_short_tiles_kernel<D><<<short_tiles_grid(d, L), 256, 0, stream>>>(p);
+        } else if (do_dq && gangs) {
             if (pairs) launch_dq_pair(p, true, grid_dq / 2, stream);
             else dq_kernel<D><<<grid_dq, 256, 0, stream>>>(p);
             dq_merge_kernel<D><<<grid_dq * kGangMergeSplit, 256, 0, stream>>>(p);
         } else if (do_dq && pairs) {
             launch_dq_pair(p, false, grid_dq_items / 2, stream);           // (no parts)
-            if (p.use_short) dq_short_tiles_kernel<D><<<2 * compute_units(), 256, 0, stream>>>(p);
+            if (p.use_short) dq_short_tiles_kernel<D><<<short_tiles_grid(d, L), 256, 0, stream>>>(p);
         } else if (do_dq) {
             dq_items_kernel<D><<<grid_dq_items, 256, 0, stream>>>(p);
             if (parts) dq_merge_parts_kernel<D><<<grid_dq_parts, 256, 0, stream>>>(p);

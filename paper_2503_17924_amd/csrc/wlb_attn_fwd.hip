@@ -550,7 +550,7 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
     fwd_piece<D>(p, smem, pc);
 }
 
-// The short-hull tiles of a launch whose other tiles fwd_pair_items_kernel takes.
+// The short-hull tiles of a launch whose other tiles fwd_pair_items_kernel or fwd_span_kernel takes.
 template <int D>
 __global__ void __launch_bounds__(256, 2) fwd_short_tiles_kernel(const FwdParams p) {
     __shared__ __attribute__((aligned(1024))) char smem[ShortTile<D>::LDS_BYTES];
@@ -668,6 +668,7 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.n_q = d.n_q; p.t_kv = d.t_kv; p.hq = d.hq; p.hkv = d.hkv;
     p.n_tiles = L.n_fwd_tiles;
     p.block_hull = (const int32_t*)(ws + L.off_block_hull);
+    p.tile_short = (const int32_t*)(ws + L.off_tile_short);
     p.n_blocks32 = L.n_blocks32;
     p.use_short = use_short_path(d, L) ? 1 : 0;
     p.gang_clock = (unsigned long long*)(ws + L.off_gang_clock);
@@ -675,7 +676,12 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     p.scale_log2e = d.scale * 1.4426950408889634f;
     const bool gangs = use_row_gangs(d, L), pairs = use_row_pairs(d, L);
     if (gangs && pairs) pair_weights(p.sched.weight);
-    if (gangs) {
+    if (use_span(d, L)) {
+        launch_fwd_span(p, d.head_dim, stream);
+        p.row_item = (const int32_t*)(ws + L.off_row_item);
+        if (d.head_dim == 128) fwd_short_tiles_kernel<128><<<short_tiles_grid(d, L), 256, 0, stream>>>(p);
+        else fwd_short_tiles_kernel<64><<<short_tiles_grid(d, L), 256, 0, stream>>>(p);
+    } else if (gangs) {
         const unsigned grid = (unsigned)L.row_gangs * (unsigned)(d.hq / d.hkv);
         if (pairs) {
             launch_fwd_pair(p, d.head_dim, true, grid / 2, stream);
@@ -694,7 +700,7 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
         const unsigned grid_merge = (unsigned)row_tiles_divided(d, L) * (unsigned)d.hq * kMergeSplit;
         if (pairs) {
             launch_fwd_pair(p, d.head_dim, false, grid / 2, stream);       // (no parts, head dimension 128)
-            if (p.use_short) fwd_short_tiles_kernel<128><<<2 * compute_units(), 256, 0, stream>>>(p);
+            if (p.use_short) fwd_short_tiles_kernel<128><<<short_tiles_grid(d, L), 256, 0, stream>>>(p);
         } else if (d.head_dim == 128) {
             fwd_items_kernel<128><<<grid, 256, 0, stream>>>(p);
             if (parts) fwd_merge_parts_kernel<128><<<grid_merge, 256, 0, stream>>>(p);

@@ -126,6 +126,19 @@ void pair_weights(int (&weight)[2][8]);
 // whether this launch sends short-hull query tiles to the short-hull kernels (only in the
 // one-workgroup-per-item schedule; WLB_ATTN_NO_SHORT_PATH switches it off)
 bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L);
+// Whether forward and dQ of the tiles that are not short-hull ones run as units that hold the keys of a block of rows in LDS for all heads
+// (wlb_attn_span.hip): the ranks divide documents so that a block of 32 rows spans kSpanMinReach tokens (with 61, one of two ranks, many tiles are
+// short-hull ones, and a second launch for them costs more than the others gain: 0.84 - 1.08 of the whole pass), documents (2 * pairs / rows: the pair
+// count has to be known) are of kSpanMaxLength tokens (old / new of forward and dQ alone at 45 - 207: 1.05 - 1.7), there are four heads or more to a KV head
+// (one: 0.4 - 0.9), and a unit's keys fit two windows or units are enough to fill half of the compute units (4 heads to a KV head, one of 8 ranks
+// of 4096 tokens in documents of 1 - 160, 20 units: 0.82 - 0.95; of 32768, 158 units: 1.3).
+constexpr int kSpanMinReach = 96, kSpanMaxLength = 256, kSpanMaxKeys = 384, kSpanMinUnits = 128;
+bool use_span(const wlb_attn_desc& d, const PlanLayout& L);
+// workgroups of a launch for short-hull tiles alone (for_short_tiles): it may find none
+inline unsigned short_tiles_grid(const wlb_attn_desc& d, const PlanLayout& L) {
+    const int units = L.n_fwd_tiles * d.hkv * (kFwdTileRows / kShortBlockRows), most = 2 * compute_units();
+    return (unsigned)(units < most ? units : most);
+}
 // floats of one partial result of a query tile and head: 128 x D accumulator, then 128 row sums and
 // 128 reference exponents
 inline size_t row_partial_floats(int head_dim) { return (size_t)kFwdTileRows * head_dim + 2 * kFwdTileRows; }

@@ -113,6 +113,14 @@ bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L) {
     return !(d.flags & WLB_ATTN_NO_SHORT_PATH) && !use_row_gangs(d, L);
 }
 
+bool use_span(const wlb_attn_desc& d, const PlanLayout& L) {
+    const int G = d.hq / d.hkv, per = G >= 8 ? 1 : 8 / G;                          // blocks of rows in a unit
+    if (!use_short_path(d, L) || d.visible_pairs <= 0 || per > 2) return false;
+    const long long reach = (long long)kShortBlockRows * d.t_kv / d.n_q, length = 2 * (d.visible_pairs / d.n_q);
+    if (reach < kSpanMinReach || length > kSpanMaxLength) return false;
+    return per * reach + length <= kSpanMaxKeys || (long long)((L.n_blocks32 + per - 1) / per) * d.hkv >= kSpanMinUnits;
+}
+
 bool short_documents(const wlb_attn_desc& d) {
     if ((long long)d.n_docs * kShortMeanDoc < d.t_kv) return false;
     const long long length = d.visible_pairs > 0 ? std::min<long long>(2 * (d.visible_pairs / d.n_q), d.t_kv) : d.t_kv / d.n_docs;

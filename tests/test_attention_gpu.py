@@ -348,6 +348,31 @@ def test_query_tiles_stay_whole_where_the_launch_is_balanced(docs, hq, hkv, cp, 
     assert (t["row_part_base"][:-1, 1].max() > 1) == divided
 
 
+@pytest.mark.parametrize("hq,hkv,d,cp,rank,mode", [
+    (8, 1, 128, 4, 1, osh.PER_DOC_PADDED), (8, 2, 128, 4, 2, osh.PER_DOC_NOPAD), (32, 2, 128, 8, 7, osh.PER_DOC_PADDED), (12, 1, 64, 4, 0, osh.PER_DOC_PADDED),
+    (6, 1, 128, 8, 0, osh.PER_SEQ), (16, 4, 64, 4, 3, osh.PER_DOC_NOPAD), (5, 1, 64, 8, 2, osh.PER_SEQ)])
+@pytest.mark.parametrize("docs", [
+    # (not fewer tokens: the mean error of 2e-3 of the largest element holds for tensors whose largest element is three times the mean
+    # of all; a dK of three rows, each element off by up to three roundings of 2^-9, is at 2.0e-3)
+    [35], [1] * 70, [64, 1, 33, 7, 48] * 9 + [5],
+    [90, 3, 700, 40, 1, 17] + [31] * 40])          # a hull of three windows of keys
+def test_short_documents_divided_among_ranks(hq, hkv, d, cp, rank, mode, docs):
+    """Launches whose units hold the keys of a block of rows for all heads of a KV head (taken with the pair count of short documents)."""
+    if mode == osh.PER_SEQ:
+        docs = docs + [-sum(docs) % (2 * cp)] if sum(docs) % (2 * cp) else docs
+    w, tens = wl.small_case(97, docs, hq, hkv, d)
+    sh = osh.shard(docs, cp, rank, mode)
+    if len(sh["q_idx"]) == 0:
+        pytest.skip("no rows on this rank")
+    c = Case(tens, sh["q_idx"], sh["cu_seqlens_k"], hq, hkv, d, w.scale, visible_pairs=60 * len(sh["q_idx"]))
+    if not (sh["q_idx"] >= 0).any():                   # padding alone
+        o, lse = c.run_fwd()
+        assert (o == 0).all() and np.isneginf(lse).all() and all((x == 0).all() for x in c.run_bwd())
+        return
+    c.check_fwd(f" span {hq}/{hkv} d{d} cp{cp}")
+    c.check_bwd(f" span {hq}/{hkv} d{d} cp{cp}")
+
+
 @pytest.mark.parametrize("hq,hkv,d,cp,rank,mode,docs", [
     # shares of a gang: tiles cut anywhere, pieces of a few keys, a last tile of 5 rows, padding, two heads and eight to a KV head
     (8, 1, 128, 2, 1, osh.PER_DOC_PADDED, [2600, 1, 37, 900, 130, 64, 705]),
