@@ -267,6 +267,12 @@ __global__ void __launch_bounds__(512, 2) fwd_span_kernel(const FwdParams p) {
         const float lt = l + xhalf(l);
         const bool live = t.hi > 0 && lt > 0.f;
         const float inv = live ? 1.0f / lt : 0.f;
+        if (!live) {                      // (0 x V is NaN where V is not finite)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+        }
         t.store_rows(o_buf, h, acc, inv);
         if (t.row >= 0 && t.half == 0) p.lse[(size_t)h * p.n_q + t.row] = live ? m * p.scale + __logf(lt) : -INFINITY;
     });

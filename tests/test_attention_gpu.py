@@ -1064,3 +1064,34 @@ def test_graph_replay_matches_eager_calls(flag):
         step()                                        # eager work between the replays
         for name, x, y in zip(("O", "LSE", "dQ", "dK", "dV"), results(), eager):
             assert torch.equal(x, y), f"{name} differs in the eager call after replay {replay}"
+
+
+@pytest.mark.parametrize("hq,hkv,d,cp,mode,docs,pairs", [
+    # units of short documents on a rank, a padding row in most blocks of 32 rows
+    (8, 1, 128, 4, osh.PER_DOC_PADDED, [61, 33, 7, 48, 21] * 9, 50),
+    (8, 2, 64, 8, osh.PER_DOC_PADDED, [61, 133, 7, 48, 21] * 9, 50),
+])
+def test_padding_rows_are_zero_whatever_lies_beside_them(hq, hkv, d, cp, mode, docs, pairs):
+    """Padding rows that hold NaN and Inf in Q and dO leave everything else as it is; beside keys and values that are not finite, O and dQ of
+    padding are 0 and LSE -inf all the same."""
+    import torch
+    w, tens = wl.small_case(65, docs, hq, hkv, d)
+    sh = osh.shard(docs, cp, 0, mode)
+    q_idx = sh["q_idx"]
+    pad = np.nonzero(q_idx < 0)[0]
+    assert len(pad)
+    c = Case(tens, q_idx, sh["cu_seqlens_k"], hq, hkv, d, w.scale, visible_pairs=pairs * len(q_idx))
+    for name in ("q", "do"):
+        t = c.dev[name].view(dtype=torch.int16)
+        t[pad[0::2]] = 0x7FC0          # NaN
+        t[pad[1::2]] = 0x7F80          # +Inf
+    c.check_fwd()
+    c.check_bwd()
+    for name in ("k", "v"):
+        t = c.dev[name].view(dtype=torch.int16)
+        t[0::7, :, 3] = 0x7F80
+        t[2::7, :, d - 1] = 0x7FC0
+    o, lse = c.run_fwd()
+    dq, _, _ = c.run_bwd()
+    assert (o[pad] == 0).all() and np.isneginf(lse[:, pad]).all()
+    assert (dq[pad] == 0).all()
