@@ -532,13 +532,18 @@ __device__ __forceinline__ void dq_short_unit(const BwdParams& p, char* smem, in
             }
         }
         // dQ rows through the staging tile (Q and dO are in registers by now), stored as whole rows
-        const float f = real ? p.scale : 0.f;
+        if (!real) {                                // (0 x K is NaN where K is not finite)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+        }
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4)
                 *reinterpret_cast<WLB_LDS bf16x4*>((uintptr_t)(stage + l32 * ROWB + swz<CPR>(l32, db * 4 + r4) * 16 + half * 8)) =
-                    pack4(acc[db][r4 * 4 + 0] * f, acc[db][r4 * 4 + 1] * f, acc[db][r4 * 4 + 2] * f, acc[db][r4 * 4 + 3] * f);
+                    pack4(acc[db][r4 * 4 + 0] * p.scale, acc[db][r4 * 4 + 1] * p.scale, acc[db][r4 * 4 + 2] * p.scale, acc[db][r4 * 4 + 3] * p.scale);
         RowBlock<D> dq_rows;
         dq_rows.from_tile(stage, lane);
         dq_rows.store(dq_buf, row_voff, head_soff(hs), q_row_bytes);

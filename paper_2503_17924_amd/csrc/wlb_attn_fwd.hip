@@ -496,6 +496,12 @@ __device__ __forceinline__ void fwd_short_unit(const FwdParams& p, char* smem, i
         const float lt = l + xhalf(l);
         const bool live = real && (lt > 0.f);
         const float inv = live ? 1.0f / lt : 0.f;
+        if (!live) {                                // (0 x V is NaN where V is not finite)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+        }
         // O rows through the staging tile (its Q rows are in registers by now): written in the
         // accumulator's layout, read back and stored as whole rows
 #pragma unroll

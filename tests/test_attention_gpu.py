@@ -1070,6 +1070,9 @@ def test_graph_replay_matches_eager_calls(flag):
     # units of short documents on a rank, a padding row in most blocks of 32 rows
     (8, 1, 128, 4, osh.PER_DOC_PADDED, [61, 33, 7, 48, 21] * 9, 50),
     (8, 2, 64, 8, osh.PER_DOC_PADDED, [61, 133, 7, 48, 21] * 9, 50),
+    # short-hull units
+    (8, 1, 128, 1, osh.PER_DOC_PADDED, [61, 33, 7, 48, 21] * 4, 0),
+    (3, 1, 64, 1, osh.PER_DOC_PADDED, [61, 33, 7, 48, 21] * 4, 0),
 ])
 def test_padding_rows_are_zero_whatever_lies_beside_them(hq, hkv, d, cp, mode, docs, pairs):
     """Padding rows that hold NaN and Inf in Q and dO leave everything else as it is; beside keys and values that are not finite, O and dQ of
@@ -1077,7 +1080,7 @@ def test_padding_rows_are_zero_whatever_lies_beside_them(hq, hkv, d, cp, mode, d
     import torch
     w, tens = wl.small_case(65, docs, hq, hkv, d)
     sh = osh.shard(docs, cp, 0, mode)
-    q_idx = sh["q_idx"]
+    q_idx = sh["q_idx"] if cp > 1 else np.insert(sh["q_idx"], np.arange(0, sum(docs), 11), -1)
     pad = np.nonzero(q_idx < 0)[0]
     assert len(pad)
     c = Case(tens, q_idx, sh["cu_seqlens_k"], hq, hkv, d, w.scale, visible_pairs=pairs * len(q_idx))
