@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "wlb_attn_fwd.h"
+#include "wlb_attn_short.h"
 #include "wlb_device.h"
 #include "wlb_internal.h"
 
@@ -333,191 +334,6 @@ __global__ void __launch_bounds__(256, 2) fwd_kernel(const FwdParams p) {
     }
 }
 
-// Short-hull tiles (documents of a few dozen tokens, where a tile's rows see only the keys next to
-// them: the short-chunk case of paper Section 5.2).  There the general piece of work is bound by
-// latency: per (tile, head) it fetches K/V, waits, and computes a handful of blocks.  A short-hull
-// unit is one block of 32 rows and one KV head, run by a workgroup of the one-workgroup-per-item
-// launch: it copies the (at most 96) keys the block sees into LDS
-// once -- K and V, in one shot -- and its four wavefronts then work independently, one query head
-// each at a time (heads w, w+4, ... of the KV head), with no further barrier.  Per head a wavefront
-// loads its 32 Q rows as whole rows and passes them through a staging tile of its own into the MFMA
-// operand layout (loading the operand straight from global memory would touch 32 rows x 32 bytes per
-// instruction), computes the scores of the up to three 32-key blocks, the exact row maximum, the
-// exponentials and O^T += V^T P^T, and sends O through the staging tile so that it leaves in whole
-// rows as well.  Eight wavefronts per compute unit keep Q loads and O stores in flight; K/V
-// traffic is one LDS fill per 32 rows and KV head instead of one per head.
-template <int D>
-struct ShortTile {
-    static constexpr int KS = D / 16, DB = D / 32, CPR = D / 8, ROWB = D * 2;
-    static constexpr int HULL = kShortHullKeys, NB = HULL / 32, NW = 4;
-    static constexpr int STAGE = kShortBlockRows * ROWB;              // one wavefront's staging tile: 32 rows
-    static constexpr int LDS_BYTES = 2 * HULL * ROWB + NW * STAGE;    // K window | V window | staging tiles
-    static constexpr int RPI = 64 / CPR;                              // rows moved by one 64 x 16-byte instruction
-};
-
-template <int D>
-__device__ __forceinline__ void fwd_short_unit(const FwdParams& p, char* smem, int blk, int hk) {
-    using T = ShortTile<D>;
-    constexpr int NW = T::NW, KS = T::KS, DB = T::DB, CPR = T::CPR, ROWB = T::ROWB, HULL = T::HULL, NB = T::NB;
-    const int G = p.hq / p.hkv;
-    __syncthreads();              // every wavefront has left the LDS of the unit before
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
-    const int l32 = lane & 31, half = lane >> 5;
-    const int j16 = lane & 15, gi = (lane >> 4) & 1;
-    const int h_lo = ld_const(p.block_hull + 2 * blk), h_hi = ld_const(p.block_hull + 2 * blk + 1);
-    const int row0 = blk * kShortBlockRows;
-    const int row = row0 + l32;
-    const bool in = row < p.n_q;
-    const int rc = in ? row : p.n_q - 1;
-    const uint32_t q_row = (uint32_t)p.hq * D;
-
-    const uint32_t q_row_bytes = q_row * 2u;
-    const buf_rsrc_t q_buf = make_buf(p.q, (uint32_t)p.n_q * q_row_bytes), o_buf = make_buf(p.o, (uint32_t)p.n_q * q_row_bytes);
-    const int row_voff = RowBlock<D>::lane_off(lane, q_row_bytes);
-    auto head_soff = [&](int hs) { return uniform((uint32_t)row0 * q_row_bytes + (uint32_t)(hk * G + hs) * ROWB); };
-
-    if (h_hi <= h_lo) {
-        // no real row in this block: O = 0, LSE = -inf for every head of the KV head
-        RowBlock<D> zero;
-#pragma unroll
-        for (int i = 0; i < RowBlock<D>::N; ++i) zero.v[i] = i32x4{0, 0, 0, 0};
-        for (int hs = wave; hs < G; hs += NW) {
-            zero.store(o_buf, row_voff, head_soff(hs), q_row_bytes);
-            if (in && half == 0) p.lse[(size_t)(hk * G + hs) * p.n_q + row] = -INFINITY;
-        }
-        return;
-    }
-    const int kstart = h_lo & ~31;
-    const int nblk = (h_hi - kstart + 31) >> 5;          // 1 .. NB (the schedule marks the tile short only then)
-
-    const uint32_t smem_base = (uint32_t)(uintptr_t)(WLB_LDS char*)smem;
-    const uint32_t stage = uniform(smem_base + 2 * HULL * ROWB + (uint32_t)wave * T::STAGE);
-    const uint32_t kv_row = (uint32_t)p.hkv * D;
-    const uint32_t kv_bytes = ((uint32_t)p.t_kv * kv_row - (uint32_t)hk * D) * 2u;
-    BufRsrc krs, vrs;
-    krs.init(p.k + (size_t)hk * D, kv_bytes);
-    vrs.init(p.v + (size_t)hk * D, kv_bytes);
-    TileDma<D, 32 * NW, NW> dma;                          // wavefront w copies the 32-key block w
-    static_assert(TileDma<D, 32 * NW, NW>::PER * TileDma<D, 32 * NW, NW>::RPI == 32, "one 32-key block per wavefront");
-    dma.init(wave, lane, kv_row);
-    if (wave < nblk) {
-        dma.issue(krs, smem_base, kstart, wave);
-        dma.issue(vrs, smem_base + HULL * ROWB, kstart, wave);
-    }
-
-    const int lo = in ? p.row_lo[rc] : kPadLo;
-    const int hi = in ? p.row_hi[rc] : 0;
-    const bool real = hi > 0;
-
-    int kaddr[KS], vaddr[DB][2];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kaddr[ks] = l32 * ROWB + swz<CPR>(l32, ks * 2 + half) * 16;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int key = t * 8 + half * 4 + (j16 >> 2);
-            const int dch = db * 4 + gi * 2 + ((j16 & 3) >> 1);
-            vaddr[db][t] = smem_base + HULL * ROWB + key * ROWB + swz<CPR>(key, dch) * 16 + (j16 & 1) * 8;
-        }
-    const float cs = p.scale_log2e;
-
-    wait_vmem();
-    __syncthreads();              // the key window is in LDS; from here on the wavefronts do not meet again
-
-#pragma nounroll
-    for (int hs = wave; hs < G; hs += NW) {
-        const int h = hk * G + hs;
-        // this head's Q rows: whole rows into registers, then through the staging tile into the operand layout
-        // (eight wavefronts per compute unit cover each other's load latency)
-        {
-            RowBlock<D> q_rows;
-            q_rows.load(q_buf, row_voff, head_soff(hs), q_row_bytes);
-            q_rows.to_tile(stage, lane);
-        }
-        bf16x8 qf[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const WLB_LDS bf16x8*>((uintptr_t)(stage + kaddr[ks]));
-
-        f32x16 s[NB];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) s[b][r] = -INFINITY;
-            if (b < nblk) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[b][r] = 0.f;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    const bf16x8 a = *reinterpret_cast<const WLB_LDS bf16x8*>((uintptr_t)(smem_base + kaddr[ks] + b * 32 * ROWB));
-                    s[b] = mfma32(a, qf[ks], s[b]);
-                }
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int key = kstart + b * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-                    s[b][r] = (key >= lo && key < hi) ? s[b][r] : -INFINITY;
-                    mx = fmaxf(mx, s[b][r]);
-                }
-            }
-        }
-        mx = fmaxf(mx, xhalf(mx));
-        const float mc = (mx == -INFINITY) ? 0.f : mx * cs;
-        f32x16 acc[DB];
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
-        float l = 0.f;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            if (b < nblk) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float e = fast_exp2(fmaf(s[b][r], cs, -mc));
-                    s[b][r] = e;
-                    l += e;
-                }
-#pragma unroll
-                for (int cc = 0; cc < 2; ++cc) {
-                    const bf16x8 pf = pack8(s[b][8 * cc + 0], s[b][8 * cc + 1], s[b][8 * cc + 2], s[b][8 * cc + 3],
-                                            s[b][8 * cc + 4], s[b][8 * cc + 5], s[b][8 * cc + 6], s[b][8 * cc + 7]);
-#pragma unroll
-                    for (int db = 0; db < DB; ++db) {
-                        const int off = (b * 32 + cc * 16) * ROWB;
-                        const bf16x4 v0 = lds_read_tr4_at(vaddr[db][0] + off);
-                        const bf16x4 v1 = lds_read_tr4_at(vaddr[db][1] + off);
-                        acc[db] = mfma32(cat4(v0, v1), pf, acc[db]);
-                    }
-                }
-            }
-        }
-        const float lt = l + xhalf(l);
-        const bool live = real && (lt > 0.f);
-        const float inv = live ? 1.0f / lt : 0.f;
-        if (!live) {                                // (0 x V is NaN where V is not finite)
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
-        }
-        // O rows through the staging tile (its Q rows are in registers by now): written in the
-        // accumulator's layout, read back and stored as whole rows
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-                *reinterpret_cast<WLB_LDS bf16x4*>((uintptr_t)(stage + l32 * ROWB + swz<CPR>(l32, db * 4 + r4) * 16 + half * 8)) =
-                    pack4(acc[db][r4 * 4 + 0] * inv, acc[db][r4 * 4 + 1] * inv, acc[db][r4 * 4 + 2] * inv, acc[db][r4 * 4 + 3] * inv);
-        RowBlock<D> o_rows;
-        o_rows.from_tile(stage, lane);
-        o_rows.store(o_buf, row_voff, head_soff(hs), q_row_bytes);
-        if (in && half == 0) p.lse[(size_t)h * p.n_q + row] = live ? mx * p.scale + __logf(lt) : -INFINITY;
-        wait_lds();                                 // the staging tile has been read back
-    }
-}
-
 // The other schedule: one workgroup per (query tile in order, query head), dispatched heaviest
 // first.  With many tiles per workgroup slot the hardware's dynamic dispatch balances the load by
 // itself and adapts to whatever makes workgroups differ in speed; the gangs' fixed shares win when
@@ -556,7 +372,7 @@ __global__ void __launch_bounds__(256, 2) fwd_items_kernel(const FwdParams p) {
     fwd_piece<D>(p, smem, pc);
 }
 
-// The short-hull tiles of a launch whose other tiles fwd_pair_items_kernel or fwd_span_kernel takes.
+// The short-hull tiles of a launch whose other tiles fwd_pair_items_kernel takes.
 template <int D>
 __global__ void __launch_bounds__(256, 2) fwd_short_tiles_kernel(const FwdParams p) {
     __shared__ __attribute__((aligned(1024))) char smem[ShortTile<D>::LDS_BYTES];
@@ -684,9 +500,6 @@ wlb_status launch_fwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     if (gangs && pairs) pair_weights(p.sched.weight);
     if (use_span(d, L)) {
         launch_fwd_span(p, d.head_dim, stream);
-        p.row_item = (const int32_t*)(ws + L.off_row_item);
-        if (d.head_dim == 128) fwd_short_tiles_kernel<128><<<short_tiles_grid(d, L), 256, 0, stream>>>(p);
-        else fwd_short_tiles_kernel<64><<<short_tiles_grid(d, L), 256, 0, stream>>>(p);
     } else if (gangs) {
         const unsigned grid = (unsigned)L.row_gangs * (unsigned)(d.hq / d.hkv);
         if (pairs) {

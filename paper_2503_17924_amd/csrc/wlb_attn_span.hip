@@ -6,6 +6,7 @@
 #include "wlb_acc.h"
 #include "wlb_attn_bwd.h"
 #include "wlb_attn_fwd.h"
+#include "wlb_attn_short.h"
 #include "wlb_device.h"
 #include "wlb_internal.h"
 
@@ -18,14 +19,18 @@ namespace wlb {
 // fewer than eight heads to a KV head a unit takes more blocks of rows.  Rows arrive and leave whole through a staging tile of 16 rows of the
 // wavefront's own.  Any mask is handled (more than 256 keys in several turns, keys that none of the unit's rows sees passed over: rows of two distant
 // chunks); which launches come here: use_span.  Bound: latency (a unit's
-// rows and keys are requested, arrive, are worked on and leave with nothing beside them: 160 KiB of LDS hold one unit).
-// 32768 tokens in documents of 1 - 64, 16/2 heads, before -> after, forward and dQ: one of 4 ranks 81 -> 49 and 92 -> 63 us, one of 8 75 -> 43 and
-// 84 -> 52; 8/2 heads, D = 64, one of 4 ranks 31 -> 18 and 40 -> 29.  One of 4 ranks of 52896 tokens, contiguous chunks, 32/8 heads, where a few rows of
-// two distant chunks share a block: the whole pass 1392 -> 525.
+// rows and keys are requested, arrive, are worked on and leave with nothing beside them: 160 KiB of LDS hold one unit).  The blocks of short-hull tiles
+// (contiguous chunks of short documents) are short-hull units in the same launch: in one of their own, 5 us each in forward and in
+// dQ, a whole pass over 2320 tokens in contiguous chunks, 8/1 heads, one of 4 ranks, took 127 us for 102 here (115 without this file).
+// 32768 tokens in documents of 1 - 64, 16/2 heads, before -> after, forward and dQ: one of 4 ranks 73 -> 47 and 84 -> 60 us; 36448 tokens, 8/1 heads, one of 8 ranks
+// 42 -> 22 and 47 -> 27; 9000 tokens, 8/2 heads, D = 64, one of 4 ranks 20 -> 12.6 and 18 -> 14.  Contiguous chunks, 36448 tokens, 8/1 heads, one of 4 ranks,
+// where a few rows of two distant chunks share a block: the whole pass 785 -> 136.  Slower: contiguous chunks of 131072 tokens, nearly all tiles short-hull
+// ones, 0.92 - 1.0 (one workgroup to a compute unit, where short-hull units in a launch of their own kernel have two).
 template <int D>
 struct Span {
     static constexpr int NW = 8, KEYS = 32 * NW, KS = D / 16, DB = D / 32, CPR = D / 8, ROWB = D * 2;
     static constexpr int STAGE = 16 * ROWB, LDS_BYTES = 2 * KEYS * ROWB + NW * STAGE;
+    static_assert(LDS_BYTES >= 2 * ShortTile<D>::LDS_BYTES && ShortTile<D>::LDS_BYTES == ShortDq<D>::LDS_BYTES, "two short-hull units");
 
     int lane, wave, l32, half;
     int hk, heads, blk, first_head;      // the wavefront's block of rows; -1: none
@@ -36,22 +41,22 @@ struct Span {
     BufRsrc krs, vrs;
     TileDma<D, KEYS, NW> dma;
 
-    // The workgroup's unit, -1: none, or of a short-hull tile (its units are faster, and form delta more precisely).  Neighbouring units share
-    // keys, so they go to the same XCD.
+    // The workgroup's unit: its first block of rows and KV head (false: none).  Neighbouring units share keys, so they go to the same XCD.
     template <class P>
-    static __device__ __forceinline__ int unit_of(const P& p, int per) {
-        const int n = (p.n_blocks32 + per - 1) / per;
+    static __device__ __forceinline__ bool unit_of(const P& p, int per, int& blk0, int& hk) {
+        const int n = p.n_blocks32 / per;
         const int unit = uniform((int)(blockIdx.x % kLists) * (int)(gridDim.x / kLists) + (int)(blockIdx.x / kLists));
-        if (unit >= n * p.hkv) return -1;
-        return ld_const(p.tile_short + uniform(unit % n * per / (kFwdTileRows / kShortBlockRows))) ? -1 : unit;
-    }
-    template <class P>
-    __device__ __forceinline__ void init(const P& p, char* lds, int unit, int per) {
-        heads = min(p.hq / p.hkv, NW);
-        const int n = (p.n_blocks32 + per - 1) / per;
+        blk0 = uniform(unit % n * per);
         hk = uniform(unit / n);
-        const int blk0 = uniform(unit % n * per);
-        lane = threadIdx.x & 63; wave = uniform((int)(threadIdx.x >> 6)); l32 = lane & 31; half = lane >> 5;
+        return unit < n * p.hkv;
+    }
+    // the lane once more, where addresses of the staging tile are made from it (kept from the start they take more registers than there are)
+    static __device__ __forceinline__ int lane_here() { return (int)opaque(threadIdx.x) & 63; }
+    template <class P>
+    __device__ __forceinline__ void init(const P& p, char* lds, int blk0, int kv_head, int per) {
+        heads = min(p.hq / p.hkv, NW);
+        hk = kv_head;
+        lane = lane_here(); wave = uniform((int)(threadIdx.x >> 6)); l32 = lane & 31; half = lane >> 5;
         blk = blk0 + wave / heads;
         if (wave / heads >= per || blk >= p.n_blocks32) blk = -1;
         first_head = wave % heads;
@@ -82,8 +87,6 @@ struct Span {
         vrs.init(p.v + (size_t)hk * D, kv_bytes);
         dma.init(wave, lane, kv_row);
     }
-    // the lane once more, where addresses of the staging tile are made from it (kept from the start they take more registers than there are)
-    static __device__ __forceinline__ int lane_here() { return (int)opaque(threadIdx.x) & 63; }
     // scalar offset of a head's first row of the wavefront's block
     __device__ __forceinline__ uint32_t head_soff(int h) const { return uniform((uint32_t)blk * (uint32_t)kShortBlockRows * q_row_bytes + (uint32_t)h * ROWB); }
     // copies of K and V of the keys from key0 on, 32 to a wavefront; every wavefront must have left the keys before
@@ -191,14 +194,21 @@ struct Span {
 };
 
 template <int D>
-__global__ void __launch_bounds__(512, 2) fwd_span_kernel(const FwdParams p) {
+__global__ void __launch_bounds__(512, D == 64 ? 4 : 2) fwd_span_kernel(const FwdParams p) {
     using T = Span<D>;
     constexpr int KS = T::KS, DB = T::DB, ROWB = T::ROWB;
     __shared__ __attribute__((aligned(1024))) char smem[T::LDS_BYTES];
+    const int per = T::NW / min(p.hq / p.hkv, T::NW);
+    int blk0, hk;
+    if (!T::unit_of(p, per, blk0, hk)) return;
+    if (ld_const(p.tile_short + blk0 / (kFwdTileRows / kShortBlockRows))) {       // short-hull units are faster there, and dQ's form delta more precisely
+        short_units_of_512<T::LDS_BYTES / 2>(smem, blk0, per, [&](auto waves, char* lds, int blk) __attribute__((always_inline)) {
+            fwd_short_unit<D, decltype(waves)::value>(p, lds, blk, hk);
+        });
+        return;
+    }
     T t;
-    const int per = T::NW / min(p.hq / p.hkv, T::NW), unit = T::unit_of(p, per);
-    if (unit < 0) return;
-    t.init(p, smem, unit, per);
+    t.init(p, smem, blk0, hk, per);
     const buf_rsrc_t q_buf = make_buf(p.q, (uint32_t)p.n_q * t.q_row_bytes), o_buf = make_buf(p.o, (uint32_t)p.n_q * t.q_row_bytes);
     const float cs = p.scale_log2e;
     RowBlock<D> q_rows;
@@ -283,10 +293,17 @@ __global__ void __launch_bounds__(512, 2) dq_span_kernel(const BwdParams p) {
     using T = Span<D>;
     constexpr int KS = T::KS, DB = T::DB, ROWB = T::ROWB;
     __shared__ __attribute__((aligned(1024))) char smem[T::LDS_BYTES];
+    const int per = T::NW / min(p.hq / p.hkv, T::NW);
+    int blk0, hk;
+    if (!T::unit_of(p, per, blk0, hk)) return;
+    if (ld_const(p.tile_short + blk0 / (kFwdTileRows / kShortBlockRows))) {       // short-hull units are faster there, and dQ's form delta more precisely
+        short_units_of_512<T::LDS_BYTES / 2>(smem, blk0, per, [&](auto waves, char* lds, int blk) __attribute__((always_inline)) {
+            dq_short_unit<D, decltype(waves)::value>(p, lds, blk, hk);
+        });
+        return;
+    }
     T t;
-    const int per = T::NW / min(p.hq / p.hkv, T::NW), unit = T::unit_of(p, per);
-    if (unit < 0) return;
-    t.init(p, smem, unit, per);
+    t.init(p, smem, blk0, hk, per);
     const uint32_t q_bytes = (uint32_t)p.n_q * t.q_row_bytes;
     const buf_rsrc_t q_buf = make_buf(p.q, q_bytes), do_buf = make_buf(p.d_o, q_bytes), o_buf = make_buf(p.o, q_bytes), dq_buf = make_buf(p.dq, q_bytes);
     const float cs = p.scale_log2e;
@@ -366,7 +383,7 @@ __global__ void __launch_bounds__(512, 2) dq_span_kernel(const BwdParams p) {
 
 static unsigned span_grid(int n_blocks32, int hq, int hkv) {
     const int per = 8 / std::min(hq / hkv, 8);
-    return (unsigned)(((n_blocks32 + per - 1) / per * hkv + kLists - 1) / kLists * kLists);
+    return (unsigned)((n_blocks32 / per * hkv + kLists - 1) / kLists * kLists);
 }
 void launch_fwd_span(const FwdParams& p, int head_dim, hipStream_t stream) {
     const unsigned grid = span_grid(p.n_blocks32, p.hq, p.hkv);

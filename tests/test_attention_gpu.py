@@ -373,6 +373,29 @@ def test_short_documents_divided_among_ranks(hq, hkv, d, cp, rank, mode, docs):
     c.check_bwd(f" span {hq}/{hkv} d{d} cp{cp}")
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(8, 1, 128), (8, 2, 128), (16, 2, 64), (10, 2, 128), (24, 4, 64), (12, 4, 64)])
+def test_contiguous_short_documents_in_launches_of_units(hq, hkv, d):
+    """Contiguous chunks of short documents: query tiles whose blocks are short-hull units, two to a workgroup, in the same launch as units
+    of rows of distant places; blocks of padding alone beside blocks with rows, a last tile of one row, padding that holds NaN and Inf."""
+    import torch
+    docs = [21, 40, 5, 64, 33, 1, 50] * 12
+    t_kv = sum(docs)
+    near = np.arange(256, dtype=np.int32) + 700
+    near[32:64] = near[96:160] = near[250:] = -1
+    apart = np.random.default_rng(7).permutation(t_kv)[:128].astype(np.int32)
+    q_idx = np.concatenate([near, apart, np.arange(128, dtype=np.int32), [t_kv - 1]])
+    w, tens = wl.small_case(98, docs, hq, hkv, d)
+    c = Case(tens, q_idx, _cu(docs), hq, hkv, d, w.scale, visible_pairs=20 * len(q_idx))
+    pad = np.nonzero(q_idx < 0)[0]
+    for name in ("q", "do"):
+        t = c.dev[name].view(dtype=torch.int16)
+        t[pad[0::2]] = 0x7FC0
+        t[pad[1::2]] = 0x7F80
+    c.check_fwd()
+    c.check_bwd()
+    assert B.plan_tables(c.attn)["tile_short"].tolist() == [1, 1, 0, 1, 1]
+
+
 @pytest.mark.parametrize("hq,hkv,d,cp,rank,mode,docs", [
     # shares of a gang: tiles cut anywhere, pieces of a few keys, a last tile of 5 rows, padding, two heads and eight to a KV head
     (8, 1, 128, 2, 1, osh.PER_DOC_PADDED, [2600, 1, 37, 900, 130, 64, 705]),
