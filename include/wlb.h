@@ -227,6 +227,12 @@ wlb_status wlb_attn_workspace_size(const wlb_attn_desc* desc, size_t* fwd_bytes,
 wlb_status wlb_attn_plan(const wlb_attn_desc* desc, const int32_t* q_idx, const int32_t* cu_seqlens_k,
                          void* workspace, size_t workspace_bytes, void* stream);
 
+/* wlb_plan_layout.row_kernels: forward / dQ take two query heads of a KV head to a workgroup, one workgroup to a compute unit; both
+ * hold the keys of a block of rows in LDS for all heads (short documents divided among ranks). */
+#define WLB_ROW_FWD_TWO_HEADS 1
+#define WLB_ROW_DQ_TWO_HEADS 2
+#define WLB_ROW_SPAN 4
+
 /* Where the schedule's arrays sit inside the workspace (byte offsets; for inspection and
  * tests).  Row arrays have n_q entries; group arrays n_groups entries of 4 int32
  * {k_lo, k_hi, max_lo, min_hi} per group of group_rows consecutive slots; the work lists are
@@ -252,8 +258,9 @@ typedef struct {
     size_t  off_dkv_counters;            /* int32 [8]: dK/dV items handed out per XCD list beyond the first of each workgroup; zero between launches */
     /* forward / dQ work: the query tiles in order, each repeated for every KV head, form one line of
        work measured in key tiles (plus a fixed per-tile cost); row_gangs gangs of hq/hkv workgroups
+       (half as many where a workgroup takes two heads)
        take consecutive shares of it (the first half of the gangs, whose workgroups run faster, a
-       somewhat larger one), so a tile cut by a share's end is finished by the next gang and the
+       somewhat larger one; all the same where a workgroup takes two heads), so a tile cut by a share's end is finished by the next gang and the
        parts are merged from fp32 partial results */
     int32_t row_gangs;
     int32_t uses_gangs;                  /* 1: forward and dQ of this desc (its flags included) run the gang schedule */
@@ -261,11 +268,14 @@ typedef struct {
     /* short-hull path: per block of 32 slots the hull {k_lo, k_hi} of the keys its real rows see (k_hi <= k_lo:
        no real row), and per query tile whether each of its blocks' hulls fits the short-hull kernels' LDS window */
     int32_t n_blocks32;
+    int32_t row_kernels;                 /* which kernels forward and dQ of this desc (its flags included) run, a sum of WLB_ROW_* */
     size_t  off_block_hull;              /* int32 [n_blocks32][2] */
     size_t  off_tile_short;              /* int32 [n_fwd_tiles]: 1 = short-hull tile */
     /* diagnostics of the gang schedule: each workgroup of the forward (k = 0) and dQ (k = 1) gang kernels leaves
        the GPU's constant-rate real-time counter (100 MHz) at its start and at its end, so that a caller can see
-       how evenly the gangs finish: uint64 [2][row_gangs * hq / hkv][2], workgroup index as launched */
+       how evenly the gangs finish: uint64 [2][row_gangs * hq / hkv][2].  Entry b is member (b / 8) % G of gang (b / 8) / G * 8 + b % 8,
+       G = hq / hkv members (query heads) to a gang: the workgroup's index where there is one to a head, and a workgroup of two heads
+       (WLB_ROW_*_TWO_HEADS) leaves its times in the entries of both */
     size_t  off_gang_clock;
     size_t  plan_bytes;
 } wlb_plan_layout;
@@ -300,7 +310,8 @@ wlb_status wlb_attn_plan_records(const wlb_attn_desc* desc, wlb_plan_records* re
  * (kernel = 1) launch take shares of the work proportional to weights[half * 8 + xcd]: half = 0 for the first
  * n_gangs / 2 gangs of the launch, 1 for the others; gang g runs on XCD g % 8.  The defaults give the first half
  * a larger share (its workgroups are the older wavefronts of their SIMDs and advance faster) and treat the XCDs
- * alike; the XCDs of one GPU differ in speed by several percent (which ones are slow differs from GPU to GPU),
+ * alike.  Where a workgroup takes two heads (wlb_plan_layout.row_kernels) it has its SIMDs to itself, no half is faster, and
+ * a gang's weight is the sum of its XCD's two, weights[xcd] + weights[8 + xcd]; the XCDs of one GPU differ in speed by several percent (which ones are slow differs from GPU to GPU),
  * so a caller may measure them -- run its own problem, or any with WLB_ATTN_SCHEDULE_GANGS, read the gangs'
  * clocks at off_gang_clock, and scale the weights of each XCD by mean end time / that XCD's end time; two or
  * three rounds settle.  Weights change where query tiles are cut, i.e. the rounding of the

@@ -28,6 +28,9 @@ ATTN_BWD_SKIP_DKV = 8
 ATTN_SCHEDULE_GANGS = 32
 ATTN_SCHEDULE_ITEMS = 64
 ATTN_NO_SHORT_PATH = 128
+ROW_FWD_TWO_HEADS = 1
+ROW_DQ_TWO_HEADS = 2
+ROW_SPAN = 4
 
 STATUS_NAMES = {0: "WLB_OK", 1: "WLB_ERR_INVALID_ARG", 2: "WLB_ERR_BUFFER_TOO_SMALL",
                 3: "WLB_ERR_UNSUPPORTED", 4: "WLB_ERR_HIP"}
@@ -57,7 +60,7 @@ class PlanLayout(C.Structure):
                 ("off_key_range", C.c_size_t), ("dkv_max_items", C.c_int32), ("dkv_max_partials", C.c_int32),
                 ("off_key_ways", C.c_size_t), ("off_key_item_base", C.c_size_t), ("off_key_slot_base", C.c_size_t), ("off_dkv_counters", C.c_size_t),
                 ("row_gangs", C.c_int32), ("uses_gangs", C.c_int32), ("off_fwd_prefix", C.c_size_t),
-                ("n_blocks32", C.c_int32), ("off_block_hull", C.c_size_t), ("off_tile_short", C.c_size_t),
+                ("n_blocks32", C.c_int32), ("row_kernels", C.c_int32), ("off_block_hull", C.c_size_t), ("off_tile_short", C.c_size_t),
                 ("off_gang_clock", C.c_size_t),
                 ("plan_bytes", C.c_size_t)]
 
@@ -473,15 +476,20 @@ def plan_report(attn: "Attention", name: str = "") -> str:
              f"{'gang' if lay.uses_gangs else 'item'} schedule for forward and dQ"]
     q = lambda a: "min %d  median %d  max %d  sum %d" % (a.min(), np.median(a), a.max(), a.sum()) if len(a) else "none"
     lines.append(f"  query tile cost (64-key tiles visited, heaviest first): {q(cost)}; first ten: {cost[:10].tolist()}")
+    lines += [f"  {what}" for bit, what in ((ROW_FWD_TWO_HEADS, "forward: two query heads to a workgroup"), (ROW_DQ_TWO_HEADS, "dQ: two query heads to a workgroup"),
+                                            (ROW_SPAN, "forward and dQ: the keys of a block of rows in LDS for all heads")) if lay.row_kernels & bit]
     if lay.uses_gangs:
+        two = bool(lay.row_kernels & ROW_FWD_TWO_HEADS)
         w = wlb_attn_get_gang_weights(0).astype(np.int64).reshape(2, 8)
+        if two:
+            w[:] = w.sum(axis=0)         # with two heads to a workgroup no half of the launch is slower
         ng = lay.row_gangs
         gw = np.array([w[0 if g < ng // 2 else 1][g % 8] for g in range(ng)])
         cum = np.concatenate([[0], np.cumsum(gw)])
         total = int(t["fwd_prefix"][-1]) * hkv
         begin = total * cum // cum[-1]
         share = np.diff(begin)
-        lines.append(f"  forward work line: {total} units (tile cost + fixed part, x KV heads) over {ng} gangs of {hq // hkv} "
+        lines.append(f"  forward work line: {total} units (tile cost + fixed part, x KV heads) over {ng} gangs of {hq // hkv // (2 if two else 1)} "
                      f"workgroups: share {q(share)}")
     elif t["records"].uses_parts:
         part = t["row_part"]

@@ -760,7 +760,7 @@ wlb_status launch_bwd(const wlb_attn_desc& d, const PlanLayout& L, const void* q
     const unsigned grid_dq = (unsigned)L.row_gangs * (unsigned)(d.hq / d.hkv);
     const unsigned grid_dq_items = (unsigned)((L.n_fwd_tiles + (parts ? row_parts_added(d, L) : 0) + 7) / 8) * 8u * (unsigned)d.hq;
     const unsigned grid_dq_parts = (unsigned)row_tiles_divided(d, L) * (unsigned)d.hq * kMergeSplit;
-    const bool gangs = use_row_gangs(d, L), pairs = use_row_pairs(d, L) && d.head_dim == 128;     // (64: 2546 and 2527 us as gangs)
+    const bool gangs = use_row_gangs(d, L), pairs = use_dq_pairs(d, L);
     if (gangs && pairs) pair_weights(p.sched.weight);
     // one workgroup per compute unit, each taking item after item
     const unsigned grid_dkv = (unsigned)std::min(L.dkv_max_items, compute_units());   // one workgroup per compute unit, each taking item after item

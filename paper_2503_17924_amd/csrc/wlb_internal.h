@@ -121,6 +121,8 @@ bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L);
 // 0.73 - 0.99 and 0.85 - 0.99).
 constexpr int kRowPairMinItemUnits = 30, kRowPairMinUnitsPerSlot = 1000;
 bool use_row_pairs(const wlb_attn_desc& d, const PlanLayout& L);
+// dQ as well: at head dimension 64 it is no faster (2546 us with two heads, 2527 as gangs of one)
+inline bool use_dq_pairs(const wlb_attn_desc& d, const PlanLayout& L) { return use_row_pairs(d, L) && d.head_dim == 128; }
 // share weights of its gangs: with one workgroup to a compute unit no half of the launch is slower than the other
 void pair_weights(int (&weight)[2][8]);
 // whether this launch sends short-hull query tiles to the short-hull kernels (only in the

@@ -162,6 +162,7 @@ void plan_layout(const wlb_attn_desc& d, PlanLayout* L) {
     L->uses_gangs = use_row_gangs(d, *L) ? 1 : 0;
     L->off_fwd_prefix = take(sizeof(int64_t) * (L->n_fwd_tiles + 1));
     L->n_blocks32 = L->n_groups * (kGroupRows / kShortBlockRows);
+    L->row_kernels = (use_row_pairs(d, *L) ? WLB_ROW_FWD_TWO_HEADS : 0) | (use_dq_pairs(d, *L) ? WLB_ROW_DQ_TWO_HEADS : 0) | (use_span(d, *L) ? WLB_ROW_SPAN : 0);
     L->off_block_hull = take(sizeof(int32_t) * 2 * L->n_blocks32);
     L->off_tile_short = take(sizeof(int32_t) * L->n_fwd_tiles);
     L->off_gang_clock = take(sizeof(uint64_t) * 2 * 2 * (size_t)L->row_gangs * (d.hq / d.hkv));

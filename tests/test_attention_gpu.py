@@ -393,7 +393,8 @@ def test_contiguous_short_documents_in_launches_of_units(hq, hkv, d):
         t[pad[1::2]] = 0x7F80
     c.check_fwd()
     c.check_bwd()
-    assert B.plan_tables(c.attn)["tile_short"].tolist() == [1, 1, 0, 1, 1]
+    t = B.plan_tables(c.attn)
+    assert t["layout"].row_kernels == B.ROW_SPAN and t["tile_short"].tolist() == [1, 1, 0, 1, 1]
 
 
 @pytest.mark.parametrize("hq,hkv,d,cp,rank,mode,docs", [
@@ -412,8 +413,11 @@ def test_two_heads_to_a_workgroup(hq, hkv, d, cp, rank, mode, docs):
     c = Case(tens, sh["q_idx"], sh["cu_seqlens_k"], hq, hkv, d, w.scale, visible_pairs=10 ** 12)
     lay = B.wlb_attn_plan_layout(c.attn.desc)
     assert bool(lay.uses_gangs) == (hq < 64)
+    assert lay.row_kernels == B.ROW_FWD_TWO_HEADS + (B.ROW_DQ_TWO_HEADS if d == 128 else 0)
     c.check_fwd(f" pairs {hq}/{hkv} d{d}")
     c.check_bwd(f" pairs {hq}/{hkv} d{d}")
+    if lay.uses_gangs:
+        assert f"gangs of {hq // hkv // 2} workgroups" in B.plan_report(c.attn)
     # a maximum that rises along the keys, so that what is accumulated is rescaled again and again
     ramp = c.torch.linspace(0.2, 4.0, c.t_kv, device="cuda")[:, None, None]
     q0, k0 = c.dev["q"], c.dev["k"]
