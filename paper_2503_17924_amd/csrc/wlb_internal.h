@@ -129,13 +129,21 @@ void pair_weights(int (&weight)[2][8]);
 // one-workgroup-per-item schedule; WLB_ATTN_NO_SHORT_PATH switches it off)
 bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L);
 // Whether forward and dQ of the tiles that are not short-hull ones run as units that hold the keys of a block of rows in LDS for all heads
-// (wlb_attn_span.hip): the ranks divide documents so that a block of 32 rows spans kSpanMinReach tokens (with 61, one of two ranks, many tiles are
-// short-hull ones, and a second launch for them costs more than the others gain: 0.84 - 1.08 of the whole pass), documents (2 * pairs / rows: the pair
-// count has to be known) are of kSpanMaxLength tokens (old / new of forward and dQ alone at 45 - 207: 1.05 - 1.7), there are four heads or more to a KV head
-// (one: 0.4 - 0.9), and a unit's keys fit two windows or units are enough to fill half of the compute units (4 heads to a KV head, one of 8 ranks
+// (wlb_attn_span.hip): the ranks divide documents so that a block of 32 rows spans kSpanMinReach tokens (61, one of two ranks, measured
+// 0.84 - 1.08 of the whole pass when short-hull tiles had a launch of their own), documents (2 * pairs / rows: the pair
+// count has to be known) are of kSpanMaxLength tokens (old / new of forward and dQ alone at 45 - 207: 1.05 - 2.0), there are four heads or more to a KV head
+// (three, which leave two of eight wavefronts idle, 36448 tokens on one of 4 ranks: 0.85 - 0.96; one: 0.4 - 0.9), and a unit's keys fit two windows or units are enough to fill half of the compute units (4 heads to a KV head, one of 8 ranks
 // of 4096 tokens in documents of 1 - 160, 20 units: 0.82 - 0.95; of 32768, 158 units: 1.3).
-constexpr int kSpanMinReach = 96, kSpanMaxLength = 256, kSpanMaxKeys = 384, kSpanMinUnits = 128;
+// And no document is so long that its units, which walk its keys one window after another (0.042 us a token at head dimension 128, 0.03 at 64), end after
+// the launch they replace (20 us and 0.11 us per 32 rows and 8 heads): long_tokens is at most kSpanLongBase + kSpanLongPerBlock for each of those.
+// Whole pass, old / new, documents of 1 - 64 tokens and one of n: below that line (n = 1400 - 5000 of 32768 - 131072, 16/2 and 16/4 heads) 0.95 - 1.24,
+// above it (n = 1200 - 5000 of 8192 - 131072) 0.67 - 1.02.
+constexpr int kSpanMinReach = 96, kSpanMaxLength = 256, kSpanMaxKeys = 384, kSpanMinUnits = 128, kSpanMinHeads = 4;
+constexpr double kSpanLongBase = 285, kSpanLongPerBlock = 2.5;
 bool use_span(const wlb_attn_desc& d, const PlanLayout& L);
+// Tokens of the documents that are far longer than the others, if there are any: weighted by tokens, documents are 2 * pairs / rows long; lengths that
+// are spread evenly from 1 on make that 4/3 of their mean, and what goes beyond is taken for one long document beside short ones.
+double long_tokens(const wlb_attn_desc& d);
 // workgroups of a launch for short-hull tiles alone (for_short_tiles): it may find none
 inline unsigned short_tiles_grid(const wlb_attn_desc& d, const PlanLayout& L) {
     const int units = L.n_fwd_tiles * d.hkv * (kFwdTileRows / kShortBlockRows), most = 2 * compute_units();

@@ -113,9 +113,15 @@ bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L) {
     return !(d.flags & WLB_ATTN_NO_SHORT_PATH) && !use_row_gangs(d, L);
 }
 
+double long_tokens(const wlb_attn_desc& d) {
+    const double weighted = 2.0 * (double)d.visible_pairs / d.n_q, mean = (double)d.t_kv / d.n_docs;
+    return std::sqrt(std::max(0.0, weighted - mean * 4 / 3) * d.t_kv);
+}
+
 bool use_span(const wlb_attn_desc& d, const PlanLayout& L) {
-    const int G = d.hq / d.hkv, per = G >= 8 ? 1 : 8 / G;                          // blocks of rows in a unit
-    if (!use_short_path(d, L) || d.visible_pairs <= 0 || per > 2) return false;
+    const int G = d.hq / d.hkv, per = G >= 8 ? 1 : 2;                              // blocks of rows in a unit
+    if (!use_short_path(d, L) || d.visible_pairs <= 0 || G < kSpanMinHeads) return false;
+    if (long_tokens(d) > kSpanLongBase + kSpanLongPerBlock * L.n_blocks32 * d.hq / 8) return false;
     const long long reach = (long long)kShortBlockRows * d.t_kv / d.n_q, length = 2 * (d.visible_pairs / d.n_q);
     if (reach < kSpanMinReach || length > kSpanMaxLength) return false;
     return per * reach + length <= kSpanMaxKeys || (long long)((L.n_blocks32 + per - 1) / per) * d.hkv >= kSpanMinUnits;

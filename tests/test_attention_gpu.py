@@ -350,11 +350,12 @@ def test_query_tiles_stay_whole_where_the_launch_is_balanced(docs, hq, hkv, cp, 
 
 @pytest.mark.parametrize("hq,hkv,d,cp,rank,mode", [
     (8, 1, 128, 4, 1, osh.PER_DOC_PADDED), (8, 2, 128, 4, 2, osh.PER_DOC_NOPAD), (32, 2, 128, 8, 7, osh.PER_DOC_PADDED), (12, 1, 64, 4, 0, osh.PER_DOC_PADDED),
-    (6, 1, 128, 8, 0, osh.PER_SEQ), (16, 4, 64, 4, 3, osh.PER_DOC_NOPAD), (5, 1, 64, 8, 2, osh.PER_SEQ)])
+    (6, 1, 128, 4, 0, osh.PER_SEQ), (16, 4, 64, 4, 3, osh.PER_DOC_NOPAD), (5, 1, 64, 4, 2, osh.PER_SEQ)])
 @pytest.mark.parametrize("docs", [
     # (not fewer tokens: the mean error of 2e-3 of the largest element holds for tensors whose largest element is three times the mean
     # of all; a dK of three rows, each element off by up to three roundings of 2^-9, is at 2.0e-3)
-    [35], [1] * 70, [64, 1, 33, 7, 48] * 9 + [5],
+    [35], [1] * 70,                                # short-hull tiles alone, or another launch
+    [64, 1, 33, 7, 48] * 9 + [5],
     [90, 3, 700, 40, 1, 17] + [31] * 40])          # a hull of three windows of keys
 def test_short_documents_divided_among_ranks(hq, hkv, d, cp, rank, mode, docs):
     """Launches whose units hold the keys of a block of rows for all heads of a KV head (taken with the pair count of short documents)."""
@@ -364,7 +365,11 @@ def test_short_documents_divided_among_ranks(hq, hkv, d, cp, rank, mode, docs):
     sh = osh.shard(docs, cp, rank, mode)
     if len(sh["q_idx"]) == 0:
         pytest.skip("no rows on this rank")
-    c = Case(tens, sh["q_idx"], sh["cu_seqlens_k"], hq, hkv, d, w.scale, visible_pairs=60 * len(sh["q_idx"]))
+    c = Case(tens, sh["q_idx"], sh["cu_seqlens_k"], hq, hkv, d, w.scale, visible_pairs=30 * len(sh["q_idx"]))
+    if len(docs) > 2 and max(docs) > 1:
+        c.attn.plan()
+        t = B.plan_tables(c.attn)
+        assert t["layout"].row_kernels == B.ROW_SPAN and (mode == osh.PER_SEQ or (t["tile_short"] == 0).any())
     if not (sh["q_idx"] >= 0).any():                   # padding alone
         o, lse = c.run_fwd()
         assert (o == 0).all() and np.isneginf(lse).all() and all((x == 0).all() for x in c.run_bwd())
@@ -373,7 +378,34 @@ def test_short_documents_divided_among_ranks(hq, hkv, d, cp, rank, mode, docs):
     c.check_bwd(f" span {hq}/{hkv} d{d} cp{cp}")
 
 
-@pytest.mark.parametrize("hq,hkv,d", [(8, 1, 128), (8, 2, 128), (16, 2, 64), (10, 2, 128), (24, 4, 64), (12, 4, 64)])
+@pytest.mark.parametrize("hq,hkv,d", [(8, 1, 128), (4, 1, 64), (16, 1, 64), (10, 2, 128)])
+@pytest.mark.parametrize("n_q", [24, 31, 33, 65, 129])
+def test_units_of_few_rows_in_any_order(n_q, hq, hkv, d):
+    """Launches of a few units whose rows lie all over the sequence, in no order, padding that holds NaN and Inf among them: a last block of one
+    row, blocks that end inside one, fewer and more heads than wavefronts.  The keys of a block fill one window, two, and three."""
+    import torch
+    t_kv = 16 * n_q // 3
+    docs = [50, 3, 40, 1, 22] * 6
+    docs = docs[:int(np.searchsorted(np.cumsum(docs), t_kv))]
+    docs.append(t_kv - sum(docs))
+    rng = np.random.default_rng(n_q)
+    q_idx = rng.choice(t_kv, n_q, replace=False).astype(np.int32)
+    pad = rng.choice(n_q - 1, n_q // 7, replace=False)         # (the last row is one)
+    q_idx[pad] = -1
+    w, tens = wl.small_case(99, docs, hq, hkv, d)
+    c = Case(tens, q_idx, _cu(docs), hq, hkv, d, w.scale, visible_pairs=20 * n_q)
+    for name in ("q", "do"):
+        t = c.dev[name].view(dtype=torch.int16)
+        t[pad[0::2]] = 0x7FC0
+        t[pad[1::2]] = 0x7F80
+    c.attn.plan()
+    t = B.plan_tables(c.attn)
+    assert t["layout"].row_kernels == B.ROW_SPAN and not t["tile_short"][0]
+    c.check_fwd()
+    c.check_bwd()
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 1, 128), (8, 2, 128), (16, 2, 64), (10, 2, 128), (24, 4, 64)])
 def test_contiguous_short_documents_in_launches_of_units(hq, hkv, d):
     """Contiguous chunks of short documents: query tiles whose blocks are short-hull units, two to a workgroup, in the same launch as units
     of rows of distant places; blocks of padding alone beside blocks with rows, a last tile of one row, padding that holds NaN and Inf."""
@@ -1096,7 +1128,7 @@ def test_graph_replay_matches_eager_calls(flag):
 @pytest.mark.parametrize("hq,hkv,d,cp,mode,docs,pairs", [
     # units of short documents on a rank, a padding row in most blocks of 32 rows
     (8, 1, 128, 4, osh.PER_DOC_PADDED, [61, 33, 7, 48, 21] * 9, 50),
-    (8, 2, 64, 8, osh.PER_DOC_PADDED, [61, 133, 7, 48, 21] * 9, 50),
+    (8, 2, 64, 4, osh.PER_DOC_PADDED, [61, 133, 7, 48, 21] * 9, 50),
     # short-hull units
     (8, 1, 128, 1, osh.PER_DOC_PADDED, [61, 33, 7, 48, 21] * 4, 0),
     (3, 1, 64, 1, osh.PER_DOC_PADDED, [61, 33, 7, 48, 21] * 4, 0),
@@ -1111,6 +1143,7 @@ def test_padding_rows_are_zero_whatever_lies_beside_them(hq, hkv, d, cp, mode, d
     pad = np.nonzero(q_idx < 0)[0]
     assert len(pad)
     c = Case(tens, q_idx, sh["cu_seqlens_k"], hq, hkv, d, w.scale, visible_pairs=pairs * len(q_idx))
+    assert B.wlb_attn_plan_layout(c.attn.desc).row_kernels == (B.ROW_SPAN if pairs else 0)
     for name in ("q", "do"):
         t = c.dev[name].view(dtype=torch.int16)
         t[pad[0::2]] = 0x7FC0          # NaN

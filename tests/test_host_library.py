@@ -136,6 +136,24 @@ def test_schedule_choice_uses_the_pair_count_when_given():
         B.wlb_attn_plan_layout(B._desc(n_q, 131072, len(docs), 8, 1, 128, 0.1, visible_pairs=-1))
 
 
+@pytest.mark.parametrize("docs,hq,hkv,cp,span", [
+    ([20, 44] * 512, 16, 2, 4, 1),
+    ([20, 44] * 512, 12, 3, 4, 1),
+    ([20, 44] * 512, 6, 2, 4, 0),                                # three heads to a KV head
+    ([20, 44] * 512, 16, 2, 2, 0),                               # a block of 32 rows spans 64 tokens
+    # one long document: its units take 0.042 us a token one window of keys after another, longer than the launch they replace
+    ([1400] + [20, 44] * 490 + [8], 8, 1, 4, 0),
+    ([1400] + [20, 44] * 490 + [8], 16, 2, 4, 1),
+    ([2400] + [20, 44] * 474 + [32], 16, 2, 4, 0),
+    ([1200] + [20, 44] * 109 + [16], 8, 2, 4, 0),
+    ([3000] + [20, 44] * 2001 + [8], 16, 2, 8, 1),
+])
+def test_units_of_short_documents_on_ranks(docs, hq, hkv, cp, span):
+    sh = B.wlb_shard(docs, cp, 1, B.SHARD_PER_DOC_PADDED)
+    lay = B.wlb_attn_plan_layout(B._desc(len(sh["q_idx"]), sum(docs), len(docs), hq, hkv, 128, 0.1, visible_pairs=sh["useful_pairs"]))
+    assert lay.row_kernels == (B.ROW_SPAN if span else 0)
+
+
 @pytest.mark.parametrize("docs,hq,hkv,cp,parts", [
     ([32] * 32, 8, 2, 1, 0),                 # 1024 tokens: no tile has more key tiles than a part may hold
     ([384] * 2 + [256], 8, 2, 1, 0),
