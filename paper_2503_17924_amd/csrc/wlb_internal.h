@@ -117,9 +117,21 @@ bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L);
 // least as many items as keep gangs away, and kRowPairMinItemUnits on average (forward, old / new at 34 - 73 units 1.02 - 1.07, at 20 - 26 0.99 - 1.05,
 // at 13 0.88 - 1.0; at head dimension 64 0.80 - 0.93 up to 58 units; dQ at 33 - 58 units 1.025 - 1.08, at 20 - 26 0.98 - 1.08, at 13
 // 0.92 - 0.98).  Or shares of kRowPairMinUnitsPerSlot units in a gang launch: a share's fixed part and the rows of short documents weigh more than in
-// launches of two workgroups (1620 units: forward 1.06, at head dimension 64 1.035, dQ 1.08 and 1.01; 650: 0.96 - 0.995 and 0.93 - 0.98; 70 - 300:
-// 0.73 - 0.99 and 0.85 - 0.99).
+// launches of two workgroups (documents that are long alone, 1024 - 1860 units: forward 1.09 - 1.12, at head dimension 64 0.99 - 1.035, dQ 1.095 - 1.12;
+// 650: forward 0.96 - 0.995, dQ 0.93 - 0.98; 70 - 300: 0.73 - 0.99 and 0.85 - 0.99).
+// There the rows of short documents must be few as well: their tiles are masked block after block, each with new maxima, which takes twice as long a
+// unit (the mask and the rescaling of 64 rows at once), and being the lightest they come last, all in the last gangs.  One of 8 ranks of 131072 tokens, 8/1 heads,
+// one long document and short ones, old / new of the forward (at D = 64) and of dQ: short ones of 1 - 64 tokens, 30 % of all: 0.64 (0.64), 0.81; 18 %: 0.82
+// (0.81), 0.96; 8.5 %: 0.99 (0.92), 1.09; 3 %: 1.11 (0.99), 1.11; of 64 - 256, 30 %: 0.81 (0.78), 0.87; 18 %: 0.95 (0.88), 1.01; of 64 - 1536, 30 %: 0.95 (0.89), 1.0;
+// 18 %: 1.04 (0.95), 1.07, and with 8/2 heads 0.95 (0.89), 0.955; of 500 - 4000, 30 %: 1.04 (0.97), 1.055.  So short_rows has a limit: at head dimension 128
+// kRowPairShortRows with eight heads or more to a KV head (above it 0.81 - 0.99 of the whole pass, below it 1.01 - 1.075), kRowPairShortRowsFew with fewer;
+// kRowPairShortRows64 at 64 (0.82 - 0.99 and 0.99 - 1.02).
 constexpr int kRowPairMinItemUnits = 30, kRowPairMinUnitsPerSlot = 1000;
+constexpr double kRowPairShortRows = 0.15, kRowPairShortRowsFew = 0.1, kRowPairShortRows64 = 0.06;
+// Share of a rank's rows that probably lie in short documents beside one long: its tokens follow from what rows see on average, the others'
+// mean length from the count of documents.  Documents count by how far their chunk on the rank (a rank has two chunks of each) falls short of kShortChunkRows rows.
+constexpr int kShortChunkRows = 256;
+double short_rows(const wlb_attn_desc& d);
 bool use_row_pairs(const wlb_attn_desc& d, const PlanLayout& L);
 // dQ as well: at head dimension 64 it is no faster (2546 us with two heads, 2527 as gangs of one)
 inline bool use_dq_pairs(const wlb_attn_desc& d, const PlanLayout& L) { return use_row_pairs(d, L) && d.head_dim == 128; }

@@ -75,10 +75,20 @@ bool use_row_gangs(const wlb_attn_desc& d, const PlanLayout& L) {
     return items * mean_item_units(d, L) >= (long long)kRowGangMinUnitsPerSlot * slots;
 }
 
+double short_rows(const wlb_attn_desc& d) {
+    if (d.visible_pairs <= 0) return 0;           // documents alike
+    const double t = d.t_kv, rest = std::max(0.0, t - std::sqrt(2.0 * (double)d.visible_pairs / d.n_q * t));
+    const double chunk = rest / std::max(d.n_docs - 1, 1) * d.n_q / t / 2;
+    return rest / t * std::max(0.0, 1 - chunk / kShortChunkRows);
+}
+
 bool use_row_pairs(const wlb_attn_desc& d, const PlanLayout& L) {
     if ((d.hq / d.hkv) % 2 != 0) return false;
     const long long items = (long long)L.n_fwd_tiles * d.hq, slots = 2LL * compute_units(), units = mean_item_units(d, L);
-    if (use_row_gangs(d, L)) return items * units >= (long long)kRowPairMinUnitsPerSlot * slots;
+    if (use_row_gangs(d, L)) {
+        const double most = d.head_dim == 64 ? kRowPairShortRows64 : d.hq / d.hkv >= 8 ? kRowPairShortRows : kRowPairShortRowsFew;
+        return items * units >= (long long)kRowPairMinUnitsPerSlot * slots && short_rows(d) <= most;
+    }
     return d.head_dim == 128 && items >= (long long)kRowGangMaxItemsPerSlot * slots && units >= kRowPairMinItemUnits;
 }
 

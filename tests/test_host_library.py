@@ -136,6 +136,33 @@ def test_schedule_choice_uses_the_pair_count_when_given():
         B.wlb_attn_plan_layout(B._desc(n_q, 131072, len(docs), 8, 1, 128, 0.1, visible_pairs=-1))
 
 
+@pytest.mark.parametrize("docs,hq,hkv,d,cp,kernels", [
+    # documents that are long alone
+    ([131072], 8, 1, 128, 8, B.ROW_FWD_TWO_HEADS | B.ROW_DQ_TWO_HEADS),
+    ([131072], 8, 1, 64, 8, B.ROW_FWD_TWO_HEADS),
+    ([80000, 51072], 8, 1, 128, 8, B.ROW_FWD_TWO_HEADS | B.ROW_DQ_TWO_HEADS),
+    ([90000, 20000, 21072], 8, 2, 64, 8, B.ROW_FWD_TWO_HEADS),
+    ([65536], 8, 1, 128, 8, 0),                                  # 512 key tiles a slot
+    # a long one and few rows of short ones, many rows of short ones, and of middling ones
+    ([127000] + [34] * 119 + [26], 8, 1, 128, 8, B.ROW_FWD_TWO_HEADS | B.ROW_DQ_TWO_HEADS),
+    ([127000] + [34] * 119 + [26], 8, 1, 64, 8, B.ROW_FWD_TWO_HEADS),
+    ([120000] + [34] * 325 + [22], 8, 1, 64, 8, 0),
+    ([100000] + [62] * 500 + [72], 8, 1, 128, 8, 0),
+    ([108000] + [32] * 721, 4, 2, 128, 8, 0),
+    ([92000] + [800] * 48 + [672], 8, 2, 128, 8, 0),
+    ([108000] + [800] * 28 + [672], 8, 2, 128, 8, 0),
+    ([108000] + [800] * 28 + [672], 8, 1, 128, 8, B.ROW_FWD_TWO_HEADS | B.ROW_DQ_TWO_HEADS),
+    ([92000] + [2250] * 17 + [822], 8, 1, 128, 8, B.ROW_FWD_TWO_HEADS | B.ROW_DQ_TWO_HEADS),
+    ([92000] + [2250] * 17 + [822], 8, 1, 64, 8, 0),
+])
+def test_two_heads_to_a_workgroup_where_documents_are_long(docs, hq, hkv, d, cp, kernels):
+    """A gang that holds the rows of many short documents is slow with two heads to a workgroup and ends last."""
+    assert sum(docs) == 131072 or len(docs) == 1
+    sh = B.wlb_shard(docs, cp, 3, B.SHARD_PER_DOC_PADDED)
+    lay = B.wlb_attn_plan_layout(B._desc(len(sh["q_idx"]), sum(docs), len(docs), hq, hkv, d, 0.1, visible_pairs=sh["useful_pairs"]))
+    assert (lay.uses_gangs, lay.row_kernels) == (1, kernels)
+
+
 @pytest.mark.parametrize("docs,hq,hkv,cp,span", [
     ([20, 44] * 512, 16, 2, 4, 1),
     ([20, 44] * 512, 12, 3, 4, 1),
