@@ -460,6 +460,36 @@ def test_two_heads_to_a_workgroup(hq, hkv, d, cp, rank, mode, docs):
     c.check_fwd(f" rising maxima {hq}/{hkv} d{d}")
 
 
+@pytest.mark.parametrize("hq,hkv,d,shuffled", [(8, 1, 128, False), (8, 1, 128, True), (4, 2, 128, True), (8, 2, 64, True), (64, 2, 128, False), (64, 2, 128, True)])
+def test_two_heads_to_a_workgroup_with_garbage_in_padding(hq, hkv, d, shuffled):
+    """The same launches (shares of gangs, whose cut tiles are merged, and from 64 heads on items) on rows in no order, and padding rows
+    that hold NaN and Inf: they reach nothing else, and beside keys and values that are not finite their O and dQ are 0."""
+    import torch
+    docs = [1300, 1, 37, 900, 130, 64, 705]
+    t_kv = sum(docs)
+    w, tens = wl.small_case(92, docs, hq, hkv, d)
+    rng = np.random.default_rng(3)
+    q_idx = rng.permutation(t_kv).astype(np.int32) if shuffled else np.arange(t_kv, dtype=np.int32)
+    q_idx = np.insert(q_idx, np.arange(5, t_kv, 41), -1)
+    pad = np.nonzero(q_idx < 0)[0]
+    c = Case(tens, q_idx, _cu(docs), hq, hkv, d, w.scale, visible_pairs=10 ** 12)
+    lay = B.wlb_attn_plan_layout(c.attn.desc)
+    assert bool(lay.uses_gangs) == (hq < 64) and lay.row_kernels == B.ROW_FWD_TWO_HEADS + (B.ROW_DQ_TWO_HEADS if d == 128 else 0)
+    for name in ("q", "do"):
+        t = c.dev[name].view(dtype=torch.int16)
+        t[pad[0::2]] = 0x7FC0          # NaN
+        t[pad[1::2]] = 0x7F80          # +Inf
+    c.check_fwd()
+    c.check_bwd()
+    for name in ("k", "v"):
+        t = c.dev[name].view(dtype=torch.int16)
+        t[0::7, :, 3] = 0x7F80
+        t[2::7, :, d - 1] = 0x7FC0
+    o, lse = c.run_fwd()
+    dq, _, _ = c.run_bwd()
+    assert (o[pad] == 0).all() and np.isneginf(lse[:, pad]).all() and (dq[pad] == 0).all()
+
+
 def test_gang_share_weights_change_the_cuts_not_the_result():
     """wlb_attn_set_gang_weights: very uneven weights (by half of the launch and by XCD) move the points where
     query tiles are cut between gangs; the results still match the oracle, and the defaults come back."""
