@@ -9,11 +9,18 @@
 
 namespace wlb {
 
+// Layout of the tiles in LDS of these kernels.
+// Tiles of rows x D that operands are read from both row-wise and transposed lie in LDS as blocks of 1 KiB: 8 rows x 64 columns, block
+// (row / 8) * CH + column / 64.  Of a block's 64 chunks of 16 bytes the one of row r and chunk column c is number
+// ((c & 7) ^ (r >> 3 & 1)) * 8 + ((r & 7) ^ (c >> 1 & 1) * 4).  Both ways to read a tile are then free of bank conflicts, and an operand's place
+// is one of two registers plus a constant.
+
 // The accumulators of such a kernel fill half or all of the accumulation registers (AGPRs), and the compiler does not keep such a
 // set in place through a loop with branches (it copies and spills all of it).  They are therefore registers by number, 16 to an
 // accumulator, named in the statements below and declared as written by each; build.py refuses code in which the compiler
 // touches one on its own account.  What an accumulating MFMA leaves is read by that accumulator's next one (which the hardware orders)
-// and, after acc_settle(), by acc_to_lds.
+// and, after acc_settle(), by acc_to_lds, acc_read and acc_scale; what acc_write and acc_scale leave, by MFMAs some
+// instructions later (acc_written() where none lie between).
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 #define WLB_ACC_ALL \
     "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", "a10", "a11", "a12", "a13", "a14", "a15", \
@@ -116,10 +123,5 @@ __device__ __forceinline__ void acc_write(uint32_t x) {
     asm volatile("v_accvgpr_write_b32 a[%0], %1 ; acc" ::"n"(N), "v"(x) : WLB_ACC_ALL);
 }
 __device__ __forceinline__ void acc_written() { asm volatile("s_nop 3" ::: "memory"); }
-
-// Tiles of rows x D that operands are read from both row-wise and transposed lie in LDS as blocks of 1 KiB: 8 rows x 64 columns, block
-// (row / 8) * CH + column / 64.  Of a block's 64 chunks of 16 bytes the one of row r and chunk column c is number
-// ((c & 7) ^ (r >> 3 & 1)) * 8 + ((r & 7) ^ (c >> 1 & 1) * 4).  Both ways to read a tile are then free of bank conflicts, and an operand's place
-// is one of two registers plus a constant.
 
 }  // namespace wlb

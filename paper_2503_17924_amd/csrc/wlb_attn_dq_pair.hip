@@ -31,6 +31,7 @@ __device__ __forceinline__ void dq_pair_piece(const BwdParams& p, char* smem, co
     constexpr int PER = TILEB / 4096, PIECES = 2 * PER;      // 1 KiB blocks of a tile that a wavefront copies; of K and V
     constexpr int HALF = 4 * CH * 1024;                      // 32 rows further
     constexpr int ACC_Q = 2 * DB * 16;                       // accumulators of dQ^T, then the operands of Q
+    static_assert(D == 128, "the schedule of a block of 32 keys is laid out for 16 MFMAs a product");
     static_assert(BM == 128 && PER == 2 * CH, "a wavefront copies 16 rows");
 
     const int G = p.hq / p.hkv;
@@ -72,7 +73,7 @@ __device__ __forceinline__ void dq_pair_piece(const BwdParams& p, char* smem, co
         const int voff = (int)(n / CH ? voff1 : voff0);
         if constexpr (k & 1) dma_issue_at<TILEB + n * 1024>(v_rs.r, at_lds, voff, at_so);
         else if constexpr (k == 0) dma_issue_at<0>(k_rs.r, at_lds, voff, at_so);
-        else at_so = dma_issue_step<n * 1024>(k_rs.r, at_lds, voff, at_so, n % CH ? 128u : CH == 2 ? rows8 - 128u : rows8);
+        else at_so = dma_issue_step<n * 1024>(k_rs.r, at_lds, voff, at_so, n % CH ? 128u : rows8 - 128u);
     };
     auto issue_at = [&](int k) __attribute__((always_inline)) {
         switch (k) {
@@ -98,7 +99,7 @@ __device__ __forceinline__ void dq_pair_piece(const BwdParams& p, char* smem, co
         for_all<8 * CH>([&](auto n) __attribute__((always_inline)) {
             const int voff = (int)(n / CH % 2 ? qoff ^ 16u : qoff);
             if constexpr (n == 0) dma_issue_at<0>(rs.r, lds, voff, so);
-            else so = dma_issue_step<n * 1024>(rs.r, lds, voff, so, n % CH ? 128u : CH == 2 ? 8u * q_row - 128u : 8u * q_row);
+            else so = dma_issue_step<n * 1024>(rs.r, lds, voff, so, n % CH ? 128u : 8u * q_row - 128u);
         });
     };
     const uint32_t q_lds = uniform(smem_base + 2 * TILEB + (uint32_t)wave * TILEB), do_lds = q_lds + 4 * TILEB;
@@ -244,7 +245,7 @@ __device__ __forceinline__ void dq_pair_piece(const BwdParams& p, char* smem, co
         // A block of 32 keys: 6 NU MFMAs without a gap: dP, the scores of the next block, dQ.  Beside them the exponentials (from the second half of
         // the dQ of the block before to the end of dP) and dS (beside the scores).  Operands are requested three units (of two MFMAs)
         // ahead, right behind a unit's first MFMA.  The barrier of a tile lies in its second block, in front of the first read of the next tile's K.
-        constexpr int E0 = NU == 8 ? 7 : 5, EXP_SLOTS = 2 * NU - E0 + 2 * NU;      // first slot of dQ with exponentials; slots with them
+        constexpr int E0 = 7, EXP_SLOTS = 2 * NU - E0 + 2 * NU;      // first slot of dQ with exponentials; slots with them
         auto exp_end = [](int k) { const int e = (k * 32 + EXP_SLOTS - 2) / (EXP_SLOTS - 1); return e < 0 ? 0 : e < 32 ? e : 32; };
         auto exp_slot = [&](f32x16 (&s)[2], int k) __attribute__((always_inline)) {
 #pragma unroll
@@ -285,7 +286,7 @@ __device__ __forceinline__ void dq_pair_piece(const BwdParams& p, char* smem, co
                     else if constexpr (H == 1) issue_at(u);                // the copies of the tile after the next two
                     fence();
                     // dS = P o (dP - delta)
-                    constexpr int D0 = NU == 8 ? 3 : 2, k = 2 * u + i - D0, A = (k < 0 ? 0 : k) * 32 / (2 * NU - D0), B = (k < 0 ? 0 : k + 1) * 32 / (2 * NU - D0);
+                    constexpr int D0 = 3, k = 2 * u + i - D0, A = (k < 0 ? 0 : k) * 32 / (2 * NU - D0), B = (k < 0 ? 0 : k + 1) * 32 / (2 * NU - D0);
                     for_all<B - A>([&](auto n) __attribute__((always_inline)) {
                         constexpr int e = A + decltype(n)::value, r = e >> 4, x = e & 15;
                         const float v = sc[r][x] * (dp[r][x] + dl[r]);

@@ -150,7 +150,7 @@ bool use_short_path(const wlb_attn_desc& d, const PlanLayout& L);
 // the launch they replace (20 us and 0.11 us per 32 rows and 8 heads): long_tokens is at most kSpanLongBase + kSpanLongPerBlock for each of those.
 // Whole pass, old / new, documents of 1 - 64 tokens and one of n: below that line (n = 1400 - 5000 of 32768 - 131072, 16/2 and 16/4 heads) 0.95 - 1.24,
 // above it (n = 1200 - 5000 of 8192 - 131072) 0.67 - 1.02.
-constexpr int kSpanMinReach = 96, kSpanMaxLength = 256, kSpanMaxKeys = 384, kSpanMinUnits = 128, kSpanMinHeads = 4;
+constexpr int kSpanMinReach = 96, kSpanMaxLength = 256, kSpanMaxKeys = 384, kSpanMinHeads = 4;
 constexpr double kSpanLongBase = 285, kSpanLongPerBlock = 2.5;
 bool use_span(const wlb_attn_desc& d, const PlanLayout& L);
 // Tokens of the documents that are far longer than the others, if there are any: weighted by tokens, documents are 2 * pairs / rows long; lengths that

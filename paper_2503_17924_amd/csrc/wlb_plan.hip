@@ -134,7 +134,7 @@ bool use_span(const wlb_attn_desc& d, const PlanLayout& L) {
     if (long_tokens(d) > kSpanLongBase + kSpanLongPerBlock * L.n_blocks32 * d.hq / 8) return false;
     const long long reach = (long long)kShortBlockRows * d.t_kv / d.n_q, length = 2 * (d.visible_pairs / d.n_q);
     if (reach < kSpanMinReach || length > kSpanMaxLength) return false;
-    return per * reach + length <= kSpanMaxKeys || (long long)((L.n_blocks32 + per - 1) / per) * d.hkv >= kSpanMinUnits;
+    return per * reach + length <= kSpanMaxKeys || (long long)((L.n_blocks32 + per - 1) / per) * d.hkv >= compute_units() / 2;
 }
 
 bool short_documents(const wlb_attn_desc& d) {
