@@ -38,9 +38,9 @@ COST_A, COST_B = 6, 640000    # packer cost model, picoseconds per token^2 / per
 WINDOW = 131072               # context window of the packing workload
 # HBM-side bytes per launch (FETCH_SIZE + WRITE_SIZE, scaled by a copy of known size), measured with
 # rocprofv3 --pmc on this workload: profiles/hbm_traffic_c2_128k_cp8.txt
-MEASURED_TRAFFIC_BYTES = {("c2_128k_cp8", "dkv_kernel"): int((4.430 + 0.246) * 2**30),
-                          ("c2_128k_cp8", "dq_kernel"): int((3.020 + 0.080) * 2**30),
-                          ("c2_128k_cp8", "fwd_kernel"): int((2.929 + 0.078) * 2**30)}
+MEASURED_TRAFFIC_BYTES = {("c2_128k_cp8", "dkv_kernel"): int((4.388 + 0.246) * 2**30),
+                          ("c2_128k_cp8", "dq_kernel"): int((2.987 + 0.078) * 2**30),
+                          ("c2_128k_cp8", "fwd_kernel"): int((2.886 + 0.079) * 2**30)}
 
 
 def parse():

@@ -55,7 +55,7 @@ def main():
     qi = sh["q_idx"]
     rows = torch.from_numpy(np.maximum(qi, 0).astype(np.int64)).to(dev)
     q, do = full["q"].index_select(0, rows).contiguous(), full["do"].index_select(0, rows).contiguous()
-    attn = B.Attention(qi, sh["cu_seqlens_k"], w.total_tokens, hq, hkv, d, w.scale, dev)
+    attn = B.Attention(qi, sh["cu_seqlens_k"], w.total_tokens, hq, hkv, d, w.scale, dev, visible_pairs=sh["useful_pairs"])
     o, lse = attn.forward(q, full["k"], full["v"])
     dq, dk, dv = attn.backward(q, full["k"], full["v"], o, lse, do)
     torch.cuda.synchronize()
@@ -110,7 +110,7 @@ def main():
     mk = lambda n, h: torch.randn((n, h, d), device=dev, generator=gen, dtype=torch.float32).to(torch.bfloat16)
     q, do, k, v = mk(nq_u, hq), mk(nq_u, hq), mk(t_u, hkv), mk(t_u, hkv)
     attn = B.Attention(np.full(nq_u, t_u - 1, dtype=np.int32), np.array([0, t_u], dtype=np.int32), t_u, hq, hkv, d,
-                       1.0 / float(np.sqrt(d)), dev)
+                       1.0 / float(np.sqrt(d)), dev, visible_pairs=nq_u * t_u)
     o, lse = attn.forward(q, k, v)
     dq, dk, dv = attn.backward(q, k, v, o, lse, do)
     torch.cuda.synchronize()
